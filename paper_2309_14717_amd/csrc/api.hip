@@ -289,14 +289,10 @@ int qalora_quantize_compensated(const qalora_desc* d, const float* W, const floa
   if (128 % d->group != 0) return QALORA_EUNSUPPORTED;  // groups must not straddle the lazy blocks
   const size_t n = (size_t)d->d_in * d->d_out;
   if (!ws || ws_bytes < align_up(n * 4) + align_up(n)) return QALORA_EWORKSPACE;
-  float* work = static_cast<float*>(ws);
-  uint8_t* codes = static_cast<uint8_t*>(ws) + align_up(n * 4);
-  if (launch_compensate(W, hinv_chol, d->d_in, d->d_out, d->bits, d->group, work, codes, alpha, beta,
-                        as_stream(stream)) != hipSuccess)
-    return QALORA_EHIP;
-  // the codes enter the packed format the way any other quantizer's would
-  launch_pack(d->bits, codes, packed, d->d_in, d->d_out, as_stream(stream));
-  return hipGetLastError() == hipSuccess ? QALORA_OK : QALORA_EHIP;
+  return launch_compensate(W, hinv_chol, d->d_in, d->d_out, d->bits, d->group, static_cast<float*>(ws), packed,
+                           alpha, beta, as_stream(stream)) == hipSuccess
+             ? QALORA_OK
+             : QALORA_EHIP;
 }
 
 int qalora_unpack(const qalora_desc* d, const void* packed, uint8_t* codes, void* stream) {

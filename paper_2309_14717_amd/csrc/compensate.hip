@@ -8,120 +8,487 @@
 // Eq. 1's min-max recipe, from the group's rows as they stand when its first row is reached;
 // rows beyond the current block of kBlock rows receive the block's errors in one lazy update.
 //
-// Columns are independent, rows strictly sequential.  A block of 1024 threads owns 16 columns:
-// thread (c, rl) is column c and row lane rl (64 of them).  Per block of rows: the 128 x 16
-// tile of weights and the 128 x 128 diagonal block of U sit in LDS; every thread follows its
-// column's row i redundantly (code, error), then the 64 row lanes update the tile rows behind
-// i -- one barrier per row; afterwards the rows behind the block are updated 64 at a time from
-// a staged 128 x 64 piece of U.  fp32 throughout, every sum in ascending row order with fused
-// multiply-adds: the operation order is part of the definition, so the codes are reproducible
-// bit for bit.
+// The operation order is part of the definition (fp32, fused multiply-adds, every sum in
+// ascending row order), so the codes are reproducible bit for bit:
+//   inside a block of 128 rows   w_r <- fma(-U[i,r], e_i, w_r)            for i = first row .. r - 1
+//   beyond it, once per block    w_r <- w_r - (fma chain from 0 over the block's 128 rows)
+// Both are chains v_mfma_f32_16x16x4_f32 computes exactly: that instruction adds its four
+// products one after the other, k ascending, each with one rounding (checked on the device
+// against fmaf, subnormals included; the bit-exact tests stand on it).
+//
+// What bounds it: d_in dependent rows (a rounding, a division by U[i,i] and an update each) and
+// d_in^2 d_out / 2 multiply-adds.  A block of four wavefronts, one per SIMD, owns 16 columns -- one
+// matrix tile; 256 blocks for a 4096-column layer -- and runs the two side by side:
+//   * ONE wavefront walks the rows of the current 128-row panel.  Sixteen rows at a time are
+//     held whole in every lane's registers (lane = column; the four lane groups repeat each
+//     other), so a row costs no barrier, no LDS round trip and no cross-lane step; the sixteen
+//     rows' errors then go to the panel's later rows as matrix instructions.
+//   * THREE wavefronts meanwhile bring the NEXT panel up to date with all finished blocks
+//     (left-looking: W is read once, the blocks' errors are kept instead and re-read as matrix
+//     operands), so that only the newest block's errors remain to be applied when the walker
+//     is done.  (Four of them, one sharing the walker's SIMD, are slower: vector and matrix
+//     instructions of a SIMD take turns, so that SIMD's times add up.)
+// Two barriers per panel.
+// The divisions of the walk.  e = t / U[i,i] is a product with the reciprocal in two parts and one
+// remainder step (Markstein's theorem: with the correctly rounded reciprocal and a quotient
+// within one unit in the last place the result is the correctly rounded quotient, while nothing
+// under- or overflows).  The code needs the quotient (w - beta) / alpha only up to rounding to an
+// integer: a product with the rounded reciprocal is within two units in the last place, and
+// decides the same integer unless it lies next to a tie.  Sixteen rows in which some operand
+// leaves the range where this holds, or some quotient comes near a tie, are done again with
+// real divisions.
+// 4096 x 4096 INT4 g = 32: 10130 us with 16 columns x 64 row lanes, a barrier per row and two LDS
+// operands per multiply-add; 920 us like this (walker alone about 400, the matrix work of three
+// SIMDs 650 at its full rate).
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
 namespace qalora {
 
 namespace {
-constexpr int kBlock = 128;   // rows per lazy block (a multiple of every supported group size <= 128)
-constexpr int kCols = 16;     // columns per thread block
-constexpr int kLanes = 64;    // row lanes
-constexpr int kThreads = kCols * kLanes;
-constexpr int kLds = (kBlock * kCols * 2 + kBlock * kBlock) * 4;
-}  // namespace
+constexpr int kBlock = 128;              // rows per lazy block (a multiple of every supported group size)
+constexpr int kCols = 16;                // columns per thread block
+constexpr int kTiles = kBlock / 16;      // 16-row tiles of a panel
+constexpr int kUpd = 3;                  // updating wavefronts: three tiles (48 rows) each, the last one two
+constexpr int kThreads = 64 * (kUpd + 1);
+constexpr int kTrLd = 20;                // floats per column of the transposed sub-block (16 + 4: bank spread)
 
-__global__ __launch_bounds__(kThreads) void compensate_kernel(const float* __restrict__ W,
-                                                              const float* __restrict__ U, int d_in,
-                                                              int d_out, int bits, int g,
-                                                              float* __restrict__ work,
-                                                              uint8_t* __restrict__ codes,
-                                                              float* __restrict__ alpha,
-                                                              float* __restrict__ beta) {
-  extern __shared__ __align__(16) float lds[];
-  float* tile = lds;                          // [kBlock][kCols] current weights of the block's rows
-  float* err = tile + kBlock * kCols;         // [kBlock][kCols] errors of the block's rows
-  float* Us = err + kBlock * kCols;           // [kBlock][kBlock] diagonal block of U, or [kBlock][kLanes]
-  const int tid = threadIdx.x, c = tid & (kCols - 1), rl = tid >> 4;
-  const int j = blockIdx.x * kCols + c;
-  const bool col_ok = j < d_out;
-  const float levels = (float)((1 << bits) - 1);
+struct CompArgs {
+  const float* W;
+  const float* U;
+  int d_in, d_out, g;
+  float* err;        // errors of finished blocks: 16-row blocks of a column block, [kb][column][4] each
+  uint32_t* plane0;
+  uint32_t* plane1;
+  float* alpha;
+  float* beta;
+};
 
-  // the block's columns of W become its working copy
-  for (int r = rl; r < d_in; r += kLanes)
-    if (col_ok) work[(size_t)r * d_out + j] = W[(size_t)r * d_out + j];
-  __syncthreads();
-
-  for (int i1 = 0; i1 < d_in; i1 += kBlock) {
-    const int n = min(kBlock, d_in - i1);
-    for (int r = rl; r < n; r += kLanes) tile[r * kCols + c] = col_ok ? work[(size_t)(i1 + r) * d_out + j] : 0.0f;
-    for (int idx = tid; idx < n * kBlock; idx += kThreads) {
-      const int i = idx / kBlock, r = idx - i * kBlock;
-      Us[i * kBlock + r] = r < n ? U[(size_t)(i1 + i) * d_in + i1 + r] : 0.0f;
-    }
-    __syncthreads();
-    float a = 1.0f, b = 0.0f;  // factors of the column's current group
-    for (int i = 0; i < n; ++i) {
-      if ((i1 + i) % g == 0) {  // a new group: min-max of its rows as they stand now (Eq. 1)
-        float mn = tile[i * kCols + c], mx = mn;
-        for (int q = i + 1; q < i + g; ++q) {
-          const float w = tile[q * kCols + c];
-          mn = w < mn ? w : mn;
-          mx = w > mx ? w : mx;
-        }
-        a = __fdiv_rn(__fsub_rn(mx, mn), levels);
-        if (!(a > 0.0f)) a = 0x1p-60f;
-        b = mn;
-        if (rl == 0 && col_ok) {
-          const size_t o = (size_t)((i1 + i) / g) * d_out + j;
-          alpha[o] = a;
-          beta[o] = b;
-        }
-        // every row lane has read the group's rows before any lane updates them below (the
-        // condition is uniform over the block)
-        __syncthreads();
-      }
-      const float w = tile[i * kCols + c];
-      float rq = rintf(__fdiv_rn(__fsub_rn(w, b), a));
-      if (!(rq >= 0.0f)) rq = 0.0f;
-      if (rq > levels) rq = levels;
-      const float e = __fdiv_rn(__fsub_rn(w, __fmaf_rn(a, rq, b)), Us[i * kBlock + i]);
-      if (rl == 0) {
-        err[i * kCols + c] = e;
-        if (col_ok) codes[(size_t)(i1 + i) * d_out + j] = (uint8_t)(int)rq;
-      }
-      for (int r = i + 1 + rl; r < n; r += kLanes)
-        tile[r * kCols + c] = __fmaf_rn(-Us[i * kBlock + r], e, tile[r * kCols + c]);
-      __syncthreads();  // row i + 1 is complete
-    }
-    // the block's errors onto the rows behind it, kLanes rows at a time
-    for (int r0 = i1 + n; r0 < d_in; r0 += kLanes) {
-      __syncthreads();  // the previous piece of U (or its diagonal block) has been used
-      for (int idx = tid; idx < n * kLanes; idx += kThreads) {
-        const int i = idx / kLanes, rr = idx - i * kLanes;
-        Us[i * kLanes + rr] = r0 + rr < d_in ? U[(size_t)(i1 + i) * d_in + r0 + rr] : 0.0f;
-      }
-      __syncthreads();
-      float acc = 0.0f;
-      for (int i = 0; i < n; ++i) acc = __fmaf_rn(Us[i * kLanes + rl], err[i * kCols + c], acc);
-      const int r = r0 + rl;
-      if (r < d_in && col_ok) {
-        const size_t o = (size_t)r * d_out + j;
-        work[o] = __fsub_rn(work[o], acc);
-      }
-    }
-    __syncthreads();  // this thread block's updates of `work` are visible to its next load
+// f(integral_constant<I>), ..., f(integral_constant<N - 1>): loops over register arrays whose indices must
+// stay constants (left to the optimiser, the row loops below were rolled up again and the
+// registers indexed at run time)
+template <int I, int N, typename Fn>
+__device__ __forceinline__ void static_for(Fn&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
   }
 }
 
-// work: d_in * d_out fp32; codes: d_in * d_out bytes (canonical, one code per byte)
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+constexpr uint32_t kOob = 0xffff0000u;  // past every buffer below: reads zero
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* base, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)(bytes > kOob ? kOob : bytes), 0x00020000);
+}
+__device__ __forceinline__ float load1(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, 0));
+}
+__device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+  return __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
+}
+
+// LDS-only barrier: does not wait for the global loads that are in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// |v| in [2^-60, 2^60]
+__device__ __forceinline__ bool in_safe_range(float v) { return fabsf(v) >= 0x1p-60f && fabsf(v) <= 0x1p60f; }
+}  // namespace
+
+template <int NBITS>
+__global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs p) {
+  __shared__ f32x4 tile[kTiles * 64];  // the panel to be walked, as matrix accumulator fragments
+  __shared__ f32x4 errs[kTiles * 64];  // the walked panel's errors, as matrix operand fragments
+  __shared__ float tr[kCols * kTrLd];  // the walker's sixteen rows, column by column
+  __shared__ float diag[16 * 16];      // their block of U
+  __shared__ f32x2 rcp[kBlock];        // 1 / U[i,i] of the panel's rows: rounded, and what is left of it
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool walker = wave == kUpd;
+  const int n = lane & 15, kb = lane >> 4;  // column; rows 4 kb + r of a fragment
+  const int d_in = p.d_in, d_out = p.d_out, g = p.g;
+  const uint32_t row_b = (uint32_t)d_in * 4u;  // bytes of a row of U
+  const int j0 = blockIdx.x * kCols, j = j0 + n;
+  const int nc = min(kCols, d_out - j0);  // 16, or 8 at the right edge
+  const bool col_ok = n < nc;
+  const float* __restrict__ U = p.U;
+  // this column block's share of the error store; a fragment of 16 rows is 16 nc floats
+  float* err = p.err + (size_t)j0 * d_in;
+  const int e_lane = (kb * nc + min(n, nc - 1)) * 4;
+  const int panels = ceil_div(d_in, kBlock);
+
+  // An updating wavefront's 16 NT rows are dealt to its NT tiles in turn -- row m of tile h is
+  // r0 + NT m + h -- so that a lane's NT elements of a row of U are adjacent (one load).
+  auto load_w = [&](auto nt_c, int r0, f32x4* v) {  // zeros outside the matrix
+    constexpr int NT = decltype(nt_c)::value;
+#pragma unroll
+    for (int h = 0; h < NT; ++h)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = r0 + NT * (4 * kb + r) + h;
+        v[h][r] = (row < d_in && col_ok) ? p.W[(size_t)row * d_out + j] : 0.0f;
+      }
+  };
+  // ... into the walker's fragments: row 16 t + 4 k + r of the panel at lane (n, k) of tile t
+  float* tile_f = reinterpret_cast<float*>(tile);
+  auto store_tile = [&](auto nt_c, const f32x4* v) {
+    constexpr int NT = decltype(nt_c)::value;
+#pragma unroll
+    for (int h = 0; h < NT; ++h)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 48 * wave + NT * (4 * kb + r) + h;
+        tile_f[((row >> 4) * 64 + 16 * ((row >> 2) & 3) + n) * 4 + (row & 3)] = v[h][r];
+      }
+  };
+
+  if (!walker) {
+    auto update = [&](auto nt_c) __attribute__((always_inline)) {
+      constexpr int NT = decltype(nt_c)::value;
+      f32x4 cur[NT], nxt[NT];  // the tiles being brought up to date; W of the ones after
+      float u[kTiles][4][NT];  // U of one block of rows, eight pieces of 16
+      f32x4 ev[kTiles];        // the block's errors
+      const uint32_t e_off = 4u * (uint32_t)e_lane, e_step = 64u * (uint32_t)nc;  // bytes
+      auto rs_u = [&](int blk) { return rsrc(U + (size_t)blk * kBlock * d_in, (size_t)min(kBlock, d_in - blk * kBlock) * row_b); };
+      auto rs_e = [&](int blk) { return rsrc(err + (size_t)blk * kBlock * nc, (size_t)kTiles * e_step); };
+      // U operand: lane (row m = n of the tiles, kb) supplies U[i + 4 q + kb][r0 + NT n + h]; columns
+      // outside the matrix are some other element of the block's rows (or zero): never used
+      auto u_offset = [&](int r0) { return (uint32_t)kb * row_b + 4u * (uint32_t)(r0 + NT * n); };
+      auto load_u = [&](int k, __amdgpu_buffer_rsrc_t r, uint32_t off) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const uint32_t so = (uint32_t)(16 * k + 4 * q) * row_b;
+          if constexpr (NT == 3) {
+            const u32x3 v = __builtin_amdgcn_raw_buffer_load_b96(r, (int)off, (int)so, 0);
+#pragma unroll
+            for (int h = 0; h < 3; ++h) u[k][q][h] = __uint_as_float(v[h]);
+          } else {
+            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, (int)so, 0);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) u[k][q][h] = __uint_as_float(v[h]);
+          }
+        }
+      };
+      load_w(nt_c, 48 * wave, cur);
+      store_tile(nt_c, cur);
+      int r0 = kBlock + 48 * wave;
+      uint32_t u_off = u_offset(r0);
+      load_w(nt_c, r0, cur);
+#pragma unroll
+      for (int k = 0; k < kTiles; ++k) load_u(k, rs_u(0), u_off);
+      lds_barrier();  // the first panel is in place
+      for (int pn = 0; pn < panels; ++pn) {
+        const bool work = pn + 1 < panels;  // (rows past the end of a ragged last panel are carried along as zeros)
+        if (work) {
+          // a piece's registers are reloaded for the next block as soon as it has been used, so a
+          // whole block of loads is in flight
+          for (int blk = 0; blk < pn; ++blk) {
+            f32x4 acc[NT];
+#pragma unroll
+            for (int h = 0; h < NT; ++h) acc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            // U ends with block pn; its errors are not known yet: the last known block's are loaded again
+            const __amdgpu_buffer_rsrc_t ru = rs_u(blk + 1), re = rs_e(min(blk + 1, pn - 1));
+#pragma unroll
+            for (int k = 0; k < kTiles; ++k) {
+#pragma unroll
+              for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int h = 0; h < NT; ++h)
+                  acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[k][q][h], ev[k][q], acc[h], 0, 0, 0);
+              __builtin_amdgcn_sched_barrier(0);
+              load_u(k, ru, u_off);
+              ev[k] = load4(re, e_off, (uint32_t)k * e_step);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int h = 0; h < NT; ++h)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) cur[h][r] = __fsub_rn(cur[h][r], acc[h][r]);
+          }
+        }
+        lds_barrier();  // block pn's errors are known
+        if (work) {
+          // block pn, and the loads the next panel starts with
+          r0 += kBlock;
+          u_off = u_offset(r0);
+          load_w(nt_c, r0, nxt);
+          const __amdgpu_buffer_rsrc_t ru = rs_u(0), re = rs_e(0);
+          f32x4 acc[NT];
+#pragma unroll
+          for (int h = 0; h < NT; ++h) acc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+          f32x4 el[kTiles];
+#pragma unroll
+          for (int k = 0; k < kTiles; ++k) el[k] = errs[k * 64 + lane];
+#pragma unroll
+          for (int k = 0; k < kTiles; ++k) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+              for (int h = 0; h < NT; ++h)
+                acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[k][q][h], el[k][q], acc[h], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            load_u(k, ru, u_off);
+            ev[k] = load4(re, e_off, (uint32_t)k * e_step);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+#pragma unroll
+          for (int h = 0; h < NT; ++h)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) cur[h][r] = __fsub_rn(cur[h][r], acc[h][r]);
+          store_tile(nt_c, cur);
+#pragma unroll
+          for (int h = 0; h < NT; ++h) cur[h] = nxt[h];
+        }
+        lds_barrier();  // the next panel is in place
+      }
+    };
+    if (wave + 1 < kUpd) update(std::integral_constant<int, 3>{});
+    else update(std::integral_constant<int, 2>{});
+    return;
+  }
+
+  // ---- the walker ---------------------------------------------------------------------------
+  lds_barrier();  // the first panel is in place
+  float a = 1.0f, b = 0.0f, ya = 1.0f;  // walker: the column's current group: alpha, beta, 1 / alpha
+  for (int pn = 0; pn < panels; ++pn) {
+    const int i1 = pn * kBlock;
+    // U's rows of the panel; columns outside the matrix are pointed past the buffer
+    const __amdgpu_buffer_rsrc_t rs_u = rsrc(U + (size_t)i1 * d_in, (size_t)min(kBlock, d_in - i1) * row_b);
+    bool odd = false;  // a diagonal element outside the reciprocal's range
+#pragma unroll
+    for (int h = 0; h < kBlock / 64; ++h) {
+      const int i = 64 * h + lane;
+      const float d = i1 + i < d_in ? load1(rs_u, (uint32_t)i * row_b + 4u * (uint32_t)(i1 + i), 0) : 1.0f;
+      const float y = __fdiv_rn(1.0f, d);
+      rcp[i] = f32x2{y, __fmul_rn(__fmaf_rn(-d, y, 1.0f), y)};
+      odd |= !(d >= 0x1p-40f && d <= 0x1p40f);
+    }
+    const bool any_odd = __any(odd);
+    f32x4 pt[kTiles];  // pt[t]: tile s + t of the panel, rotating with the sub-block s
+#pragma unroll
+    for (int t = 0; t < kTiles; ++t) pt[t] = tile[t * 64 + lane];
+    // U of a sub-block's own rows and columns: row lane / 4, four columns
+    auto load_diag = [&](int s) {
+      const int i0 = i1 + 16 * s, c = i0 + 4 * (lane & 3);  // d_in is a multiple of 8: all four or none
+      const bool ok = c < d_in && i0 + (lane >> 2) < d_in;
+      return load4(rs_u, ok ? (uint32_t)(lane >> 2) * row_b + 4u * (uint32_t)c : kOob, 16u * s * row_b);
+    };
+    f32x4 dg = load_diag(0);
+    uint32_t hiword = 0;  // 3 bits: the high-bit word, two sub-blocks per word
+    for (int s = 0; s < kTiles; ++s) {
+      const int row0 = i1 + 16 * s;
+      if (row0 >= d_in) break;
+      *reinterpret_cast<f32x4*>(tr + n * kTrLd + 4 * kb) = pt[0];
+      *reinterpret_cast<f32x4*>(diag + 4 * lane) = dg;
+      if (s + 1 < kTiles) dg = load_diag(s + 1);
+      // U of this sub-block's rows against the panel's later tiles: requested now, used after the walk
+      float au[kTiles - 1][4];
+#pragma unroll
+      for (int t = 1; t < kTiles; ++t) {
+        const int c = row0 + 16 * t + n;
+        const uint32_t vo = s + t < kTiles && c < d_in ? (uint32_t)kb * row_b + 4u * (uint32_t)c : kOob;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) au[t - 1][q] = load1(rs_u, vo, (uint32_t)(16 * s + 4 * q) * row_b);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("" ::: "memory");  // one wavefront: its LDS accesses complete in order
+
+      f32x4 eb;  // the sixteen errors as the matrix operand: lane (column n, kb) supplies rows 4 q + kb
+      uint32_t word0 = 0, word1 = 0;
+      float a_s, b_s, ya_s;  // the group state after the sixteen rows
+      uint32_t hi_s;
+      auto walk = [&](auto fast_c) __attribute__((always_inline)) -> bool {  // true: an operand left the safe range
+        constexpr bool FAST = decltype(fast_c)::value;
+        float w[16];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(tr + n * kTrLd + 4 * q);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) w[4 * q + r] = v[r];
+        }
+        a_s = a, b_s = b, ya_s = ya, hi_s = hiword;
+        word0 = word1 = 0;
+        bool bad = !in_safe_range(a);
+        // |t| in [2^-60, 2^60] or +0 (as bits rotated left by one, less one: +0 comes out largest, -0
+        // smallest), and how near the quotients come to a tie
+        uint32_t tmin = 0xffffffffu;
+        float tmax = 0.0f, dmax = 0.0f;
+        const float levels = (float)((1 << NBITS) - 1);
+        f32x4 ur[2][4];  // the row's piece of U and the next row's, requested one row ahead
+        f32x2 ry[2];
+        auto fetch_row = [&](auto i_c) {
+          constexpr int i = decltype(i_c)::value;
+          static_for<i / 4, 4>([&](auto q) {
+            ur[i & 1][decltype(q)::value] = *reinterpret_cast<const f32x4*>(diag + 16 * i + 4 * decltype(q)::value);
+          });
+          ry[i & 1] = rcp[16 * s + i];
+        };
+        fetch_row(std::integral_constant<int, 0>{});
+        static_for<0, 16>([&](auto i_c) {
+          constexpr int i = decltype(i_c)::value;
+          if constexpr (i + 1 < 16) fetch_row(std::integral_constant<int, i + 1>{});
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (i == 0 || i == 8) {
+            if ((row0 + i) % g == 0) {  // a new group: min-max of its rows as they stand (Eq. 1)
+              float mn, mx;
+              if (i == 8 || g == 8) {
+                mn = mx = w[i];
+                static_for<1, 8>([&](auto q_c) {
+                  constexpr int q = i < 9 ? i + decltype(q_c)::value : 15;
+                  mn = w[q] < mn ? w[q] : mn;
+                  mx = w[q] > mx ? w[q] : mx;
+                });
+              } else {
+                const int nt = g >> 4;
+                mn = mx = pt[0][0];
+                static_for<0, kTiles>([&](auto t_c) {
+                  constexpr int t = decltype(t_c)::value;
+                  if (t < nt) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                      mn = fminf(mn, pt[t][r]);
+                      mx = fmaxf(mx, pt[t][r]);
+                    }
+                  }
+                });
+                mn = fminf(mn, __shfl_xor(mn, 16, 64)), mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+                mn = fminf(mn, __shfl_xor(mn, 32, 64)), mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                if (__any(mn == 0.0f)) {  // a minimum of zero keeps the sign of the first zero of the group
+                  int key = 1 << 20;
+                  static_for<0, kTiles>([&](auto t_c) {
+                    constexpr int t = decltype(t_c)::value;
+                    if (t < nt) {
+#pragma unroll
+                      for (int r = 0; r < 4; ++r)
+                        if (pt[t][r] == 0.0f)
+                          key = min(key, 2 * (16 * t + r) + (int)(__float_as_uint(pt[t][r]) >> 31));
+                    }
+                  });
+                  key += 8 * kb;  // the lane's rows are 4 kb + r of each tile
+                  key = min(key, __shfl_xor(key, 16, 64));
+                  key = min(key, __shfl_xor(key, 32, 64));
+                  if (mn == 0.0f) mn = (key & 1) ? -0.0f : 0.0f;
+                }
+              }
+              a_s = __fdiv_rn(__fsub_rn(mx, mn), levels);
+              if (!(a_s > 0.0f)) a_s = 0x1p-60f;
+              b_s = mn;
+              ya_s = __fdiv_rn(1.0f, a_s);
+              bad |= !in_safe_range(a_s);
+              if (kb == 0 && col_ok && row0 + i < d_in) {
+                const size_t o = (size_t)((row0 + i) / g) * d_out + j;
+                p.alpha[o] = a_s;
+                p.beta[o] = b_s;
+              }
+            }
+          }
+          const float x = __fsub_rn(w[i], b_s);
+          float rq, q;
+          if constexpr (FAST) {
+            const float q0 = __fmul_rn(x, ya_s), rn = rintf(q0);
+            dmax = fmaxf(dmax, fabsf(__fsub_rn(q0, rn)));
+            rq = __builtin_amdgcn_fmed3f(rn, 0.0f, levels);
+          } else {
+            rq = rintf(__fdiv_rn(x, a_s));
+            if (!(rq >= 0.0f)) rq = 0.0f;
+            if (rq > levels) rq = levels;
+          }
+          const float t = __fsub_rn(w[i], __fmaf_rn(a_s, rq, b_s));
+          const float d = ur[i & 1][i / 4][i % 4];
+          if constexpr (FAST) {
+            const float q1 = __fmaf_rn(t, ry[i & 1][0], __fmul_rn(t, ry[i & 1][1]));
+            q = __fmaf_rn(__fmaf_rn(-d, q1, t), ry[i & 1][0], q1);
+            const uint32_t tb = __float_as_uint(t);
+            tmin = min(tmin, ((tb << 1) | (tb >> 31)) - 1u);
+            tmax = fmaxf(tmax, fabsf(t));
+          } else {
+            q = __fdiv_rn(t, d);
+          }
+          eb[i >> 2] = (i & 3) == 0 || kb == (i & 3) ? q : eb[i >> 2];
+          static_for<i + 1, 16>([&](auto r_c) {
+            constexpr int r = decltype(r_c)::value;
+            w[r] = __fmaf_rn(-ur[i & 1][r / 4][r % 4], q, w[r]);
+          });
+          const uint32_t c = (uint32_t)(int)rq;
+          if constexpr (NBITS == 4) {
+            constexpr int ps = 4 * ((i & 7) >> 1) + 16 * (i & 1);
+            if constexpr (i < 8) word0 |= c << ps;
+            else word1 |= c << ps;
+          } else {
+            word0 |= (c & 3u) << (2 * (i >> 1) + 16 * (i & 1));
+            if constexpr (NBITS == 3) hi_s |= (c >> 2) << ((i >> 1) + 16 * (i & 1) + 8 * (s & 1));
+          }
+        });
+        // (2^-60 has the bits 67 << 23; a quotient of up to 31 carries an error below 2^-18, larger
+        // ones are clamped whichever way they round)
+        return bad || tmin < (67u << 24) - 1u || !(tmax <= 0x1p60f) || !(dmax < 0.5f - 0x1p-16f);
+      };
+      if (any_odd || __any(walk(std::true_type{}))) walk(std::false_type{});
+      a = a_s, b = b_s, ya = ya_s, hiword = hi_s;
+
+      errs[s * 64 + lane] = eb;
+      if (pn + 1 < panels && col_ok) *reinterpret_cast<f32x4*>(err + (size_t)(row0 >> 4) * 16 * nc + e_lane) = eb;
+      if (col_ok) {
+        if constexpr (NBITS == 4) {
+          if (kb < 2 && row0 + 8 * kb < d_in) p.plane0[(size_t)(row0 / 8 + kb) * d_out + j] = kb ? word1 : word0;
+        } else {
+          if (kb == 0) p.plane0[(size_t)(row0 / 16) * d_out + j] = word0;
+          if constexpr (NBITS == 3)
+            if (kb == 1 && (s & 1)) p.plane1[(size_t)(row0 / 32) * d_out + j] = hiword;
+        }
+      }
+      if (s & 1) hiword = 0;
+      // ... onto the panel's later tiles, exactly as many as there are (the switch keeps the
+      // chains of different tiles interleaved without computing absent ones)
+      auto behind = [&](auto nt_c) {
+        constexpr int NT = decltype(nt_c)::value;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int t = 1; t <= NT; ++t)
+            pt[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(-au[t - 1][q], eb[q], pt[t], 0, 0, 0);
+      };
+      switch (kTiles - 1 - s) {
+        case 7: behind(std::integral_constant<int, 7>{}); break;
+        case 6: behind(std::integral_constant<int, 6>{}); break;
+        case 5: behind(std::integral_constant<int, 5>{}); break;
+        case 4: behind(std::integral_constant<int, 4>{}); break;
+        case 3: behind(std::integral_constant<int, 3>{}); break;
+        case 2: behind(std::integral_constant<int, 2>{}); break;
+        case 1: behind(std::integral_constant<int, 1>{}); break;
+        default: break;
+      }
+#pragma unroll
+      for (int t = 0; t + 1 < kTiles; ++t) pt[t] = pt[t + 1];
+    }
+    // block pn's errors are known: in LDS, and (for this block's later loads) in the error store
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    lds_barrier();  // the next panel is in place
+  }
+}
+
+// err: d_in * d_out fp32 of scratch.  g must divide 128.
 hipError_t launch_compensate(const float* W, const float* U, int d_in, int d_out, int bits, int g,
-                             float* work, uint8_t* codes, float* alpha, float* beta, hipStream_t st) {
-  if (kBlock % g != 0) return hipErrorInvalidValue;
-  static std::atomic<uint64_t> granted{0};
-  if (hipError_t e = grant_dynamic_lds(reinterpret_cast<const void*>(compensate_kernel), kLds, granted);
-      e != hipSuccess)
-    return e;
-  compensate_kernel<<<ceil_div(d_out, kCols), kThreads, kLds, st>>>(W, U, d_in, d_out, bits, g, work, codes,
-                                                                    alpha, beta);
+                             float* err, void* packed, float* alpha, float* beta, hipStream_t st) {
+  if (kBlock % g != 0 || d_out % 8 != 0 || d_in % 8 != 0) return hipErrorInvalidValue;
+  CompArgs a{};
+  a.W = W;
+  a.U = U;
+  a.d_in = d_in;
+  a.d_out = d_out;
+  a.g = g;
+  a.err = err;
+  a.plane0 = static_cast<uint32_t*>(packed);
+  a.plane1 = a.plane0 + plane0_words(bits, d_in, d_out);
+  a.alpha = alpha;
+  a.beta = beta;
+  const int grid = ceil_div(d_out, kCols);
+  if (bits == 4) compensate_kernel<4><<<grid, kThreads, 0, st>>>(a);
+  else if (bits == 3) compensate_kernel<3><<<grid, kThreads, 0, st>>>(a);
+  else compensate_kernel<2><<<grid, kThreads, 0, st>>>(a);
   return hipGetLastError();
 }
 

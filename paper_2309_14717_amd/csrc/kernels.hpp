@@ -18,9 +18,9 @@ void launch_pack(int bits, const uint8_t* codes, void* packed, int d_in, int d_o
                  hipStream_t st);
 
 // --- compensate.hip: error-compensated code selection on a given inverse-Hessian factor ------
-// work: d_in * d_out fp32 scratch; codes: canonical, one code per byte.  g must divide 128.
+// err: d_in * d_out fp32 scratch; writes the packed codes.  g must divide 128.
 hipError_t launch_compensate(const float* W, const float* U, int d_in, int d_out, int bits, int g,
-                             float* work, uint8_t* codes, float* alpha, float* beta, hipStream_t st);
+                             float* err, void* packed, float* alpha, float* beta, hipStream_t st);
 
 // --- gemm_dq.hip --------------------------------------------------------------------
 struct GemmArgs {

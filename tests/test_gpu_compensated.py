@@ -31,6 +31,42 @@ def test_compensated_bit_exact(gpu_api, bits, g, d_in, d_out):
     assert hessian_error(W, codes, a, b, g, H) < e_rtn
 
 
+@pytest.mark.parametrize("bits,g,d_in,d_out,w_exp,u_exp,kind", [
+    (4, 8, 136, 8, 0, 0, "plain"),       # a panel and half a tile; groups inside a tile; half a column block
+    (4, 8, 8, 16, 0, 0, "plain"),
+    (4, 128, 256, 24, 0, 0, "plain"),    # a group per panel
+    (3, 32, 416, 40, 0, 0, "plain"),     # high-bit words of a ragged last panel
+    (2, 16, 144, 56, 0, 0, "plain"),
+    (4, 32, 384, 24, -70, 0, "plain"),   # operands outside the reciprocals' range: real divisions
+    (4, 32, 384, 24, 70, 0, "plain"),
+    (4, 32, 256, 24, 0, -50, "plain"),
+    (4, 32, 256, 24, 0, 50, "plain"),
+    (4, 32, 256, 24, 0, 0, "zeros"),     # groups of signed zeros
+    (4, 8, 256, 24, 0, 0, "pruned"),     # minima that are signed zeros
+    (4, 16, 256, 48, 0, 0, "columns"),   # safe and unsafe columns side by side
+    (3, 32, 384, 40, 0, 0, "tiny"),      # single elements far below the rest
+])
+def test_compensated_edges(gpu_api, bits, g, d_in, d_out, w_exp, u_exp, kind):
+    r = np.random.RandomState(d_in + d_out + bits)
+    W = (r.randn(d_in, d_out) * 0.02).astype(np.float32) * np.float32(2.0 ** w_exp)
+    if kind == "zeros":
+        W = np.where(r.rand(d_in, d_out) < 0.5, np.float32(-0.0), np.float32(0.0))
+    elif kind == "pruned":
+        W = np.maximum(W, 0) * np.where(r.rand(d_in, d_out) < 0.5, 1, -0.0).astype(np.float32)
+    elif kind == "columns":
+        W *= np.float32(2.0) ** r.randint(-140, 100, size=(1, d_out)).astype(np.float32)
+    elif kind == "tiny":
+        W[r.rand(d_in, d_out) < 0.1] *= np.float32(1e-36)
+    _, U = hessian(d_in, 2 * d_in, seed=3)
+    U32 = np.ascontiguousarray((U * 2.0 ** u_exp).astype(np.float32))
+    desc = gpu_api.make_desc(d_in, d_out, bits, g)
+    packed, alpha, beta = gpu_api.quantize_compensated(desc, dev(W), dev(U32))
+    c, a, b = oracle.quantize_compensated(W, U32, bits, g, block=128)
+    assert np.array_equal(gpu_api.unpack(desc, packed).cpu().numpy(), c)
+    assert np.array_equal(alpha.cpu().numpy().view(np.uint32), a.view(np.uint32))
+    assert np.array_equal(beta.cpu().numpy().view(np.uint32), b.view(np.uint32))
+
+
 def test_compensated_many_blocks_and_rerun(gpu_api):
     """A layer of sixteen lazy row blocks and 128 column blocks (all compute units busy, two
     block generations), bit for bit against the oracle, and twice: the row lanes of a column
