@@ -173,7 +173,10 @@ int qalora_pack(const qalora_desc* desc, const uint8_t* codes, void* packed, voi
  * value.  The library only ever sets that word: a caller who wants the status zeroes it once
  * (e.g. when allocating ws) and reads it after the stream has completed; after a non-zero
  * status the first QALORA_WS_STATUS_OFFSET bytes of ws must be zeroed before ws is used again
- * (a late flag of the failed call may still be there). */
+ * (a late flag of the failed call may still be there).  From there to 64 tokens, same shapes, a
+ * kernel with the operands described first (two fp16 factors) serves the adapter-free layer; its sum
+ * across blocks waits in the same way, with NaN outputs and no status word should a wait run out
+ * (a captured call may be replayed after that only once ws has been zeroed). */
 #define QALORA_WS_STATUS_OFFSET 2048
 int qalora_forward(const qalora_desc* desc, int tokens, const void* x, const void* packed,
                    const float* alpha, const float* beta, const float* A, const float* B,
@@ -288,10 +291,11 @@ int qalora_merge(const qalora_desc* desc, const float* beta, const float* A, con
  * qalora_forward_deployed is the adapter-free forward from it: up to
  * QALORA_DEPLOYED_STREAM_TOKENS tokens the decode kernel on the stream (`packed` is not read
  * and may be NULL; same arithmetic and results, bit for bit, as qalora_forward on the triple);
- * beyond that the dense contraction on `packed` (required) with the prepared words (results
- * as qalora_forward, bit for bit, without its per-call factor pass).  Five to thirty-two
- * tokens are served faster by qalora_forward on the original triple, which has a streaming
- * kernel for them.  Supported: bits 4, group 32/64/128, d_in a multiple of 128; otherwise
+ * beyond that `packed` is required: up to 64 tokens the codes come from it and the factors from the
+ * stream, above that the dense contraction uses the prepared words (results as qalora_forward where
+ * that has no exact-operand kernel, bit for bit, without its per-call factor pass).  Five to
+ * thirty-two tokens are served faster by qalora_forward on the original triple, which has a
+ * streaming kernel for them.  Supported: bits 4, group 32/64/128, d_in a multiple of 128; otherwise
  * QALORA_EUNSUPPORTED (qalora_deployed_bytes returns 0).  Workspace: that of
  * QALORA_OP_FORWARD; status word as for qalora_forward. */
 #define QALORA_DEPLOYED_STREAM_TOKENS 4
@@ -314,8 +318,8 @@ int qalora_pack_factors16(const qalora_desc* desc, const float* alpha, const flo
 
 /* Adapter-free forward y = x W~ of a layer whose factors are stored as above; otherwise as
  * qalora_forward with A = B = NULL.  In the few-token regime (conditions as for qalora_forward) the
- * streaming kernel reads the 16-bit factors directly; beyond that they are expanded to fp32
- * in the workspace first.  Workspace: qalora_workspace_bytes(.., QALORA_OP_FORWARD_FACTORS16). */
+ * streaming kernel reads the 16-bit factors directly, and so does the kernel for up to 64 tokens;
+ * beyond that they are expanded to fp32 in the workspace first.  Workspace: qalora_workspace_bytes(.., QALORA_OP_FORWARD_FACTORS16). */
 int qalora_forward_factors16(const qalora_desc* desc, int tokens, const void* x,
                              const void* packed, const void* factors16, void* y, int y_dtype,
                              void* ws, size_t ws_bytes, void* stream);

@@ -154,6 +154,15 @@ inline bool use_smallt(const qalora_desc& d, int tokens) {
   return plane0_words(d.bits, d.d_in, d.d_out) * 4 < kAddressable;
 }
 
+// The mid-token kernel: the same shapes at every code width, beyond the few-token kernels' range.
+inline bool midt_shape(const qalora_desc& d, int tokens) {
+  if (tokens > MT_MAX_TOKENS) return false;
+  if (d.group != 32 && d.group != 64 && d.group != 128) return false;
+  if (d.d_in % 128 != 0) return false;
+  // (the deployment stream of 4-bit codes is half as large again; triple and stream take the same path)
+  return addressable(d, tokens) && plane0_words(4, d.d_in, d.d_out) * 6 < kAddressable;
+}
+
 // Workspace of the small-token path: one flag and one [16 x slab] fp32 partial per block.
 inline size_t smallt_workspace(const qalora_desc& d, int tokens) {
   const int blocks = (tokens <= 4 || d.bits != 4) ? smallt4_plan(d.d_in, d.d_out, tokens).blocks
@@ -331,9 +340,10 @@ static KeptLayout kept_layout(const qalora_desc& d, int T, int n_parts, const in
   return k;
 }
 
-struct PreparedFactors {  // factor words and column scales made ahead of the call (deployment)
-  const uint32_t* words;
+struct PreparedFactors {  // made ahead of the call (deployment)
+  const uint32_t* words;   // factor words and their column scales
   const float* inv_scale;
+  const void* stream;      // the decode stream
 };
 static int forward_impl(const qalora_desc* d, int tokens, const void* x, const void* packed,
                         const float* alpha, const float* beta, const PartSpec& ps, void* y, int y_dtype,
@@ -343,6 +353,9 @@ static int backward_impl(const qalora_desc* d, int tokens, const void* dy, const
                          const void* kept, bool use_kept, const void* packed, const float* alpha,
                          const float* beta, const PartSpec& ps, void* dx, int dx_dtype, int accumulate,
                          void* ws, size_t ws_bytes, void* stream);
+static int forward_mid(const qalora_desc& d, int tokens, const void* x, const void* packed, const float* alpha,
+                       const float* beta, const void* fac16, const void* dep_stream, void* y, int y_dtype, void* ws,
+                       size_t ws_bytes, hipStream_t st);
 
 // A single layer as one part over all its columns; exactly one of A, B null is an error the
 // caller has checked for.
@@ -466,6 +479,47 @@ int qalora_backward_shared(const qalora_desc* d, int tokens, const void* dy, con
                        dx_dtype, accumulate, ws, ws_bytes, stream);
 }
 
+// The adapter-free forward on the mid-token kernel, in a workspace of plan_forward's size (its row
+// scales and fp16 copy of x stay where they are; flags and partial sums take the place of the
+// factor words and what follows them).  Factors: two planes, or fac16, or the deployment stream.
+// Returns -1 where the kernel does not apply (nothing enqueued), else 0 or a positive error.
+static int forward_mid(const qalora_desc& d, int tokens, const void* x, const void* packed, const float* alpha,
+                       const float* beta, const void* fac16, const void* dep_stream, void* y, int y_dtype, void* ws,
+                       size_t ws_bytes, hipStream_t st) {
+  if (!midt_shape(d, tokens)) return -1;
+  qalora_desc plain = d;
+  plain.rank = 0;
+  const FwdPlan plan = plan_forward(plain, tokens);  // by the shape alone: triple and stream take the same path
+  if (plan.total > ws_bytes) return -1;
+  const int blocks = midt_blocks(d.d_in, d.d_out, tokens, plan.total - plan.fac);
+  if (blocks < 1) return -1;
+  char* w = static_cast<char*>(ws);
+  MidTArgs a{};
+  float2* rs = reinterpret_cast<float2*>(w + plan.rs);
+  uint16_t* x16 = reinterpret_cast<uint16_t*>(w + plan.a16);
+  float* u_none[MAX_PARTS] = {};
+  if (launch_front_forward(static_cast<const uint16_t*>(x), tokens, d.d_in, rs, x16, AdapterParts{}, d.group, nullptr,
+                           u_none, FactorJob{}, st) != hipSuccess)
+    return 1;
+  a.x16 = x16;
+  a.row_scale = rs;
+  a.plane0 = static_cast<const uint32_t*>(packed);
+  a.plane1 = a.plane0 + plane0_words(d.bits, d.d_in, d.d_out);
+  a.alpha = alpha;
+  a.beta = beta;
+  a.fac16 = static_cast<const uint32_t*>(fac16);
+  a.stream = dep_stream;
+  a.out = y;
+  a.flags = reinterpret_cast<unsigned long long*>(w + plan.fac);
+  a.partial = reinterpret_cast<float*>(w + plan.fac + ST_HEAD_BYTES);
+  a.out_bf16 = (y_dtype == QALORA_BF16);
+  a.T = tokens;
+  a.d_in = d.d_in;
+  a.d_out = d.d_out;
+  a.group = d.group;
+  return launch_midt(d.bits, a, blocks, st) == hipSuccess ? 0 : 1;
+}
+
 static int forward_impl(const qalora_desc* d, int tokens, const void* x, const void* packed,
                         const float* alpha, const float* beta, const PartSpec& ps, void* y, int y_dtype,
                         void* kept, bool keep, void* ws, size_t ws_bytes, void* stream,
@@ -516,6 +570,11 @@ static int forward_impl(const qalora_desc* d, int tokens, const void* x, const v
   float2* rs = reinterpret_cast<float2*>(w + plan.rs);
   uint16_t* x16 = reinterpret_cast<uint16_t*>(w + plan.a16);
   const int L = d->d_in / d->group;
+  if (!adapter)
+    if (const int mrc = forward_mid(*d, tokens, x, packed, alpha, beta, nullptr, pre ? pre->stream : nullptr, y, y_dtype,
+                                    ws, plan.total, st);
+        mrc >= 0)
+      return mrc == 0 ? QALORA_OK : QALORA_EHIP;
 
   // front launch: row scales and the fp16 copy of x; the adapter folded into the zero factors
   // and the factor words of the dense kernel; P and s P A for the backward when asked for
@@ -813,7 +872,7 @@ int qalora_forward_deployed(const qalora_desc* d, int tokens, const void* x, con
     if (!packed) return QALORA_EINVAL;
     const DeployLayout l = deploy_layout(*d);
     const PreparedFactors pre{reinterpret_cast<const uint32_t*>(static_cast<const char*>(deployed) + l.words),
-                              reinterpret_cast<const float*>(static_cast<const char*>(deployed) + l.inv)};
+                              reinterpret_cast<const float*>(static_cast<const char*>(deployed) + l.inv), deployed};
     return forward_impl(d, tokens, x, packed, nullptr, nullptr, PartSpec{}, y, y_dtype, nullptr, false, ws,
                         ws_bytes, stream, &pre);
   }
@@ -876,10 +935,14 @@ int qalora_forward_factors16(const qalora_desc* d, int tokens, const void* x, co
     a.group = d->group;
     return launch_smallt(a, as_stream(stream)) == hipSuccess ? QALORA_OK : QALORA_EHIP;
   }
-  // matrix path: expand the factors behind the forward's own workspace and run it
   qalora_desc plain = *d;
   plain.rank = 0;
   const size_t fwd_ws = align_up(qalora_workspace_bytes(&plain, tokens, QALORA_OP_FORWARD));
+  if (const int mrc = forward_mid(*d, tokens, x, packed, nullptr, nullptr, factors16, nullptr, y, y_dtype, ws, fwd_ws,
+                                  as_stream(stream));
+      mrc >= 0)
+    return mrc == 0 ? QALORA_OK : QALORA_EHIP;
+  // matrix path: expand the factors behind the forward's own workspace and run it
   const size_t n = (size_t)(d->d_in / d->group) * d->d_out;
   float* alpha = reinterpret_cast<float*>(static_cast<char*>(ws) + fwd_ws);
   float* beta = reinterpret_cast<float*>(static_cast<char*>(ws) + fwd_ws + align_up(n * 4));

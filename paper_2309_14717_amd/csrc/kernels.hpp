@@ -118,6 +118,28 @@ SmallTPlan smallt4_plan(int d_in, int d_out, int tokens);
 hipError_t launch_smallt4(const SmallTArgs& a, hipStream_t st);  // nonce set by the caller
 hipError_t launch_smallt4_f16(const SmallTArgs& a, hipStream_t st);  // the 16-bit-factor instantiations
 
+// --- midt.hip: adapter-free forward up to 64 tokens, every code width, group 32 / 64 / 128 ------
+constexpr int MT_MAX_TOKENS = 64;
+struct MidTArgs {
+  const uint16_t* x16;     // fp16 [round_up(T, 256), d_in]: x, each row multiplied by its power-of-two scale
+  const float2* row_scale; // [T] (scale, 1/scale)
+  const uint32_t* plane0;  // packed codes
+  const uint32_t* plane1;
+  const float* alpha;      // [L, d_out] fp32 planes,
+  const float* beta;
+  const uint32_t* fac16;   // or words fp16 alpha | fp16 beta << 16,
+  const void* stream;      // or the deployment stream (its factor units; 4-bit codes)
+  void* out;               // [T, d_out] fp32 or bf16
+  float* partial;          // [blocks] fp32 partial tiles
+  unsigned long long* flags;  // [blocks]: set to `nonce` once the block's partial is complete
+  unsigned long long nonce;   // filled in by the launcher, unique per call
+  int out_bf16;
+  int T, d_in, d_out, group;
+};
+// Launch shape, given the room for flags (ST_HEAD_BYTES) and partials behind them; 0 if there is none.
+int midt_blocks(int d_in, int d_out, int tokens, size_t scratch);
+hipError_t launch_midt(int bits, const MidTArgs& a, int blocks, hipStream_t st);  // nonce set here
+
 // --- adapter.hip --------------------------------------------------------------------
 // Rows of the hi (and of the lo) section of a bf16 hi/lo split of a [rank, *] matrix.
 __host__ __device__ inline int rank_pad32(int rank) { return ((rank + 31) / 32) * 32; }

@@ -1,0 +1,75 @@
+"""The adapter-free forward between the few-token kernels and the dense one (up to 64 tokens): edges of its
+token tiles, its slabs of 128 columns and its units of 512 rows, every code width and factor layout,
+against the oracle, against the dense kernel and against itself.
+
+Tolerance: operands are the dense kernel's (two fp16 factors per group and column and their fp16
+combination, each rounded once: 3 * 2^-11 of the column's largest weight), whose bar of 2e-3 of the
+largest output the other tests of that kernel use."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2309_14717_amd import synth
+from helpers import layer_on_gpu, record, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("bits,group,d_in,d_out,tokens", [
+    (4, 32, 384, 640, 33),      # one unit per slab, its fourth chunk absent
+    (4, 32, 1024, 520, 48),     # ragged last slab, two units per slab
+    (4, 64, 640, 264, 49),      # a unit of one chunk; two columns groups, the second nearly empty
+    (4, 128, 4096, 1032, 64),   # one group per chunk, several parts per slab
+    (4, 32, 2688, 4104, 64),    # runs that end inside a slab and go on in the next
+    (3, 32, 1152, 2056, 17),
+    (3, 64, 512, 136, 32),
+    (3, 128, 2048, 1160, 64),
+    (2, 32, 1024, 2048, 33),
+    (2, 64, 896, 72, 31),
+    (2, 128, 4224, 4096, 60),
+])
+def test_mid_token_forward(gpu_api, bits, group, d_in, d_out, tokens):
+    cfg = synth.LayerConfig("mid", tokens + 64, d_in, d_out, bits, group, 8, 0.5, seed=71)
+    L = layer_on_gpu(gpu_api, cfg)
+    d, x = L["desc"], L["x"][:tokens].contiguous()
+    # columns whose groups span twenty binades, growing and shrinking along the rows: the scale that
+    # a column's accumulators carry has to follow
+    alpha, beta = L["g_alpha"].clone(), L["g_beta"].clone()
+    grow = torch.exp2(torch.linspace(-10, 10, alpha.shape[0], device=alpha.device))[:, None]
+    for cols, f in ((slice(3, None, 8), grow), (slice(4, None, 8), grow.flip(0))):
+        alpha[:, cols] *= f
+        beta[:, cols] *= f
+    ref = oracle.forward(L["np"]["x"][:tokens], L["codes"], alpha.cpu().numpy(), beta.cpu().numpy(), group)
+    y = gpu_api.forward(d, x, L["packed"], alpha, beta)
+    # the wide columns would hide the others: each column against its own largest output
+    err = float(np.max(np.abs(y.cpu().numpy() - ref) / np.abs(ref).max(axis=0)))
+    dense = gpu_api.forward(d, L["x"], L["packed"], alpha, beta)[:tokens]
+    dense_err = float(np.max(np.abs(dense.cpu().numpy() - ref) / np.abs(ref).max(axis=0)))
+    record(f"mid-token b={bits} g={group} {d_in}x{d_out} T={tokens}", y=err, dense=dense_err)
+    assert err <= 2e-3
+    assert float(((y - dense).abs().amax(0) / dense.abs().amax(0)).max()) <= 2e-3
+    for _ in range(3):
+        assert torch.equal(gpu_api.forward(d, x, L["packed"], alpha, beta), y)
+    yb = gpu_api.forward(d, x, L["packed"], alpha, beta, out_dtype=torch.bfloat16)
+    assert torch.equal(yb, y.to(torch.bfloat16))
+    if bits == 4:
+        dep = gpu_api.deploy(d, L["packed"], alpha, beta)
+        assert torch.equal(gpu_api.forward_deployed(d, x, dep, packed=L["packed"]), y)
+    f16 = gpu_api.pack_factors16(d, alpha, beta)
+    same = gpu_api.forward(d, x, L["packed"], alpha.half().float(), beta.half().float())
+    assert torch.equal(gpu_api.forward_factors16(d, x, L["packed"], f16), same)
+
+
+def test_mid_token_forward_non_finite(gpu_api):
+    """Infinities and NaN in a group reach the outputs of that column and no other."""
+    cfg = synth.LayerConfig("mid_nan", 40, 1024, 520, 4, 32, 8, 0.5, seed=72)
+    L = layer_on_gpu(gpu_api, cfg)
+    alpha, beta = L["g_alpha"].clone(), L["g_beta"].clone()
+    y0 = gpu_api.forward(L["desc"], L["x"], L["packed"], alpha, beta)
+    alpha[5, 17], beta[31, 300], beta[0, 519] = float("nan"), float("inf"), float("-inf")
+    y = gpu_api.forward(L["desc"], L["x"], L["packed"], alpha, beta)
+    hit = [17, 300, 519]
+    assert not torch.isfinite(y[:, hit]).any()
+    keep = [j for j in range(520) if j not in hit]
+    assert torch.equal(y[:, keep], y0[:, keep])
