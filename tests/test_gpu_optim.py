@@ -83,3 +83,21 @@ def test_adamw_without_clip_needs_no_workspace_and_reruns_identically(gpu_api):
         gpu_api.adamw_step(hp2, 3, p, g, m, v)
         runs.append([x.clone() for x in p])
     assert all(torch.equal(a, b) for a, b in zip(*runs))
+
+
+@pytest.mark.parametrize("which", ["lengths", "dtype", "shape", "strides", "host"])
+def test_adamw_refuses_what_does_not_match(gpu_api, which):
+    make = lambda: [[torch.ones((8, 16), device="cuda") for _ in range(3)] for _ in range(4)]
+    p, g, m, v = make()
+    if which == "lengths":  # the total is right
+        g, m = g + m[:1], m[1:]
+    elif which == "dtype":
+        m[1] = m[1].half()
+    elif which == "shape":
+        v[2] = torch.ones((16, 8), device="cuda")
+    elif which == "strides":
+        g[0] = torch.ones((16, 8), device="cuda").t()
+    else:
+        g[2] = g[2].cpu()
+    with pytest.raises(ValueError):
+        gpu_api.adamw_step(gpu_api.AdamW(1e-3, 0.9, 0.95, 1e-8, 0.0, 0.3), 1, p, g, m, v)
