@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqalora_hip.so")
 SOURCES = ["api.hip", "quantize.hip", "gemm_dq.hip", "adapter.hip", "smallt.hip", "smallt4.hip", "smallt4_f16.hip",
-           "midt.hip", "glue.hip", "optim.hip", "probe.hip", "compensate.hip"]
+           "midt.hip", "gemm_dq_192.hip", "glue.hip", "optim.hip", "probe.hip", "compensate.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -29,7 +29,7 @@ FLAGS = [
 # counter), and the adapter-gradient kernel, whose staging arrays once ended up in scratch
 # unnoticed (a local array the compiler does not promote to registers costs a round trip to
 # memory per element).
-NO_SCRATCH = {"gemm_dq.hip": "gemm_dq_kernel", "midt.hip": "midt_kernel", "smallt.hip": "smallt_kernel", "smallt4.hip": "smallt4_kernel", "smallt4_f16.hip": "smallt4_kernel",
+NO_SCRATCH = {"gemm_dq.hip": "gemm_dq_kernel", "gemm_dq_192.hip": "gemm_dq_kernel", "midt.hip": "midt_kernel", "smallt.hip": "smallt_kernel", "smallt4.hip": "smallt4_kernel", "smallt4_f16.hip": "smallt4_kernel",
               "adapter.hip": ("adapter_grads_kernel", "front_kernel", "front_wide_kernel")}
 
 
