@@ -506,7 +506,46 @@ __device__ __forceinline__ float2 process_row(const uint16_t* __restrict__ src, 
   return sc;
 }
 
+// The same for a long row by a whole block: its pieces stay in registers between the maximum and the
+// conversion up to 256 x 8 x RB elements, a quarter of the registers per thread that a wavefront of its
+// own needs, so long rows are read once at full occupancy.
 template <int RB>
+__device__ __forceinline__ float2 process_row_block(const uint16_t* __restrict__ src, int cols,
+                                                    uint16_t* __restrict__ dst16, uint32_t* wave_amax, int tid) {
+  const int nch = cols / 8;
+  uint32_t amax = 0;
+  uint4 v[RB];
+  for (int base = 0; base < nch; base += 256 * RB) {
+#pragma unroll
+    for (int c = 0; c < RB; ++c) {
+      const int ch = base + c * 256 + tid;
+      v[c] = ch < nch ? *reinterpret_cast<const uint4*>(src + 8 * ch) : uint4{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int c = 0; c < RB; ++c) amax = max_abs_bits(v[c], amax);
+  }
+  amax = wave_max_u32(amax);
+  if ((tid & 63) == 0) wave_amax[tid >> 6] = amax;
+  __syncthreads();
+  amax = max(max(wave_amax[0], wave_amax[1]), max(wave_amax[2], wave_amax[3]));
+  const float2 sc = scale_from_maxbits(amax);
+  if (nch <= 256 * RB) {
+#pragma unroll
+    for (int c = 0; c < RB; ++c) {
+      const int ch = c * 256 + tid;
+      if (ch < nch) *reinterpret_cast<uint4*>(dst16 + 8 * ch) = bf16x8_to_f16x8_scaled(v[c], sc.x);
+    }
+  } else {  // second sweep, served by L2
+    for (int ch = tid; ch < nch; ch += 256)
+      *reinterpret_cast<uint4*>(dst16 + 8 * ch) =
+          bf16x8_to_f16x8_scaled(*reinterpret_cast<const uint4*>(src + 8 * ch), sc.x);
+  }
+  return sc;
+}
+
+// Y_WIDE: rows job 2 takes a block per row instead of a wavefront.  (A template parameter: with both forms
+// in one kernel the launches of rows short enough for a wavefront took 1 us longer each.)
+template <int RB, bool Y_WIDE>
 __global__ __launch_bounds__(256) void front_kernel(const FrontArgs a) {
   extern __shared__ float P_all[];  // [ROWS_PER_BLOCK][L] when pooling
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -598,6 +637,12 @@ __global__ __launch_bounds__(256) void front_kernel(const FrontArgs a) {
   bid -= a.nb_rows1;
   if (bid < a.nb_rows2) {
     // ---- rows job 2: dy -> scale + fp16 copy ----------------------------------------------
+    if constexpr (Y_WIDE) {
+      const float2 sc = process_row_block<RB>(a.y + (size_t)bid * a.d_y, a.d_y, a.y16 + (size_t)bid * a.d_y,
+                                              reinterpret_cast<uint32_t*>(P_all), tid);
+      if (tid == 0) a.rs_y[bid] = sc;
+      return;
+    }
     const int t = bid * ROWS_PER_BLOCK + wave;
     if (t < a.Ty) {
       const float2 sc = process_row<RB>(a.y + (size_t)t * a.d_y, a.d_y, a.y16 + (size_t)t * a.d_y,
@@ -711,6 +756,21 @@ static int factor_cols(int L) {
   return fc;
 }
 
+constexpr size_t kFrontLdsMax = 160 * 1024;  // a compute unit's LDS
+template <int RB, bool Y_WIDE>
+static hipError_t launch_front_as(const FrontArgs& a, int nblocks, size_t smem, hipStream_t st) {
+  if (smem > 48 * 1024) {
+    static std::atomic<uint64_t> granted{0};  // per instantiation
+    if (hipError_t e = grant_dynamic_lds(reinterpret_cast<const void*>(front_kernel<RB, Y_WIDE>), (int)kFrontLdsMax,
+                                         granted);
+        e != hipSuccess)
+      return e;
+  }
+  front_kernel<RB, Y_WIDE><<<nblocks, 256, smem, st>>>(a);
+  return hipGetLastError();
+}
+static hipError_t launch_front_wide(const FrontArgs& a, int rb, int nblocks, size_t smem, hipStream_t st);
+
 static hipError_t launch_front(FrontArgs a, hipStream_t st) {
   const bool prep = a.n_parts > 0 && a.part[0].b_hl;
   const bool transposes = a.n_parts > 0 && a.part[0].u_kept;
@@ -724,7 +784,11 @@ static hipError_t launch_front(FrontArgs a, hipStream_t st) {
   int max_rank = 0;
   for (int p = 0; p < a.n_parts; ++p) max_rank = a.part[p].rank > max_rank ? a.part[p].rank : max_rank;
   a.nb_rows1 = a.x ? ceil_div((a.pool && a.part[0].us_t) ? a.t_pad : a.T, ROWS_PER_BLOCK) : 0;
-  a.nb_rows2 = a.y ? ceil_div(a.Ty, ROWS_PER_BLOCK) : 0;
+  // dy rows that do not fit the smallest register batch of one wavefront: a block each (backward front
+  // launch, 4096 rows of 22016: 123 -> 87 us, 1531 rows of 13824: 44 -> 34; two sweeps, or one at 28 pieces
+  // per lane, before)
+  const bool y_wide = a.y && a.d_y > 512 * ROW_BATCH;
+  a.nb_rows2 = a.y ? (y_wide ? a.Ty : ceil_div(a.Ty, ROWS_PER_BLOCK)) : 0;
   a.nb_prep = 0;
   if (prep)
     for (int p = 0; p < a.n_parts; ++p) {
@@ -737,6 +801,7 @@ static hipError_t launch_front(FrontArgs a, hipStream_t st) {
       (a.x && a.pool) ? ((size_t)ROWS_PER_BLOCK * (a.d_in / a.g) + 4 * ROWS_PER_BLOCK * 128) * sizeof(float) : 0;
   const size_t tr_smem = (size_t)TR_TOK * (max_rank + 1) * sizeof(float);
   if (a.nb_tr > 0 && smem < tr_smem) smem = tr_smem;
+  if (y_wide && smem < 4 * sizeof(uint32_t)) smem = 4 * sizeof(uint32_t);
   a.nb_fac = 0;
   if (a.f_alpha) {
     a.f_cols = factor_cols(a.f_L);
@@ -748,23 +813,15 @@ static hipError_t launch_front(FrontArgs a, hipStream_t st) {
                  : 256 * sizeof(float);
     if (smem < f_smem) smem = f_smem;
   }
-  constexpr size_t kFrontLdsMax = 160 * 1024;  // a compute unit's LDS
   if (smem > kFrontLdsMax) return hipErrorInvalidValue;
   const int nblocks = a.nb_rows1 + a.nb_rows2 + a.nb_tr + a.nb_fac + a.nb_prep;
   if (nblocks == 0) return hipSuccess;
-  // the register batch that holds the launch's longest row (two sweeps beyond 14336 elements)
-  const int longest = std::max(a.x ? a.d_in : 0, a.y ? a.d_y : 0);
+  // the register batch that holds the launch's longest row of one wavefront (two sweeps beyond 14336
+  // elements)
+  const int longest = std::max(a.x ? a.d_in : 0, a.y && !y_wide ? a.d_y : 0);
   auto launch = [&](auto rb) -> hipError_t {
     constexpr int RB = decltype(rb)::value;
-    if (smem > 48 * 1024) {
-      static std::atomic<uint64_t> granted{0};  // per instantiation
-      if (hipError_t e = grant_dynamic_lds(reinterpret_cast<const void*>(front_kernel<RB>), (int)kFrontLdsMax,
-                                           granted);
-          e != hipSuccess)
-        return e;
-    }
-    front_kernel<RB><<<nblocks, 256, smem, st>>>(a);
-    return hipGetLastError();
+    return y_wide ? launch_front_wide(a, RB, nblocks, smem, st) : launch_front_as<RB, false>(a, nblocks, smem, st);
   };
   // ... when the rows are most of the launch: the larger batches cost occupancy, which a launch
   // whose factor job is the longer part pays back with interest (measured at 5120 x 13824 with
@@ -775,6 +832,8 @@ static hipError_t launch_front(FrontArgs a, hipStream_t st) {
     if (longest > 512 * 8 && longest <= 512 * 16) return launch(std::integral_constant<int, 16>{});
     if (longest > 512 * 16 && longest <= 512 * 28) return launch(std::integral_constant<int, 28>{});
   }
+  // a block's batch of ROW_BATCH holds rows of up to 16384 elements, one of 16 twice that
+  if (y_wide && a.d_y > 2048 * ROW_BATCH && a.d_y <= 2048 * 16) return launch(std::integral_constant<int, 16>{});
   return launch(std::integral_constant<int, ROW_BATCH>{});
 }
 
@@ -1307,6 +1366,14 @@ hipError_t launch_zero_point(const float* alpha, const float* in, float* out, si
                                                      reinterpret_cast<const f32x4*>(in),
                                                      reinterpret_cast<f32x4*>(out), n4);
   return hipGetLastError();
+}
+
+// (last in the file: the launches of the other form, on the same instructions, were about 1 us slower with
+// these kernels placed between them)
+static hipError_t launch_front_wide(const FrontArgs& a, int rb, int nblocks, size_t smem, hipStream_t st) {
+  if (rb == 28) return launch_front_as<28, true>(a, nblocks, smem, st);
+  if (rb == 16) return launch_front_as<16, true>(a, nblocks, smem, st);
+  return launch_front_as<ROW_BATCH, true>(a, nblocks, smem, st);
 }
 
 }  // namespace qalora
