@@ -55,6 +55,13 @@ __device__ __forceinline__ void split_bf16(float v, uint16_t& hi, uint16_t& lo) 
 __host__ __device__ constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 __host__ __device__ constexpr int round_up(int a, int b) { return ceil_div(a, b) * b; }
 
+// Rows between the first 64 rows of a tile at row m0 and the 64 rows that load `band` of it fetches, in a
+// copy of `padded` rows (a multiple of 64, like m0).  A tile may end past the copy: bands past it fetch the
+// first 64 rows again (their results are never stored), so that no address leaves the copy.
+__host__ __device__ constexpr int tile_band_rows(int m0, int band, int padded) {
+  return m0 + 64 * band < padded ? 64 * band : 0;
+}
+
 // ---------------------------------------------------------------------------
 // Private packed-code format.
 //

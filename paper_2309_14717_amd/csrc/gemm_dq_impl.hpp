@@ -247,9 +247,10 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
   // lane i lands at byte 16*i of it, so it fetches the (row, chunk) the swizzle puts there.
   // Rows past M are clamped to the last row (their results are never stored); K chunks past
   // the end re-read chunk 0 (the B tile is zero there, any finite data will do).
-  const __amdgpu_buffer_rsrc_t rs_a_main = make_rsrc(
-      // (192-row tiles may end past the copies, which are padded to 256 rows: what is beyond reads zero)
-      p.a_main, HAS_MAIN ? (size_t)(FAST ? round_up(p.M, BM == 192 ? 256 : BM) : p.M) * p.lda_main * 2 : 0);
+  constexpr int A_PAD = BM == 192 ? 256 : BM;  // rows the copies are padded to a multiple of, as far as this tile needs
+  const int a_padded = round_up(p.M, A_PAD);
+  const __amdgpu_buffer_rsrc_t rs_a_main =
+      make_rsrc(p.a_main, HAS_MAIN ? (size_t)(FAST ? a_padded : p.M) * p.lda_main * 2 : 0);
   const __amdgpu_buffer_rsrc_t rs_a_tail = make_rsrc(p.a_tail, (size_t)p.M * p.lda_tail * 2);
   uint32_t a_row[A_LOADS];  // global row of each load (rows past M read as zero)
   int a_chunk8[A_LOADS];
@@ -260,9 +261,13 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
     a_row[q] = (uint32_t)(m0 + n);
     a_chunk8[q] = 8 * c;
   }
-  // fast path: one lane offset for all loads of the kernel (rows of later loads are 64*q
-  // further down; the copies are padded to whole tiles, so no row check is needed)
+  // fast path: one lane offset for all loads of the kernel; the rows of later loads, 64*q further
+  // down, are a scalar offset.  The copies are padded to whole tiles, so no row check is needed,
+  // except for 192-row tiles, which can end up to 128 rows past the padding.
   const uint32_t a_voff_main = (a_row[0] * (uint32_t)p.lda_main + (uint32_t)a_chunk8[0]) * 2u;
+  auto a_band = [&](int q) {
+    return (uint32_t)(BM % A_PAD == 0 ? 64 * q : tile_band_rows(m0, q, a_padded)) * (uint32_t)p.lda_main * 2u;
+  };
   // `live` = false (a step past the end of the K range): same number of loads, aimed outside
   // the buffer, so the in-flight count the waits rely on does not depend on the position.
   auto issue_a = [&](auto kind, int it, uint16_t* a_dst, bool live) {
@@ -270,14 +275,14 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
     const int k0 = kMain ? (it - nk_tail) * BK : it * BK;
     if constexpr (FAST && kMain) {
       // branch-free on purpose: OR-ing the mask into a valid offset puts it past any buffer
-      // (the range check looks at the vector offset alone, whatever the scalar offset is).
+      // (the range check looks at the vector offset, whatever the scalar offset is; so a scalar
+      // offset must not lead out of the buffer by itself, see a_band).
       // A branch around a load would make the compiler's count of loads in flight -- and with
       // it every wait it inserts for the code registers -- one too strict.
       const uint32_t voff = a_voff_main | (live ? 0u : kOobOffset);
 #pragma unroll
       for (int q = 0; q < A_LOADS; ++q) {
-        const uint32_t soff = (uint32_t)(QALORA_ABLATE == 3 ? (k0 & 255) : k0) * 2u +
-                              (uint32_t)q * 64u * (uint32_t)p.lda_main * 2u;
+        const uint32_t soff = (uint32_t)(QALORA_ABLATE == 3 ? (k0 & 255) : k0) * 2u + a_band(q);
         uint16_t* dst = a_dst + (q * 8 + wave) * 512;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a_main,
                                                  (__attribute__((address_space(3))) void*)dst, 16,

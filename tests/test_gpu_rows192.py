@@ -17,6 +17,8 @@ pytestmark = pytest.mark.gpu
     (4, 32, 129, 512, 520),    # one tile, mostly padding
     (4, 64, 192, 768, 256),    # one whole tile
     (3, 32, 193, 512, 520),    # a second tile of one row
+    (4, 32, 200, 512, 520),    # tiles end 128 rows past the copies
+    (2, 32, 960, 320, 520),    # five whole tiles, 64 rows short of the copies
     (2, 32, 384, 320, 1032),   # two whole tiles
     (3, 64, 320, 640, 776),
     (4, 32, 600, 256, 22016),  # 256-row tiles leave a ragged round: 258 blocks
