@@ -43,12 +43,13 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "compensate_addr.hpp"
 #include "kernels.hpp"
 
 namespace qalora {
 
 namespace {
-constexpr int kBlock = 128;              // rows per lazy block (a multiple of every supported group size)
+constexpr int kBlock = kCompBlock;
 constexpr int kCols = 16;                // columns per thread block
 constexpr int kTiles = kBlock / 16;      // 16-row tiles of a panel
 constexpr int kUpd = 3;                  // updating wavefronts: three tiles (48 rows) each, the last one two
@@ -152,15 +153,15 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
       float u[kTiles][4][NT];  // U of one block of rows, eight pieces of 16
       f32x4 ev[kTiles];        // the block's errors
       const uint32_t e_off = 4u * (uint32_t)e_lane, e_step = 64u * (uint32_t)nc;  // bytes
-      auto rs_u = [&](int blk) { return rsrc(U + (size_t)blk * kBlock * d_in, (size_t)min(kBlock, d_in - blk * kBlock) * row_b); };
+      auto rs_u = [&](int blk) { return rsrc(U + (size_t)blk * kBlock * d_in, (size_t)comp_block_rows(d_in, blk) * row_b); };
       auto rs_e = [&](int blk) { return rsrc(err + (size_t)blk * kBlock * nc, (size_t)kTiles * e_step); };
       // U operand: lane (row m = n of the tiles, kb) supplies U[i + 4 q + kb][r0 + NT n + h]; columns
       // outside the matrix are some other element of the block's rows (or zero): never used
-      auto u_offset = [&](int r0) { return (uint32_t)kb * row_b + 4u * (uint32_t)(r0 + NT * n); };
+      auto u_offset = [&](int r0) { return comp_update_lane(row_b, NT, r0, n, kb); };
       auto load_u = [&](int k, __amdgpu_buffer_rsrc_t r, uint32_t off) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const uint32_t so = (uint32_t)(16 * k + 4 * q) * row_b;
+          const uint32_t so = comp_update_row(row_b, k, q);
           if constexpr (NT == 3) {
             const u32x3 v = __builtin_amdgcn_raw_buffer_load_b96(r, (int)off, (int)so, 0);
 #pragma unroll
@@ -177,8 +178,10 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
       int r0 = kBlock + 48 * wave;
       uint32_t u_off = u_offset(r0);
       load_w(nt_c, r0, cur);
+      if (comp_updates(panels)) {
 #pragma unroll
-      for (int k = 0; k < kTiles; ++k) load_u(k, rs_u(0), u_off);
+        for (int k = 0; k < kTiles; ++k) load_u(k, rs_u(0), u_off);
+      }
       lds_barrier();  // the first panel is in place
       for (int pn = 0; pn < panels; ++pn) {
         const bool work = pn + 1 < panels;  // (rows past the end of a ragged last panel are carried along as zeros)
@@ -256,7 +259,8 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
   for (int pn = 0; pn < panels; ++pn) {
     const int i1 = pn * kBlock;
     // U's rows of the panel; columns outside the matrix are pointed past the buffer
-    const __amdgpu_buffer_rsrc_t rs_u = rsrc(U + (size_t)i1 * d_in, (size_t)min(kBlock, d_in - i1) * row_b);
+    const int rows = comp_block_rows(d_in, pn);
+    const __amdgpu_buffer_rsrc_t rs_u = rsrc(U + (size_t)i1 * d_in, (size_t)rows * row_b);
     bool odd = false;  // a diagonal element outside the reciprocal's range
 #pragma unroll
     for (int h = 0; h < kBlock / 64; ++h) {
@@ -274,7 +278,7 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
     auto load_diag = [&](int s) {
       const int i0 = i1 + 16 * s, c = i0 + 4 * (lane & 3);  // d_in is a multiple of 8: all four or none
       const bool ok = c < d_in && i0 + (lane >> 2) < d_in;
-      return load4(rs_u, ok ? (uint32_t)(lane >> 2) * row_b + 4u * (uint32_t)c : kOob, 16u * s * row_b);
+      return load4(rs_u, ok ? (uint32_t)(lane >> 2) * row_b + 4u * (uint32_t)c : kOob, comp_walk_row(row_b, rows, s, 0));
     };
     f32x4 dg = load_diag(0);
     uint32_t hiword = 0;  // 3 bits: the high-bit word, two sub-blocks per word
@@ -291,7 +295,7 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
         const int c = row0 + 16 * t + n;
         const uint32_t vo = s + t < kTiles && c < d_in ? (uint32_t)kb * row_b + 4u * (uint32_t)c : kOob;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) au[t - 1][q] = load1(rs_u, vo, (uint32_t)(16 * s + 4 * q) * row_b);
+        for (int q = 0; q < 4; ++q) au[t - 1][q] = load1(rs_u, vo, comp_walk_row(row_b, rows, s, q));
       }
       __builtin_amdgcn_sched_barrier(0);
       asm volatile("" ::: "memory");  // one wavefront: its LDS accesses complete in order

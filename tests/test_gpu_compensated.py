@@ -34,6 +34,10 @@ def test_compensated_bit_exact(gpu_api, bits, g, d_in, d_out):
 @pytest.mark.parametrize("bits,g,d_in,d_out,w_exp,u_exp,kind", [
     (4, 8, 136, 8, 0, 0, "plain"),       # a panel and half a tile; groups inside a tile; half a column block
     (4, 8, 8, 16, 0, 0, "plain"),
+    (4, 32, 64, 24, 0, 0, "plain"),      # one panel, not a whole one
+    (4, 8, 120, 40, 0, 0, "plain"),
+    (3, 32, 96, 16, 0, 0, "plain"),
+    (4, 8, 264, 24, 0, 0, "plain"),      # half a tile in the last of three panels
     (4, 128, 256, 24, 0, 0, "plain"),    # a group per panel
     (3, 32, 416, 40, 0, 0, "plain"),     # high-bit words of a ragged last panel
     (2, 16, 144, 56, 0, 0, "plain"),
