@@ -5,6 +5,7 @@ Run as ``python -m paper_2309_14717_amd.build``.  hipcc cross-compiles without a
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -16,6 +17,7 @@ LIB = os.path.join(HERE, "libqalora_hip.so")
 SOURCES = ["api.hip", "quantize.hip", "gemm_dq.hip", "adapter.hip", "smallt.hip", "smallt4.hip", "smallt4_f16.hip",
            "midt.hip", "glue.hip", "optim.hip", "probe.hip", "compensate.hip", "gemm_dq_192.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+LLVM = os.environ.get("HIP_CLANG_PATH", "/opt/rocm/llvm/bin")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed fp32 VALU forms are kept out of the generated code on purpose
@@ -50,6 +52,29 @@ def _check_no_scratch(src: str, remarks: str) -> None:
         raise RuntimeError(f"{src}: kernels that must not use scratch memory do: {bad}")
 
 
+def _device_code(obj: str) -> str:
+    """Assembly listing of the gfx950 code inside a compiled object."""
+    bundle, code = obj + ".bundle", obj + ".gfx950"
+    subprocess.check_call([os.path.join(LLVM, "llvm-objcopy"), "--dump-section", ".hip_fatbin=" + bundle, obj, obj + ".tmp"])
+    subprocess.check_call([os.path.join(LLVM, "clang-offload-bundler"), "--type=bc", "--unbundle",
+                           "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", "--input=" + bundle, "--output=" + code])
+    text = subprocess.check_output([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", code], text=True)
+    for f in (bundle, code, obj + ".tmp"):
+        os.remove(f)
+    return text
+
+
+_WIDE_STORE = re.compile(r"\bbuffer_store_(?:dwordx[34]|format_xyzw?)\s+v\[[^\]]*\],\s*[^,]+,\s*s\[[^\]]*\],\s*([a-z]\w*)")
+
+
+def _check_wide_stores(src: str, listing: str) -> None:
+    """Refuse buffer stores of more than 64 bits with a scalar offset register: behind these the compiler lets
+    a vector instruction overwrite the data registers at once, and wrong values have been stored."""
+    bad = [line.strip() for line in listing.splitlines() if _WIDE_STORE.search(line)]
+    if bad:
+        raise RuntimeError(f"{src}: {len(bad)} wide buffer stores with a scalar offset register, the first: {bad[0]}")
+
+
 def _compile(src: str, extra) -> str:
     obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
     cmd = [HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
@@ -62,6 +87,7 @@ def _compile(src: str, extra) -> str:
         _check_no_scratch(src, res.stdout)
     else:
         subprocess.check_call(cmd)
+    _check_wide_stores(src, _device_code(obj))
     return obj
 
 

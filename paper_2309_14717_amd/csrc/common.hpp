@@ -52,6 +52,23 @@ __device__ __forceinline__ void split_bf16(float v, uint16_t& hi, uint16_t& lo) 
   lo = f32_to_bf16_bits(v - bf16_bits_to_f32(hi));
 }
 
+// A block's partial sums on their way to another block: 16-byte stores with the cache policy of a
+// device-scope atomic ("sc1": coherent at the level all compute units share).  The base of the buffer is the
+// block's own and the stores carry no scalar offset: a store of more than 64 bits may still be reading
+// its data registers when the next instruction issues, and the compiler keeps a vector instruction that
+// overwrites them one apart only behind stores without a scalar offset register.  (One with it, followed
+// directly by an add into its first data register, now and then stored the sum's bits in the wavefront's
+// last lanes.)  The build refuses wide stores that have one.
+constexpr int kDeviceCoherent = 16;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t own_partial(float* partial, int block, uint32_t block_bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(partial) + (size_t)block * block_bytes, 0,
+                                           (int)block_bytes, 0x00020000);
+}
+typedef uint32_t partial_vec __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_partial(__amdgpu_buffer_rsrc_t own, partial_vec v, uint32_t offset) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, own, (int)offset, 0, kDeviceCoherent);
+}
+
 __host__ __device__ constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 __host__ __device__ constexpr int round_up(int a, int b) { return ceil_div(a, b) * b; }
 

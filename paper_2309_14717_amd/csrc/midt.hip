@@ -50,7 +50,6 @@ constexpr int MT_DEEP = 4;                    // chunks of 128 rows per unit, on
 constexpr uint32_t MT_SPIN_LIMIT = 1u << 18;  // bounded wait: the kernel always terminates
 constexpr uint32_t kMtOob = 0xffff0000u;      // beyond every buffer: the range check returns zero
 constexpr int MT_NT = 2;                      // cache policy "nontemporal": streamed once
-constexpr int kDeviceCoherent = 16;           // "sc1": coherent at the level all compute units share
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -254,17 +253,12 @@ __global__ __launch_bounds__(MT_THREADS) void midt_kernel(const MidTArgs p) {
     });
     constexpr uint32_t kBlockBytes = TT * 4 * 128 * 16;
     const __amdgpu_buffer_rsrc_t rs_p = mt_rsrc(p.partial, (size_t)nb * kBlockBytes);
-    const uint32_t p_off = deep < TT ? (uint32_t)(deep * 4 * 128 + ftid) * 16u : kMtOob;  // + q * 2 KB + block, in the scalar offset
+    const uint32_t p_off = deep < TT ? (uint32_t)(deep * 4 * 128 + ftid) * 16u : kMtOob;  // + q * 2 KB
     if (ce < CU) {
       if (deep < TT) {
-        // One vector offset for all of them, the rest in the scalar one: with an offset of its own each
-        // store was followed by a vector add into the first register of the data just handed over,
-        // and the store now and then wrote the sum's bits for the wavefront's last lanes (the compiler
-        // keeps that distance only for stores without a scalar offset).
+        const __amdgpu_buffer_rsrc_t own = own_partial(p.partial, b, kBlockBytes);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, sum[q]), rs_p, (int)p_off,
-                                                 (int)((uint32_t)b * kBlockBytes + (uint32_t)q * 2048u), kDeviceCoherent);
+        for (int q = 0; q < 4; ++q) store_partial(own, __builtin_bit_cast(u32x4, sum[q]), p_off + (uint32_t)q * 2048u);
       }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every store of this wavefront has landed
       __syncthreads();

@@ -341,7 +341,6 @@ __global__ __launch_bounds__(ST_THREADS) void smallt_kernel(const SmallTArgs p) 
     // write-back or invalidate is needed -- those walk a whole L2 and cost far more than the
     // few KB moved here.
     float* tile = reinterpret_cast<float*>(xs);  // [NTOK][ST_SLAB_COLS]
-    constexpr int kDeviceCoherent = 16;          // "sc1"
     constexpr int C4 = ST_SLAB_COLS / 4;         // items per token row
     constexpr int ITEMS_PER_THREAD = (NTOK * C4 + ST_THREADS - 1) / ST_THREADS;
     constexpr int PART_FLOATS = TGS * ST_PARTIAL_FLOATS;  // a block's partial: the [NTOK][512] tile at most
@@ -359,14 +358,14 @@ __global__ __launch_bounds__(ST_THREADS) void smallt_kernel(const SmallTArgs p) 
     const int items = p.T * C4;
     const __amdgpu_buffer_rsrc_t rs_p = st_rsrc(p.partial, (size_t)gridDim.x * PART_FLOATS * 4);
     if (part < m - 1) {
+      const __amdgpu_buffer_rsrc_t own = own_partial(p.partial, b, PART_FLOATS * 4u);
 #pragma unroll
       for (int k = 0; k < ITEMS_PER_THREAD; ++k) {
         const int it = tid + k * ST_THREADS;
         if (it < items) {
           const int r = it / C4, c4 = it - r * C4;
           const u32x4 v = *reinterpret_cast<const u32x4*>(tile + r * ST_SLAB_COLS + 4 * c4);
-          __builtin_amdgcn_raw_buffer_store_b128(v, rs_p, (r * ST_SLAB_COLS + 4 * c4) * 4,
-                                                 (int)((uint32_t)b * (PART_FLOATS * 4u)), kDeviceCoherent);
+          store_partial(own, v, (uint32_t)(r * ST_SLAB_COLS + 4 * c4) * 4u);
         }
       }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every store of this wavefront has landed

@@ -386,7 +386,6 @@ __global__ __launch_bounds__(S4_THREADS) void smallt4_kernel(const SmallTArgs p)
   // They carry the cache policy of a device-scope atomic (coherent at the level all compute
   // units share), so no cache write-back or invalidate is needed.
   float* tile = reinterpret_cast<float*>(xs);  // [NTOK][SLAB_COLS]
-  constexpr int kDeviceCoherent = 16;          // "sc1"
   constexpr int C4 = SLAB_COLS / 4;            // items per token row
   constexpr int ITEMS_PER_THREAD = (NTOK * C4 + S4_THREADS - 1) / S4_THREADS;
   static_assert(NTOK * SLAB_COLS <= ST_PARTIAL_FLOATS, "a partial holds the whole tile");
@@ -401,14 +400,14 @@ __global__ __launch_bounds__(S4_THREADS) void smallt4_kernel(const SmallTArgs p)
   const int items = p.T * C4;
   const __amdgpu_buffer_rsrc_t rs_p = s4_rsrc(p.partial, (size_t)gridDim.x * ST_PARTIAL_FLOATS * 4);
   if (part < m - 1) {
+    const __amdgpu_buffer_rsrc_t own = own_partial(p.partial, b, ST_PARTIAL_FLOATS * 4u);
 #pragma unroll
     for (int k = 0; k < ITEMS_PER_THREAD; ++k) {
       const int it = tid + k * S4_THREADS;
       if (it < items) {
         const int r = it / C4, c4 = it - r * C4;
         const u32x4 v = *reinterpret_cast<const u32x4*>(tile + r * SLAB_COLS + 4 * c4);
-        __builtin_amdgcn_raw_buffer_store_b128(v, rs_p, (r * SLAB_COLS + 4 * c4) * 4,
-                                               (int)((uint32_t)b * (ST_PARTIAL_FLOATS * 4u)), kDeviceCoherent);
+        store_partial(own, v, (uint32_t)(r * SLAB_COLS + 4 * c4) * 4u);
       }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every store of this wavefront has landed
