@@ -482,8 +482,10 @@ __global__ __launch_bounds__(MT_THREADS) void midt_kernel(const MidTArgs p) {
   };
   Pos p0{s_last, s_last == s_first ? c_first : 0, u1 - s_last * CU};
   load_x(lds, p0);
+  __builtin_amdgcn_sched_barrier(0);  // the wait counts on x being requested before the rest
   load_fac(p0);
   static_for<0, 4>([&](auto st) { load_step(st, p0); });
+  __builtin_amdgcn_sched_barrier(0);
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NLOADS) : "memory");
   int x_cur = 0;
 #pragma nounroll

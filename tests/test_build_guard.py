@@ -60,3 +60,25 @@ def test_the_built_kernels_have_none():
         b._check_wide_stores(src, text)
         stores += len(re.findall(r"buffer_store_dwordx4\b", text))
     assert stores > 0   # (the hand-over of partial sums: the listing is read as it should be)
+
+
+def test_counted_waits_cover_the_lds_loads():
+    """midt_kernel waits for x in LDS by counting: all but the newest n memory operations.  That covers the
+    LDS loads only if at least n others were requested after the last of them."""
+    obj = os.path.join(b.OBJ, "midt.o")
+    if not os.path.exists(obj):
+        pytest.skip("not built here")
+    waits = 0
+    for kernel in re.split(r"\n(?=[0-9a-f]+ <)", b._device_code(obj)):
+        if "midt_kernel" not in kernel.split("\n", 1)[0]:
+            continue
+        lines = [ln.split("//")[0].strip() for ln in kernel.splitlines()]
+        since = None   # memory operations since the last LDS load
+        for ln, nxt in zip(lines, lines[1:]):
+            if re.match(r"(buffer|global)_(load|store|atomic)", ln):
+                since = 0 if ln.endswith(" lds") else (None if since is None else since + 1)
+            m = re.match(r"s_waitcnt vmcnt\((\d+)\) lgkmcnt\(0\)", ln)
+            if m and int(m.group(1)) > 0 and nxt == "s_barrier":
+                assert since is not None and since >= int(m.group(1)), (lines[0], ln)
+                waits += 1
+    assert waits >= 2 * 21   # prologue and loop of every instantiation
