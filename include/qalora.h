@@ -174,9 +174,9 @@ int qalora_pack(const qalora_desc* desc, const uint8_t* codes, void* packed, voi
  * (e.g. when allocating ws) and reads it after the stream has completed; after a non-zero
  * status the first QALORA_WS_STATUS_OFFSET bytes of ws must be zeroed before ws is used again
  * (a late flag of the failed call may still be there).  From there to 64 tokens, same shapes, a
- * kernel with the operands described first (two fp16 factors) serves the adapter-free layer; its sum
- * across blocks waits in the same way, with NaN outputs and no status word should a wait run out
- * (a captured call may be replayed after that only once ws has been zeroed). */
+ * kernel with the operands described first (two fp16 factors) serves the adapter-free layer, in most
+ * cases; its sum across blocks waits in the same way, with the same status word and the same to do
+ * after a wait that ran out (also before a captured call is replayed). */
 #define QALORA_WS_STATUS_OFFSET 2048
 int qalora_forward(const qalora_desc* desc, int tokens, const void* x, const void* packed,
                    const float* alpha, const float* beta, const float* A, const float* B,

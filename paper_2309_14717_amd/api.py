@@ -412,7 +412,7 @@ WS_STATUS_OFFSET = 2048
 
 
 def streaming_status(ws) -> int:
-    """The status word the few-token kernels set in a forward workspace when a bounded wait ran
+    """The status word the kernels for up to 64 tokens set in a forward workspace when a bounded wait ran
     out (0 = never, provided the caller zeroed it first).  Synchronises."""
     _need(ws, "ws", nbytes=WS_STATUS_OFFSET + 8)
     return int(ws.view(torch.uint8)[WS_STATUS_OFFSET:WS_STATUS_OFFSET + 8].cpu().view(torch.int64).item())

@@ -479,9 +479,9 @@ int qalora_backward_shared(const qalora_desc* d, int tokens, const void* dy, con
                        dx_dtype, accumulate, ws, ws_bytes, stream);
 }
 
-// The adapter-free forward on the mid-token kernel, in a workspace of plan_forward's size (its row
-// scales and fp16 copy of x stay where they are; flags and partial sums take the place of the
-// factor words and what follows them).  Factors: two planes, or fac16, or the deployment stream.
+// The adapter-free forward on the mid-token kernel, in a workspace of plan_forward's size: flags and
+// status word first, where the few-token kernels have them, then row scales and fp16 copy of x, and the
+// partial sums in what the factor words and whatever follows them leave.  Factors: two planes, or fac16, or the deployment stream.
 // Returns -1 where the kernel does not apply (nothing enqueued), else 0 or a positive error.
 static int forward_mid(const qalora_desc& d, int tokens, const void* x, const void* packed, const float* alpha,
                        const float* beta, const void* fac16, const void* dep_stream, void* y, int y_dtype, void* ws,
@@ -491,12 +491,14 @@ static int forward_mid(const qalora_desc& d, int tokens, const void* x, const vo
   plain.rank = 0;
   const FwdPlan plan = plan_forward(plain, tokens);  // by the shape alone: triple and stream take the same path
   if (plan.total > ws_bytes) return -1;
-  const int blocks = midt_blocks(d.d_in, d.d_out, tokens, plan.total - plan.fac);
+  const size_t scratch = plan.total - plan.fac;  // for flags and partials: none (and no waits) where that is too little
+  const int blocks = midt_blocks(d.d_in, d.d_out, tokens, scratch);
   if (blocks < 1) return -1;
+  const size_t head = scratch < ST_HEAD_BYTES ? 0 : ST_HEAD_BYTES;
   char* w = static_cast<char*>(ws);
   MidTArgs a{};
-  float2* rs = reinterpret_cast<float2*>(w + plan.rs);
-  uint16_t* x16 = reinterpret_cast<uint16_t*>(w + plan.a16);
+  float2* rs = reinterpret_cast<float2*>(w + head + plan.rs);
+  uint16_t* x16 = reinterpret_cast<uint16_t*>(w + head + plan.a16);
   float* u_none[MAX_PARTS] = {};
   if (launch_front_forward(static_cast<const uint16_t*>(x), tokens, d.d_in, rs, x16, AdapterParts{}, d.group, nullptr,
                            u_none, FactorJob{}, st) != hipSuccess)
@@ -510,8 +512,9 @@ static int forward_mid(const qalora_desc& d, int tokens, const void* x, const vo
   a.fac16 = static_cast<const uint32_t*>(fac16);
   a.stream = dep_stream;
   a.out = y;
-  a.flags = reinterpret_cast<unsigned long long*>(w + plan.fac);
-  a.partial = reinterpret_cast<float*>(w + plan.fac + ST_HEAD_BYTES);
+  a.flags = reinterpret_cast<unsigned long long*>(w);
+  a.status = a.flags + ST_MAX_BLOCKS;
+  a.partial = reinterpret_cast<float*>(w + head + plan.fac);
   a.out_bf16 = (y_dtype == QALORA_BF16);
   a.T = tokens;
   a.d_in = d.d_in;

@@ -68,8 +68,9 @@ int gemm_plain_tile_rows(int K);  // row tile launch_gemm_plain uses for a K of 
 // Adapter-free forward for T <= 16 tokens, INT4, group 32 / 64 / 128 (memory-bound path).
 constexpr int ST_MAX_BLOCKS = 256; // one block per compute unit
 constexpr int ST_PARTIAL_FLOATS = 16 * 512;  // one [16 tokens x widest slab] tile per block
-// Head of the small-token workspace: one 64-bit flag per block, then one 64-bit status word that
-// a kernel sets (and never clears) when a bounded wait for a flag ran out; partials follow.
+// Head of the workspace of the kernels whose blocks wait for each other (up to 64 tokens): one 64-bit
+// flag per block, then one 64-bit status word that a kernel sets (and never clears) when a bounded
+// wait for a flag ran out; what else the kernel needs follows.
 constexpr size_t ST_STATUS_OFFSET = (size_t)ST_MAX_BLOCKS * 8;
 constexpr size_t ST_HEAD_BYTES = ((ST_STATUS_OFFSET + 8 + 255) / 256) * 256;
 struct SmallTArgs {
@@ -132,6 +133,7 @@ struct MidTArgs {
   void* out;               // [T, d_out] fp32 or bf16
   float* partial;          // [blocks] fp32 partial tiles
   unsigned long long* flags;  // [blocks]: set to `nonce` once the block's partial is complete
+  unsigned long long* status; // one word: set to a non-zero value if a wait for a flag ran out
   unsigned long long nonce;   // filled in by the launcher, unique per call
   int out_bf16;
   int T, d_in, d_out, group;

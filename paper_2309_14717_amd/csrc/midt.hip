@@ -29,8 +29,8 @@
 // partials of the blocks before it in their order and writes y.  (Slabs of 256 columns and 256 rows have
 // twice the parts, each twice the size, for half as many blocks to add: 64 tokens of 22016 x 8192 took
 // 55.4 us with them, 50 with these, 86 on the dense kernel with its factor launch.)  Waits are on
-// lower-numbered blocks only and bounded (a wait that runs out gives NaN outputs); every order of
-// summation is fixed by the shape.
+// lower-numbered blocks only and bounded (a wait that runs out gives NaN outputs and sets the
+// workspace's status word); every order of summation is fixed by the shape.
 // x goes through LDS by LDS-DMA, double-buffered, its 16-byte pieces XOR-swizzled by the token so
 // that operand reads are conflict free.
 #include <atomic>
@@ -281,7 +281,10 @@ __global__ __launch_bounds__(MT_THREADS) void midt_kernel(const MidTArgs p) {
           __builtin_amdgcn_s_sleep(1);
         }
         // consumed: cleared, so that a replay of a captured launch waits for its own producers
-        if (!timed_out) __hip_atomic_store(p.flags + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!timed_out)
+          __hip_atomic_store(p.flags + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+          __hip_atomic_store(p.status, p.nonce | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
       __syncthreads();
       bad = poison != 0;

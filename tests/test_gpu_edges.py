@@ -204,6 +204,30 @@ def test_streaming_status_word_stays_clear(gpu_api):
     assert gpu_api.streaming_status(ws) == 0
 
 
+@pytest.mark.parametrize("layout", ["triple", "deployed", "factors16"])
+def test_status_word_stays_clear_up_to_64_tokens(gpu_api, layout):
+    """The same of the kernel for 33 to 64 tokens (deployed from 5), whose blocks wait for each other too: its
+    flags and the word are where the few-token kernels have them, so one workspace serves both."""
+    cfg = synth.LayerConfig("stat", 64, 4096, 4096, 4, 64, 8, 0.5, seed=6)
+    L = layer_on_gpu(gpu_api, cfg)
+    d, ab = L["desc"], (L["g_alpha"], L["g_beta"])
+    op = gpu_api.OP_FORWARD_FACTORS16 if layout == "factors16" else gpu_api.OP_FORWARD
+    ws = torch.zeros(gpu_api.workspace_bytes(d, 64, op), dtype=torch.uint8, device="cuda")
+    dep = gpu_api.deploy(d, L["packed"], *ab)
+    f16 = gpu_api.pack_factors16(d, *ab)
+    for T in (64, 40, 4, 64):
+        x = L["x"][:T].contiguous()
+        if layout == "triple":
+            gpu_api.forward(d, x, L["packed"], *ab, ws=ws)
+        elif layout == "deployed":
+            gpu_api.forward_deployed(d, x, dep, packed=L["packed"], ws=ws)
+        else:
+            gpu_api.forward_factors16(d, x, L["packed"], f16, ws=ws)
+        assert gpu_api.streaming_status(ws) == 0, T
+        flags = ws.view(torch.int64)[:256]
+        assert int(flags.count_nonzero()) == 0, T   # every flag raised has been consumed
+
+
 @pytest.mark.parametrize("w_std", [1e-5, 1e-7, 30.0])
 def test_weights_far_from_unit_scale(gpu_api, w_std):
     """The dense path converts the factors to fp16 only after a power-of-two scale of its own
