@@ -12,8 +12,9 @@
 //   * The fp16 factors are made here from alpha and beta (fp32 planes, fp16 pairs or the deployment
 //     stream), so there is no factor launch and no second trip of the factors through memory.
 //     The scale of a column is kept by the wavefront: it starts from the first groups it meets,
-//     four binades below the most, and should a later group exceed it the accumulators of that
-//     column are rescaled (by a power of two: exact).  No column's scale has to be known before.
+//     whose bound it brings where the factor job brings the whole column's, to [2^13, 2^14); should a
+//     later group exceed 2^15 the accumulators of that column are rescaled (by a power of two:
+//     exact).  No column's scale has to be known before, and none ends below the factor job's.
 // What bounds it: the weight's bytes (135 MB of 8192 x 22016 at g = 32 are 25 us) and the issue time
 // of the SIMDs, on which matrix and vector instructions take turns: per 16 columns x 32 rows 60
 // cycles of rebuilding whatever the token count and 16 per sixteen tokens.  (A form with exact
@@ -74,12 +75,13 @@ constexpr int FAC_F32 = 0;  // two fp32 planes [L, d_out]
 constexpr int FAC_F16 = 1;  // one plane of words fp16 alpha | fp16 beta << 16
 constexpr int FAC_DEP = 2;  // the factor units of the deployment stream (4-bit codes)
 
-// Power of two that brings a bound m to [2^9, 2^10), four binades below the limit of 2^14 (one for
-// m = 0 or a non-finite m, as in the factor job).
+// Power of two that brings a bound m to [2^13, 2^14) (one for m = 0 or a non-finite m), as in the factor
+// job; the limit above which a column is rescaled leaves fp16's largest value a factor of two away.
+constexpr float kScaledLimit = 0x1p15f;
 __device__ __forceinline__ float column_scale(float m) {
   const int E = (int)(__float_as_uint(m) >> 23) & 255;
   if (m == 0.0f || E == 255) return 1.0f;
-  int e = 136 - E;
+  int e = 140 - E;
   e = e > 100 ? 100 : (e < -100 ? -100 : e);
   return __uint_as_float((uint32_t)(127 + e) << 23);
 }
@@ -382,7 +384,7 @@ __global__ __launch_bounds__(MT_THREADS) void midt_kernel(const MidTArgs p) {
         own_scales();
         bool over = false;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) over |= bound[e] * own[e] > 0x1p14f;
+        for (int e = 0; e < 4; ++e) over |= bound[e] * own[e] > kScaledLimit;
         if (__any(over)) {  // first unit of a segment, or a group beyond all before it
           float m[4];  // this chunk's bound of columns 4 n + q
           if constexpr (FAC == FAC_DEP) {
@@ -398,7 +400,7 @@ __global__ __launch_bounds__(MT_THREADS) void midt_kernel(const MidTArgs p) {
           }
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            const float ns = m[q] * sc[q] > 0x1p14f ? column_scale(m[q]) : sc[q];
+            const float ns = m[q] * sc[q] > kScaledLimit ? column_scale(m[q]) : sc[q];
             const float ratio = ns * inverse_pow2(sc[q]);
             sc[q] = ns;
             static_for<0, TT>([&](auto t_c) {

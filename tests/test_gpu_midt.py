@@ -61,6 +61,32 @@ def test_mid_token_forward(gpu_api, bits, group, d_in, d_out, tokens):
     assert torch.equal(gpu_api.forward_factors16(d, x, L["packed"], f16), same)
 
 
+@pytest.mark.parametrize("layout", ["triple", "deployed"])
+def test_small_groups_beside_large_ones(gpu_api, layout):
+    """Groups 2^22 below the largest of their column, multiplied by activations that are zero elsewhere: their
+    fp16 factors must stay normal numbers, as they do on the dense kernel (a column's bound is brought to
+    [2^13, 2^14), alpha is a sixteenth of it or more and 2^-14 the smallest normal number).  With a scale
+    four binades lower the error is four times the dense kernel's."""
+    g, d_in, d_out, T = 32, 1024, 1024, 40
+    cfg = synth.LayerConfig("small", 2 * T, d_in, d_out, 4, g, 8, 0.5, seed=73)
+    L = layer_on_gpu(gpu_api, cfg)
+    groups = torch.arange(d_in // g, device="cuda") % 4     # of every chunk the first group is the large one
+    f = torch.where(groups == 0, 1.0, 2.0 ** -22)[:, None]
+    alpha, beta = L["g_alpha"] * f, L["g_beta"] * f
+    x = torch.where(groups.repeat_interleave(g) == 0, torch.zeros((), device="cuda"), L["x"].float()).to(torch.bfloat16)
+    xt = x[:T].contiguous()
+    if layout == "deployed":
+        y = gpu_api.forward_deployed(L["desc"], xt, gpu_api.deploy(L["desc"], L["packed"], alpha, beta), packed=L["packed"])
+    else:
+        y = gpu_api.forward(L["desc"], xt, L["packed"], alpha, beta)
+    ref = oracle.forward(xt.float().cpu().numpy(), L["codes"], alpha.cpu().numpy(), beta.cpu().numpy(), g)
+    err = float(np.max(np.abs(y.cpu().numpy() - ref) / np.abs(ref).max(axis=0)))
+    dense = gpu_api.forward(L["desc"], x, L["packed"], alpha, beta)[:T]
+    dense_err = float(np.max(np.abs(dense.cpu().numpy() - ref) / np.abs(ref).max(axis=0)))
+    record(f"small groups, {layout}", y=err, dense=dense_err)
+    assert dense_err <= 2e-3 and err <= 1.5 * dense_err
+
+
 def test_mid_token_forward_non_finite(gpu_api):
     """Infinities and NaN in a group reach the outputs of that column and no other."""
     cfg = synth.LayerConfig("mid_nan", 40, 1024, 520, 4, 32, 8, 0.5, seed=72)
