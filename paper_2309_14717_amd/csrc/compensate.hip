@@ -360,6 +360,7 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
                 });
                 mn = fminf(mn, __shfl_xor(mn, 16, 64)), mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
                 mn = fminf(mn, __shfl_xor(mn, 32, 64)), mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                if (w[i] != w[i]) mn = mx = w[i];  // a NaN in the group's first row stays (as above), others are passed over
                 if (__any(mn == 0.0f)) {  // a minimum of zero keeps the sign of the first zero of the group
                   int key = 1 << 20;
                   static_for<0, kTiles>([&](auto t_c) {

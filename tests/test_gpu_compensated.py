@@ -71,6 +71,29 @@ def test_compensated_edges(gpu_api, bits, g, d_in, d_out, w_exp, u_exp, kind):
     assert np.array_equal(beta.cpu().numpy().view(np.uint32), b.view(np.uint32))
 
 
+@pytest.mark.parametrize("bits,g", [(4, 8), (4, 16), (4, 32), (3, 64), (2, 128)])
+def test_compensated_non_finite_weights(gpu_api, bits, g):
+    """A NaN or an infinity spoils its column from its row on, in the group's factors too where Eq. 1's running
+    minimum and maximum meet it first; the other columns keep their bits."""
+    d_in, d_out = 384, 40
+    r = np.random.RandomState(g)
+    W = (r.randn(d_in, d_out) * 0.02).astype(np.float32)
+    for k, v in enumerate((np.nan, np.inf, -np.inf)):
+        W[g, 3 + k] = v                 # first row of a group
+        W[128 + g // 2, 13 + k] = v     # inside a group
+        W[0, 23 + k] = v
+    _, U = hessian(d_in, 2 * d_in, seed=4)
+    U32 = np.ascontiguousarray(U.astype(np.float32))
+    desc = gpu_api.make_desc(d_in, d_out, bits, g)
+    packed, alpha, beta = gpu_api.quantize_compensated(desc, dev(W), dev(U32))
+    c, a, b = oracle.quantize_compensated(W, U32, bits, g, block=128)
+    assert np.array_equal(alpha.cpu().numpy(), a, equal_nan=True)
+    assert np.array_equal(beta.cpu().numpy(), b, equal_nan=True)
+    clean = np.isfinite(W).all(axis=0)
+    assert clean.sum() == d_out - 9
+    assert np.array_equal(gpu_api.unpack(desc, packed).cpu().numpy()[:, clean], c[:, clean])
+
+
 def test_compensated_many_blocks_and_rerun(gpu_api):
     """A layer of sixteen lazy row blocks and 128 column blocks (all compute units busy, two
     block generations), bit for bit against the oracle, and twice: the row lanes of a column
