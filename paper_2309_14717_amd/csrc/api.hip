@@ -4,6 +4,7 @@
 
 #include "common.hpp"
 #include "kernels.hpp"
+#include "midt_plan.hpp"
 
 #include <cmath>
 

@@ -138,8 +138,6 @@ struct MidTArgs {
   int out_bf16;
   int T, d_in, d_out, group;
 };
-// Launch shape, given the room for flags (ST_HEAD_BYTES) and partials behind them; 0 if there is none.
-int midt_blocks(int d_in, int d_out, int tokens, size_t scratch);
 hipError_t launch_midt(int bits, const MidTArgs& a, int blocks, hipStream_t st);  // nonce set here
 
 // --- adapter.hip --------------------------------------------------------------------

@@ -39,6 +39,7 @@
 
 #include "common.hpp"
 #include "kernels.hpp"
+#include "midt_plan.hpp"
 
 namespace qalora {
 
@@ -46,8 +47,6 @@ namespace {
 
 constexpr int MT_WAVES = 8;
 constexpr int MT_THREADS = 64 * MT_WAVES;
-constexpr int MT_SLAB = 128;                  // columns per block: two wavefronts of 64
-constexpr int MT_DEEP = 4;                    // chunks of 128 rows per unit, one per pair of wavefronts
 constexpr uint32_t MT_SPIN_LIMIT = 1u << 18;  // bounded wait: the kernel always terminates
 constexpr uint32_t kMtOob = 0xffff0000u;      // beyond every buffer: the range check returns zero
 constexpr int MT_NT = 2;                      // cache policy "nontemporal": streamed once
@@ -501,42 +500,6 @@ __global__ __launch_bounds__(MT_THREADS) void midt_kernel(const MidTArgs p) {
     p0 = p1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the last unit's prefetch
-}
-
-static int midt_tiles(int tokens) { return tokens <= 32 ? 2 : (tokens <= 48 ? 3 : 4); }
-
-// Blocks of the launch, at most one per compute unit.  More blocks shorten the runs but cut the slabs into
-// more parts, whose sums the block that finishes a slab adds.  Priced in us, fitted to sweeps over the
-// count: a unit 1 + 0.35 per token tile, a hand-over 2 and 0.2 per part, runs that end inside a slab
-// 1.5 (a second flush), and 2.3 for more than 31 blocks per XCD unless the runs are long (64 tokens,
-// 4096 x 4096: 20.3 us on 128 blocks, 19.5 on 224, 20.2 on 248, 22.6 on 255 and 256; 5120 x 13824: 28.5 on
-// 216 = two per slab, 30.1 on 248; 22016 x 8192: 53.4 on 224, 49.8 on 256).  `scratch` bytes hold the flags
-// and a partial per block; runs of whole slabs need none.  0 where that room would cost more than a
-// quarter: the dense kernel is for these.
-int midt_blocks(int d_in, int d_out, int tokens, size_t scratch) {
-  const int CU = ceil_div(d_in / 128, MT_DEEP), S = ceil_div(d_out, MT_SLAB);
-  const long units = (long)S * CU;
-  if (units > (1l << 22)) return 0;
-  const int tt = midt_tiles(tokens);
-  const long room = scratch <= ST_HEAD_BYTES ? 0 : (long)((scratch - ST_HEAD_BYTES) / ((size_t)tt * 4 * 128 * 16));
-  int best = 0;
-  double best_cost = 0, free_cost = 0;  // with the room there is, and with any
-  for (int nb = 1; nb <= ST_MAX_BLOCKS && nb <= units; ++nb) {
-    const long run = (units + nb - 1) / nb;
-    const bool even = units % nb == 0;
-    const bool whole = even && run % CU == 0;                 // runs of whole slabs
-    const bool inside = CU == 1 || whole || (even && CU % run == 0);  // no run goes on into another slab
-    const int n = whole || CU == 1 ? 0 : ceil_div(nb, S) - 1 + !inside;  // sums to wait for, about
-    const double per = inside ? (double)run : (double)units / nb;
-    const double cost = per * (1.0 + 0.35 * tt) + (n > 0 ? 2.0 + 0.2 * n : 0.0) + (inside ? 0.0 : 1.5) +
-                        (nb > 248 && units < 6 * 256 ? 2.3 : 0.0);
-    if (free_cost == 0 || cost < free_cost) free_cost = cost;
-    if ((whole || CU == 1 || nb <= room) && (best == 0 || cost < best_cost)) {
-      best = nb;
-      best_cost = cost;
-    }
-  }
-  return best > 0 && best_cost <= 1.25 * free_cost ? best : 0;
 }
 
 template <int NBITS, int FAC, int TT>

@@ -11,6 +11,6 @@ def host_library(tmp_path, name, source):
     src, so = str(tmp_path / (name + ".hip")), str(tmp_path / (name + ".so"))
     with open(src, "w") as f:
         f.write(source)
-    subprocess.run([b.HIPCC, "--offload-host-only", "-std=c++17", "-O1", "-fPIC", "-shared", "-I", b.CSRC, src, "-o", so],
+    subprocess.run([b.HIPCC, "--offload-host-only", "-std=c++17", "-O3", "-fPIC", "-shared", "-I", b.CSRC, src, "-o", so],
                    check=True, capture_output=True)
     return ctypes.CDLL(os.path.abspath(so))

@@ -1,0 +1,74 @@
+"""The launch shape of the mid-token forward: the search that ends early finds what pricing every block count
+finds, in less host time (every call makes it)."""
+import ctypes
+import random
+
+import pytest
+
+from host_code import host_library
+
+HEAD, PARTIAL = 2304, 4 * 8192   # flags and status word; the partial of a block at 64 tokens
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    lib = host_library(tmp_path_factory.mktemp("plan"), "plan", """
+#include <chrono>
+#include "midt_plan.hpp"
+using namespace qalora;
+extern "C" int blocks(int d_in, int d_out, int tokens, size_t scratch) { return midt_blocks(d_in, d_out, tokens, scratch); }
+// every count from one up, the smallest of equally cheap ones
+extern "C" int full_search(int d_in, int d_out, int tokens, size_t scratch) {
+  const int CU = ceil_div(d_in / 128, MT_DEEP), S = ceil_div(d_out, MT_SLAB);
+  const long units = (long)S * CU;
+  if (units > (1l << 22)) return 0;
+  const int tt = midt_tiles(tokens);
+  const long room = scratch <= ST_HEAD_BYTES ? 0 : (long)((scratch - ST_HEAD_BYTES) / ((size_t)tt * 4 * 128 * 16));
+  int best = 0;
+  double best_cost = 0, free_cost = 0;
+  for (int nb = 1; nb <= ST_MAX_BLOCKS && nb <= units; ++nb) {
+    const long run = (units + nb - 1) / nb;
+    const bool even = units % nb == 0;
+    const bool whole = even && run % CU == 0;
+    const bool inside = CU == 1 || whole || (even && CU % run == 0);
+    const int n = whole || CU == 1 ? 0 : ceil_div(nb, S) - 1 + !inside;
+    const double per = inside ? (double)run : (double)units / nb;
+    const double cost = per * (1.0 + 0.35 * tt) + (n > 0 ? 2.0 + 0.2 * n : 0.0) + (inside ? 0.0 : 1.5) +
+                        (nb > 248 && units < 6 * 256 ? 2.3 : 0.0);
+    if (free_cost == 0 || cost < free_cost) free_cost = cost;
+    if ((whole || CU == 1 || nb <= room) && (best == 0 || cost < best_cost)) {
+      best = nb;
+      best_cost = cost;
+    }
+  }
+  return best > 0 && best_cost <= 1.25 * free_cost ? best : 0;
+}
+extern "C" double us_per_call(int full, int d_in, int d_out) {
+  volatile int sink = 0;
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int i = 0; i < 1000; ++i) sink = sink + (full ? full_search : blocks)(d_in, d_out, 64, 1ul << 30);
+  return std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() / 1000;
+}
+""")
+    lib.us_per_call.restype = ctypes.c_double
+    return lib
+
+
+def test_early_end_changes_no_plan(plan):
+    rng = random.Random(5)
+    shapes = [(4096, 4096), (8192, 22016), (22016, 8192), (5120, 13824), (128, 8), (128, 22016), (1024, 520), (65536, 8192)]
+    shapes += [(128 * rng.randint(1, 172), 8 * rng.randint(1, 2752)) for _ in range(400)]
+    shapes += [(128 * rng.randint(1, 40), 8 * rng.randint(1, 600)) for _ in range(400)]
+    for d_in, d_out in shapes:
+        for tokens in (5, 33, 64):
+            for scratch in (0, HEAD, HEAD + 256 * PARTIAL, rng.randint(HEAD, HEAD + 256 * PARTIAL),
+                            (d_in // rng.choice([32, 64, 128]) + 1) * d_out * 4):
+                args = (d_in, d_out, tokens, ctypes.c_size_t(scratch))
+                assert plan.blocks(*args) == plan.full_search(*args), args[:3] + (scratch,)
+
+
+@pytest.mark.parametrize("d_in,d_out", [(4096, 4096), (8192, 22016), (65536, 8192)])
+def test_search_is_shorter(plan, d_in, d_out):
+    full, early = (min(plan.us_per_call(f, d_in, d_out) for _ in range(7)) for f in (1, 0))
+    print(f"plan {d_in}x{d_out}: {early:.2f} us, all counts {full:.2f}")
+    assert early < 0.75 * full
