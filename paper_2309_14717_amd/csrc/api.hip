@@ -493,7 +493,7 @@ static int forward_mid(const qalora_desc& d, int tokens, const void* x, const vo
   const FwdPlan plan = plan_forward(plain, tokens);  // by the shape alone: triple and stream take the same path
   if (plan.total > ws_bytes) return -1;
   const size_t scratch = plan.total - plan.fac;  // for flags and partials: none (and no waits) where that is too little
-  const int blocks = midt_blocks(d.d_in, d.d_out, tokens, scratch);
+  const int blocks = midt_blocks(d.bits, d.d_in, d.d_out, tokens, scratch);
   if (blocks < 1) return -1;
   const size_t head = scratch < ST_HEAD_BYTES ? 0 : ST_HEAD_BYTES;
   char* w = static_cast<char*>(ws);

@@ -341,25 +341,32 @@ __global__ __launch_bounds__(MT_THREADS) void midt_kernel(const MidTArgs p) {
       __builtin_amdgcn_sched_barrier(0);
       const bool live = MT_DEEP * at.c + deep < C;
       // fp16 factor words fp16(alpha S) | fp16((beta + mid alpha) S) << 16, four per lane: element e is
-      // group kb, column 4 n + e (planes) or group e, column 4 n + kb (stream)
+      // group kb, column 4 n + e (planes) or the group of step e, column 4 n + kb (stream)
       uint32_t fw[4];
       {
-        float al[4], cst[4], bound[4];
+        float al[4], be[4], cst[4], bound[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          float be;
           if constexpr (FAC == FAC_F16) {
             al[e] = (float)__builtin_bit_cast(_Float16, (uint16_t)(fa[e] & 0xffffu));
-            be = (float)__builtin_bit_cast(_Float16, (uint16_t)(fa[e] >> 16));
-          } else if constexpr (FAC == FAC_DEP) {
-            // group 32: alpha of four groups | beta of four; 64: alpha0 alpha1 beta0 beta1; 128: alpha beta - -
-            al[e] = __uint_as_float(sub_sh == 0 ? fa[e] : (sub_sh == 1 ? (e < 2 ? fa[e] : 0u) : (e == 0 ? fa[0] : 0u)));
-            be = __uint_as_float(sub_sh == 0 ? fb[e] : (sub_sh == 1 ? (e < 2 ? fa[(e & 1) + 2] : 0u) : (e == 0 ? fa[1] : 0u)));
+            be[e] = (float)__builtin_bit_cast(_Float16, (uint16_t)(fa[e] >> 16));
           } else {
             al[e] = __uint_as_float(fa[e]);
-            be = __uint_as_float(fb[e]);
+            be[e] = __uint_as_float(fb[e]);
           }
-          cst[e] = __builtin_fmaf(mid, al[e], be);
+        }
+        if constexpr (FAC == FAC_DEP) {  // a factor per step; group 64: alpha0 alpha1 beta0 beta1; 128: alpha beta - -
+          if (sub_sh == 1) {
+            be[0] = be[1] = al[2], be[2] = be[3] = al[3], al[2] = al[3] = al[1], al[1] = al[0];
+            asm volatile("" : "+v"(be[0]));  // (a branch, not selects)
+          } else if (sub_sh == 2) {
+            be[0] = be[1] = be[2] = be[3] = al[1], al[1] = al[2] = al[3] = al[0];
+            asm volatile("" : "+v"(be[0]));
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          cst[e] = __builtin_fmaf(mid, al[e], be[e]);
           bound[e] = __builtin_fmaf(mid, fabsf(al[e]), fabsf(cst[e]));
           // Values are complete before their registers are reloaded (here and below): were any use of the old
           // contents left behind a load, the new ones would land elsewhere and be copied back at the
@@ -420,12 +427,10 @@ __global__ __launch_bounds__(MT_THREADS) void midt_kernel(const MidTArgs p) {
       auto hand_round = [&](auto st_c) {
         constexpr int st = decltype(st_c)::value;
         const int u = st >> sub_sh;  // the step's group inside the chunk
-        uint32_t e = 0;
-        if constexpr (FAC == FAC_DEP) e = sub_sh == 0 ? fw[st] : (sub_sh == 1 ? fw[st >> 1] : fw[0]);  // (constant indices: no scratch)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           if constexpr (FAC == FAC_DEP)
-            fwd[st & 1][q] = (uint32_t)__builtin_amdgcn_ds_bpermute((n + 16 * q) * 4, (int)e);
+            fwd[st & 1][q] = (uint32_t)__builtin_amdgcn_ds_bpermute((n + 16 * q) * 4, (int)fw[st]);
           else
             fwd[st & 1][q] = (uint32_t)__builtin_amdgcn_ds_bpermute((n + 16 * u) * 4, (int)fw[q]);
           if constexpr (NBITS == 3) hw[st & 1][q] = (uint32_t)__builtin_amdgcn_ds_bpermute((n + 16 * q) * 4, (int)chi[st]);

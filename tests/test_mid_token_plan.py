@@ -16,37 +16,32 @@ def plan(tmp_path_factory):
 #include <chrono>
 #include "midt_plan.hpp"
 using namespace qalora;
-extern "C" int blocks(int d_in, int d_out, int tokens, size_t scratch) { return midt_blocks(d_in, d_out, tokens, scratch); }
+extern "C" int blocks(int bits, int d_in, int d_out, int tokens, size_t scratch) {
+  return midt_blocks(bits, d_in, d_out, tokens, scratch);
+}
 // every count from one up, the smallest of equally cheap ones
-extern "C" int full_search(int d_in, int d_out, int tokens, size_t scratch) {
+extern "C" int full_search(int bits, int d_in, int d_out, int tokens, size_t scratch) {
   const int CU = ceil_div(d_in / 128, MT_DEEP), S = ceil_div(d_out, MT_SLAB);
-  const long units = (long)S * CU;
-  if (units > (1l << 22)) return 0;
+  const int units = S * CU;
   const int tt = midt_tiles(tokens);
   const long room = scratch <= ST_HEAD_BYTES ? 0 : (long)((scratch - ST_HEAD_BYTES) / ((size_t)tt * 4 * 128 * 16));
   int best = 0;
   double best_cost = 0, free_cost = 0;
   for (int nb = 1; nb <= ST_MAX_BLOCKS && nb <= units; ++nb) {
-    const long run = (units + nb - 1) / nb;
-    const bool even = units % nb == 0;
-    const bool whole = even && run % CU == 0;
-    const bool inside = CU == 1 || whole || (even && CU % run == 0);
-    const int n = whole || CU == 1 ? 0 : ceil_div(nb, S) - 1 + !inside;
-    const double per = inside ? (double)run : (double)units / nb;
-    const double cost = per * (1.0 + 0.35 * tt) + (n > 0 ? 2.0 + 0.2 * n : 0.0) + (inside ? 0.0 : 1.5) +
-                        (nb > 248 && units < 6 * 256 ? 2.3 : 0.0);
+    const bool whole = midt_whole_slabs(CU, S, nb);
+    const double cost = midt_cost(units, CU, S, midt_unit(bits, tt), tt, nb, ceil_div(nb, S));
     if (free_cost == 0 || cost < free_cost) free_cost = cost;
-    if ((whole || CU == 1 || nb <= room) && (best == 0 || cost < best_cost)) {
+    if ((whole || nb <= room) && (best == 0 || cost < best_cost)) {
       best = nb;
       best_cost = cost;
     }
   }
-  return best > 0 && best_cost <= 1.25 * free_cost ? best : 0;
+  return best > 0 && best_cost <= midt_short_of(bits) * free_cost ? best : 0;
 }
 extern "C" double us_per_call(int full, int d_in, int d_out) {
   volatile int sink = 0;
   const auto t0 = std::chrono::steady_clock::now();
-  for (int i = 0; i < 1000; ++i) sink = sink + (full ? full_search : blocks)(d_in, d_out, 64, 1ul << 30);
+  for (int i = 0; i < 1000; ++i) sink = sink + (full ? full_search : blocks)(4, d_in, d_out, 64, 1ul << 30);
   return std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() / 1000;
 }
 """)
@@ -63,11 +58,22 @@ def test_early_end_changes_no_plan(plan):
         for tokens in (5, 33, 64):
             for scratch in (0, HEAD, HEAD + 256 * PARTIAL, rng.randint(HEAD, HEAD + 256 * PARTIAL),
                             (d_in // rng.choice([32, 64, 128]) + 1) * d_out * 4):
-                args = (d_in, d_out, tokens, ctypes.c_size_t(scratch))
-                assert plan.blocks(*args) == plan.full_search(*args), args[:3] + (scratch,)
+                args = (rng.choice([2, 3, 4]), d_in, d_out, tokens, ctypes.c_size_t(scratch))
+                assert plan.blocks(*args) == plan.full_search(*args), args[:4] + (scratch,)
 
 
-@pytest.mark.parametrize("d_in,d_out", [(4096, 4096), (8192, 22016), (65536, 8192)])
+@pytest.mark.parametrize("bits,d_in,d_out,tokens,blocks", [
+    (4, 2048, 8192, 64, 192), (4, 8192, 8192, 64, 256), (2, 8192, 8192, 24, 256), (3, 8192, 8192, 53, 256),
+])
+def test_counts_that_measured_best(plan, bits, d_in, d_out, tokens, blocks):
+    """A multiple of the slabs' number cuts every slab into as many parts and no run crosses one, whether or
+    not the parts are equally long (2048 x 8192: three parts of four units).  While only equal parts were
+    taken to stay inside a slab 248 blocks were chosen at the first two: 18.9 and 32.2 us against 18.2
+    and 29.6."""
+    assert plan.blocks(bits, d_in, d_out, tokens, ctypes.c_size_t(HEAD + 256 * PARTIAL)) == blocks
+
+
+@pytest.mark.parametrize("d_in,d_out", [(8192, 8192), (8192, 22016), (65536, 8192)])
 def test_search_is_shorter(plan, d_in, d_out):
     full, early = (min(plan.us_per_call(f, d_in, d_out) for _ in range(7)) for f in (1, 0))
     print(f"plan {d_in}x{d_out}: {early:.2f} us, all counts {full:.2f}")
