@@ -786,8 +786,10 @@ static hipError_t launch_front(FrontArgs a, hipStream_t st) {
   a.nb_rows1 = a.x ? ceil_div((a.pool && a.part[0].us_t) ? a.t_pad : a.T, ROWS_PER_BLOCK) : 0;
   // dy rows that do not fit the smallest register batch of one wavefront: a block each (backward front
   // launch, 4096 rows of 22016: 123 -> 87 us, 1531 rows of 13824: 44 -> 34; two sweeps, or one at 28 pieces
-  // per lane, before)
-  const bool y_wide = a.y && a.d_y > 512 * ROW_BATCH;
+  // per lane, before).  Rows beyond 32768 elements take two sweeps either way, and many of them are better
+  // off by wavefronts (forward and backward, 512 x 33000: 1531 tokens 360 us against 373, 512 tokens 188
+  // against 180).
+  const bool y_wide = a.y && a.d_y > 512 * ROW_BATCH && (a.d_y <= 2048 * 16 || a.Ty <= 512);
   a.nb_rows2 = a.y ? (y_wide ? a.Ty : ceil_div(a.Ty, ROWS_PER_BLOCK)) : 0;
   a.nb_prep = 0;
   if (prep)
@@ -832,8 +834,11 @@ static hipError_t launch_front(FrontArgs a, hipStream_t st) {
     if (longest > 512 * 8 && longest <= 512 * 16) return launch(std::integral_constant<int, 16>{});
     if (longest > 512 * 16 && longest <= 512 * 28) return launch(std::integral_constant<int, 28>{});
   }
-  // a block's batch of ROW_BATCH holds rows of up to 16384 elements, one of 16 twice that
-  if (y_wide && a.d_y > 2048 * ROW_BATCH && a.d_y <= 2048 * 16) return launch(std::integral_constant<int, 16>{});
+  // a block's batch of ROW_BATCH holds rows of up to 16384 elements, one of 16 twice that, at the price of
+  // occupancy again: only where the rows outweigh the factor job (forward and backward of 64 tokens,
+  // 1024 x 22016: 117.9 us in two sweeps, 121.4 in one; 512 tokens 158.2 / 158.8 and 161.8 by wavefronts)
+  if (y_wide && a.d_y > 2048 * ROW_BATCH && a.d_y <= 2048 * 16 && row_bytes >= 4 * fac_bytes)
+    return launch(std::integral_constant<int, 16>{});
   return launch(std::integral_constant<int, ROW_BATCH>{});
 }
 

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d_out", [4104, 16384, 16392, 22016, 32768, 32776])
-@pytest.mark.parametrize("tokens", [3, 130])
+@pytest.mark.parametrize("tokens", [3, 130, 520])
 def test_long_gradient_rows(gpu_api, tokens, d_out):
     cfg = synth.LayerConfig("wide", tokens, 128, d_out, 4, 32, 8, 0.5, seed=91)
     L = layer_on_gpu(gpu_api, cfg)
