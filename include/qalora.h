@@ -378,7 +378,8 @@ int qalora_profile_arm(int direction, void* start_event, void* stop_event);
  * again when it ends.  (cycles_end - cycles_start) / (ticks_end - ticks_start) x the wall-clock
  * rate (qalora_profile_wall_clock_khz; 100 MHz on this hardware) is the average shader clock
  * over that block's life -- under load well below the nominal 2.4 GHz that the published
- * matrix-core peak assumes.  The small-token kernel does not report.  NULL disarms. */
+ * matrix-core peak assumes.  The kernels for up to 64 tokens of an adapter-free layer do not report
+ * (nor to qalora_profile_arm_blocks).  NULL disarms. */
 int qalora_profile_arm_clock(int direction, void* counts);
 
 /* Measurement aid: the time line of a launch.  Call after qalora_profile_arm for the same
