@@ -389,6 +389,12 @@ int qalora_profile_arm_clock(int direction, void* counts);
  * XCD it ran on.  Blocks >= capacity store nothing; slices of a split-K launch other than the
  * first store nothing.  NULL disarms; capacity <= 0 with a buffer is QALORA_EINVAL. */
 int qalora_profile_arm_blocks(int direction, void* times, int capacity);
+
+/* Measurement aid: how many blocks the kernel for up to 64 tokens launches for the adapter-free forward of
+ * this layer, or 0 where the dense kernel serves it (beyond 64 tokens, other shapes, or where the
+ * workspace has no room for its partial sums at a worthwhile count).  Counts that a streaming kernel takes
+ * first (see qalora_forward) are answered as if it did not exist, as for a deployed layer.  Host only. */
+int qalora_profile_mid_blocks(const qalora_desc* desc, int tokens, int* blocks /* host */);
 int qalora_profile_wall_clock_khz(int* khz /* host */);
 
 /* Create / time / destroy timing events for qalora_profile_arm (thin wrappers over

@@ -27,6 +27,7 @@ EXPORTS = (
     "qalora_profile_event_elapsed_ms", "qalora_profile_event_destroy", "qalora_profile_copy",
     "qalora_swiglu_forward", "qalora_swiglu_backward",
     "qalora_profile_arm_clock", "qalora_profile_arm_blocks", "qalora_profile_wall_clock_khz",
+    "qalora_profile_mid_blocks",
     "qalora_beta_from_zero_point", "qalora_zero_point_from_beta",
     "qalora_pack_factors16", "qalora_forward_factors16",
     "qalora_adamw_workspace_bytes", "qalora_adamw_step",
@@ -105,6 +106,7 @@ def load() -> ctypes.CDLL:
     lib.qalora_swiglu_forward.argtypes = [vp, vp, vp, sz, vp]
     lib.qalora_profile_arm_clock.argtypes = [ctypes.c_int, vp]
     lib.qalora_profile_arm_blocks.argtypes = [ctypes.c_int, vp, ctypes.c_int]
+    lib.qalora_profile_mid_blocks.argtypes = [cp, i, ctypes.POINTER(ctypes.c_int)]
     lib.qalora_profile_wall_clock_khz.argtypes = [ctypes.POINTER(ctypes.c_int)]
     lib.qalora_swiglu_backward.argtypes = [vp, vp, vp, vp, vp, sz, vp]
     lib.qalora_pack_factors16.argtypes = [cp, vp, vp, vp, vp]
@@ -389,8 +391,9 @@ def deploy(desc: Desc, packed, alpha, beta):
 
 
 def forward_deployed(desc: Desc, x, deployed, packed=None, out_dtype=torch.float32, ws=None, y=None):
-    """Adapter-free forward of a deployed layer: the decode stream up to four tokens, beyond that
-    the dense kernel on ``packed`` (then required) with the prepared factor words."""
+    """Adapter-free forward of a deployed layer: the decode stream up to four tokens; beyond that
+    ``packed`` is required: the mid-token kernel up to 64 tokens, the dense kernel with the prepared factor
+    words above (see mid_blocks)."""
     _need(x, "x", torch.bfloat16)
     T, dev = x.shape[0], x.device
     if check_desc(desc) == OK:
@@ -416,6 +419,13 @@ def streaming_status(ws) -> int:
     out (0 = never, provided the caller zeroed it first).  Synchronises."""
     _need(ws, "ws", nbytes=WS_STATUS_OFFSET + 8)
     return int(ws.view(torch.uint8)[WS_STATUS_OFFSET:WS_STATUS_OFFSET + 8].cpu().view(torch.int64).item())
+
+
+def mid_blocks(desc: Desc, tokens: int) -> int:
+    """Blocks the kernel for up to 64 tokens launches for the adapter-free forward, 0: the dense kernel."""
+    n = ctypes.c_int()
+    _check(load().qalora_profile_mid_blocks(ctypes.byref(desc), int(tokens), ctypes.byref(n)), "qalora_profile_mid_blocks")
+    return n.value
 
 
 def pack_factors16(desc: Desc, alpha, beta, out=None):

@@ -480,6 +480,17 @@ int qalora_backward_shared(const qalora_desc* d, int tokens, const void* dy, con
                        dx_dtype, accumulate, ws, ws_bytes, stream);
 }
 
+// Blocks of the mid-token kernel for this layer, 0 where the dense kernel is for it, and the room that leaves
+// for flags and partials.  By the shape alone: triple, stream and 16-bit factors take the same path.
+static int mid_blocks(const qalora_desc& d, int tokens, size_t& scratch) {
+  if (!midt_shape(d, tokens)) return 0;
+  qalora_desc plain = d;
+  plain.rank = 0;
+  const FwdPlan plan = plan_forward(plain, tokens);
+  scratch = plan.total - plan.fac;
+  return midt_blocks(d.bits, d.d_in, d.d_out, tokens, scratch);
+}
+
 // The adapter-free forward on the mid-token kernel, in a workspace of plan_forward's size: flags and
 // status word first, where the few-token kernels have them, then row scales and fp16 copy of x, and the
 // partial sums in what the factor words and whatever follows them leave.  Factors: two planes, or fac16, or the deployment stream.
@@ -487,14 +498,13 @@ int qalora_backward_shared(const qalora_desc* d, int tokens, const void* dy, con
 static int forward_mid(const qalora_desc& d, int tokens, const void* x, const void* packed, const float* alpha,
                        const float* beta, const void* fac16, const void* dep_stream, void* y, int y_dtype, void* ws,
                        size_t ws_bytes, hipStream_t st) {
-  if (!midt_shape(d, tokens)) return -1;
+  size_t scratch = 0;  // for flags and partials: none (and no waits) where that is too little
+  const int blocks = mid_blocks(d, tokens, scratch);
+  if (blocks < 1) return -1;
   qalora_desc plain = d;
   plain.rank = 0;
-  const FwdPlan plan = plan_forward(plain, tokens);  // by the shape alone: triple and stream take the same path
+  const FwdPlan plan = plan_forward(plain, tokens);
   if (plan.total > ws_bytes) return -1;
-  const size_t scratch = plan.total - plan.fac;  // for flags and partials: none (and no waits) where that is too little
-  const int blocks = midt_blocks(d.bits, d.d_in, d.d_out, tokens, scratch);
-  if (blocks < 1) return -1;
   const size_t head = scratch < ST_HEAD_BYTES ? 0 : ST_HEAD_BYTES;
   char* w = static_cast<char*>(ws);
   MidTArgs a{};
@@ -871,8 +881,8 @@ int qalora_forward_deployed(const qalora_desc* d, int tokens, const void* x, con
     return QALORA_EALIGN;
   if (!deployable(*d)) return QALORA_EUNSUPPORTED;
   if (tokens > QALORA_DEPLOYED_STREAM_TOKENS) {
-    // beyond the decode kernel: the dense contraction on the codes as packed, with the factor
-    // words the deployment prepared
+    // beyond the decode kernel: the codes as packed, with the stream's factors up to 64 tokens and
+    // the factor words the deployment prepared above
     if (!packed) return QALORA_EINVAL;
     const DeployLayout l = deploy_layout(*d);
     const PreparedFactors pre{reinterpret_cast<const uint32_t*>(static_cast<const char*>(deployed) + l.words),
@@ -1043,6 +1053,15 @@ int qalora_profile_arm(int direction, void* start_event, void* stop_event) {
   if (direction != 0 && direction != 1) return QALORA_EINVAL;
   g_profile_hook[direction] = ProfileHook{static_cast<hipEvent_t>(start_event),
                                           static_cast<hipEvent_t>(stop_event), nullptr, nullptr, 0};
+  return QALORA_OK;
+}
+
+int qalora_profile_mid_blocks(const qalora_desc* d, int tokens, int* blocks) {
+  const int rc = qalora_check_desc(d);
+  if (rc != QALORA_OK) return rc;
+  if (tokens <= 0 || !blocks) return QALORA_EINVAL;
+  size_t scratch = 0;
+  *blocks = mid_blocks(*d, tokens, scratch);
   return QALORA_OK;
 }
 

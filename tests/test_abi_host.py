@@ -133,6 +133,19 @@ def test_argument_errors_are_caught_before_launch(lib):
     assert lib.qalora_backward(ctypes.byref(huge), 1 << 16, P(good), P(good), P(good), P(good), P(good), None, None, P(good), 0, None, None, 0, P(good), big_ws, None) == api.EUNSUPPORTED
 
 
+def test_mid_token_blocks(lib):
+    """Which calls go to the kernel for up to 64 tokens (host only)."""
+    d = api.make_desc(4096, 4096, 4, 32)
+    assert 0 < api.mid_blocks(d, 5) <= 256 and 0 < api.mid_blocks(d, 64) <= 256
+    assert api.mid_blocks(d, 65) == 0
+    assert api.mid_blocks(api.make_desc(4032, 4096, 4, 32), 64) == 0     # not whole chunks of 128 rows
+    assert api.mid_blocks(api.make_desc(4096, 4096, 4, 16), 64) == 0     # group
+    n = ctypes.c_int()
+    assert lib.qalora_profile_mid_blocks(ctypes.byref(d), 0, ctypes.byref(n)) == api.EINVAL
+    assert lib.qalora_profile_mid_blocks(ctypes.byref(d), 64, None) == api.EINVAL
+    assert lib.qalora_profile_mid_blocks(None, 64, ctypes.byref(n)) == api.EINVAL
+
+
 def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(api, "_lib", None)
     monkeypatch.setattr(api, "LIB_PATH", str(tmp_path / "missing.so"))

@@ -37,9 +37,9 @@ def test_deployed_forward_config5(gpu_api, name):
     d = L["np"]
     beta_m = gpu_api.merge(L["desc"], L["g_beta"], L["A"], L["B"])
     dep = gpu_api.deploy(L["desc"], L["packed"], L["g_alpha"], beta_m)
-    # 64 and 256 tokens (the 64-row tile with its finer K split, and the configuration's largest
-    # count): the dense kernel on the prepared factor words gives qalora_forward's bits, which
-    # the full-size test of the configuration holds to the oracle
+    # 64 tokens (the mid-token kernel on the stream's factors) and 256, the configuration's largest
+    # count (the dense kernel on the prepared factor words): qalora_forward's bits, which the
+    # full-size test of the configuration holds to the oracle
     for T in (64, 256):
         x = L["x"][:T].contiguous()
         yd = gpu_api.forward_deployed(L["desc"], x, dep, packed=L["packed"])
@@ -54,13 +54,15 @@ def test_deployed_forward_config5(gpu_api, name):
         assert err <= 1e-5
 
 
-@pytest.mark.parametrize("tokens", [5, 40, 300])
+@pytest.mark.parametrize("tokens", [5, 40, 65, 300])
 def test_deployed_forward_beyond_the_decode_kernel(gpu_api, tokens):
-    """More than four tokens: the dense kernel on the packed codes with the factor words the
-    deployment prepared -- the same words qalora_forward makes per call, so the same bits."""
+    """More than four tokens: up to 64 the mid-token kernel on the packed codes and the stream's factors,
+    beyond that the dense kernel with the factor words the deployment prepared -- the same factors and
+    words qalora_forward works with, so the same bits."""
     cfg = synth.LayerConfig("dep_dense", tokens, 1024, 520, 4, 64, 8, 0.5, seed=63)
     L = layer_on_gpu(gpu_api, cfg)
     beta_m = gpu_api.merge(L["desc"], L["g_beta"], L["A"], L["B"])
+    assert (gpu_api.mid_blocks(L["desc"], tokens) > 0) == (tokens <= 64)
     dep = gpu_api.deploy(L["desc"], L["packed"], L["g_alpha"], beta_m)
     yd = gpu_api.forward_deployed(L["desc"], L["x"], dep, packed=L["packed"])
     # (qalora_forward itself streams up to 32 tokens; its dense path is what must match beyond)

@@ -104,11 +104,13 @@ def test_graph_replay_forward_backward(gpu_api, keep):
             assert rel_err(e.cpu().numpy(), r) <= TOL, name
 
 
-@pytest.mark.parametrize("tokens", [2, 64])
+@pytest.mark.parametrize("tokens", [2, 64, 96])
 def test_graph_replay_deployed_forward(gpu_api, tokens):
-    """The deployed layer under capture: the decode kernel on the stream (2 tokens: flags and
-    partial sums in the workspace) and the dense kernel on the prepared factor words (64)."""
+    """The deployed layer under capture: the decode kernel on the stream (2 tokens) and the mid-token kernel
+    (64), both with flags and partial sums in the workspace, and the dense kernel on the prepared factor
+    words (96)."""
     cfg = synth.LayerConfig("graph_dep", tokens, 2048, 512, 4, 32, 8, 0.5, seed=33)
+    assert tokens != 64 or gpu_api.mid_blocks(gpu_api.make_desc(2048, 512, 4, 32), tokens) > 4   # four slabs: hand-overs
     L = layer_on_gpu(gpu_api, cfg)
     d = L["desc"]
     beta_m = gpu_api.merge(d, L["g_beta"], L["A"], L["B"])

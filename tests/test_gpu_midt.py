@@ -16,20 +16,33 @@ from helpers import layer_on_gpu, record, rel_err
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("bits,group,d_in,d_out,tokens", [
-    (4, 32, 384, 640, 33),      # one unit per slab, its fourth chunk absent
-    (4, 32, 1024, 520, 48),     # ragged last slab, two units per slab
-    (4, 64, 640, 264, 49),      # a unit of one chunk; two columns groups, the second nearly empty
-    (4, 128, 4096, 1032, 64),   # one group per chunk, several parts per slab
-    (4, 32, 2688, 4104, 64),    # runs that end inside a slab and go on in the next
-    (3, 32, 1152, 2056, 17),
-    (3, 64, 512, 136, 32),
-    (3, 128, 2048, 1160, 64),
-    (2, 32, 1024, 2048, 33),
-    (2, 64, 896, 72, 31),
-    (2, 128, 4224, 4096, 60),
+# `runs`: how the launch cuts the slabs of 128 columns -- whole slabs per block, every slab into the same number
+# of parts (a hand-over each), or runs that end inside a slab and go on in the next.
+@pytest.mark.parametrize("bits,group,d_in,d_out,tokens,runs", [
+    (4, 32, 384, 640, 33, "whole"),      # one unit per slab, its fourth chunk absent
+    (4, 32, 1024, 520, 48, "whole"),     # ragged last slab, two units per slab
+    (4, 64, 640, 264, 49, "whole"),      # a unit of one chunk; two columns groups, the second nearly empty
+    (4, 128, 4096, 1032, 64, "parts"),   # one group per chunk, a unit or two per part
+    (4, 32, 2688, 4104, 64, "parts"),    # one unit per part
+    (4, 32, 2048, 8200, 48, "parts"),    # the last part longer than the others
+    (4, 128, 4096, 11008, 64, "cross"),
+    (4, 64, 4096, 11016, 48, "cross"),
+    (4, 32, 4096, 11016, 33, "cross"),
+    (3, 32, 1152, 2056, 17, "parts"),
+    (3, 64, 512, 136, 32, "whole"),
+    (3, 128, 2048, 1160, 64, "parts"),
+    (3, 64, 4096, 11016, 20, "cross"),
+    (3, 32, 4096, 11016, 48, "cross"),
+    (2, 32, 1024, 2048, 33, "whole"),
+    (2, 64, 896, 72, 31, "whole"),
+    (2, 128, 4224, 4096, 60, "parts"),
+    (2, 32, 4096, 11016, 17, "cross"),
 ])
-def test_mid_token_forward(gpu_api, bits, group, d_in, d_out, tokens):
+def test_mid_token_forward(gpu_api, bits, group, d_in, d_out, tokens, runs):
+    units, slabs = -(-d_in // 512), -(-d_out // 128)
+    blocks = gpu_api.mid_blocks(gpu_api.make_desc(d_in, d_out, bits, group), tokens)
+    whole = blocks > 0 and (units == 1 or slabs % blocks == 0)
+    assert ("dense" if blocks == 0 else "whole" if whole else "parts" if blocks % slabs == 0 else "cross") == runs
     cfg = synth.LayerConfig("mid", tokens + 64, d_in, d_out, bits, group, 8, 0.5, seed=71)
     L = layer_on_gpu(gpu_api, cfg)
     d, x = L["desc"], L["x"][:tokens].contiguous()
