@@ -132,7 +132,8 @@ int qalora_quantize(const qalora_desc* desc, const float* W, void* packed, float
  * update per block (sums in ascending row order, fused multiply-adds, fp32): with this order
  * fixed the result is reproducible bit for bit.  U = identity gives qalora_quantize's result.
  * group must divide 128 (QALORA_EUNSUPPORTED otherwise).
- * Workspace: qalora_workspace_bytes(.., QALORA_OP_QUANTIZE_COMPENSATED) = 5 bytes per weight. */
+ * Workspace: qalora_workspace_bytes(.., QALORA_OP_QUANTIZE_COMPENSATED) = 4 bytes per weight
+ * (the rows' errors). */
 int qalora_quantize_compensated(const qalora_desc* desc, const float* W, const float* hinv_chol,
                                 void* packed, float* alpha, float* beta, void* ws, size_t ws_bytes,
                                 void* stream);

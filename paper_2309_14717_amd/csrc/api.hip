@@ -248,10 +248,7 @@ size_t qalora_workspace_bytes(const qalora_desc* d, int tokens, int op) {
   switch (op) {
     case QALORA_OP_QUANTIZE:
     case QALORA_OP_MERGE: return 0;
-    case QALORA_OP_QUANTIZE_COMPENSATED: {
-      const size_t n = (size_t)d->d_in * d->d_out;
-      return align_up(n * 4) + align_up(n);
-    }
+    case QALORA_OP_QUANTIZE_COMPENSATED: return align_up((size_t)d->d_in * d->d_out * 4);
     case QALORA_OP_FORWARD: {
       if (tokens <= 0) return 0;
       size_t need = plan_forward(*d, tokens).total;
@@ -297,8 +294,7 @@ int qalora_quantize_compensated(const qalora_desc* d, const float* W, const floa
       misaligned(ws))
     return QALORA_EALIGN;
   if (128 % d->group != 0) return QALORA_EUNSUPPORTED;  // groups must not straddle the lazy blocks
-  const size_t n = (size_t)d->d_in * d->d_out;
-  if (!ws || ws_bytes < align_up(n * 4) + align_up(n)) return QALORA_EWORKSPACE;
+  if (!ws || ws_bytes < qalora_workspace_bytes(d, 0, QALORA_OP_QUANTIZE_COMPENSATED)) return QALORA_EWORKSPACE;
   return launch_compensate(W, hinv_chol, d->d_in, d->d_out, d->bits, d->group, static_cast<float*>(ws), packed,
                            alpha, beta, as_stream(stream)) == hipSuccess
              ? QALORA_OK

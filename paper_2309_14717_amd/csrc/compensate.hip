@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
       auto rs_u = [&](int blk) { return rsrc(U + (size_t)blk * kBlock * d_in, (size_t)comp_block_rows(d_in, blk) * row_b); };
       auto rs_e = [&](int blk) { return rsrc(err + (size_t)blk * kBlock * nc, (size_t)kTiles * e_step); };
       // U operand: lane (row m = n of the tiles, kb) supplies U[i + 4 q + kb][r0 + NT n + h]; columns
-      // outside the matrix are some other element of the block's rows (or zero): never used
+      // outside the matrix are some other element of U (or zero): they reach rows outside the matrix only
       auto u_offset = [&](int r0) { return comp_update_lane(row_b, NT, r0, n, kb); };
       auto load_u = [&](int k, __amdgpu_buffer_rsrc_t r, uint32_t off) {
 #pragma unroll
@@ -184,7 +184,9 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
       }
       lds_barrier();  // the first panel is in place
       for (int pn = 0; pn < panels; ++pn) {
-        const bool work = pn + 1 < panels;  // (rows past the end of a ragged last panel are carried along as zeros)
+        // (rows past the end of a ragged last panel come to hold sums over whatever their columns' loads of U
+        // returned; the walker takes them through its sixteen rows and stores nothing of them)
+        const bool work = pn + 1 < panels;
         if (work) {
           // a piece's registers are reloaded for the next block as soon as it has been used, so a
           // whole block of loads is in flight

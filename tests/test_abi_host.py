@@ -70,6 +70,8 @@ def test_packed_and_workspace_sizes(lib):
     assert api.workspace_bytes(d0, 4096, api.OP_FORWARD) == f
     assert 4096 * 8 <= api.workspace_bytes(d0, 4096, api.OP_BACKWARD) < b
     assert api.packed_bytes(api.make_desc(4096, 4096, 7, 32)) == 0
+    # error-compensated selection keeps the rows' errors, nothing else
+    assert api.workspace_bytes(d, 0, api.OP_QUANTIZE_COMPENSATED) == 4096 * 4096 * 4
 
 
 def test_argument_errors_are_caught_before_launch(lib):
@@ -93,6 +95,8 @@ def test_argument_errors_are_caught_before_launch(lib):
     assert lib.qalora_backward(ref, 64, P(good), P(good), P(good), P(odd), P(good), None, None, P(good), 0, None, None, 0, None, 0, None) == api.EALIGN
     assert lib.qalora_quantize(ref, None, P(good), P(good), P(good), None, 0, None) == api.EINVAL
     assert lib.qalora_quantize(ref, P(good), P(good), P(odd), P(good), None, 0, None) == api.EALIGN
+    assert lib.qalora_quantize_compensated(ref, P(good), P(good), P(good), P(good), P(good), P(good), 1024 * 1024 * 4 - 1, None) == api.EWORKSPACE
+    assert lib.qalora_quantize_compensated(ref, P(good), P(good), P(good), P(good), P(good), None, 1 << 30, None) == api.EWORKSPACE
     assert lib.qalora_merge(ref, P(good), None, P(good), P(good), None) == api.EINVAL
     assert lib.qalora_beta_from_zero_point(ref, P(good), None, P(good), None) == api.EINVAL
     assert lib.qalora_beta_from_zero_point(ref, P(good), P(odd), P(good), None) == api.EALIGN
