@@ -155,8 +155,9 @@ int qalora_pack(const qalora_desc* desc, const uint8_t* codes, void* packed, voi
  * Precision: x is used exactly (each token row is scaled by a power of two and converted to
  * fp16); accumulation is fp32.  The adapter is folded into the zero factors for the call,
  * beta' = beta + (s/g) A B (App. B.3, fp32), and the weight is rebuilt around the mid code
- * mid = 2^(N-1) from two fp16 factors per (group, column), scaled by a power of two so that
- * the conversion keeps 11 significant bits at any magnitude:
+ * mid = 2^(N-1) from two fp16 factors per (group, column), scaled by a power of two per column so
+ * that the conversion keeps 11 significant bits at any magnitude of the column (of factors down to
+ * 2^-27 of its largest; smaller ones lose bits as fp16 subnormals do):
  *     W~' = fp16(alpha) (code - mid) + fp16(beta' + mid alpha),
  * so per element |error| <= 2^-11 (|beta' + mid alpha| + |alpha (code - mid)|).  For min-max
  * triples (qalora_quantize, qalora_quantize_compensated) that is 2^-11 of the group's largest

@@ -8,8 +8,9 @@ namespace qalora {
 // does not shrink), so they pay where they save rows of padding or a ragged last round of blocks:
 // 2-bit 5120 x 13824, us per call with 256 / 192 rows: 192 tokens 61.5 / 55.6, 320 90.7 / 78, 700 118 / 112,
 // 1531 248 / 219; 4096 x 11008 with 3 bits at 2048 tokens 218 / 202; level where both need the same
-// number of rounds times rows.  The split of K stays what gemm_dq_ksplit says, and every element is
-// summed in the same order by the same instructions: the results are the same bits.
+// number of rounds times rows.  The split of K stays what gemm_dq_ksplit plans for 256-row tiles (tile and split
+// are not searched together), and every element is summed in the same order by the same instructions:
+// the results are the same bits.
 static bool prefer_192(const GemmArgs& a, int ks) {
   auto cost = [&](int bm, double step) {
     const long blocks = (long)ceil_div(a.M, bm) * ceil_div(a.N, 256) * ks;

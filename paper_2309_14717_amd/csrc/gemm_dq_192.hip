@@ -1,6 +1,7 @@
-// The dequantising product on 192-row tiles (when: prefer_192 in gemm_dq.hip).  A file of its own: inside the
-// other's code object these kernels made a 4096-token step of 4096 x 4096, which does not use them,
-// 2 us in 312 slower, on the same instructions at other addresses.
+// The dequantising product on 192-row tiles (when: prefer_192 in gemm_dq.hip).  A file of its own:
+// inside the other's code object a 4096-token step of 4096 x 4096, which does not use these kernels, measured
+// 0.6 % slower on the same instructions at other addresses.  (At the edge of what runs differ by; the cause
+// was not found.)
 #include "gemm_dq_impl.hpp"
 
 namespace qalora {
