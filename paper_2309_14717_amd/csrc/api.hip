@@ -3,6 +3,7 @@
 #include "../../include/qalora.h"
 
 #include "common.hpp"
+#include "gemm_plan.hpp"
 #include "kernels.hpp"
 #include "midt_plan.hpp"
 
@@ -21,7 +22,7 @@ int row_align_for_bits(int bits) { return bits == 4 ? 8 : (bits == 2 ? 16 : 32);
 // Workspace plans.  Offsets are a pure function of (desc, tokens), so the size query and
 // the compute call always agree.
 struct FwdPlan {
-  int gsplit;
+  GemmPlan gemm;
   size_t rs, a16, fac, inv, gpart, total;
 };
 // One adapter among those sharing x (a single layer is one part over all columns).
@@ -36,7 +37,8 @@ struct BwdPartPlan {
   size_t us_t, b_hl, du_raw, db_part, da_part;
 };
 struct BwdPlan {
-  int t_pad, gsplit, nmax;
+  int t_pad, nmax;
+  GemmPlan gemm;
   size_t rs, a16, fac, cst, bmax, inv, P, gpart, total;
   BwdPartPlan part[MAX_PARTS];
 };
@@ -56,8 +58,8 @@ FwdPlan plan_forward(const qalora_desc& d, int T) {
   p.a16 = take((size_t)round_up(T, 256) * d.d_in * 2);
   p.fac = take(L * d.d_out * 4);
   p.inv = take((size_t)d.d_out * 4);
-  p.gsplit = gemm_dq_ksplit(T, d.d_out, d.d_in);
-  if (p.gsplit > 1) p.gpart = take((size_t)p.gsplit * T * d.d_out * 4);
+  p.gemm = gemm_dq_plan(d.bits, T, d.d_out, d.d_in, d.group);
+  p.gpart = take(gemm_dq_partial_room(T, d.d_out));
   p.total = off;
   return p;
 }
@@ -82,8 +84,8 @@ BwdPlan plan_backward(const qalora_desc& d, int T, int n_parts, const int* part_
   p.cst = take((size_t)L * d.d_out * 4);
   p.bmax = take((size_t)p.nmax * 4);
   p.inv = take(16);
-  p.gsplit = gemm_dq_ksplit(T, d.d_in, d.d_out);
-  if (p.gsplit > 1) p.gpart = take((size_t)p.gsplit * T * d.d_in * 4);
+  p.gemm = gemm_dq_plan(d.bits, T, d.d_in, d.d_out, d.group);
+  p.gpart = take(gemm_dq_partial_room(T, d.d_in));
   if (n_parts <= 0) {
     p.total = off;
     return p;
@@ -629,8 +631,9 @@ static int forward_impl(const qalora_desc* d, int tokens, const void* x, const v
   g.d_out = d->d_out;
   g.group = d->group;
   g.row_scale = rs;
-  g.ksplit = plan.gsplit;
-  g.partial = plan.gsplit > 1 ? reinterpret_cast<float*>(w + plan.gpart) : nullptr;
+  g.ksplit = plan.gemm.ksplit;
+  g.tile_rows = plan.gemm.tile_rows;
+  g.partial = plan.gemm.ksplit > 1 ? reinterpret_cast<float*>(w + plan.gpart) : nullptr;
   return launch_gemm_dq(d->bits, false, g, st) == hipSuccess ? QALORA_OK : QALORA_EHIP;
 }
 
@@ -740,8 +743,9 @@ static int backward_impl(const qalora_desc* d, int tokens, const void* dy, const
     g.d_out = d->d_out;
     g.group = d->group;
     g.row_scale = rs;
-    g.ksplit = plan.gsplit;
-    g.partial = plan.gsplit > 1 ? reinterpret_cast<float*>(w + plan.gpart) : nullptr;
+    g.ksplit = plan.gemm.ksplit;
+    g.tile_rows = plan.gemm.tile_rows;
+    g.partial = plan.gemm.ksplit > 1 ? reinterpret_cast<float*>(w + plan.gpart) : nullptr;
     if (launch_gemm_dq(d->bits, true, g, st) != hipSuccess) return QALORA_EHIP;
   }
   for (int q = 0; q < ps.n; ++q) {  // the adapter gradients of every part, on its columns of dy

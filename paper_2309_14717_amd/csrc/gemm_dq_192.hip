@@ -1,4 +1,4 @@
-// The dequantising product on 192-row tiles (when: prefer_192 in gemm_dq.hip).  A file of its own:
+// The dequantising product on 192-row tiles (when: gemm_plan.hpp).  A file of its own:
 // inside the other's code object a 4096-token step of 4096 x 4096, which does not use these kernels, measured
 // 0.6 % slower on the same instructions at other addresses.  (At the edge of what runs differ by; the cause
 // was not found.)

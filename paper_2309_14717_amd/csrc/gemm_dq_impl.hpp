@@ -50,11 +50,12 @@
 #include <hip/hip_ext.h>
 
 #include "common.hpp"
+#include "gemm_plan.hpp"
 #include "kernels.hpp"
 
 namespace qalora {
 
-constexpr int BK = 64;
+constexpr int BK = kGemmStep;
 constexpr int NT = 512;  // threads per block
 
 // Measurement aid: -DQALORA_ABLATE=n builds the dequantising kernels with one part of their work

@@ -1,0 +1,83 @@
+// Launch shape of the dequantising product (gemm_dq.hip).
+#pragma once
+#include "common.hpp"
+
+namespace qalora {
+
+constexpr int kGemmStep = 64;  // K values per step
+constexpr int kGemmMaxSplits = 16;
+constexpr size_t kGemmPartialRoom = 64ull << 20;  // a 256 x 256 fp32 tile per compute unit
+
+// What the fast addressing path of gemm_dq_kernel needs besides padded activation copies.
+inline bool gemm_fast_shape(int K_main, int group) {
+  return K_main % kGemmStep == 0 && (kGemmStep % group == 0 || group % kGemmStep == 0);
+}
+
+struct GemmPlan {
+  int tile_rows;  // 64, 128, 192 or 256
+  int ksplit;     // slices of K
+};
+
+// The slices' copies of the output stay within gemm_dq_partial_room, which grows with the tokens: so does the
+// workspace, and one sized for a longer batch serves every shorter one.
+inline size_t gemm_dq_partial_room(int M, int N) {
+  const size_t most = (size_t)kGemmMaxSplits * M * N * 4;
+  return most < kGemmPartialRoom ? most : kGemmPartialRoom;
+}
+
+// Tile rows and K splits of the dequantising product, searched together: a launch takes
+// rounds(tiles x splits) x (K steps per block + prologue and epilogue), and a split adds the sum over the
+// slices (its launch, `splits` fp32 copies of the output written and read again).  A step of a small tile
+// costs more per row -- the producer dequantises the same 256 x 64 weights whatever the tile's height -- but
+// while compute units are idle that costs nothing, and its blocks start and end sooner: 64-row tiles run
+// one or two per unit.  Constants (us) fitted to 484 sweeps over tile and split (16 .. 4096 tokens,
+// 512 .. 22016 features, 2 to 4 bits, both directions): the plan is 0.7 % from the best of each sweep on
+// average; heights and splits planned one after the other, with at least eight steps per slice, were 13 %
+// from it (per call of 512 tokens: 1024 x 4096 38.6 -> 24.5 us, 2048 x 2048 36.9 -> 31.1, 4096 x 4096 48.9 -> 44.6;
+// 1024 tokens of 4096 x 4096 71.3 -> 62.2).
+inline GemmPlan gemm_dq_plan(int bits, int M, int N, int K_main, int group) {
+  struct Tile {
+    int rows;
+    double step, block;  // of a K step and of a block's prologue and epilogue
+  };
+  constexpr Tile kTiles[4] = {{64, 0.63, 1.0}, {128, 0.73, 4.0}, {192, 0.89, 6.1}, {256, 1.05, 8.1}};
+  constexpr double kPairStep = 0.98, kPairBlock = 2.0;  // two 64-row blocks on every unit
+  constexpr double kClock = 0.1;       // of a round's time that its idle units give back (power)
+  constexpr int kUnits = 256;
+  const double bits_step = bits == 3 ? 1.28 : 1.0;  // two planes to put together
+  const bool fast = gemm_fast_shape(K_main, group);
+  const int nk = ceil_div(K_main, kGemmStep);
+  const double out_us = (double)M * N * 1e-6;
+  const size_t room = gemm_dq_partial_room(M, N);
+  GemmPlan best{};
+  double best_cost = 0;
+  for (const Tile& t : kTiles) {
+    if (!fast && t.rows > 128) break;  // (the general form is built for the two small tiles)
+    if (t.rows > 64 && t.rows - 64 >= M) break;
+    const long tiles = (long)ceil_div(M, t.rows) * ceil_div(N, 256);
+    for (int ks = 1; ks <= kGemmMaxSplits && ks <= nk; ++ks) {
+      if (ks > 1 && (size_t)ks * M * N * 4 > room) break;
+      const int steps = ceil_div(nk, ks);
+      if (ceil_div(nk, steps) != ks) continue;  // a slice would be empty
+      const long blocks = tiles * ks;
+      const double one = steps * t.step * bits_step + t.block;
+      double cost;
+      if (t.rows == 64) {
+        const double pair = steps * kPairStep * bits_step + kPairBlock;
+        const long rounds = blocks / (2 * kUnits), rest = blocks - rounds * 2 * kUnits;
+        cost = rounds * pair + (rest > kUnits ? pair : (rest > 0 ? one : 0.0));
+      } else {
+        const long rounds = blocks / kUnits, rest = blocks - rounds * kUnits;
+        cost = rounds * one + (rest > 0 ? one * (1.0 - kClock * (1.0 - (double)rest / kUnits)) : 0.0);
+      }
+      if (ks > 1) cost += 3.0 + 0.34 * ks + out_us * (0.73 * ks + 0.6);
+      if (best.tile_rows == 0 || cost < best_cost) {
+        best = GemmPlan{t.rows, ks};
+        best_cost = cost;
+      }
+    }
+  }
+  return best;
+}
+
+}  // namespace qalora

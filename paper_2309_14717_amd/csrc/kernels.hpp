@@ -40,6 +40,7 @@ struct GemmArgs {
   int out_bf16;
   float* partial;          // [ksplit][M, N] fp32 when ksplit > 1 (dequantising product)
   int ksplit;              // K slices of the dequantising product (0 or 1: none)
+  int tile_rows;           // of the dequantising product: 64, 128, 192 or 256
   int M, N;                // tokens; d_out (forward) or d_in (backward)
   int K_main;              // d_in (forward) or d_out (backward); 0 for a plain product
   int K_tail;              // multiple of 64 (zero padded), may be 0
@@ -51,8 +52,6 @@ struct GemmArgs {
                                     // the id of the XCD it ran on, [4 b .. 4 b + 3]
 };
 hipError_t launch_gemm_dq(int bits, bool bwd, const GemmArgs& a, hipStream_t st);
-// K slices the dequantising product should use for an [M x K_main] x [K_main x N] problem.
-int gemm_dq_ksplit(int M, int N, int K_main);
 // Measurement aid: events recorded around the next launch_gemm_dq of each direction.
 struct ProfileHook {
   hipEvent_t start, stop;
