@@ -15,7 +15,8 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqalora_hip.so")
 SOURCES = ["api.hip", "quantize.hip", "gemm_dq.hip", "adapter.hip", "smallt.hip", "smallt4.hip", "smallt4_f16.hip",
-           "midt.hip", "glue.hip", "optim.hip", "probe.hip", "compensate.hip", "gemm_dq_192.hip"]
+           "midt.hip", "glue.hip", "optim.hip", "probe.hip", "compensate.hip", "gemm_dq_192.hip",
+           "grads.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 LLVM = os.environ.get("HIP_CLANG_PATH", "/opt/rocm/llvm/bin")
 FLAGS = [
@@ -28,11 +29,11 @@ FLAGS = [
 
 # Kernels that must compile with zero scratch memory: those whose waits on outstanding memory
 # operations are counted by hand (a register spill would add scratch traffic to the same
-# counter), and the adapter-gradient kernel, whose staging arrays once ended up in scratch
+# counter), and the adapter-gradient kernels, whose staging arrays once ended up in scratch
 # unnoticed (a local array the compiler does not promote to registers costs a round trip to
 # memory per element).
 NO_SCRATCH = {"gemm_dq.hip": "gemm_dq_kernel", "gemm_dq_192.hip": "gemm_dq_kernel", "midt.hip": "midt_kernel", "smallt.hip": "smallt_kernel", "smallt4.hip": "smallt4_kernel", "smallt4_f16.hip": "smallt4_kernel",
-              "adapter.hip": ("adapter_grads_kernel", "front_kernel", "front_wide_kernel")}
+              "adapter.hip": ("front_kernel", "front_wide_kernel"), "grads.hip": ("z_kernel", "finish_kernel", "fused_kernel", "tail_kernel")}
 
 
 def _as_tuple(v):

@@ -1,11 +1,6 @@
-// The low-rank branch of the QA-LoRA linear (Alg. 1; Sec. 3.3): group pooling of the
-// input, the small products with A and B, their gradients, and the merge of the adapter
-// into the zero factors (App. B.3).  All of it is tiny next to the two dense contractions;
-// the kernels here are shaped for latency and for deterministic (fixed-order) reductions.
-//
-// Small fp32 factors that must go through the bf16 matrix cores are split as hi + lo
-// (hi = bf16(v), lo = bf16(v - hi)); a product U.B is then evaluated as
-// hi.hi + lo.hi + hi.lo, which is accurate to about 2^-16.
+// What goes before the dense contractions (Alg. 1; Sec. 3.3): row scales and fp16 copies, group pooling
+// of the input, the adapter folded into the zero factors for the call at hand -- and its merge into
+// them for good (App. B.3).  (The adapter's gradients: grads.hip.)
 #include <algorithm>
 
 #include "common.hpp"
@@ -55,13 +50,12 @@ __device__ __forceinline__ uint4 bf16x8_to_f16x8_scaled(uint4 v, float sc) {
 // ---------------------------------------------------------------------------------------
 // The "front" launch: every row-wise and elementwise preparation step of a forward or a
 // backward call, as independent jobs of ONE kernel (the steps are tiny; launches are not).
-//   rows job 1 : x -> row scale, fp16 scaled copy (forward), P = pool_g(x), U = P A (kept for
-//                the backward, or transposed into us_t).  One wavefront per token, the row held in registers: a single
+//   rows job 1 : x -> row scale, fp16 scaled copy (forward), P = pool_g(x) as bf16 hi + lo (for the
+//                gradients).  One wavefront per token, the row held in registers: a single
 //                sweep of 128-bit loads gives the maximum (scale), the group sums (wavefront
 //                butterfly over the g/8 lanes of a group) and the converted copy.
 //   rows job 2 : dy -> row scale + fp16 scaled copy (backward)
 //   factor job : the adapter folded into the zero factors, as the dense kernels' factor words
-//   prep job   : hi/lo split of B into the operand layout of the dU product
 // ---------------------------------------------------------------------------------------
 constexpr int ROWS_PER_BLOCK = 4;  // one wavefront each
 // 128-bit chunks per lane of a row that a wavefront holds in registers (64 lanes x 8 elements
@@ -69,7 +63,6 @@ constexpr int ROWS_PER_BLOCK = 4;  // one wavefront each
 // smallest that holds its longest row, so that rows up to 14336 elements are read once; the
 // larger forms cost the launch occupancy, which is why they are not the only one.
 constexpr int ROW_BATCH = 8;
-constexpr int TR_TOK = 32;         // tokens per block of the transpose job
 
 // One linear's adapter among those that share the input x (a single layer is one part).
 struct FrontPart {
@@ -78,11 +71,6 @@ struct FrontPart {
   float s;
   int rank;
   int col0, d_out;      // its columns [col0, col0 + d_out) of the (wide) layer
-  float* u_keep;        // optional [T, rank]: s U in fp32, for a later launch's transpose job
-  const float* u_kept;  // transpose job: the [T, rank] rows an earlier launch kept
-  uint16_t* us_t;       // optional [2*rp, t_pad]
-  uint16_t* b_hl;       // backward: [2*rp, d_out]
-  int prep_block0;      // first block of its share of the prep job
 };
 
 struct FrontArgs {
@@ -91,13 +79,10 @@ struct FrontArgs {
   int T, d_in;
   float2* rs_x;         // optional
   uint16_t* x16;        // optional, [T, d_in]
-  int pool;             // rows job 1 also pools x and forms U = P A of every part
   int g;
-  float* P_out;         // optional [T, L]
-  int t_pad;
+  uint16_t* P_out;      // optional, bf16 [T][2 Lp] (pooled_ld): rows job 1 also pools x
   FrontPart part[MAX_PARTS];
   int n_parts;
-  int tr_blocks;        // transpose job: blocks per part (t_pad / TR_TOK), or 0
   // rows job 2 (dy): scale + convert only
   const uint16_t* y;
   int Ty, d_y;
@@ -117,7 +102,7 @@ struct FrontArgs {
   const float* f_known; // backward, optional [nb_fac]: those bounds as an earlier launch on the
                         // same operands left them -- the call's S is then known here, and the
                         // words are written at once (f_words, f_inv[0]; no f_const)
-  int nb_rows1, nb_rows2, nb_tr, nb_prep, nb_fac;
+  int nb_rows1, nb_rows2, nb_fac;
 };
 
 // Power of two S = 2^e that brings a magnitude bound m to [2^13, 2^14), as (S, 1/S); (1, 1) for
@@ -575,137 +560,40 @@ __global__ __launch_bounds__(256) void front_kernel(const FrontArgs a) {
   if (bid < a.nb_rows1) {
     // ---- rows job 1: x ---------------------------------------------------------------
     const int t = bid * ROWS_PER_BLOCK + wave;
-    const int L = a.pool ? a.d_in / a.g : 0;
-    float* P_s = a.pool ? P_all + wave * L : nullptr;
-    float2 sc = float2{1.0f, 1.0f};
-    if (t < a.T) {
-      sc = process_row<RB>(a.x + (size_t)t * a.d_in, a.d_in,
-                       a.x16 ? a.x16 + (size_t)t * a.d_in : nullptr, P_s, a.g, lane);
-      if (lane == 0 && a.rs_x) a.rs_x[t] = sc;
-    } else if (a.pool) {
-      for (int l = lane; l < L; l += 64) P_s[l] = 0.0f;
-    }
-    if (!a.pool) return;
-    __syncthreads();
-    if (t < a.T && a.P_out)
-      for (int l = lane; l < L; l += 64) a.P_out[(size_t)t * L + l] = P_s[l];
-    // U = P A of every part for the block's 4 tokens, cooperatively: thread (k, q) covers a
-    // quarter of the groups for all 4 tokens (each A element is loaded once per block), then
-    // the quarters are added in fixed order.
-    float* part = P_all + ROWS_PER_BLOCK * L;  // [4 quarters][4 tokens][128]
-    const int lq0 = (L * wave) / 4, lq1 = (L * (wave + 1)) / 4;
-    for (int pi = 0; pi < a.n_parts; ++pi) {
-      const FrontPart& pt = a.part[pi];
-      const int rank = pt.rank, rp = rank_pad32(rank);
-      if (pi > 0) __syncthreads();  // the previous part's sums have been read
-      for (int k = lane; k < rank; k += 64) {
-        float u[ROWS_PER_BLOCK] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 4
-        for (int l = lq0; l < lq1; ++l) {
-          const float av = pt.A[(size_t)l * rank + k];
-#pragma unroll
-          for (int r = 0; r < ROWS_PER_BLOCK; ++r) u[r] = __builtin_fmaf(P_all[r * L + l], av, u[r]);
-        }
-#pragma unroll
-        for (int r = 0; r < ROWS_PER_BLOCK; ++r) part[(wave * ROWS_PER_BLOCK + r) * 128 + k] = u[r];
+    if (t >= a.T) return;
+    const int L = a.P_out ? a.d_in / a.g : 0;
+    float* P_s = a.P_out ? P_all + wave * L : nullptr;
+    const float2 sc = process_row<RB>(a.x + (size_t)t * a.d_in, a.d_in,
+                                      a.x16 ? a.x16 + (size_t)t * a.d_in : nullptr, P_s, a.g, lane);
+    if (lane == 0 && a.rs_x) a.rs_x[t] = sc;
+    if (!a.P_out) return;
+    const int Lp = pooled_ld(L);
+    uint16_t* P = a.P_out + (size_t)t * 2 * Lp;
+    asm volatile("" ::: "memory");  // the row's own wavefront wrote P_s: its LDS accesses complete in order
+    for (int l = lane; l < Lp; l += 64) {
+      uint16_t hi = 0, lo = 0;
+      if (l < L) {
+        split_bf16(P_s[l], hi, lo);
+        if ((hi & 0x7f80) == 0x7f80) lo = 0;  // infinite: no remainder
       }
-      __syncthreads();
-      if (t < a.T) {
-        for (int k = lane; k < rp; k += 64) {
-          float u = 0.0f;
-          if (k < rank) {
-            u = ((part[(0 * ROWS_PER_BLOCK + wave) * 128 + k] + part[(1 * ROWS_PER_BLOCK + wave) * 128 + k]) +
-                 part[(2 * ROWS_PER_BLOCK + wave) * 128 + k]) +
-                part[(3 * ROWS_PER_BLOCK + wave) * 128 + k];
-            u *= pt.s;
-          }
-          uint16_t hi, lo;
-          if (pt.u_keep && k < rank) pt.u_keep[(size_t)t * rank + k] = u;
-          if (pt.us_t) {
-            split_bf16(u, hi, lo);  // zero for the padding rows k >= rank
-            pt.us_t[(size_t)k * a.t_pad + t] = hi;
-            pt.us_t[(size_t)(rp + k) * a.t_pad + t] = lo;
-          }
-        }
-      } else if (pt.us_t && t < a.t_pad) {
-        // token padding of the transposed operand must read as zero
-        for (int k = lane; k < 2 * rp; k += 64) pt.us_t[(size_t)k * a.t_pad + t] = 0;
-      }
+      P[l] = hi;
+      P[Lp + l] = lo;
     }
     return;
   }
   bid -= a.nb_rows1;
-  if (bid < a.nb_rows2) {
-    // ---- rows job 2: dy -> scale + fp16 copy ----------------------------------------------
-    if constexpr (Y_WIDE) {
-      const float2 sc = process_row_block<RB>(a.y + (size_t)bid * a.d_y, a.d_y, a.y16 + (size_t)bid * a.d_y,
-                                              reinterpret_cast<uint32_t*>(P_all), tid);
-      if (tid == 0) a.rs_y[bid] = sc;
-      return;
-    }
-    const int t = bid * ROWS_PER_BLOCK + wave;
-    if (t < a.Ty) {
-      const float2 sc = process_row<RB>(a.y + (size_t)t * a.d_y, a.d_y, a.y16 + (size_t)t * a.d_y,
-                                    nullptr, 0, lane);
-      if (lane == 0) a.rs_y[t] = sc;
-    }
+  // ---- rows job 2: dy -> scale + fp16 copy ------------------------------------------------
+  if constexpr (Y_WIDE) {
+    const float2 sc = process_row_block<RB>(a.y + (size_t)bid * a.d_y, a.d_y, a.y16 + (size_t)bid * a.d_y,
+                                            reinterpret_cast<uint32_t*>(P_all), tid);
+    if (tid == 0) a.rs_y[bid] = sc;
     return;
   }
-  bid -= a.nb_rows2;
-  if (bid < a.nb_tr) {
-    // ---- transpose job: TR_TOK tokens of the kept s U -> token-contiguous hi/lo rows --------
-    // (the same values and the same split as rows job 1 writes when it computes U itself).
-    // The loads go out in batches of eight per thread before any is used: the launch is
-    // memory-saturated by the row jobs, and a round trip per element would outlast them.
-    float* tile = P_all;  // [TR_TOK][rank + 1]
-    const FrontPart& pt = a.part[bid / a.tr_blocks];
-    const int t0 = (bid % a.tr_blocks) * TR_TOK, rank = pt.rank, rp = rank_pad32(rank), ld = rank + 1;
-    const int n = TR_TOK * rank;
-    for (int e0 = 0; e0 < n; e0 += 8 * 256) {
-      float r[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int e = e0 + j * 256 + tid;
-        const int t = e / rank;
-        r[j] = (e < n && t0 + t < a.T) ? pt.u_kept[(size_t)t0 * rank + e] : 0.0f;
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int e = e0 + j * 256 + tid;
-        const int t = e / rank;
-        if (e < n) tile[t * ld + (e - t * rank)] = r[j];
-      }
-    }
-    __syncthreads();
-    const int tl = lane & (TR_TOK - 1);
-    for (int k = 2 * wave + (lane >> 5); k < rp; k += 8) {
-      uint16_t hi, lo;
-      split_bf16(k < rank ? tile[tl * ld + k] : 0.0f, hi, lo);  // zero for padding rows and tokens
-      pt.us_t[(size_t)k * a.t_pad + t0 + tl] = hi;
-      pt.us_t[(size_t)(rp + k) * a.t_pad + t0 + tl] = lo;
-    }
-    return;
-  }
-  bid -= a.nb_tr;
-  // ---- prep job: hi/lo split of every part's B for its dU product -----------------------
-  int pi = 0;
-  for (int q = 1; q < a.n_parts; ++q)
-    if (bid >= a.part[q].prep_block0) pi = q;
-  const FrontPart& pt = a.part[pi];
-  const size_t idx = (size_t)(bid - pt.prep_block0) * 256 + tid;
-  const int rp = rank_pad32(pt.rank);
-  const size_t nb = (size_t)2 * rp * pt.d_out;
-  if (idx < nb) {
-    // b_hl rows = hi(B) then lo(B) (rows padded to rp with zeros)
-    const int row = (int)(idx / pt.d_out), j = (int)(idx % pt.d_out);
-    const int k = row % rp;
-    uint16_t v = 0;
-    if (k < pt.rank) {
-      uint16_t hi, lo;
-      split_bf16(pt.B[(size_t)k * pt.d_out + j], hi, lo);
-      v = (row < rp) ? hi : lo;
-    }
-    pt.b_hl[idx] = v;
+  const int t = bid * ROWS_PER_BLOCK + wave;
+  if (t < a.Ty) {
+    const float2 sc = process_row<RB>(a.y + (size_t)t * a.d_y, a.d_y, a.y16 + (size_t)t * a.d_y,
+                                  nullptr, 0, lane);
+    if (lane == 0) a.rs_y[t] = sc;
   }
 }
 
@@ -772,9 +660,7 @@ static hipError_t launch_front_as(const FrontArgs& a, int nblocks, size_t smem, 
 static hipError_t launch_front_wide(const FrontArgs& a, int rb, int nblocks, size_t smem, hipStream_t st);
 
 static hipError_t launch_front(FrontArgs a, hipStream_t st) {
-  const bool prep = a.n_parts > 0 && a.part[0].b_hl;
-  const bool transposes = a.n_parts > 0 && a.part[0].u_kept;
-  if (a.x && !a.pool && !a.y && !prep && !transposes && a.T <= kWideRows && a.d_in % 8 == 0 &&
+  if (a.x && !a.P_out && !a.y && a.T <= kWideRows && a.d_in % 8 == 0 &&
       a.d_in <= 256 * 8 * WIDE_BATCH) {
     // few rows: a block per row; the factor job (if any) follows as a launch of its own
     front_wide_kernel<<<a.T, 256, 0, st>>>(a.x, a.d_in, a.rs_x, a.x16);
@@ -783,7 +669,7 @@ static hipError_t launch_front(FrontArgs a, hipStream_t st) {
   }
   int max_rank = 0;
   for (int p = 0; p < a.n_parts; ++p) max_rank = a.part[p].rank > max_rank ? a.part[p].rank : max_rank;
-  a.nb_rows1 = a.x ? ceil_div((a.pool && a.part[0].us_t) ? a.t_pad : a.T, ROWS_PER_BLOCK) : 0;
+  a.nb_rows1 = a.x ? ceil_div(a.T, ROWS_PER_BLOCK) : 0;
   // dy rows that do not fit the smallest register batch of one wavefront: a block each (backward front
   // launch, 4096 rows of 22016: 123 -> 87 us, 1531 rows of 13824: 44 -> 34; two sweeps, or one at 28 pieces
   // per lane, before).  Rows beyond 32768 elements take two sweeps either way, and many of them are better
@@ -791,18 +677,7 @@ static hipError_t launch_front(FrontArgs a, hipStream_t st) {
   // against 180).
   const bool y_wide = a.y && a.d_y > 512 * ROW_BATCH && (a.d_y <= 2048 * 16 || a.Ty <= 512);
   a.nb_rows2 = a.y ? (y_wide ? a.Ty : ceil_div(a.Ty, ROWS_PER_BLOCK)) : 0;
-  a.nb_prep = 0;
-  if (prep)
-    for (int p = 0; p < a.n_parts; ++p) {
-      a.part[p].prep_block0 = a.nb_prep;
-      a.nb_prep += (int)(((size_t)2 * rank_pad32(a.part[p].rank) * a.part[p].d_out + 255) / 256);
-    }
-  a.tr_blocks = transposes ? a.t_pad / TR_TOK : 0;
-  a.nb_tr = a.tr_blocks * a.n_parts;
-  size_t smem =
-      (a.x && a.pool) ? ((size_t)ROWS_PER_BLOCK * (a.d_in / a.g) + 4 * ROWS_PER_BLOCK * 128) * sizeof(float) : 0;
-  const size_t tr_smem = (size_t)TR_TOK * (max_rank + 1) * sizeof(float);
-  if (a.nb_tr > 0 && smem < tr_smem) smem = tr_smem;
+  size_t smem = a.x && a.P_out ? (size_t)ROWS_PER_BLOCK * (a.d_in / a.g) * sizeof(float) : 0;
   if (y_wide && smem < 4 * sizeof(uint32_t)) smem = 4 * sizeof(uint32_t);
   a.nb_fac = 0;
   if (a.f_alpha) {
@@ -816,7 +691,7 @@ static hipError_t launch_front(FrontArgs a, hipStream_t st) {
     if (smem < f_smem) smem = f_smem;
   }
   if (smem > kFrontLdsMax) return hipErrorInvalidValue;
-  const int nblocks = a.nb_rows1 + a.nb_rows2 + a.nb_tr + a.nb_fac + a.nb_prep;
+  const int nblocks = a.nb_rows1 + a.nb_rows2 + a.nb_fac;
   if (nblocks == 0) return hipSuccess;
   // the register batch that holds the launch's longest row of one wavefront (two sweeps beyond 14336
   // elements)
@@ -856,7 +731,7 @@ static void set_parts(FrontArgs& a, const AdapterParts& ap) {
 
 static void set_factor_job(FrontArgs& a, const FactorJob& f) {
   a.f_alpha = f.alpha; a.f_beta = f.beta; a.f_fold = f.parts.n > 0;
-  if (a.n_parts == 0) set_parts(a, f.parts);
+  set_parts(a, f.parts);
   a.f_inv_g = 1.0f / (float)f.g; a.f_mid = (float)(1 << (f.bits - 1));
   a.f_L = f.L; a.f_dout = f.d_out;
   a.f_words = f.words; a.f_inv = f.inv_scale; a.f_const = f.cst; a.f_max = f.block_max;
@@ -872,41 +747,22 @@ hipError_t launch_factor_job(const FactorJob& f, hipStream_t st) {
   return launch_front(a, st);
 }
 
-hipError_t launch_front_forward(const uint16_t* x, int T, int d_in, float2* rs, uint16_t* x16,
-                                const AdapterParts& parts, int g, float* P_keep,
-                                float* const* u_keep, const FactorJob& fac, hipStream_t st) {
+hipError_t launch_front_forward(const uint16_t* x, int T, int d_in, float2* rs, uint16_t* x16, int g,
+                                uint16_t* P_keep, const FactorJob& fac, hipStream_t st) {
   FrontArgs a{};
   a.x = x; a.T = T; a.d_in = d_in; a.rs_x = rs; a.x16 = x16; a.g = g;
-  if (parts.n > 0 && P_keep) {  // only a caller that keeps them needs P and s P A here
-    set_parts(a, parts);
-    a.pool = 1;
-    a.P_out = P_keep;
-    for (int p = 0; p < parts.n; ++p) a.part[p].u_keep = u_keep[p];
-  }
+  a.P_out = P_keep;
   set_factor_job(a, fac);
   return launch_front(a, st);
 }
 
-hipError_t launch_front_backward(const uint16_t* dy, int T, int d_out, float2* rs_dy,
-                                 uint16_t* dy16, const uint16_t* x, int d_in,
-                                 const AdapterParts& parts, int g, float* P, uint16_t* const* us_t,
-                                 int t_pad, uint16_t* const* b_hl, const float* const* u_kept,
-                                 const FactorJob& fac, hipStream_t st) {
+hipError_t launch_front_backward(const uint16_t* dy, int T, int d_out, float2* rs_dy, uint16_t* dy16,
+                                 const uint16_t* x, int d_in, int g, uint16_t* P, const FactorJob& fac,
+                                 hipStream_t st) {
   FrontArgs a{};
   a.y = dy; a.Ty = T; a.d_y = d_out; a.rs_y = rs_dy; a.y16 = dy16; a.g = g;
-  if (parts.n > 0) {
-    set_parts(a, parts);
-    const bool kept = u_kept != nullptr;
-    a.x = kept ? nullptr : x;  // with the kept rows, P is the caller's and us_t is a transpose
-    a.pool = kept ? 0 : 1;
-    a.T = T; a.d_in = d_in;
-    a.P_out = P; a.t_pad = t_pad;
-    for (int p = 0; p < parts.n; ++p) {
-      a.part[p].us_t = us_t[p];
-      a.part[p].b_hl = b_hl[p];
-      a.part[p].u_kept = kept ? u_kept[p] : nullptr;
-    }
-  }
+  a.x = x; a.T = T; a.d_in = d_in;
+  a.P_out = P;
   if (fac.alpha) set_factor_job(a, fac);
   return launch_front(a, st);
 }
@@ -952,317 +808,6 @@ hipError_t launch_factor_scale(const float* alpha, const float* cst, const float
   factor_scale_kernel<<<blocks, 256, 0, st>>>(reinterpret_cast<const f32x4*>(alpha),
                                               reinterpret_cast<const f32x4*>(cst), block_max, nmax, n4,
                                               words, inv_scale);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------------------
-// dB = (sU)^T dy : contraction over tokens with a tiny output, on the bf16 matrix cores.
-// A operand = (sU)^T hi/lo rows (token-contiguous in memory); B operand = dy, whose
-// contraction index (token) is the strided one, so the 8-token fragments are gathered
-// from the LDS tile with 16-bit reads.  Block = 128 output columns x one token slice;
-// wavefront w owns columns [32w, 32w+32) and all hi/lo rows.
-// ---------------------------------------------------------------------------------------
-constexpr int DB_BN = 128;
-constexpr int DB_DY_ROW = 136;  // bf16 per LDS row of the dy tile (128 + 8 pad)
-
-struct DbArgs {
-  const uint16_t* us_t;  // bf16 [2*rp, t_pad]: hi rows, then lo rows, of (s U)^T
-  int t_pad;
-  const uint16_t* dy;    // bf16 [T, d_out], rows dy_ld elements apart (a column slice of a wider dy)
-  int dy_ld;
-  int T, d_out, rank, tsplit;
-  float* part;           // [tsplit][rank, d_out]
-};
-template <int MT>
-constexpr int db_lds_bytes() { return (32 * MT * LDS_ROW_72 + 64 * DB_DY_ROW) * 2; }
-
-template <int MT>  // number of 32-row tiles of the hi/lo operand = 2*rp/32
-__device__ __forceinline__ void db_partial_block(const DbArgs& a, int bx, int z,
-                                                 unsigned char* lds) {
-  constexpr int ROWS = 32 * MT;
-  const uint16_t* __restrict__ us_t = a.us_t;
-  const uint16_t* __restrict__ dy = a.dy;
-  float* __restrict__ part = a.part;
-  const int t_pad = a.t_pad, T = a.T, d_out = a.d_out, rank = a.rank, tsplit = a.tsplit;
-  uint16_t* us_s = reinterpret_cast<uint16_t*>(lds);  // [ROWS][LDS_ROW_72]
-  uint16_t* dy_s = us_s + ROWS * LDS_ROW_72;          // [64][DB_DY_ROW]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int j0 = bx * DB_BN;
-  const int steps = ceil_div(t_pad / 64, tsplit);
-  const int step_begin = z * steps, step_end = min(t_pad / 64, step_begin + steps);
-
-  f32x16 acc[MT];
-#pragma unroll
-  for (int a = 0; a < MT; ++a)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[a][r] = 0.0f;
-
-  // The tiles of step+1 are fetched into registers while step runs on the matrix cores (one
-  // loop body with the three phases guarded, so that each phase is written once and the
-  // staging registers stay plain registers).
-  constexpr int US_LOADS = ROWS * 8 / 256, DY_LOADS = 64 * 16 / 256;
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  u32x4 us_r[US_LOADS], dy_r[DY_LOADS];
-  for (int step = step_begin - 1; step < step_end; ++step) {
-    const bool have = step >= step_begin;  // registers hold the tiles of `step`
-    if (have) {
-#pragma unroll
-      for (int q = 0; q < US_LOADS; ++q) {
-        const int idx = tid + 256 * q, row = idx >> 3, ch = idx & 7;
-        *reinterpret_cast<u32x4*>(us_s + row * LDS_ROW_72 + 8 * ch) = us_r[q];
-      }
-#pragma unroll
-      for (int q = 0; q < DY_LOADS; ++q) {
-        const int idx = tid + 256 * q, row = idx >> 4, ch = idx & 15;
-        *reinterpret_cast<u32x4*>(dy_s + row * DB_DY_ROW + 8 * ch) = dy_r[q];
-      }
-      __syncthreads();
-    }
-    if (step + 1 < step_end) {
-      const int t0 = (step + 1) * 64;
-#pragma unroll
-      for (int q = 0; q < US_LOADS; ++q) {
-        const int idx = tid + 256 * q, row = idx >> 3, ch = idx & 7;
-        us_r[q] = *reinterpret_cast<const u32x4*>(us_t + (size_t)row * t_pad + t0 + 8 * ch);
-      }
-#pragma unroll
-      for (int q = 0; q < DY_LOADS; ++q) {
-        const int idx = tid + 256 * q, row = idx >> 4, ch = idx & 15;
-        const int t = t0 + row, j = j0 + 8 * ch;
-        dy_r[q] = u32x4{0, 0, 0, 0};
-        if (t < T && j < d_out) dy_r[q] = *reinterpret_cast<const u32x4*>(dy + (size_t)t * a.dy_ld + j);
-      }
-    }
-    if (have) {
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        // B fragment: eight tokens of one column, gathered with 16-bit reads and packed in pairs
-        const uint16_t* src = dy_s + (kk * 16 + 8 * (lane >> 5)) * DB_DY_ROW + 32 * wave + (lane & 31);
-        uint32_t h[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) h[e] = src[e * DB_DY_ROW];
-        const u32x4 packed = {h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
-        const bf16x8 bfrag = __builtin_bit_cast(bf16x8, packed);
-#pragma unroll
-        for (int a = 0; a < MT; ++a) {
-          const bf16x8 af = *reinterpret_cast<const bf16x8*>(
-              us_s + (32 * a + (lane & 31)) * LDS_ROW_72 + kk * 16 + 8 * (lane >> 5));
-          acc[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bfrag, acc[a], 0, 0, 0);
-        }
-      }
-      __syncthreads();
-    }
-  }
-
-  const int j = j0 + 32 * wave + (lane & 31);
-  if (j < d_out) {
-#pragma unroll
-    for (int a = 0; a < MT / 2; ++a)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int k = 32 * a + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (k < rank)
-          part[((size_t)z * rank + k) * d_out + j] = acc[a][r] + acc[a + MT / 2][r];
-      }
-  }
-}
-
-// ---------------------------------------------------------------------------------------
-// dA = P^T dU over a token slice, fp32 on the vector units (67 MFLOP at LLaMA-7B shapes),
-// fused with the finalisation of dU: dU[t,k] = s * sum_z (raw[z][t][k] + raw[z][t][rp+k]) is
-// rebuilt from the split-K partials of the dU product while staging.
-// Block = 64 groups x all ranks; thread = 4 groups x up to 8 ranks.
-// ---------------------------------------------------------------------------------------
-constexpr int DA_TT = 16;
-
-struct DaArgs {
-  const float* P;    // [T, L] group averages of x
-  const float* raw;  // [ksplit][T, 2*rp] split-K partials of dy [B_hi | B_lo]^T
-  int ksplit;
-  float s;
-  int T, L, rank, tsplit;
-  float* part;       // [tsplit][L, rank]
-};
-constexpr int da_lds_bytes() { return DA_TT * (64 + 128) * 4; }
-
-__device__ __forceinline__ void da_partial_block(const DaArgs& a, int bx, int z,
-                                                 unsigned char* lds) {
-  const float* __restrict__ P = a.P;
-  const float* __restrict__ raw = a.raw;
-  float* __restrict__ part = a.part;
-  const int ksplit = a.ksplit, T = a.T, L = a.L, rank = a.rank, tsplit = a.tsplit;
-  const float s = a.s;
-  float (*p_s)[64] = reinterpret_cast<float (*)[64]>(lds);                        // [DA_TT][64]
-  float (*du_s)[128] = reinterpret_cast<float (*)[128]>(lds + DA_TT * 64 * 4);    // [DA_TT][128]
-  const int tid = threadIdx.x;
-  const int lq = tid >> 4, kq = tid & 15;
-  const int l0 = bx * 64;
-  const int rp = rank_pad32(rank);
-  // The split-K partials are read through a buffer resource: the lane offset is fixed per
-  // (token, rank) element and the partial index lives in the scalar offset, so the four
-  // partials' loads in flight together cost no address registers.  (The host refuses token
-  // counts for which the partials exceed 32-bit byte offsets.)
-  constexpr uint32_t kDaOob = 0xffff0000u;
-  const uint32_t q_stride = (uint32_t)T * (uint32_t)(2 * rp) * 4u;
-  const __amdgpu_buffer_rsrc_t rs_raw = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<float*>(raw), 0, (int)((uint32_t)ksplit * q_stride), 0x00020000);
-  const int per = ceil_div(ceil_div(T, DA_TT), tsplit) * DA_TT;
-  const int t_begin = z * per, t_end = min(T, t_begin + per);
-
-  float acc[4][8];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[a][c] = 0.0f;
-
-  for (int t0 = t_begin; t0 < t_end; t0 += DA_TT) {
-    for (int idx = tid; idx < DA_TT * 64; idx += 256) {
-      const int tt = idx >> 6, l = l0 + (idx & 63);
-      p_s[tt][idx & 63] = (t0 + tt < t_end && l < L) ? P[(size_t)(t0 + tt) * L + l] : 0.0f;
-    }
-    // dU of this thread's eight (token, rank) elements: the loads of one split-K partial are
-    // all issued before any is used (element loop unrolled inside the partial loop)
-    constexpr int DU_E = DA_TT * 128 / 256;
-    float duv[DU_E];
-    uint32_t voff[DU_E];  // byte offset of (t, k) inside one split-K partial; elements that do
-                          // not exist point past the buffer and read as zero
-#pragma unroll
-    for (int e = 0; e < DU_E; ++e) {
-      const int idx = tid + 256 * e;
-      const int t = t0 + (idx >> 7), k = idx & 127;
-      duv[e] = 0.0f;
-      voff[e] = (t < t_end && k < rank) ? ((uint32_t)t * (uint32_t)(2 * rp) + (uint32_t)k) * 4u : kDaOob;
-    }
-    constexpr int QB = 2;  // split-K partials whose loads are in flight together
-    for (int q0 = 0; q0 < ksplit; q0 += QB) {
-      float ld[QB][DU_E][2];
-#pragma unroll
-      for (int j = 0; j < QB; ++j) {
-        const bool live = q0 + j < ksplit;  // uniform
-        const uint32_t so = live ? (uint32_t)(q0 + j) * q_stride : 0u;
-#pragma unroll
-        for (int e = 0; e < DU_E; ++e) {
-          const uint32_t v = live ? voff[e] : kDaOob;
-          ld[j][e][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs_raw, (int)v, (int)so, 0));
-          ld[j][e][1] = __builtin_bit_cast(
-              float, __builtin_amdgcn_raw_buffer_load_b32(rs_raw, (int)v, (int)(so + (uint32_t)rp * 4u), 0));
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < QB; ++j)  // partial order, as a plain loop over q would add them
-#pragma unroll
-        for (int e = 0; e < DU_E; ++e)
-          if (q0 + j < ksplit) duv[e] += ld[j][e][0] + ld[j][e][1];
-    }
-#pragma unroll
-    for (int e = 0; e < DU_E; ++e) {
-      const int idx = tid + 256 * e;
-      const int tt = idx >> 7, k = idx & 127;
-      du_s[tt][k] = duv[e] * s;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int tt = 0; tt < DA_TT; ++tt) {
-      float pv[4], dv[8];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) pv[a] = p_s[tt][4 * lq + a];
-#pragma unroll
-      for (int c = 0; c < 8; ++c) dv[c] = du_s[tt][kq + 16 * c];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[a][c] = __builtin_fmaf(pv[a], dv[c], acc[a][c]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int l = l0 + 4 * lq + a;
-    if (l >= L) continue;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const int k = kq + 16 * c;
-      if (k < rank) part[((size_t)z * L + l) * rank + k] = acc[a][c];
-    }
-  }
-}
-
-// Both gradient jobs in ONE launch (neither needs the other; the dB blocks, the longer job,
-// come first): blocks [0, db_blocks) are (column block, token slice) pairs of dB, the rest
-// (group block, token slice) pairs of dA.
-// (Three wavefronts per SIMD fit in registers up to rank 64; the larger ranks' accumulators
-// need the room of one.)
-template <int MT>
-__global__ __launch_bounds__(256, MT <= 4 ? 3 : 1) void adapter_grads_kernel(const DbArgs db, const DaArgs da,
-                                                            int db_bx, int db_blocks, int da_bx) {
-  constexpr int kLds = db_lds_bytes<MT>() > da_lds_bytes() ? db_lds_bytes<MT>() : da_lds_bytes();
-  __shared__ __align__(16) unsigned char lds[kLds];
-  const int b = blockIdx.x;
-  if (b < db_blocks) {
-    db_partial_block<MT>(db, b % db_bx, b / db_bx, lds);
-  } else {
-    const int c = b - db_blocks;
-    da_partial_block(da, c % da_bx, c / da_bx, lds);
-  }
-}
-
-hipError_t launch_adapter_grads(const uint16_t* us_t, int t_pad, const uint16_t* dy, int dy_ld, int T,
-                                int d_out, int rank, int tsplit_b, float* db_part, const float* P,
-                                const float* raw, int ksplit, float s, int L, int tsplit_a,
-                                float* da_part, hipStream_t st) {
-  const DbArgs db{us_t, t_pad, dy, dy_ld, T, d_out, rank, tsplit_b, db_part};
-  const DaArgs da{P, raw, ksplit, s, T, L, rank, tsplit_a, da_part};
-  const int db_bx = ceil_div(d_out, DB_BN), db_blocks = db_bx * tsplit_b;
-  const int da_bx = ceil_div(L, 64), da_blocks = da_bx * tsplit_a;
-  const int mt = 2 * rank_pad32(rank) / 32;
-  const dim3 grid(db_blocks + da_blocks);
-  if (mt == 2) adapter_grads_kernel<2><<<grid, 256, 0, st>>>(db, da, db_bx, db_blocks, da_bx);
-  else if (mt == 4) adapter_grads_kernel<4><<<grid, 256, 0, st>>>(db, da, db_bx, db_blocks, da_bx);
-  else if (mt == 6) adapter_grads_kernel<6><<<grid, 256, 0, st>>>(db, da, db_bx, db_blocks, da_bx);
-  else if (mt == 8) adapter_grads_kernel<8><<<grid, 256, 0, st>>>(db, da, db_bx, db_blocks, da_bx);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
-// out[i] = (accumulate ? out[i] : 0) + sum_z part[z][i] in a fixed order, for two outputs in
-// one launch.  Block = 64 outputs x 4 part groups: thread (o, q) adds parts q, q+4, q+8, ...
-// (coalesced across o, loads independent so they pipeline), then the four group sums are
-// added in order 0..3.
-__global__ __launch_bounds__(256) void reduce2_kernel(const float* __restrict__ part_a,
-                                                      int nparts_a, size_t n_a,
-                                                      float* __restrict__ out_a,
-                                                      const float* __restrict__ part_b,
-                                                      int nparts_b, size_t n_b,
-                                                      float* __restrict__ out_b, int accumulate,
-                                                      int blocks_a) {
-  __shared__ float sums[4][64];
-  const int o = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const bool second = (int)blockIdx.x >= blocks_a;
-  const float* part = second ? part_b : part_a;
-  const int nparts = second ? nparts_b : nparts_a;
-  const size_t n = second ? n_b : n_a;
-  float* out = second ? out_b : out_a;
-  const size_t i = (size_t)(second ? blockIdx.x - blocks_a : blockIdx.x) * 64 + o;
-  float v = 0.0f;
-  if (i < n) {
-#pragma unroll 8
-    for (int z = q; z < nparts; z += 4) v += part[(size_t)z * n + i];
-  }
-  sums[q][o] = v;
-  __syncthreads();
-  if (q == 0 && i < n) {
-    float r = accumulate ? out[i] : 0.0f;
-    r += ((sums[0][o] + sums[1][o]) + sums[2][o]) + sums[3][o];
-    out[i] = r;
-  }
-}
-
-hipError_t launch_reduce2(const float* part_a, int nparts_a, size_t n_a, float* out_a,
-                          const float* part_b, int nparts_b, size_t n_b, float* out_b,
-                          int accumulate, hipStream_t st) {
-  const int blocks_a = (int)((n_a + 63) / 64), blocks_b = (int)((n_b + 63) / 64);
-  reduce2_kernel<<<blocks_a + blocks_b, 256, 0, st>>>(part_a, nparts_a, n_a, out_a, part_b,
-                                                       nparts_b, n_b, out_b, accumulate, blocks_a);
   return hipGetLastError();
 }
 

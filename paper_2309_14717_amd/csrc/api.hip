@@ -32,15 +32,12 @@ struct PartSpec {
   float* dA[MAX_PARTS];
   float* dB[MAX_PARTS];
 };
-struct BwdPartPlan {
-  int rp, ksplit, tsplit_b, tsplit_a;
-  size_t us_t, b_hl, du_raw, db_part, da_part;
-};
 struct BwdPlan {
-  int t_pad, nmax;
+  int nmax;
   GemmPlan gemm;
-  size_t rs, a16, fac, cst, bmax, inv, P, gpart, total;
-  BwdPartPlan part[MAX_PARTS];
+  GradsPlan grads;
+  size_t rs, a16, fac, cst, bmax, inv, P, Z, gpart, total;
+  size_t da_part[MAX_PARTS], db_part[MAX_PARTS];
 };
 
 // forward workspace: row scales, the fp16 copy of x, the factor words and their column scales,
@@ -65,12 +62,11 @@ FwdPlan plan_forward(const qalora_desc& d, int T) {
 }
 
 // backward workspace: what the dx contraction needs (row scales, fp16 copy of dy, factor words
-// and their first stage), then P = pool(x) and per adapter part the operands and partial sums
-// of its gradient kernels.  n_parts = 0: adapter-free, only dx.
+// and their first stage), then P = pool(x), the partial sums of Z and per adapter part the shares of dA and dB.
+// n_parts = 0: adapter-free, only dx.
 BwdPlan plan_backward(const qalora_desc& d, int T, int n_parts, const int* part_rank, const int* part_dout) {
   BwdPlan p{};
   const int L = d.d_in / d.group;
-  p.t_pad = round_up(T, 64);
   p.nmax = factor_job_blocks(L, d.d_out);
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -90,41 +86,12 @@ BwdPlan plan_backward(const qalora_desc& d, int T, int n_parts, const int* part_
     p.total = off;
     return p;
   }
-  p.P = take((size_t)T * L * 4);
+  p.P = take((size_t)T * pooled_ld(L) * 4);
+  p.grads = grads_plan(T, L, d.d_out);
+  if (!p.grads.fused) p.Z = take((size_t)p.grads.slots * L * d.d_out * 4);
   for (int q = 0; q < n_parts; ++q) {
-    BwdPartPlan& pp = p.part[q];
-    const int rank = part_rank[q], dout = part_dout[q];
-    pp.rp = rank_pad32(rank);
-    // dU product: [T, 2rp] output tiles of plain_tile_rows x 128 (the taller tile pays when K
-    // is long: half the K steps per block for the same number of blocks); split K = d_out to
-    // fill the chip.
-    {
-      const int tiles = ceil_div(T, gemm_plain_tile_rows(dout)) * ceil_div(2 * pp.rp, 128);
-      const int nk = ceil_div(dout, 64);
-      int ks = ceil_div(256, tiles);
-      ks = ks < 1 ? 1 : (ks > 16 ? 16 : ks);
-      const int by_steps = nk / 12;  // a slice shorter than about twelve K steps is all prologue
-      if (ks > by_steps) ks = by_steps < 1 ? 1 : by_steps;
-      pp.ksplit = ks;
-    }
-    {
-      const int blocks = ceil_div(dout, 128);
-      int ts = ceil_div(256, blocks);  // about one block per compute unit
-      ts = ts > 32 ? 32 : ts;
-      const int steps = p.t_pad / 64;
-      pp.tsplit_b = ts > steps ? steps : ts;
-    }
-    {
-      // one 16-token chunk per block where possible: the work is tiny and latency-bound, so
-      // maximise the number of independent blocks
-      const int steps = ceil_div(T, 16);
-      pp.tsplit_a = steps > 256 ? 256 : steps;
-    }
-    pp.us_t = take((size_t)2 * pp.rp * p.t_pad * 2);
-    pp.b_hl = take((size_t)2 * pp.rp * dout * 2);
-    pp.du_raw = take((size_t)pp.ksplit * T * 2 * pp.rp * 4);
-    pp.db_part = take((size_t)pp.tsplit_b * rank * dout * 4);
-    pp.da_part = take((size_t)pp.tsplit_a * L * rank * 4);
+    p.da_part[q] = take((size_t)grads_da_shares(part_dout[q]) * L * part_rank[q] * 4);
+    p.db_part[q] = take((size_t)grads_db_shares(L) * part_rank[q] * part_dout[q] * 4);
   }
   p.total = off;
   return p;
@@ -321,21 +288,19 @@ int qalora_pack(const qalora_desc* d, const uint8_t* codes, void* packed, void* 
   return hipGetLastError() == hipSuccess ? QALORA_OK : QALORA_EHIP;
 }
 
-// What the forward leaves for the backward when asked to: P = pool_g(x) [T, L] and
-// s P A [T, rank], both fp32.
+// What the forward leaves for the backward when asked to: P = pool_g(x) as bf16 hi and lo [T][2 Lp], and the
+// factor job's bounds.
 struct KeptLayout {
-  size_t P, U[MAX_PARTS], bmax, total;
+  size_t P, bmax, total;
 };
+// (The size also counts s U [T, rank] in fp32 of every part, which buffers have room for since the gradients were
+// made from it; nothing is stored there.)
 static KeptLayout kept_layout(const qalora_desc& d, int T, int n_parts, const int* part_rank) {
   KeptLayout k{};
   k.P = 0;
-  size_t off = align_up((size_t)T * (d.d_in / d.group) * 4);
-  for (int q = 0; q < n_parts; ++q) {
-    k.U[q] = off;
-    off += align_up((size_t)T * part_rank[q] * 4);
-  }
-  k.bmax = off;
+  k.bmax = align_up((size_t)T * pooled_ld(d.d_in / d.group) * 4);
   k.total = k.bmax + align_up((size_t)factor_job_blocks(d.d_in / d.group, d.d_out) * 4);
+  for (int q = 0; q < n_parts; ++q) k.total += align_up((size_t)T * part_rank[q] * 4);
   return k;
 }
 
@@ -508,9 +473,8 @@ static int forward_mid(const qalora_desc& d, int tokens, const void* x, const vo
   MidTArgs a{};
   float2* rs = reinterpret_cast<float2*>(w + head + plan.rs);
   uint16_t* x16 = reinterpret_cast<uint16_t*>(w + head + plan.a16);
-  float* u_none[MAX_PARTS] = {};
-  if (launch_front_forward(static_cast<const uint16_t*>(x), tokens, d.d_in, rs, x16, AdapterParts{}, d.group, nullptr,
-                           u_none, FactorJob{}, st) != hipSuccess)
+  if (launch_front_forward(static_cast<const uint16_t*>(x), tokens, d.d_in, rs, x16, d.group, nullptr, FactorJob{}, st) !=
+      hipSuccess)
     return 1;
   a.x16 = x16;
   a.row_scale = rs;
@@ -589,7 +553,7 @@ static int forward_impl(const qalora_desc* d, int tokens, const void* x, const v
       return mrc == 0 ? QALORA_OK : QALORA_EHIP;
 
   // front launch: row scales and the fp16 copy of x; the adapter folded into the zero factors
-  // and the factor words of the dense kernel; P and s P A for the backward when asked for
+  // and the factor words of the dense kernel; P for the backward when asked for
   FactorJob fj{};
   fj.alpha = alpha;
   fj.beta = beta;
@@ -601,17 +565,15 @@ static int forward_impl(const qalora_desc* d, int tokens, const void* x, const v
   fj.words = reinterpret_cast<uint32_t*>(w + plan.fac);
   fj.inv_scale = reinterpret_cast<float*>(w + plan.inv);
   if (pre) fj.alpha = nullptr;  // the words exist already: no factor job
-  float* P_keep = nullptr;
-  float* u_keep[MAX_PARTS] = {};
+  uint16_t* P_keep = nullptr;
   if (keep) {
     const KeptLayout k = kept_layout(*d, tokens, ps.n, ps.ap.rank);
-    P_keep = reinterpret_cast<float*>(static_cast<char*>(kept) + k.P);
-    for (int q = 0; q < ps.n; ++q) u_keep[q] = reinterpret_cast<float*>(static_cast<char*>(kept) + k.U[q]);
+    P_keep = reinterpret_cast<uint16_t*>(static_cast<char*>(kept) + k.P);
     // the bounds on |W~'| the factor job finds anyway: with them the backward knows its scale
     fj.block_max = reinterpret_cast<float*>(static_cast<char*>(kept) + k.bmax);
   }
-  if (launch_front_forward(static_cast<const uint16_t*>(x), tokens, d->d_in, rs, x16, ps.ap, d->group,
-                           P_keep, u_keep, fj, st) != hipSuccess)
+  if (launch_front_forward(static_cast<const uint16_t*>(x), tokens, d->d_in, rs, x16, d->group, P_keep, fj, st) !=
+      hipSuccess)
     return QALORA_EHIP;
 
   GemmArgs g{};
@@ -663,9 +625,6 @@ static int backward_impl(const qalora_desc* d, int tokens, const void* dy, const
     for (int q = 0; q < ps.n; ++q)
       if (ps.ap.d_out[q] % factor_job_cols(d->d_in / d->group) != 0) return QALORA_EUNSUPPORTED;
   const BwdPlan plan = plan_backward(*d, tokens, ps.n, ps.ap.rank, ps.ap.d_out);
-  for (int q = 0; q < ps.n; ++q)
-    if ((size_t)plan.part[q].ksplit * tokens * 2 * plan.part[q].rp * 4 >= kAddressable)
-      return QALORA_EUNSUPPORTED;  // the split-K partials of dU are read with 32-bit byte offsets
   if (!ws || ws_bytes < plan.total) return QALORA_EWORKSPACE;
   hipStream_t st = as_stream(stream);
   char* w = static_cast<char*>(ws);
@@ -699,29 +658,18 @@ static int backward_impl(const qalora_desc* d, int tokens, const void* dy, const
       fj.block_max = reinterpret_cast<float*>(w + plan.bmax);
     }
   }
-  float* P = nullptr;
-  uint16_t* us_t[MAX_PARTS] = {};
-  uint16_t* b_hl[MAX_PARTS] = {};
-  const float* u_kept[MAX_PARTS] = {};
-  if (adapter) {
-    P = reinterpret_cast<float*>(w + plan.P);
-    for (int q = 0; q < ps.n; ++q) {
-      us_t[q] = reinterpret_cast<uint16_t*>(w + plan.part[q].us_t);
-      b_hl[q] = reinterpret_cast<uint16_t*>(w + plan.part[q].b_hl);
-    }
-    if (use_kept) {  // written by the forward: the front launch below then skips x altogether
-      char* kp = const_cast<char*>(static_cast<const char*>(kept));
-      P = reinterpret_cast<float*>(kp + kl.P);
-      for (int q = 0; q < ps.n; ++q) u_kept[q] = reinterpret_cast<const float*>(kp + kl.U[q]);
-    }
-  }
-  // row scales + fp16 copy of dy; first stage of the factor words; P = pool(x), sU^T hi/lo and
-  // the hi/lo rows of B for the adapter gradients
-  if (launch_front_backward(dy16, tokens, d->d_out, rs, dyh,
-                            (adapter && !use_kept) ? static_cast<const uint16_t*>(x) : nullptr, d->d_in,
-                            ps.ap, d->group, P, us_t, plan.t_pad, b_hl, use_kept ? u_kept : nullptr, fj,
-                            st) != hipSuccess)
+  // P = pool(x): the forward's, or made from x by the front launch
+  uint16_t* P = nullptr;
+  if (adapter)
+    P = use_kept ? reinterpret_cast<uint16_t*>(const_cast<char*>(static_cast<const char*>(kept)) + kl.P)
+                 : reinterpret_cast<uint16_t*>(w + plan.P);
+  // row scales + fp16 copy of dy; the factor words or their first stage; P
+  const bool pools = adapter && !use_kept;
+  if (launch_front_backward(dy16, tokens, d->d_out, rs, dyh, pools ? static_cast<const uint16_t*>(x) : nullptr, d->d_in,
+                            d->group, pools ? P : nullptr, fj, st) != hipSuccess)
     return QALORA_EHIP;
+  TailArgs tail{};
+  SplitSum dx_sum{};
   if (dx) {
     if (!use_kept && launch_factor_scale(alpha, fj.cst, fj.block_max, plan.nmax, (size_t)L * d->d_out,
                                          words, inv_scale, st) != hipSuccess)
@@ -746,36 +694,39 @@ static int backward_impl(const qalora_desc* d, int tokens, const void* dy, const
     g.ksplit = plan.gemm.ksplit;
     g.tile_rows = plan.gemm.tile_rows;
     g.partial = plan.gemm.ksplit > 1 ? reinterpret_cast<float*>(w + plan.gpart) : nullptr;
-    if (launch_gemm_dq(d->bits, true, g, st) != hipSuccess) return QALORA_EHIP;
+    if (launch_gemm_dq(d->bits, true, g, st, adapter ? &dx_sum : nullptr) != hipSuccess) return QALORA_EHIP;
   }
-  for (int q = 0; q < ps.n; ++q) {  // the adapter gradients of every part, on its columns of dy
-    const BwdPartPlan& pp = plan.part[q];
+  if (!adapter) return QALORA_OK;
+  // the gradients of every part, and what is left of dx
+  ZArgs z{};
+  z.P = P;
+  z.dy = dy16;
+  z.T = tokens;
+  z.L = L;
+  z.Lp = pooled_ld(L);
+  z.d_out = d->d_out;
+  z.runs = plan.grads.runs;
+  z.Z = reinterpret_cast<float*>(w + plan.Z);
+  FinishArgs f{};
+  f.Z = z.Z;
+  f.L = L;
+  f.d_out = d->d_out;
+  f.runs = z.runs;
+  f.accumulate = tail.accumulate = accumulate;
+  f.n_parts = tail.n_parts = ps.n;
+  for (int q = 0; q < ps.n; ++q) {
+    float* da_part = reinterpret_cast<float*>(w + plan.da_part[q]);
+    float* db_part = reinterpret_cast<float*>(w + plan.db_part[q]);
     const int rank = ps.ap.rank[q], dout = ps.ap.d_out[q];
-    const uint16_t* dyq = dy16 + ps.ap.col0[q];
-    float* du_raw = reinterpret_cast<float*>(w + pp.du_raw);
-    float* db_part = reinterpret_cast<float*>(w + pp.db_part);
-    float* da_part = reinterpret_cast<float*>(w + pp.da_part);
-    // dU = s dy B^T : plain bf16 product against the hi/lo rows of B, split over K = d_out
-    GemmArgs g{};
-    g.a_tail = dyq;
-    g.lda_tail = d->d_out;
-    g.b_tail = b_hl[q];
-    g.K_tail = dout;
-    g.out = du_raw;
-    g.M = tokens;
-    g.N = 2 * pp.rp;
-    g.group = 1;
-    if (launch_gemm_plain(g, pp.ksplit, st) != hipSuccess) return QALORA_EHIP;
-    // dB = (sU)^T dy and dA = P^T dU as partials over token slices, one launch; the dA job
-    // finalises dU on the fly
-    if (launch_adapter_grads(us_t[q], plan.t_pad, dyq, d->d_out, tokens, dout, rank, pp.tsplit_b, db_part, P,
-                             du_raw, pp.ksplit, ps.ap.s[q], L, pp.tsplit_a, da_part, st) != hipSuccess)
-      return QALORA_EHIP;
-    if (launch_reduce2(da_part, pp.tsplit_a, (size_t)L * rank, ps.dA[q], db_part, pp.tsplit_b,
-                       (size_t)rank * dout, ps.dB[q], accumulate, st) != hipSuccess)
-      return QALORA_EHIP;
+    const float s = ps.ap.s[q];
+    f.part[q] = FinishPart{ps.ap.A[q], ps.ap.B[q], s, rank, ps.ap.col0[q], dout, ps.dB[q], da_part, db_part};
+    tail.part[q] = TailPart{da_part, grads_da_shares(dout), (size_t)L * rank, s, ps.dA[q], 0};
+    if (const int n = grads_db_shares(L))  // (d_out is a multiple of 8)
+      tail.sum[tail.n_sums++] = TailSum{SplitSum{db_part, n, (size_t)rank * dout / 4, ps.dB[q], 0}, true, s, 0};
   }
-  return QALORA_OK;
+  if (dx_sum.n4 > 0) tail.sum[tail.n_sums++] = TailSum{dx_sum, false, 1.0f, 0};
+  if (launch_grads(plan.grads, z, f, st) != hipSuccess) return QALORA_EHIP;
+  return launch_tail(tail, st) == hipSuccess ? QALORA_OK : QALORA_EHIP;
 }
 
 int qalora_merge(const qalora_desc* d, const float* beta, const float* A, const float* B,

@@ -8,8 +8,8 @@ namespace qalora {
 
 template <int NBITS>
 static hipError_t launch_192_dir(bool bwd, const GemmArgs& a, int ks, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-  return bwd ? launch_cfg<NBITS, true, 192, 256, 2, 4, true, true>(a, ks, st, e0, e1)
-             : launch_cfg<NBITS, false, 192, 256, 2, 4, true, true>(a, ks, st, e0, e1);
+  return bwd ? launch_cfg<NBITS, true, 192, 256, 2, 4, true>(a, ks, st, e0, e1)
+             : launch_cfg<NBITS, false, 192, 256, 2, 4, true>(a, ks, st, e0, e1);
 }
 hipError_t launch_192(int bits, bool bwd, const GemmArgs& a, int ks, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   if (bits == 4) return launch_192_dir<4>(bwd, a, ks, st, e0, e1);

@@ -24,10 +24,6 @@
 // power of two that brings its largest magnitude into [2^14, 2^15) and written as fp16
 // (exact for bf16 inputs); the output row is scaled back in the epilogue.
 //
-// The same kernel without the dequantising part (HAS_MAIN = false) is a plain bf16 product over
-// "tail" operands; the adapter gradients use it for dU = s dy B^T with B split into bf16 hi + lo
-// parts, which keeps fp32-level accuracy and bf16's range for gradients.
-//
 // One kernel serves both directions from ONE packed copy of the codes: a thread owns half
 // of an 8x8 patch of codes, from which it emits four K-contiguous operand fragments along
 // either axis -- down the rows (forward, K = input rows) or across the columns (backward,
@@ -113,27 +109,13 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblocks) {
   return (bid % 8) * (nblocks / 8) + bid / 8;
 }
 
-// LDS-DMA loads stay in flight across barriers (three A stages), so the barrier is issued
-// raw -- the compiler would otherwise drain every counter in front of it -- with explicit
-// waits: all of this wave's LDS writes, and all but the newest `VM_KEEP` vector-memory ops.
-template <int VM_KEEP>
-__device__ __forceinline__ void wait_and_barrier() {
-  static_assert(VM_KEEP >= 0 && VM_KEEP < 64, "vmcnt is a 6-bit counter");
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(VM_KEEP) : "memory");
-}
+// LDS-DMA loads stay in flight across barriers (three A stages), so the barriers below are issued
+// raw -- the compiler would otherwise drain every counter in front of them -- with explicit waits.
 
-// Calls f with the four LDS regions of one pipeline step as restrict-qualified parameters:
-// the region the LDS-DMA is filling, the A and B regions being read, and the B region being
-// written never overlap within a step, and saying so keeps the compiler from draining the
+// Calls f with the LDS regions of one pipeline step as restrict-qualified parameters: the region the LDS-DMA is
+// filling, the A regions being read (this step's and, at its end, the next one's), the B region being read and
+// the one being written never overlap within a step, and saying so keeps the compiler from draining the
 // LDS-DMA loads before every LDS read.
-template <typename F>
-__device__ __forceinline__ void with_step_regions(uint16_t* __restrict__ a_dma,
-                                                  const uint16_t* __restrict__ a_rd,
-                                                  const uint16_t* __restrict__ b_rd,
-                                                  uint16_t* __restrict__ b_wr, F&& f) {
-  f(a_dma, a_rd, b_rd, b_wr);
-}
-// Main pipeline: additionally the A stage of the next step (read at the end of the step).
 template <typename F>
 __device__ __forceinline__ void with_step_regions(uint16_t* __restrict__ a_dma,
                                                   const uint16_t* __restrict__ a_rd,
@@ -144,38 +126,33 @@ __device__ __forceinline__ void with_step_regions(uint16_t* __restrict__ a_dma,
 }
 
 // A stages of the LDS-DMA pipeline.  Three (the tile of step it+3 is requested as soon as step it
-// has released its stage), except for the 64-row tile of the dequantising product: with two
+// has released its stage), except for the 64-row tile: with two
 // stages its LDS is 80 KB, so that two blocks fit a compute unit and cover each other's waits
 // -- a K step of that tile is mostly producer work and synchronisation, not matrix work.
-constexpr int gemm_a_stages(int bm, bool has_main) { return (has_main && bm == 64) ? 2 : 3; }
+constexpr int gemm_a_stages(int bm) { return bm == 64 ? 2 : 3; }
 // wavefronts per SIMD the kernel is compiled for (two blocks of the 64-row tile: four, i.e. 128
 // registers; the 3-bit backward producer with per-step edge handling does not fit them and
 // stays at one block per unit)
-constexpr int gemm_min_waves(int bm, bool has_main, int nbits, bool bwd, bool fast) {
-  return (has_main && bm == 64 && !(nbits == 3 && bwd && !fast)) ? 4 : 1;
+constexpr int gemm_min_waves(int bm, int nbits, bool bwd, bool fast) {
+  return (bm == 64 && !(nbits == 3 && bwd && !fast)) ? 4 : 1;
 }
 
-// HAS_MAIN = false: a plain bf16 x bf16^T product over the "tail" operands only (used for
-// dU = s dy B^T), optionally split along K over blockIdx.y.
-//
-// FAST = true (main K a multiple of 64, group size dividing or divisible by 64, activation
+// FAST = true (K a multiple of 64, group size dividing or divisible by 64, activation
 // copies padded to whole row tiles): every per-lane global offset is a kernel-lifetime
 // constant and the K advance lives in scalar offsets, so the hot loop carries no vector
 // address arithmetic.  FAST = false keeps per-step, per-lane offsets with full edge handling.
-template <int NBITS, bool BWD, int BM, int BN, int WAVES_M, int WAVES_N, bool HAS_MAIN, bool FAST>
-__global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST)) void gemm_dq_kernel(const GemmArgs p) {
-  static_assert(!FAST || HAS_MAIN, "the fast addressing path is for the dequantising product");
+template <int NBITS, bool BWD, int BM, int BN, int WAVES_M, int WAVES_N, bool FAST>
+__global__ __launch_bounds__(NT, gemm_min_waves(BM, NBITS, BWD, FAST)) void gemm_dq_kernel(const GemmArgs p) {
   static_assert(WAVES_M * WAVES_N == 8, "eight wavefronts per block");
-  static_assert(!HAS_MAIN || BN == 256, "the dequantising producer assumes 256 columns");
+  static_assert(BN == 256, "the dequantising producer assumes 256 columns");
   constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
   constexpr int TM = WTM / 32, TN = WTN / 32;
   static_assert(TM >= 1 && TN >= 1, "wave tile must hold at least one 32x32 MFMA tile");
-  constexpr int A_LOADS = (QALORA_ABLATE == 2 && HAS_MAIN) ? 1 : BM * 8 / NT;  // LDS-DMA loads per thread
-  constexpr int B_CHUNKS = (BN * 8 / NT) > 0 ? BN * 8 / NT : 1;  // plain B tile, per thread
+  constexpr int A_LOADS = QALORA_ABLATE == 2 ? 1 : BM * 8 / NT;  // LDS-DMA loads per thread
   static_assert(A_LOADS >= 1, "BM too small for 512 threads");
   constexpr int A_TILE = BM * 64;  // 16-bit elements per A buffer
   constexpr int B_TILE = BN * 64;
-  constexpr int A_STAGES = gemm_a_stages(BM, HAS_MAIN);  // LDS-DMA prefetch runs A_STAGES - 1 K steps ahead
+  constexpr int A_STAGES = gemm_a_stages(BM);  // LDS-DMA prefetch runs A_STAGES - 1 K steps ahead
 
   extern __shared__ __align__(1024) uint16_t smem[];
   // The B stages sit at the bottom: their offsets then fit the 16-bit immediate of the LDS
@@ -202,10 +179,8 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
   const int m0 = (band * kGroupM + in_band % band_rows) * BM;
   const int n0 = (in_band / band_rows) * BN;
 
-  const int nk_main = HAS_MAIN ? ceil_div(p.K_main, BK) : 0;
-  const int nk_tail = HAS_MAIN ? 0 : ceil_div(p.K_tail, BK);  // a plain product has only these
   // blockIdx.y splits the K range (partial sums, added by a later launch in a fixed order)
-  int it_begin = 0, it_end = nk_main + nk_tail;
+  int it_begin = 0, it_end = ceil_div(p.K_main, BK);
   if (gridDim.y > 1) {
     const int per = ceil_div(it_end, (int)gridDim.y);
     it_begin = blockIdx.y * per;
@@ -214,7 +189,7 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
 
   // measurement aid: the first block reports how many shader cycles and wall-clock ticks it
   // lived for (their ratio is the clock the chip actually ran this kernel at)
-  const bool probe = HAS_MAIN && p.clock_probe != nullptr && blockIdx.x == 0 && blockIdx.y == 0 &&
+  const bool probe = p.clock_probe != nullptr && blockIdx.x == 0 && blockIdx.y == 0 &&
                      tid == 0;
   if (probe) {
     p.clock_probe[0] = (unsigned long long)clock64();
@@ -222,7 +197,7 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
   }
   // measurement aid: every block reports when it started, left the K loop and ended, and on
   // which XCD (register XCC_ID, bits 3:0), so that the launch can be laid out on a time line
-  const bool timeline = HAS_MAIN && p.block_times != nullptr && blockIdx.y == 0 && tid == 0 &&
+  const bool timeline = p.block_times != nullptr && blockIdx.y == 0 && tid == 0 &&
                         (int)blockIdx.x < p.block_times_cap;
   if (timeline) {
     p.block_times[4 * blockIdx.x + 0] = (unsigned long long)wall_clock64();
@@ -237,22 +212,13 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
 
-  // Step kinds: a K step is either a MAIN step (fp16: converted activations x dequantised
-  // codes) or a TAIL step (bf16 hi/lo adapter operands, plain copies).  The pipeline below is
-  // instantiated per (current kind, next kind) so that the hot loop carries no branches.
-  using MainK = std::integral_constant<int, 0>;
-  using TailK = std::integral_constant<int, 1>;
-  using NoneK = std::integral_constant<int, 2>;
-
   // ---- A tile: global -> LDS by LDS-DMA.  Load q of wave w fills the 1 KB block q*8+w;
   // lane i lands at byte 16*i of it, so it fetches the (row, chunk) the swizzle puts there.
   // Rows past M are clamped to the last row (their results are never stored); K chunks past
   // the end re-read chunk 0 (the B tile is zero there, any finite data will do).
   constexpr int A_PAD = BM == 192 ? 256 : BM;  // rows the copies are padded to a multiple of, as far as this tile needs
   const int a_padded = round_up(p.M, A_PAD);
-  const __amdgpu_buffer_rsrc_t rs_a_main =
-      make_rsrc(p.a_main, HAS_MAIN ? (size_t)(FAST ? a_padded : p.M) * p.lda_main * 2 : 0);
-  const __amdgpu_buffer_rsrc_t rs_a_tail = make_rsrc(p.a_tail, (size_t)p.M * p.lda_tail * 2);
+  const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.a_main, (size_t)(FAST ? a_padded : p.M) * p.lda_main * 2);
   uint32_t a_row[A_LOADS];  // global row of each load (rows past M read as zero)
   int a_chunk8[A_LOADS];
 #pragma unroll
@@ -265,49 +231,46 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
   // fast path: one lane offset for all loads of the kernel; the rows of later loads, 64*q further
   // down, are a scalar offset.  The copies are padded to whole tiles, so no row check is needed,
   // except for 192-row tiles, which can end up to 128 rows past the padding.
-  const uint32_t a_voff_main = (a_row[0] * (uint32_t)p.lda_main + (uint32_t)a_chunk8[0]) * 2u;
+  const uint32_t a_voff = (a_row[0] * (uint32_t)p.lda_main + (uint32_t)a_chunk8[0]) * 2u;
   auto a_band = [&](int q) {
     return (uint32_t)(BM % A_PAD == 0 ? 64 * q : tile_band_rows(m0, q, a_padded)) * (uint32_t)p.lda_main * 2u;
   };
   // `live` = false (a step past the end of the K range): same number of loads, aimed outside
   // the buffer, so the in-flight count the waits rely on does not depend on the position.
-  auto issue_a = [&](auto kind, int it, uint16_t* a_dst, bool live) {
-    constexpr bool kMain = decltype(kind)::value == 0;
-    const int k0 = kMain ? (it - nk_tail) * BK : it * BK;
-    if constexpr (FAST && kMain) {
+  auto issue_a = [&](int it, uint16_t* a_dst, bool live) {
+    const int k0 = it * BK;
+    if constexpr (FAST) {
       // branch-free on purpose: OR-ing the mask into a valid offset puts it past any buffer
       // (the range check looks at the vector offset, whatever the scalar offset is; so a scalar
       // offset must not lead out of the buffer by itself, see a_band).
       // A branch around a load would make the compiler's count of loads in flight -- and with
       // it every wait it inserts for the code registers -- one too strict.
-      const uint32_t voff = a_voff_main | (live ? 0u : kOobOffset);
+      const uint32_t voff = a_voff | (live ? 0u : kOobOffset);
 #pragma unroll
       for (int q = 0; q < A_LOADS; ++q) {
         const uint32_t soff = (uint32_t)(QALORA_ABLATE == 3 ? (k0 & 255) : k0) * 2u + a_band(q);
         uint16_t* dst = a_dst + (q * 8 + wave) * 512;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a_main,
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a,
                                                  (__attribute__((address_space(3))) void*)dst, 16,
                                                  (int)voff, (int)soff, 0, 0);
       }
       return;
     }
-    const int klim = kMain ? p.K_main : p.K_tail;
-    const uint32_t lda = kMain ? p.lda_main : p.lda_tail;
 #pragma unroll
     for (int q = 0; q < A_LOADS; ++q) {
       const int k = k0 + a_chunk8[q];
-      const uint32_t off = (live && k < klim && a_row[q] < (uint32_t)p.M)
-                               ? (a_row[q] * lda + (uint32_t)k) * 2u
+      const uint32_t off = (live && k < p.K_main && a_row[q] < (uint32_t)p.M)
+                               ? (a_row[q] * (uint32_t)p.lda_main + (uint32_t)k) * 2u
                                : kOobOffset;
       uint16_t* dst = a_dst + (q * 8 + wave) * 512;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(kMain ? rs_a_main : rs_a_tail,
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a,
                                                (__attribute__((address_space(3))) void*)dst, 16,
                                                (int)off, 0, 0, 0);
     }
   };
 
   // ---- B tile through registers --------------------------------------------------------
-  // MAIN steps: half an 8x8 patch of codes per thread.
+  // Half an 8x8 patch of codes per thread.
   //   forward : u0 = K chunk, cq = column quad (8 adjacent lanes fill one 128-byte LDS row)
   //   backward: u0 = K chunk (column octet), u1 = row block, hb = which two row pairs
   // Out-of-range patches are read from a clamped address and get alpha = beta = 0.
@@ -316,14 +279,12 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
   constexpr int RB0 = PackFmt<NBITS>::kRowsPerWord0;
   // Codes, alpha and beta come through buffer loads; a patch outside the matrix gets
   // alpha = beta = 0 (so W~ = 0) by pointing its factor loads past the buffer.
-  const size_t n_groups = (size_t)(p.d_in / (p.group > 0 ? p.group : 1));
+  const size_t n_groups = (size_t)(p.d_in / p.group);
   const __amdgpu_buffer_rsrc_t rs_p0 =
-      make_rsrc(p.plane0, HAS_MAIN ? plane0_words(NBITS, p.d_in, p.d_out) * 4 : 0);
+      make_rsrc(p.plane0, plane0_words(NBITS, p.d_in, p.d_out) * 4);
   const __amdgpu_buffer_rsrc_t rs_p1 =
-      make_rsrc(p.plane1, HAS_MAIN ? plane1_words(NBITS, p.d_in, p.d_out) * 4 : 0);
-  const __amdgpu_buffer_rsrc_t rs_fc = make_rsrc(p.fac, HAS_MAIN ? n_groups * p.d_out * 4 : 0);
-  const __amdgpu_buffer_rsrc_t rs_bt = make_rsrc(
-      p.b_tail, (size_t)(BWD ? (int)n_groups : p.N) * p.K_tail * 2);
+      make_rsrc(p.plane1, plane1_words(NBITS, p.d_in, p.d_out) * 4);
+  const __amdgpu_buffer_rsrc_t rs_fc = make_rsrc(p.fac, n_groups * p.d_out * 4);
   const int f_j0 = n0 + 4 * f_cq;   // forward: this thread's 4 columns
   const int b_i0 = n0 + 8 * b_u1;   // backward: this thread's row block
   const bool n_valid = BWD ? (b_i0 < p.d_in) : (f_j0 < p.d_out);
@@ -332,7 +293,6 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
   // is loading (its loads then have a whole K step to land).
   u32x4_t bregs[2][4];   // fwd: codes, factor words, -, plane-1 codes | bwd: 2 codes, 2 factor words
   u32x4_t bregs1[2][2];  // bwd, N = 3: plane-1 words
-  u32x4_t btail[B_CHUNKS];
   using Set0 = std::integral_constant<int, 0>;
   using Set1 = std::integral_constant<int, 1>;
 
@@ -356,12 +316,11 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
     return __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0);
   };
 
-  auto gload_b = [&](auto kind, int it, auto set, bool live) {
-    constexpr bool kMain = decltype(kind)::value == 0;
+  auto gload_b = [&](int it, auto set, bool live) {
     u32x4_t(&breg)[4] = bregs[decltype(set)::value];
     u32x4_t(&breg1)[2] = bregs1[decltype(set)::value];
-    if constexpr (kMain && FAST) {
-      const uint32_t km = (uint32_t)(it - nk_tail);  // main step index (uniform)
+    if constexpr (FAST) {
+      const uint32_t km = (uint32_t)it;
       const uint32_t dead = live ? 0u : kOobOffset;   // branch-free, as for the A tile
       const uint32_t fb_voff_p0 = fb_voff_p0_c | dead;
       const uint32_t fb_voff_p1 = fb_voff_p1_c | dead;
@@ -387,8 +346,8 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
         breg[2] = buf_load128_s(rs_fc, fb_voff_ab, s_k);
         breg[3] = buf_load128_s(rs_fc, fb_voff_ab + 16, s_k);
       }
-    } else if constexpr (kMain) {
-      const int k0 = (it - nk_tail) * BK;
+    } else {
+      const int k0 = it * BK;
       if constexpr (!BWD) {
         const int i0 = k0 + 8 * f_u0;
         const bool ok = live && n_valid && i0 < p.d_in;
@@ -411,20 +370,6 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
         const uint32_t ab = ok ? ((uint32_t)(b_i0 / p.group) * p.d_out + j0) * 4u : kOobOffset;
         breg[2] = buf_load128(rs_fc, ab);
         breg[3] = buf_load128(rs_fc, ab + 16);
-      }
-    } else {
-      const int k0 = it * BK;
-#pragma unroll
-      for (int q = 0; q < B_CHUNKS; ++q) {
-        const int idx = tid + NT * q;
-        const int row = idx >> 3, ch = idx & 7;
-        const int n = n0 + row;
-        // forward tail: row n of B~^T; backward tail: row n/g of A~ (the unpooling of
-        // the pooled gradient is this broadcast over the g rows of a group)
-        const int src_row = BWD ? n / p.group : n;
-        const int k = k0 + 8 * ch;
-        const bool ok = live && row < BN && n < p.N && k < p.K_tail;
-        btail[q] = buf_load128(rs_bt, ok ? ((uint32_t)src_row * p.K_tail + k) * 2u : kOobOffset);
       }
     }
   };
@@ -453,15 +398,14 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
   // three pieces (piece = 0..2, or -1 for all of it) so that it can be spread over the first
   // three K-16 slices of the matrix-core work of the step before.
   uint32_t wt[8][2];  // backward: [column][row pair] (W~[2m][c], W~[2m+1][c]), kept across pieces
-  auto store_b = [&](auto kind, int it, uint16_t* b_dst, auto set, auto piece_c) {
-    constexpr bool kMain = decltype(kind)::value == 0;
+  auto store_b = [&](int it, uint16_t* b_dst, auto set, auto piece_c) {
     constexpr int piece = decltype(piece_c)::value;
     u32x4_t(&breg)[4] = bregs[decltype(set)::value];
     u32x4_t(&breg1)[2] = bregs1[decltype(set)::value];
     char* bs = reinterpret_cast<char*>(b_dst);
-    if constexpr (kMain) {
+    {
       if constexpr (!BWD) {
-        const int i0 = (it - nk_tail) * BK + 8 * f_u0;
+        const int i0 = it * BK + 8 * f_u0;
         const int sh0 = patch_preshift0<NBITS>(i0), sh1 = patch_preshift1(i0);
         const uint32_t w0[4] = {breg[0].x, breg[0].y, breg[0].z, breg[0].w};
         const uint32_t w1[4] = {breg[3].x, breg[3].y, breg[3].z, breg[3].w};
@@ -520,14 +464,6 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
               uint4{o[0], o[1], o[2], o[3]};
         }
       }
-    } else {
-      static_assert(piece < 0, "tail tiles are copied in one go");
-#pragma unroll
-      for (int q = 0; q < B_CHUNKS; ++q) {
-        const int idx = tid + NT * q;
-        const int row = idx >> 3, ch = idx & 7;
-        if (row < BN) *reinterpret_cast<u32x4_t*>(bs + swz_offset(row, ch)) = btail[q];
-      }
     }
   };
   using AllPieces = std::integral_constant<int, -1>;
@@ -541,67 +477,16 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
   const int a_lane = swz_offset(wm * WTM + (lane & 31), 0);
   const int b_lane = swz_offset(wn * WTN + (lane & 31), 0);
 
-  // `side(kk)` is extra work issued in the shadow of the matrix-core instructions of slice kk.
-  auto compute = [&](auto kind, const uint16_t* a_src, const uint16_t* b_src, auto&& side) {
-    constexpr bool kMain = decltype(kind)::value == 0;
-    const char* as = reinterpret_cast<const char*>(a_src);
-    const char* bs = reinterpret_cast<const char*>(b_src);
-    uint4 af[2][TM], bf[2][TN];
-    auto load_frags = [&](int kk, int slot) {
-      const int cx = (2 * kk + (lane >> 5)) << 4;
-      const char* ap = as + (a_lane ^ cx);
-      const char* bp = bs + (b_lane ^ cx);
-#pragma unroll
-      for (int a = 0; a < TM; ++a) af[slot][a] = *reinterpret_cast<const uint4*>(ap + a * 4096);
-#pragma unroll
-      for (int b = 0; b < TN; ++b) bf[slot][b] = *reinterpret_cast<const uint4*>(bp + b * 4096);
-    };
-    load_frags(0, 0);
-    auto slice = [&](auto kk_c) {
-      constexpr int kk = decltype(kk_c)::value;
-      constexpr int cur = kk & 1;
-      if (kk + 1 < BK / 16) load_frags(kk + 1, cur ^ 1);  // next slice in flight under the MFMAs
-      side(kk_c);
-#pragma unroll
-      for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int b = 0; b < TN; ++b) {
-          if constexpr (kMain)
-            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                __builtin_bit_cast(f16x8, af[cur][a]), __builtin_bit_cast(f16x8, bf[cur][b]),
-                acc[a][b], 0, 0, 0);
-          else
-            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                __builtin_bit_cast(bf16x8, af[cur][a]), __builtin_bit_cast(bf16x8, bf[cur][b]),
-                acc[a][b], 0, 0, 0);
-        }
-      // one matrix-core instruction, then whatever else is ready (LDS reads of the next
-      // slice, the side work), eight times over; nothing crosses into the next slice
-#pragma unroll
-      for (int i = 0; i < TM * TN; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // LDS read
-        __builtin_amdgcn_sched_group_barrier(0x002, kSideValuPerMfma, 0);  // VALU
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    slice(std::integral_constant<int, 0>{});
-    slice(std::integral_constant<int, 1>{});
-    slice(std::integral_constant<int, 2>{});
-    slice(std::integral_constant<int, 3>{});
-  };
-  auto no_side = [](auto) {};
-
-  // Main-pipeline variant.  The fragment registers live across steps: slices 0-2 carry the
+  // The fragment registers live across steps: slices 0-2 carry the
   // side work (the dequantisation of the next step, one piece each), then the block
   // synchronises, and slice 3 runs while the first fragments of the NEXT step are fetched
   // from the stages that barrier has just published -- so a step starts on the matrix cores
   // at once instead of waiting for an LDS round trip.
-  constexpr int kMainB = BWD ? (NBITS == 3 ? 6 : 4) : (NBITS == 3 ? 3 : 2);
+  constexpr int kBLoads = BWD ? (NBITS == 3 ? 6 : 4) : (NBITS == 3 ? 3 : 2);
   // see the main step below (two stages: only the registers of it+2 were requested after A(it+1))
-  constexpr int kMidKeep = A_STAGES == 2 ? kMainB : kMainB + A_LOADS + kMainB;
+  constexpr int kMidKeep = A_STAGES == 2 ? kBLoads : kBLoads + A_LOADS + kBLoads;
   uint4 maf[2][TM], mbf[2][TN];
-  auto load_frags_main = [&](const uint16_t* a_src, const uint16_t* b_src, int kk, auto slot_c) {
+  auto load_frags = [&](const uint16_t* a_src, const uint16_t* b_src, int kk, auto slot_c) {
     constexpr int slot = decltype(slot_c)::value;
     const int cx = (2 * kk + (lane >> 5)) << 4;
     const char* ap = reinterpret_cast<const char*>(a_src) + (a_lane ^ cx);
@@ -615,17 +500,17 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
     for (int b = 0; b < TN; ++b)
       mbf[slot][b] = b < kReadB ? *reinterpret_cast<const uint4*>(bp + b * 4096) : mbf[slot][0];
   };
-  auto compute_main = [&](const uint16_t* a_rd, const uint16_t* b_rd, const uint16_t* a_nx,
+  auto compute = [&](const uint16_t* a_rd, const uint16_t* b_rd, const uint16_t* a_nx,
                           const uint16_t* b_nx, auto&& side, auto&& after_barrier) {
     auto slice = [&](auto kk_c) {
       constexpr int kk = decltype(kk_c)::value;
       constexpr int cur = kk & 1;
       using Nxt = std::integral_constant<int, cur ^ 1>;
       if constexpr (kk < 3) {
-        load_frags_main(a_rd, b_rd, kk + 1, Nxt{});
+        load_frags(a_rd, b_rd, kk + 1, Nxt{});
         side(kk_c);
       } else {
-        load_frags_main(a_nx, b_nx, 0, Nxt{});
+        load_frags(a_nx, b_nx, 0, Nxt{});
       }
 #pragma unroll
       for (int a = 0; a < TM; ++a)
@@ -659,12 +544,8 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
     slice(std::integral_constant<int, 3>{});
   };
 
-  // Vector-memory ops per thread of one B-register load, per step kind (for the waits).
-  constexpr int kBLoadsMain = BWD ? (NBITS == 3 ? 6 : 4) : (NBITS == 3 ? 3 : 2);
-  constexpr int kBLoadsTail = B_CHUNKS;
-
-  if constexpr (HAS_MAIN) {
-    // Main steps.  K step `it` in pipeline slot `slot` (A stage slot % 3, B stage and register
+  {
+    // K step `it` in pipeline slot `slot` (A stage slot % 3, B stage and register
     // set slot % 2, the parity `par` being a compile-time constant):
     //   entry : A(it), B(it) visible in LDS; the LDS-DMA of A(it+1), A(it+2) and the register
     //           loads of step it+1 (set par^1) are in flight or done
@@ -696,33 +577,33 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
           Bs + (kPar ^ 1) * B_TILE,
           [&](uint16_t*, const uint16_t* a_rd, const uint16_t* a_nx, const uint16_t* b_rd,
               uint16_t* b_wr) {
-            if constexpr (!kSingleSet) gload_b(MainK{}, at(it + 2), SetCur{}, live(it + 2));
+            if constexpr (!kSingleSet) gload_b(at(it + 2), SetCur{}, live(it + 2));
             __builtin_amdgcn_sched_barrier(0);
-            compute_main(
+            compute(
                 a_rd, b_rd, a_nx, b_wr,
                 [&](auto kk) {
-                  store_b(MainK{}, it + 1, b_wr, SetNext{}, kk);
+                  store_b(it + 1, b_wr, SetNext{}, kk);
                   if constexpr (kSingleSet && decltype(kk)::value == 2)
-                    gload_b(MainK{}, at(it + 2), SetCur{}, live(it + 2));
+                    gload_b(at(it + 2), SetCur{}, live(it + 2));
                 },
-                [&]() { issue_a(MainK{}, at(it + A_STAGES), a_cur, live(it + A_STAGES)); });
+                [&]() { issue_a(at(it + A_STAGES), a_cur, live(it + A_STAGES)); });
           });
     };
     if (pe > pb) {
       // prologue: A(pb), A(pb+1), A(pb+2) in flight, registers of pb (set 0) and pb+1 (set 1)
       // loading; B(pb) dequantised into stage 0
-      issue_a(MainK{}, pb, As, true);
-      gload_b(MainK{}, pb, Set0{}, true);
-      issue_a(MainK{}, at(pb + 1), As + A_TILE, live(pb + 1));
-      if constexpr (!kSingleSet) gload_b(MainK{}, at(pb + 1), Set1{}, live(pb + 1));
-      if constexpr (A_STAGES == 3) issue_a(MainK{}, at(pb + 2), As + 2 * A_TILE, live(pb + 2));
+      issue_a(pb, As, true);
+      gload_b(pb, Set0{}, true);
+      issue_a(at(pb + 1), As + A_TILE, live(pb + 1));
+      if constexpr (!kSingleSet) gload_b(at(pb + 1), Set1{}, live(pb + 1));
+      if constexpr (A_STAGES == 3) issue_a(at(pb + 2), As + 2 * A_TILE, live(pb + 2));
       __builtin_amdgcn_sched_barrier(0);
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((A_STAGES - 1) * A_LOADS + (kSingleSet ? 0 : kBLoadsMain))
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((A_STAGES - 1) * A_LOADS + (kSingleSet ? 0 : kBLoads))
                    : "memory");
-      store_b(MainK{}, pb, Bs, Set0{}, AllPieces{});
-      if constexpr (kSingleSet) gload_b(MainK{}, at(pb + 1), Set0{}, live(pb + 1));
+      store_b(pb, Bs, Set0{}, AllPieces{});
+      if constexpr (kSingleSet) gload_b(at(pb + 1), Set0{}, live(pb + 1));
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-      load_frags_main(As, Bs, 0, Set0{});
+      load_frags(As, Bs, 0, Set0{});
       int it = pb;
       if constexpr (A_STAGES == 3) {
         uint16_t *a0 = As, *a1 = As + A_TILE, *a2 = As + 2 * A_TILE;  // stages of it, it+1, it+2
@@ -747,44 +628,6 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
       }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the out-of-range loads of the last steps
     }
-  } else {
-    // Plain product over the tail operands: one register set, so the copy of step it+1 into
-    // LDS and the loads of step it+2 follow the matrix-core work of step it.
-    //   entry : A(it), B(it) visible in LDS; A(it+1) LDS-DMA in flight; registers hold it+1
-    auto step = [&](auto n1, auto n2, int it, int slot) {
-      constexpr bool kHas1 = decltype(n1)::value != 2;
-      constexpr bool kHas2 = decltype(n2)::value != 2;
-      const int sa = slot % 3, sa2 = (slot + 2) % 3, sb = slot & 1;
-      with_step_regions(
-          As + sa2 * A_TILE, As + sa * A_TILE, Bs + sb * B_TILE, Bs + (sb ^ 1) * B_TILE,
-          [&](uint16_t* a_dma, const uint16_t* a_rd, const uint16_t* b_rd, uint16_t* b_wr) {
-            if constexpr (kHas2) issue_a(TailK{}, it + 2, a_dma, true);
-            __builtin_amdgcn_sched_barrier(0);
-            compute(TailK{}, a_rd, b_rd, no_side);
-            if constexpr (kHas1) store_b(TailK{}, it + 1, b_wr, Set0{}, AllPieces{});
-            if constexpr (kHas2) gload_b(TailK{}, it + 2, Set0{}, true);
-          });
-      constexpr int kKeepT = kHas2 ? A_LOADS + kBLoadsTail : 0;
-      wait_and_barrier<kKeepT>();
-    };
-    const int pb = it_begin, pe = it_end;
-    const int n = pe - pb;
-    if (n > 0) {
-      issue_a(TailK{}, pb, As, true);
-      gload_b(TailK{}, pb, Set0{}, true);
-      if (n > 1) issue_a(TailK{}, pb + 1, As + A_TILE, true);
-      store_b(TailK{}, pb, Bs, Set0{}, AllPieces{});
-      if (n > 1) gload_b(TailK{}, pb + 1, Set0{}, true);
-      wait_and_barrier<0>();  // prologue only: drain everything
-      int it = pb, slot = 0;
-#pragma nounroll
-      for (; it + 2 < pe; ++it, ++slot) step(TailK{}, TailK{}, it, slot);  // hot loop
-      if (it + 1 < pe) {
-        step(TailK{}, NoneK{}, it, slot);
-        ++it, ++slot;
-      }
-      step(NoneK{}, NoneK{}, it, slot);
-    }
   }
 
   // ---- epilogue: D[m][n] lives at lane n%32, register 4*(m/8) + m%4, half (m/4)%2 ----
@@ -802,17 +645,14 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
   char* stage = reinterpret_cast<char*>(smem) + BM * 4;
   __syncthreads();  // every wave is past its last LDS read of the K loop
   if (e_tid < BM)
-    inv_s[e_tid] = (HAS_MAIN && m0 + e_tid < p.M) ? p.row_scale[m0 + e_tid].y : 1.0f;
+    inv_s[e_tid] = m0 + e_tid < p.M ? p.row_scale[m0 + e_tid].y : 1.0f;
   // 1 / S of the factor words for this lane's output columns: per column (forward), one value
   // for the call (backward)
   float inv_n[TN];
 #pragma unroll
   for (int b = 0; b < TN; ++b) {
-    inv_n[b] = 1.0f;
-    if constexpr (HAS_MAIN) {
-      const int n = n0 + e_wn * WTN + b * 32 + (e_lane & 31);
-      inv_n[b] = BWD ? p.n_scale[0] : (n < p.N ? p.n_scale[n] : 1.0f);
-    }
+    const int n = n0 + e_wn * WTN + b * 32 + (e_lane & 31);
+    inv_n[b] = BWD ? p.n_scale[0] : (n < p.N ? p.n_scale[n] : 1.0f);
   }
   auto epilogue = [&](auto as_bf16) {
     constexpr bool kBf16 = decltype(as_bf16)::value;
@@ -876,11 +716,11 @@ __global__ __launch_bounds__(NT, gemm_min_waves(BM, HAS_MAIN, NBITS, BWD, FAST))
   if (timeline) p.block_times[4 * blockIdx.x + 2] = (unsigned long long)wall_clock64();
 }
 
-template <int NBITS, bool BWD, int BM, int BN, int WAVES_M, int WAVES_N, bool HAS_MAIN, bool FAST>
+template <int NBITS, bool BWD, int BM, int BN, int WAVES_M, int WAVES_N, bool FAST>
 static hipError_t launch_cfg(const GemmArgs& a, int ksplit, hipStream_t st, hipEvent_t ev_start = nullptr,
                              hipEvent_t ev_stop = nullptr) {
-  auto kern = gemm_dq_kernel<NBITS, BWD, BM, BN, WAVES_M, WAVES_N, HAS_MAIN, FAST>;
-  const size_t smem = (size_t)(gemm_a_stages(BM, HAS_MAIN) * BM + 2 * BN) * 64 * sizeof(uint16_t);
+  auto kern = gemm_dq_kernel<NBITS, BWD, BM, BN, WAVES_M, WAVES_N, FAST>;
+  const size_t smem = (size_t)(gemm_a_stages(BM) * BM + 2 * BN) * 64 * sizeof(uint16_t);
   static std::atomic<uint64_t> granted{0};  // per instantiation
   if (hipError_t e = grant_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, granted); e != hipSuccess)
     return e;

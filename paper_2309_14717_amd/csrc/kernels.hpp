@@ -28,13 +28,10 @@ struct GemmArgs {
                            // multiplied by its power-of-two row scale
   int lda_main;
   int a_main_padded_rows;   // rows a_main may be read for (>= M; the rest holds anything)
-  const uint16_t* a_tail;  // bf16 [M, K_tail]: first operand of a plain product (no main part)
-  int lda_tail;
   const uint32_t* plane0;  // packed codes
   const uint32_t* plane1;
   const uint32_t* fac;     // [L, d_out] factor words: fp16(alpha S) | fp16((beta' + mid alpha) S) << 16
   const float* n_scale;    // 1 / S: [d_out] (forward, per column) or [1] (backward)
-  const uint16_t* b_tail;  // bf16 [N, K_tail]: second operand of a plain product
   const float2* row_scale; // [M] (scale, 1/scale): power-of-two row scales of a_main
   void* out;               // [ksplit][M, N] fp32, or [M, N] bf16
   int out_bf16;
@@ -42,8 +39,7 @@ struct GemmArgs {
   int ksplit;              // K slices of the dequantising product (0 or 1: none)
   int tile_rows;           // of the dequantising product: 64, 128, 192 or 256
   int M, N;                // tokens; d_out (forward) or d_in (backward)
-  int K_main;              // d_in (forward) or d_out (backward); 0 for a plain product
-  int K_tail;              // multiple of 64 (zero padded), may be 0
+  int K_main;              // d_in (forward) or d_out (backward)
   int d_in, d_out, group;
   unsigned long long* clock_probe;  // measurement aid (may be null): block 0 stores its shader
                                     // cycle and wall-clock tick counts at start and end, [4]
@@ -51,7 +47,9 @@ struct GemmArgs {
   int block_times_cap;              // stores wall-clock ticks at start, K loop end and end, and
                                     // the id of the XCD it ran on, [4 b .. 4 b + 3]
 };
-hipError_t launch_gemm_dq(int bits, bool bwd, const GemmArgs& a, hipStream_t st);
+// `sum`: where given and K is split, the sum over the slices is not launched but described there.
+struct SplitSum;
+hipError_t launch_gemm_dq(int bits, bool bwd, const GemmArgs& a, hipStream_t st, SplitSum* sum = nullptr);
 // Measurement aid: events recorded around the next launch_gemm_dq of each direction.
 struct ProfileHook {
   hipEvent_t start, stop;
@@ -60,8 +58,6 @@ struct ProfileHook {
   int block_times_cap;
 };
 extern ProfileHook g_profile_hook[2];
-hipError_t launch_gemm_plain(const GemmArgs& a, int ksplit, hipStream_t st);
-int gemm_plain_tile_rows(int K);  // row tile launch_gemm_plain uses for a K of this length
 
 // --- smallt.hip ---------------------------------------------------------------------
 // Adapter-free forward for T <= 16 tokens, INT4, group 32 / 64 / 128 (memory-bound path).
@@ -140,8 +136,8 @@ struct MidTArgs {
 hipError_t launch_midt(int bits, const MidTArgs& a, int blocks, hipStream_t st);  // nonce set here
 
 // --- adapter.hip --------------------------------------------------------------------
-// Rows of the hi (and of the lo) section of a bf16 hi/lo split of a [rank, *] matrix.
-__host__ __device__ inline int rank_pad32(int rank) { return ((rank + 31) / 32) * 32; }
+// Elements of a token's row of hi(P), and of lo(P) behind it, in the pooled activations' storage bf16 [T][2 Lp].
+__host__ __device__ inline int pooled_ld(int L) { return (L + 7) / 8 * 8; }
 
 // The adapters of up to MAX_PARTS linears that share their input x and are evaluated as one
 // wide layer (q/k/v; gate/up): part p owns columns [col0, col0 + d_out) of it.  A single layer
@@ -182,39 +178,87 @@ hipError_t launch_factor_scale(const float* alpha, const float* cst, const float
                                size_t n, uint32_t* words, float* inv_scale, hipStream_t st);
 
 // Forward front launch: x -> rs (row scales), x16 = fp16(x * scale), the factor job, and, when
-// given, P_keep fp32 [T, L] = pool_g(x) and per part u_keep fp32 [T, rank] = s pool_g(x) A, from
-// which the backward front launch below can work without x (its u_kept argument).
-hipError_t launch_front_forward(const uint16_t* x, int T, int d_in, float2* rs, uint16_t* x16,
-                                const AdapterParts& parts, int g, float* P_keep,
-                                float* const* u_keep, const FactorJob& fac, hipStream_t st);
-// Backward front launch: dy -> rs_dy, dy16; the factor job (first stage); and per adapter part
-//   P       fp32 [T, L]          = pool_g(x)  (shared by the parts)
-//   us_t    bf16 [2*rp, t_pad]   = rows hi(sU)^T then lo(sU)^T (token-contiguous, zero padded)
-//   b_hl    bf16 [2*rp, d_out]   = hi(B) rows then lo(B) rows
-// With u_kept (the forward's u_keep) x is not read: P is not written (the caller passes the
-// forward's P_keep on to the gradient kernels) and us_t is transposed from u_kept.
-hipError_t launch_front_backward(const uint16_t* dy, int T, int d_out, float2* rs_dy,
-                                 uint16_t* dy16, const uint16_t* x, int d_in,
-                                 const AdapterParts& parts, int g, float* P, uint16_t* const* us_t,
-                                 int t_pad, uint16_t* const* b_hl, const float* const* u_kept,
-                                 const FactorJob& fac, hipStream_t st);
-// Both adapter-gradient jobs in one launch (neither depends on the other):
-//   dB partials over token slices: db_part[z][rank][d_out] = sum_{t in slice z} sU[t,:]^T dy[t,:]
-//   (dy: rows dy_ld elements apart, so that a part's columns of a wider dy can be passed)
-//   dA partials over token slices: da_part[z][L][rank] = sum_{t in slice z} P[t,:]^T dU[t,:], with
-//   dU = s * sum_q (raw[q][:, :rp] + raw[q][:, rp:]) rebuilt from the split-K partials of the dU
-//   product
-hipError_t launch_adapter_grads(const uint16_t* us_t, int t_pad, const uint16_t* dy, int dy_ld, int T,
-                                int d_out, int rank, int tsplit_b, float* db_part, const float* P,
-                                const float* raw, int ksplit, float s, int L, int tsplit_a,
-                                float* da_part, hipStream_t st);
-// out = (accumulate ? out : 0) + sum_z part[z], fixed order, for two outputs in one launch
-hipError_t launch_reduce2(const float* part_a, int nparts_a, size_t n_a, float* out_a,
-                          const float* part_b, int nparts_b, size_t n_b, float* out_b,
-                          int accumulate, hipStream_t st);
+// given, P_keep bf16 [T][2 Lp]: hi and lo of pool_g(x), for the gradients.
+hipError_t launch_front_forward(const uint16_t* x, int T, int d_in, float2* rs, uint16_t* x16, int g,
+                                uint16_t* P_keep, const FactorJob& fac, hipStream_t st);
+// Backward front launch: dy -> rs_dy, dy16; the factor job; and, given x, P bf16 [T][2 Lp] as above.
+hipError_t launch_front_backward(const uint16_t* dy, int T, int d_out, float2* rs_dy, uint16_t* dy16,
+                                 const uint16_t* x, int d_in, int g, uint16_t* P, const FactorJob& fac,
+                                 hipStream_t st);
 // beta_out = beta + (s/g) A B
 hipError_t launch_merge(const float* beta, const float* A, const float* B, int L, int d_out,
                         int rank, int g, float s, float* beta_out, hipStream_t st);
+
+// --- grads.hip: the adapters' gradients --------------------------------------------------
+// How Z = pool_g(x)^T dy is computed: in equal runs of units (a tile's step of tokens), or for few tokens inside
+// the launch that uses it.
+struct ZRuns {
+  int steps, units, blocks;  // of a tile; in all; one run each
+  __host__ __device__ int first(int b) const { return (int)((long)b * units / blocks); }            // unit of block b
+  __host__ __device__ int owner(int u) const { return (int)(((long)(u + 1) * blocks - 1) / units); }  // block of unit u
+};
+struct GradsPlan {
+  bool fused;
+  ZRuns runs;  // else
+  int slots;   // partial sums of a tile, at most
+};
+GradsPlan grads_plan(int T, int L, int d_out);
+int grads_da_shares(int d_out);  // shares of dA that a part of so many columns leaves
+int grads_db_shares(int L);      // shares of dB that so many groups leave; 0: dB comes out whole
+struct ZArgs {
+  const uint16_t* P;   // bf16 [T][2 Lp]: hi and lo of the pooled activations
+  const uint16_t* dy;  // bf16 [T, d_out], all parts
+  int T, L, Lp, d_out;
+  ZRuns runs;
+  float* Z;            // [slots][L, d_out]; unused in the fused form
+};
+struct FinishPart {
+  const float* A;  // [L, rank]
+  const float* B;  // [rank, d_out of the part]
+  float s;
+  int rank, col0, d_out;
+  float* dB;       // [rank, d_out of the part]
+  float* da_part;  // [grads_da_shares(d_out)][L, rank]
+  float* db_part;  // [grads_db_shares(L)][rank, d_out of the part]
+};
+struct FinishArgs {
+  const float* Z;
+  int L, d_out, accumulate;
+  ZRuns runs;
+  FinishPart part[MAX_PARTS];  // widths multiples of 32 when there are several
+  int n_parts;
+};
+hipError_t launch_grads(const GradsPlan& plan, const ZArgs& z, const FinishArgs& f, hipStream_t st);
+struct SplitSum {  // out = sum over the slices of a split product's partial results
+  const float* partial;  // [slices][4 n4]
+  int slices;
+  size_t n4;             // 0: nothing to do
+  void* out;
+  int out_bf16;
+};
+struct TailPart {
+  const float* da_part;
+  int shares;
+  size_t n;        // L * rank
+  float s;
+  float* dA;
+  int block0;      // filled in by the launcher
+};
+struct TailSum {
+  SplitSum sum;
+  bool gradient;   // out = (accumulate ? out : 0) + s sum, fp32
+  float s;
+  int block0;      // filled in by the launcher
+};
+struct TailArgs {
+  TailPart part[MAX_PARTS];
+  int n_parts, accumulate;
+  TailSum sum[MAX_PARTS + 1];
+  int n_sums;
+  int da_blocks;   // filled in by the launcher
+};
+// What is left to add up at the end of a backward: the shares of dA and dB, and the slices of dx.
+hipError_t launch_tail(TailArgs t, hipStream_t st);
 
 // out = -(alpha * in) (zero point -> zero factor) or -(in / alpha) (the reverse), n elements
 hipError_t launch_zero_point(const float* alpha, const float* in, float* out, size_t n, bool to_zero_point,

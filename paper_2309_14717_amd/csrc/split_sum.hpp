@@ -1,0 +1,51 @@
+// Sums over copies of a matrix, copies in order.
+#pragma once
+#include <type_traits>
+
+#include "common.hpp"
+#include "kernels.hpp"
+
+namespace qalora {
+
+// v[q] = src[q][0] + src[q][stride] + ... over n copies; the loads of up to B copies are in flight together
+template <int B, int Q>
+__device__ __forceinline__ void sum_slices(const f32x4* const (&src)[Q], size_t stride, int n, f32x4 (&v)[Q]) {
+#pragma unroll
+  for (int q = 0; q < Q; ++q) v[q] = src[q][0];
+  auto add = [&](auto n_c, int z0) {
+    constexpr int c = decltype(n_c)::value;
+    f32x4 ld[c][Q];
+#pragma unroll
+    for (int z = 0; z < c; ++z)
+#pragma unroll
+      for (int q = 0; q < Q; ++q) ld[z][q] = src[q][(size_t)(z0 + z) * stride];
+#pragma unroll
+    for (int z = 0; z < c; ++z)
+#pragma unroll
+      for (int q = 0; q < Q; ++q) v[q] += ld[z][q];
+  };
+  int z = 1;
+  if constexpr (B >= 8)
+    for (; z + 8 <= n; z += 8) add(std::integral_constant<int, 8>{}, z);
+  for (; z + 4 <= n; z += 4) add(std::integral_constant<int, 4>{}, z);
+  if (z + 2 <= n) add(std::integral_constant<int, 2>{}, z), z += 2;
+  if (z < n) add(std::integral_constant<int, 1>{}, z);
+}
+template <int B = 4>
+__device__ __forceinline__ f32x4 sum_slices(const f32x4* src, size_t stride, int n) {
+  const f32x4* s[1] = {src};
+  f32x4 v[1];
+  sum_slices<B>(s, stride, n, v);
+  return v[0];
+}
+
+// Four elements of the sum over the slices of a split product, converted on the way out.
+__device__ __forceinline__ void split_sum_one(const SplitSum& s, size_t i) {
+  const f32x4 v = sum_slices(reinterpret_cast<const f32x4*>(s.partial) + i, s.n4, s.slices);
+  if (s.out_bf16)
+    reinterpret_cast<uint2*>(s.out)[i] = uint2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+  else
+    reinterpret_cast<f32x4*>(s.out)[i] = v;
+}
+
+}  // namespace qalora

@@ -1,0 +1,64 @@
+"""The adapter's gradients by way of Z = pool(x)^T dy, at the edges of its launches: one launch (up to 640 tokens and
+256 blocks of 128 groups x 32 columns) or runs of (tile, 64 tokens) units whose partial sums meet, more than 128
+groups (dB in shares), group counts that are no multiple of eight, ranks beside multiples of sixteen.  Against
+the oracle.  Tolerance: pool(x) goes through the matrix cores as bf16 hi + lo, 2^-17 of each element; errors of
+T terms add up like their signs do, so relative to the largest gradient no more than 2^-17 sqrt(T) / 4 < 1.2e-4 for
+the 4096 tokens here at most (measured: 1e-6 to 1e-5)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import layer_on_gpu, record, rel_err
+from paper_2309_14717_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+TOL_GRAD = 1.2e-4
+
+
+@pytest.mark.parametrize("tokens,d_in,d_out,bits,group,rank", [
+    (1, 128, 8, 4, 32, 1),          # one token, a quarter of a column block
+    (63, 1024, 1000, 4, 8, 17),     # 128 groups exactly; rank beside a multiple of 16
+    (65, 1032, 264, 4, 8, 128),     # 129 groups: a second share of one group
+    (640, 4160, 40, 2, 32, 15),     # the longest batch in one launch; two shares, 130 groups
+    (641, 416, 520, 4, 32, 16),     # the first in two; 13 groups
+    (700, 2080, 1032, 4, 8, 33),    # 260 groups: three tiles of them, runs that cross tiles
+    (1000, 96, 8200, 3, 32, 64),    # three groups; more tiles than a run's
+    (130, 1024, 8256, 4, 8, 8),     # 258 blocks: two launches at few tokens
+    (4096, 256, 136, 4, 128, 64),   # two groups, two tiles of columns, 64 steps
+])
+def test_gradients(gpu_api, tokens, d_in, d_out, bits, group, rank):
+    cfg = synth.LayerConfig("grads", tokens, d_in, d_out, bits, group, rank, 0.5, seed=91)
+    L = layer_on_gpu(gpu_api, cfg)
+    d, n = L["desc"], L["np"]
+    w = (L["packed"], L["g_alpha"], L["g_beta"], L["A"], L["B"])
+    _, rdA, rdB = oracle.backward(n["dy"], n["x"], L["codes"], L["alpha"], L["beta"], group, n["A"], n["B"], cfg.s)
+    dx, dA, dB = gpu_api.backward(d, L["dy"], L["x"], *w)
+    eA, eB = rel_err(dA.cpu().numpy(), rdA), rel_err(dB.cpu().numpy(), rdB)
+    record(f"gradients T={tokens} {d_in}x{d_out} g={group} r={rank}", dA=eA, dB=eB)
+    assert eA <= TOL_GRAD and eB <= TOL_GRAD
+    # from the kept activations, added to what is there: the same sums
+    _, kept = gpu_api.forward_keep(d, L["x"], *w)
+    a0, b0 = torch.ones_like(dA), torch.full_like(dB, -2.0)
+    kdx, kA, kB = gpu_api.backward_kept(d, L["dy"], kept, *w, dA=a0.clone(), dB=b0.clone(), accumulate=True)
+    assert torch.equal(kdx, dx)
+    assert torch.equal(kA, a0 + dA) and torch.equal(kB, b0 + dB)
+    again = gpu_api.backward(d, L["dy"], L["x"], *w)
+    assert torch.equal(again[1], dA) and torch.equal(again[2], dB)
+
+
+def test_values_that_are_not_finite_stay_in_their_groups_and_columns(gpu_api):
+    """An infinity in x reaches its group's row of dA, one in dy its column of dB."""
+    cfg = synth.LayerConfig("grads", 70, 512, 256, 4, 32, 16, 0.5, seed=92)
+    L = layer_on_gpu(gpu_api, cfg)
+    w = (L["packed"], L["g_alpha"], L["g_beta"], L["A"], L["B"])
+    x, dy = L["x"].clone(), L["dy"].clone()
+    x[3, 40] = float("inf")
+    _, dA, _ = gpu_api.backward(L["desc"], dy, x, *w)
+    bad = ~torch.isfinite(dA).cpu().numpy()
+    assert bad[1].all() and not np.delete(bad, 1, axis=0).any()
+    dy[5, 77] = float("inf")
+    _, _, dB = gpu_api.backward(L["desc"], dy, L["x"], *w)
+    bad = ~torch.isfinite(dB).cpu().numpy()
+    assert bad[:, 77].all() and not np.delete(bad, 77, axis=1).any()
