@@ -217,9 +217,9 @@ int qalora_backward(const qalora_desc* desc, int tokens, const void* dy, const v
                     float* dB, int accumulate, void* ws, size_t ws_bytes, void* stream);
 
 /* The pair above for training loops that keep the pooled activations instead of x.  The
- * backward needs x only through P = pool_g(x) and U = P A (Alg. 1; App. B.2: the adapter sees
- * the group averages, never x itself), which are g times smaller than x.
- * qalora_forward_keep is qalora_forward (adapter required) that also leaves them in `kept`:
+ * backward needs x only through P = pool_g(x) (Alg. 1; App. B.2: the adapter sees
+ * the group averages, never x itself), which is g times smaller than x.
+ * qalora_forward_keep is qalora_forward (adapter required) that also leaves it in `kept`:
  * device memory of qalora_kept_bytes(desc, tokens) bytes, 16-byte aligned, contents private to
  * the library and valid for a backward call with the same desc, tokens, A and B.
  * qalora_backward_kept is qalora_backward reading `kept` in place of x: same results bit for

@@ -1,8 +1,10 @@
 """Thin Python binding of the C-ABI library (include/qalora.h).
 
 Argument marshalling only: every step of the layer runs in the HIP kernels behind the
-C ABI.  PyTorch supplies device memory and the stream.  There is no fallback: if the
-shared library has not been built, or a call returns an error status, this raises.
+C ABI.  PyTorch supplies device memory and the stream.  The calls of a training step or a serving
+loop are marshalled in native code (csrc/binding.cpp) where their arguments are plainly valid.
+There is no fallback: if the shared library has not been built, or a call returns an error
+status, this raises.
 """
 from __future__ import annotations
 
@@ -116,8 +118,37 @@ def load() -> ctypes.CDLL:
     lib.qalora_adamw_step.argtypes = [vp, i, i, vp, vp, vp, vp, vp, i, vp, vp, sz, vp]
     lib.qalora_beta_from_zero_point.argtypes = [cp, vp, vp, vp, vp]
     lib.qalora_zero_point_from_beta.argtypes = [cp, vp, vp, vp, vp]
+    _bind_native(lib)
     _lib = lib
     return lib
+
+
+_native = None
+_NATIVE_ENTRIES = (
+    "qalora_check_desc", "qalora_packed_bytes", "qalora_workspace_bytes", "qalora_quantize", "qalora_forward",
+    "qalora_kept_bytes", "qalora_forward_keep", "qalora_backward", "qalora_backward_kept", "qalora_deployed_bytes",
+    "qalora_forward_deployed", "qalora_forward_factors16", "qalora_adamw_step", "qalora_shared_kept_bytes",
+    "qalora_shared_workspace_bytes", "qalora_forward_shared", "qalora_backward_shared", "qalora_swiglu_forward_wide",
+    "qalora_swiglu_backward_wide")
+
+
+def _bind_native(lib):
+    """Hand the library's entry points to the native form of the calls below (csrc/binding.cpp).  Each function
+    asks it first: it takes the calls whose arguments are plainly valid and returns None for all others, which
+    the checks here then look at one by one."""
+    global _native
+    path = os.path.join(_HERE, "_native.so")
+    if not os.path.exists(path):
+        raise RuntimeError(f"{path} not found: build it first (python -m paper_2309_14717_amd.build)")
+    from . import _native as native
+    native.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_ENTRIES}, _check)
+    _native = native
+
+
+def _fast():
+    if _lib is None:
+        load()
+    return _native
 
 
 def status_string(status: int) -> str:
@@ -219,6 +250,9 @@ def _need_out(t, name, rows, cols, dev):
 
 def quantize(desc: Desc, W: torch.Tensor):
     """W fp32 [d_in, d_out] (device) -> (packed uint8, alpha fp32 [L, d_out], beta fp32 [L, d_out])."""
+    out = _fast().quantize(desc, W)
+    if out is not None:
+        return out
     _need(W, "W", torch.float32)
     if check_desc(desc) == OK:
         _need(W, "W", shape=(desc.d_in, desc.d_out))
@@ -269,6 +303,9 @@ def pack(desc: Desc, codes: torch.Tensor) -> torch.Tensor:
 def forward(desc: Desc, x, packed, alpha, beta, A=None, B=None, out_dtype=torch.float32, ws=None,
             y=None):
     """y = x W~ + s (pool(x) A) B.  x bf16 [T, d_in]; returns y [T, d_out]."""
+    out = _fast().forward(desc, x, packed, alpha, beta, A, B, out_dtype, ws, y)
+    if out is not None:
+        return out
     T, dev = _need_layer(desc, x, desc.d_in, packed, alpha, beta, A, B)
     if y is None:
         y = torch.empty((T, desc.d_out), dtype=out_dtype, device=dev)
@@ -324,6 +361,9 @@ def forward_shared(desc: Desc, x, packed, alpha, beta, adapters, keep=False, out
                    ws=None, y=None, kept=None):
     """Linears that share x as one wide layer (see qalora_forward_shared).  ``adapters`` is a
     list of (A, B, s), one per part in column order.  Returns y, or (y, kept) with ``keep``."""
+    out = _fast().forward_shared(desc, x, packed, alpha, beta, adapters, keep, out_dtype, ws, y, kept)
+    if out is not None:
+        return out
     T, dev = _need_layer(desc, x, desc.d_in, packed, alpha, beta, None, None)
     arr = _parts(desc, adapters, dev)
     n = len(adapters)
@@ -350,6 +390,10 @@ def backward_shared(desc: Desc, dy, x, kept, packed, alpha, beta, adapters, want
                     dx_dtype=torch.float32, grads=None, accumulate=False, ws=None, dx=None):
     """Backward of forward_shared: one dx over all parts, (dA, dB) per part.  Pass ``kept`` (from
     forward_shared(keep=True)) or ``x``.  Returns (dx, [(dA, dB), ...])."""
+    out = _fast().backward_shared(desc, dy, x, kept, packed, alpha, beta, adapters, want_dx, dx_dtype, grads, accumulate,
+                                  ws, dx)
+    if out is not None:
+        return out
     T, dev = _need_layer(desc, dy, desc.d_out, packed, alpha, beta, None, None, x_name="dy")
     if kept is None:
         _need(x, "x", torch.bfloat16, (T, desc.d_in), device=dev)
@@ -394,6 +438,9 @@ def forward_deployed(desc: Desc, x, deployed, packed=None, out_dtype=torch.float
     """Adapter-free forward of a deployed layer: the decode stream up to four tokens; beyond that
     ``packed`` is required: the mid-token kernel up to 64 tokens, the dense kernel with the prepared factor
     words above (see mid_blocks)."""
+    out = _fast().forward_deployed(desc, x, deployed, packed, out_dtype, ws, y)
+    if out is not None:
+        return out
     _need(x, "x", torch.bfloat16)
     T, dev = x.shape[0], x.device
     if check_desc(desc) == OK:
@@ -443,6 +490,9 @@ def pack_factors16(desc: Desc, alpha, beta, out=None):
 
 def forward_factors16(desc: Desc, x, packed, factors16, out_dtype=torch.float32, ws=None, y=None):
     """Adapter-free y = x W~ with the factors stored in 16 bits (see pack_factors16)."""
+    out = _fast().forward_factors16(desc, x, packed, factors16, out_dtype, ws, y)
+    if out is not None:
+        return out
     _need(x, "x", torch.bfloat16)
     T, dev = x.shape[0], x.device
     if check_desc(desc) == OK:
@@ -463,6 +513,9 @@ def forward_factors16(desc: Desc, x, packed, factors16, out_dtype=torch.float32,
 def backward(desc: Desc, dy, x, packed, alpha, beta, A=None, B=None, want_dx=True,
              dx_dtype=torch.float32, dA=None, dB=None, accumulate=False, ws=None, dx=None):
     """Returns (dx, dA, dB).  dy bf16 [T, d_out], x bf16 [T, d_in]."""
+    out = _fast().backward(desc, dy, x, packed, alpha, beta, A, B, want_dx, dx_dtype, dA, dB, accumulate, ws, dx)
+    if out is not None:
+        return out
     T, dev = _need_layer(desc, dy, desc.d_out, packed, alpha, beta, A, B, x_name="dy")
     if A is not None or x is not None:
         _need(x, "x", torch.bfloat16, (T, desc.d_in), device=dev)
@@ -493,6 +546,9 @@ def kept_bytes(desc: Desc, tokens: int) -> int:
 def forward_keep(desc: Desc, x, packed, alpha, beta, A, B, out_dtype=torch.float32, ws=None, y=None,
                  kept=None):
     """forward() that also leaves the pooled activations the backward needs.  Returns (y, kept)."""
+    out = _fast().forward_keep(desc, x, packed, alpha, beta, A, B, out_dtype, ws, y, kept)
+    if out is not None:
+        return out
     T, dev = _need_layer(desc, x, desc.d_in, packed, alpha, beta, A, B)
     if y is None:
         y = torch.empty((T, desc.d_out), dtype=out_dtype, device=dev)
@@ -511,6 +567,9 @@ def forward_keep(desc: Desc, x, packed, alpha, beta, A, B, out_dtype=torch.float
 def backward_kept(desc: Desc, dy, kept, packed, alpha, beta, A, B, want_dx=True,
                   dx_dtype=torch.float32, dA=None, dB=None, accumulate=False, ws=None, dx=None):
     """backward() from what forward_keep() left instead of x.  Returns (dx, dA, dB)."""
+    out = _fast().backward_kept(desc, dy, kept, packed, alpha, beta, A, B, want_dx, dx_dtype, dA, dB, accumulate, ws, dx)
+    if out is not None:
+        return out
     T, dev = _need_layer(desc, dy, desc.d_out, packed, alpha, beta, A, B, x_name="dy")
     _need(kept, "kept", nbytes=kept_bytes(desc, T), device=dev)
     if want_dx and dx is None:
@@ -576,35 +635,20 @@ class AdamW(ctypes.Structure):
                 ("eps", ctypes.c_float), ("weight_decay", ctypes.c_float), ("max_grad_norm", ctypes.c_float)]
 
 
-def _all_like(tensors, first, lists):
-    """True when `tensors` is `lists` times as many contiguous fp32 device tensors as `first`, of its shapes
-    in its order and on the device of its first."""
-    if not first or len(tensors) != lists * len(first):
-        return False
-    if not all(isinstance(t, torch.Tensor) for t in tensors) or not first[0].is_cuda:
-        return False
-    return ({t.dtype for t in tensors} == {torch.float32} and len(set(map(torch.Tensor.get_device, tensors))) == 1
-            and all(map(torch.Tensor.is_contiguous, tensors))
-            and [t.shape for t in tensors] == [t.shape for t in first] * lists)
-
-
 def adamw_step(hp: AdamW, step: int, params, grads, exp_avg, exp_avg_sq, zero_grads=False, grad_norm=None,
                ws=None):
     """One fused AdamW step with a joint gradient-norm clip over lists of fp32 device tensors
     (updated in place).  ``grad_norm``: optional one-element fp32 device tensor for the norm."""
+    if _fast().adamw_step(hp, step, params, grads, exp_avg, exp_avg_sq, zero_grads, grad_norm, ws):
+        return
     n = len(params)
     lists = ((params, "params"), (grads, "grads"), (exp_avg, "exp_avg"), (exp_avg_sq, "exp_avg_sq"))
-    # All tensors at once first: tensor by tensor the checks of a decoder layer's 56 took longer than the
-    # launches they are for (61 us per call against 20 us of kernels; 30 us like this, on tensors seen
-    # before; about 1.3 times as fast on new ones).  Whatever fails is looked at again one by one, for its
-    # message.
     tensors = [t for ts, _ in lists for t in ts]
-    if not (all(len(ts) == n for ts, _ in lists) and _all_like(tensors, params, 4)):
-        for ts, nm in lists:
-            if len(ts) != n:
-                raise ValueError(f"{nm}: {len(ts)} tensors, expected {n}")
-            for t, p0 in zip(ts, params):
-                _need(t, nm, torch.float32, tuple(p0.shape), device=params[0].device)
+    for ts, nm in lists:
+        if len(ts) != n:
+            raise ValueError(f"{nm}: {len(ts)} tensors, expected {n}")
+        for t, p0 in zip(ts, params):
+            _need(t, nm, torch.float32, tuple(p0.shape), device=params[0].device)
     _need(grad_norm, "grad_norm", torch.float32, nbytes=4, optional=True)
     table = array.array("Q", map(torch.Tensor.data_ptr, tensors))  # n addresses of each list
     sizes = array.array("Q", map(torch.Tensor.numel, params))
@@ -674,6 +718,9 @@ def swiglu_backward(dh, gate, up, dgate=None, dup=None):
 
 def swiglu_forward_strided(gu, cols, out=None):
     """Harness glue on gu = [gate | up] ([rows, 2 cols] bf16): h = silu(gate) * up."""
+    h = _fast().swiglu_forward_wide(gu, cols, out)
+    if h is not None:
+        return h
     _need(gu, "gu", torch.bfloat16)
     rows = gu.shape[0]
     _need(gu, "gu", shape=(rows, 2 * cols))
@@ -686,6 +733,9 @@ def swiglu_forward_strided(gu, cols, out=None):
 
 def swiglu_backward_strided(dh, gu, cols, out=None):
     """Harness glue: dgu = [dgate | dup] of h = silu(gate) * up on gu = [gate | up]."""
+    dgu = _fast().swiglu_backward_wide(dh, gu, cols, out)
+    if dgu is not None:
+        return dgu
     _need(gu, "gu", torch.bfloat16)
     rows = gu.shape[0]
     _need(gu, "gu", shape=(rows, 2 * cols))

@@ -8,7 +8,10 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
+
+NATIVE = "_native.so"  # the binding's native form, a Python extension module beside the library
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -92,6 +95,23 @@ def _compile(src: str, extra) -> str:
     return obj
 
 
+def build_native() -> str:
+    """Compile csrc/binding.cpp (host code: CPython and PyTorch headers; no GPU code)."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    out = os.path.join(HERE, NATIVE)
+    tmp = out + ".tmp%d" % os.getpid()
+    subprocess.check_call([
+        os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+        "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(),
+        "-I" + os.path.join(root, "include"), "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
+        "-I/opt/rocm/include", "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "binding.cpp"), "-o", tmp,
+        "-L" + os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+        "-Wl,-rpath," + os.path.join(root, "lib")])
+    os.replace(tmp, out)
+    return out
+
+
 def build(verbose: bool = False, extra_flags=(), variant: str = "") -> str:
     """Build the library.  `variant` names a measurement build (say, with -DQALORA_ABLATE=n in
     `extra_flags`): it goes to libqalora_hip.<variant>.so with objects of its own, so the
@@ -103,12 +123,15 @@ def build(verbose: bool = False, extra_flags=(), variant: str = "") -> str:
     saved, OBJ = OBJ, obj_dir
     try:
         with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+            native = None if variant else ex.submit(build_native)
             objs = list(ex.map(lambda s: _compile(s, list(extra_flags)), SOURCES))
     finally:
         OBJ = saved
     tmp = lib + ".tmp%d" % os.getpid()
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs])
     os.replace(tmp, lib)
+    if native:
+        native.result()
     if verbose:
         print("built", lib)
     return lib
