@@ -33,13 +33,18 @@
 // remainder step (Markstein's theorem: with the correctly rounded reciprocal and a quotient
 // within one unit in the last place the result is the correctly rounded quotient, while nothing
 // under- or overflows).  The code needs the quotient (w - beta) / alpha only up to rounding to an
-// integer: a product with the rounded reciprocal is within two units in the last place, and
+// integer: a product with a reciprocal within one unit in the last place is within three units, and
 // decides the same integer unless it lies next to a tie.  Sixteen rows in which some operand
 // leaves the range where this holds, or some quotient comes near a tie, are done again with
 // real divisions.
-// 4096 x 4096 INT4 g = 32: 10130 us with 16 columns x 64 row lanes, a barrier per row and two LDS
-// operands per multiply-add; 920 us like this (walker alone about 400, the matrix work of three
-// SIMDs 650 at its full rate).
+// The walker is the longer part up to about 2048 rows and stays issue bound there: about 170 cycles per row, 500 to
+// 1900 per sixteen rows for the matrix work behind them.  Its panel's triangle of U lies in LDS (loads of U by the
+// walker itself took 860 cycles per sixteen rows), a new group's min-max crosses lanes in registers and its division
+// by the number of levels needs no division (1160 cycles per group before, 300 now): 42 -> 34 thousand cycles per panel.
+// INT4 g = 32, us: 4096 x 4096 10130 with 16 columns x 64 row lanes, a barrier per row and two LDS operands per
+// multiply-add; 920 with a walker and updaters, 860 with the walker of today; 2048 x 4096 397 -> 340; 1024 x 4096
+// 182 -> 149; 512 x 2048 91 -> 76.  (Updaters that work ahead on later panels while the walker is the longer part:
+// 940 and 3 % off the smaller ones; their panels' way to memory and back costs what the even load saves.)
 #include <type_traits>
 
 #include "common.hpp"
@@ -95,6 +100,16 @@ __device__ __forceinline__ f32x4 load4(__amdgpu_buffer_rsrc_t r, uint32_t voff, 
 // LDS-only barrier: does not wait for the global loads that are in flight.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// f over the four rows of sixteen lanes, in every lane (two exchanges in registers)
+template <typename F>
+__device__ __forceinline__ float over_rows(float v, F&& f) {
+  const uint32_t w = __float_as_uint(v);
+  const auto h = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+  const uint32_t m = __float_as_uint(f(__uint_as_float(h[0]), __uint_as_float(h[1])));
+  const auto g = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+  return f(__uint_as_float(g[0]), __uint_as_float(g[1]));
+}
+
 // |v| in [2^-60, 2^60]
 __device__ __forceinline__ bool in_safe_range(float v) { return fabsf(v) >= 0x1p-60f && fabsf(v) <= 0x1p60f; }
 }  // namespace
@@ -104,7 +119,8 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
   __shared__ f32x4 tile[kTiles * 64];  // the panel to be walked, as matrix accumulator fragments
   __shared__ f32x4 errs[kTiles * 64];  // the walked panel's errors, as matrix operand fragments
   __shared__ float tr[kCols * kTrLd];  // the walker's sixteen rows, column by column
-  __shared__ float diag[16 * 16];      // their block of U
+  // U of the walked panel: 16 x 16 blocks (s, t >= s), and room for a row of seven read past the last one
+  __shared__ __align__(16) float up[(kTiles * (kTiles + 1) / 2 + kTiles - 1) * 256];
   __shared__ f32x2 rcp[kBlock];        // 1 / U[i,i] of the panel's rows: rounded, and what is left of it
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -256,18 +272,33 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
   }
 
   // ---- the walker ---------------------------------------------------------------------------
+  // The panel's triangle of U goes straight to LDS (a 16 x 16 block per load, 16 bytes a lane) while the updating
+  // wavefronts bring the panel itself into place: walking it needs no other memory.  Rows and columns outside the
+  // matrix read zero.
+  constexpr auto block_of = [](int s, int t) { return (s * (2 * kTiles + 1 - s) / 2 + t - s) * 256; };
+  auto fetch_u = [&](int pn) {
+    const int rows = comp_block_rows(d_in, pn), c0 = pn * kBlock + 4 * (lane & 3);
+    const __amdgpu_buffer_rsrc_t r = rsrc(U + (size_t)pn * kBlock * d_in, (size_t)rows * row_b);
+#pragma unroll
+    for (int s = 0; s < kTiles; ++s) {
+      const uint32_t row = comp_walk_row(row_b, rows, s, lane >> 4) + (uint32_t)((lane >> 2) & 3) * row_b + 4u * (uint32_t)c0;
+#pragma unroll
+      for (int t = s; t < kTiles; ++t)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(up + block_of(s, t)), 16,
+                                                 (int)(c0 + 16 * t < d_in ? row + 64u * (uint32_t)t : kOob), 0, 0, 0);
+    }
+  };
+  fetch_u(0);
   lds_barrier();  // the first panel is in place
   float a = 1.0f, b = 0.0f, ya = 1.0f;  // walker: the column's current group: alpha, beta, 1 / alpha
   for (int pn = 0; pn < panels; ++pn) {
     const int i1 = pn * kBlock;
-    // U's rows of the panel; columns outside the matrix are pointed past the buffer
-    const int rows = comp_block_rows(d_in, pn);
-    const __amdgpu_buffer_rsrc_t rs_u = rsrc(U + (size_t)i1 * d_in, (size_t)rows * row_b);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // its triangle of U too
     bool odd = false;  // a diagonal element outside the reciprocal's range
 #pragma unroll
     for (int h = 0; h < kBlock / 64; ++h) {
-      const int i = 64 * h + lane;
-      const float d = i1 + i < d_in ? load1(rs_u, (uint32_t)i * row_b + 4u * (uint32_t)(i1 + i), 0) : 1.0f;
+      const int i = 64 * h + lane, s = i >> 4;
+      const float d = i1 + i < d_in ? up[s * (2 * kTiles + 1 - s) / 2 * 256 + (i & 15) * 17] : 1.0f;
       const float y = __fdiv_rn(1.0f, d);
       rcp[i] = f32x2{y, __fmul_rn(__fmaf_rn(-d, y, 1.0f), y)};
       odd |= !(d >= 0x1p-40f && d <= 0x1p40f);
@@ -276,29 +307,19 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
     f32x4 pt[kTiles];  // pt[t]: tile s + t of the panel, rotating with the sub-block s
 #pragma unroll
     for (int t = 0; t < kTiles; ++t) pt[t] = tile[t * 64 + lane];
-    // U of a sub-block's own rows and columns: row lane / 4, four columns
-    auto load_diag = [&](int s) {
-      const int i0 = i1 + 16 * s, c = i0 + 4 * (lane & 3);  // d_in is a multiple of 8: all four or none
-      const bool ok = c < d_in && i0 + (lane >> 2) < d_in;
-      return load4(rs_u, ok ? (uint32_t)(lane >> 2) * row_b + 4u * (uint32_t)c : kOob, comp_walk_row(row_b, rows, s, 0));
-    };
-    f32x4 dg = load_diag(0);
     uint32_t hiword = 0;  // 3 bits: the high-bit word, two sub-blocks per word
     for (int s = 0; s < kTiles; ++s) {
       const int row0 = i1 + 16 * s;
       if (row0 >= d_in) break;
       *reinterpret_cast<f32x4*>(tr + n * kTrLd + 4 * kb) = pt[0];
-      *reinterpret_cast<f32x4*>(diag + 4 * lane) = dg;
-      if (s + 1 < kTiles) dg = load_diag(s + 1);
-      // U of this sub-block's rows against the panel's later tiles: requested now, used after the walk
+      const float* us = up + block_of(s, s);
+      // U of this sub-block's rows against the panel's later tiles: requested now, used after the walk (tiles past
+      // the panel: other blocks' numbers, unused)
       float au[kTiles - 1][4];
 #pragma unroll
-      for (int t = 1; t < kTiles; ++t) {
-        const int c = row0 + 16 * t + n;
-        const uint32_t vo = s + t < kTiles && c < d_in ? (uint32_t)kb * row_b + 4u * (uint32_t)c : kOob;
+      for (int t = 1; t < kTiles; ++t)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) au[t - 1][q] = load1(rs_u, vo, comp_walk_row(row_b, rows, s, q));
-      }
+        for (int q = 0; q < 4; ++q) au[t - 1][q] = us[t * 256 + q * 64 + lane];
       __builtin_amdgcn_sched_barrier(0);
       asm volatile("" ::: "memory");  // one wavefront: its LDS accesses complete in order
 
@@ -323,19 +344,20 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
         uint32_t tmin = 0xffffffffu;
         float tmax = 0.0f, dmax = 0.0f;
         const float levels = (float)((1 << NBITS) - 1);
-        f32x4 ur[2][4];  // the row's piece of U and the next row's, requested one row ahead
-        f32x2 ry[2];
+        f32x4 ur[3][4];  // the row's piece of U and the next two's, requested two rows ahead
+        f32x2 ry[3];
         auto fetch_row = [&](auto i_c) {
           constexpr int i = decltype(i_c)::value;
           static_for<i / 4, 4>([&](auto q) {
-            ur[i & 1][decltype(q)::value] = *reinterpret_cast<const f32x4*>(diag + 16 * i + 4 * decltype(q)::value);
+            ur[i % 3][decltype(q)::value] = *reinterpret_cast<const f32x4*>(us + 16 * i + 4 * decltype(q)::value);
           });
-          ry[i & 1] = rcp[16 * s + i];
+          ry[i % 3] = rcp[16 * s + i];
         };
         fetch_row(std::integral_constant<int, 0>{});
+        fetch_row(std::integral_constant<int, 1>{});
         static_for<0, 16>([&](auto i_c) {
           constexpr int i = decltype(i_c)::value;
-          if constexpr (i + 1 < 16) fetch_row(std::integral_constant<int, i + 1>{});
+          if constexpr (i + 2 < 16) fetch_row(std::integral_constant<int, i + 2>{});
           __builtin_amdgcn_sched_barrier(0);
           if constexpr (i == 0 || i == 8) {
             if ((row0 + i) % g == 0) {  // a new group: min-max of its rows as they stand (Eq. 1)
@@ -360,8 +382,8 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
                     }
                   }
                 });
-                mn = fminf(mn, __shfl_xor(mn, 16, 64)), mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-                mn = fminf(mn, __shfl_xor(mn, 32, 64)), mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                mn = over_rows(mn, [](float p, float q) { return fminf(p, q); });
+                mx = over_rows(mx, [](float p, float q) { return fmaxf(p, q); });
                 if (w[i] != w[i]) mn = mx = w[i];  // a NaN in the group's first row stays (as above), others are passed over
                 if (__any(mn == 0.0f)) {  // a minimum of zero keeps the sign of the first zero of the group
                   int key = 1 << 20;
@@ -380,10 +402,16 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
                   if (mn == 0.0f) mn = (key & 1) ? -0.0f : 0.0f;
                 }
               }
-              a_s = __fdiv_rn(__fsub_rn(mx, mn), levels);
+              // (one product and one remainder step give the rounded quotient for each of these divisors: checked for
+              // all significands; the reciprocal of alpha is within a unit in the last place)
+              const float range = __fsub_rn(mx, mn);
+              constexpr float kInverse = 1.0f / (float)((1 << NBITS) - 1);
+              const float q0 = __fmul_rn(range, kInverse);
+              a_s = __fmaf_rn(__fmaf_rn(-levels, q0, range), kInverse, q0);
+              if (__any(!in_safe_range(range))) a_s = __fdiv_rn(range, levels);
               if (!(a_s > 0.0f)) a_s = 0x1p-60f;
               b_s = mn;
-              ya_s = __fdiv_rn(1.0f, a_s);
+              ya_s = __builtin_amdgcn_rcpf(a_s);
               bad |= !in_safe_range(a_s);
               if (kb == 0 && col_ok && row0 + i < d_in) {
                 const size_t o = (size_t)((row0 + i) / g) * d_out + j;
@@ -404,10 +432,10 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
             if (rq > levels) rq = levels;
           }
           const float t = __fsub_rn(w[i], __fmaf_rn(a_s, rq, b_s));
-          const float d = ur[i & 1][i / 4][i % 4];
+          const float d = ur[i % 3][i / 4][i % 4];
           if constexpr (FAST) {
-            const float q1 = __fmaf_rn(t, ry[i & 1][0], __fmul_rn(t, ry[i & 1][1]));
-            q = __fmaf_rn(__fmaf_rn(-d, q1, t), ry[i & 1][0], q1);
+            const float q1 = __fmaf_rn(t, ry[i % 3][0], __fmul_rn(t, ry[i % 3][1]));
+            q = __fmaf_rn(__fmaf_rn(-d, q1, t), ry[i % 3][0], q1);
             const uint32_t tb = __float_as_uint(t);
             tmin = min(tmin, ((tb << 1) | (tb >> 31)) - 1u);
             tmax = fmaxf(tmax, fabsf(t));
@@ -417,8 +445,16 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
           eb[i >> 2] = (i & 3) == 0 || kb == (i & 3) ? q : eb[i >> 2];
           static_for<i + 1, 16>([&](auto r_c) {
             constexpr int r = decltype(r_c)::value;
-            w[r] = __fmaf_rn(-ur[i & 1][r / 4][r % 4], q, w[r]);
+            w[r] = __fmaf_rn(-ur[i % 3][r / 4][r % 4], q, w[r]);
           });
+          // (the parts of a fetched row that no update needs stay allocated until here: given to another fetch
+          // sooner, that fetch would first wait for this one's data)
+          static_for<i / 4, 4>([&](auto q_c) {
+            const f32x4 part = ur[i % 3][decltype(q_c)::value];
+            asm volatile("" ::"v"(part));
+          });
+          const f32x2 inverse = ry[i % 3];
+          asm volatile("" ::"v"(inverse));
           const uint32_t c = (uint32_t)(int)rq;
           if constexpr (NBITS == 4) {
             constexpr int ps = 4 * ((i & 7) >> 1) + 16 * (i & 1);
@@ -429,7 +465,7 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
             if constexpr (NBITS == 3) hi_s |= (c >> 2) << ((i >> 1) + 16 * (i & 1) + 8 * (s & 1));
           }
         });
-        // (2^-60 has the bits 67 << 23; a quotient of up to 31 carries an error below 2^-18, larger
+        // (2^-60 has the bits 67 << 23; a quotient of up to 31 carries an error below 2^-17, larger
         // ones are clamped whichever way they round)
         return bad || tmin < (67u << 24) - 1u || !(tmax <= 0x1p60f) || !(dmax < 0.5f - 0x1p-16f);
       };
@@ -450,13 +486,16 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
       if (s & 1) hiword = 0;
       // ... onto the panel's later tiles, exactly as many as there are (the switch keeps the
       // chains of different tiles interleaved without computing absent ones)
+      f32x4 ne;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) ne[q] = -eb[q];
       auto behind = [&](auto nt_c) {
         constexpr int NT = decltype(nt_c)::value;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
           for (int t = 1; t <= NT; ++t)
-            pt[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(-au[t - 1][q], eb[q], pt[t], 0, 0, 0);
+            pt[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(au[t - 1][q], ne[q], pt[t], 0, 0, 0);
       };
       switch (kTiles - 1 - s) {
         case 7: behind(std::integral_constant<int, 7>{}); break;
@@ -473,6 +512,7 @@ __global__ __launch_bounds__(kThreads, 2) void compensate_kernel(const CompArgs 
     }
     // block pn's errors are known: in LDS, and (for this block's later loads) in the error store
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (pn + 1 < panels) fetch_u(pn + 1);
     lds_barrier();  // the next panel is in place
   }
 }
