@@ -83,8 +83,9 @@ struct FrontArgs {
   uint16_t* P_out;      // optional, bf16 [T][2 Lp] (pooled_ld): rows job 1 also pools x
   FrontPart part[MAX_PARTS];
   int n_parts;
-  // rows job 2 (dy): scale + convert only
+  // rows job 2 (dy; or x, where a block takes a row): scale and convert
   const uint16_t* y;
+  int y_pool;           // pool them too
   int Ty, d_y;
   float2* rs_y;
   uint16_t* y16;
@@ -428,6 +429,36 @@ __device__ __forceinline__ void factor_block(const FrontArgs& a, int bid, float*
   }
 }
 
+// Sums over groups of a row held in pieces of eight elements: a group of 8 lpg elements is lpg adjacent lanes of a
+// wavefront (a power of two of them), or is added up element by element.
+__device__ __forceinline__ bool group_in_wave(int lpg) { return lpg > 0 && lpg <= 64 && (lpg & (lpg - 1)) == 0; }
+__device__ __forceinline__ float group_sum(uint4 q, int lpg) {
+  const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+  float sum = 0.0f;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    sum += bf16_bits_to_f32(w[e] & 0xffffu);
+    sum += __uint_as_float(w[e] & 0xffff0000u);
+  }
+  for (int off = 1; off < lpg; off <<= 1) sum += __shfl_xor(sum, off, 64);
+  return sum;
+}
+__device__ __forceinline__ float plain_group_sum(const uint16_t* __restrict__ src, int l, int g) {
+  float sum = 0.0f;
+  for (int q = 0; q < g; ++q) sum += bf16_bits_to_f32(src[l * g + q]);
+  return sum;
+}
+// Pooled activation l of a token's row of Lp, as bf16 hi and lo.
+__device__ __forceinline__ void store_pooled(uint16_t* P, int l, int L, int Lp, const float* P_s) {
+  uint16_t hi = 0, lo = 0;
+  if (l < L) {
+    split_bf16(P_s[l], hi, lo);
+    if ((hi & 0x7f80) == 0x7f80) lo = 0;  // infinite: no remainder
+  }
+  P[l] = hi;
+  P[Lp + l] = lo;
+}
+
 // One wavefront processes one bf16 row: returns the row scale; optionally writes the fp16
 // scaled copy and the group averages (to P_s, LDS, [L]).
 template <int RB>
@@ -436,7 +467,7 @@ __device__ __forceinline__ float2 process_row(const uint16_t* __restrict__ src, 
                                               int lane) {
   const int nch = cols / 8;
   const int lpg = g > 0 ? g / 8 : 0;
-  const bool butterfly = P_s && lpg <= 64 && (lpg & (lpg - 1)) == 0;
+  const bool butterfly = P_s && group_in_wave(lpg);
   const float inv_g = g > 0 ? 1.0f / (float)g : 0.0f;
   uint32_t amax = 0;
   uint4 v[RB];
@@ -452,14 +483,7 @@ __device__ __forceinline__ float2 process_row(const uint16_t* __restrict__ src, 
       amax = max_abs_bits(v[c], amax);
       if (butterfly) {
         const int ch = base + c * 64 + lane;
-        const uint32_t w[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
-        float sum = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          sum += bf16_bits_to_f32(w[e] & 0xffffu);
-          sum += __uint_as_float(w[e] & 0xffff0000u);
-        }
-        for (int off = 1; off < lpg; off <<= 1) sum += __shfl_xor(sum, off, 64);
+        const float sum = group_sum(v[c], lpg);
         if (ch < nch && (lane & (lpg - 1)) == 0) P_s[ch / lpg] = sum * inv_g;
       }
     }
@@ -481,12 +505,7 @@ __device__ __forceinline__ float2 process_row(const uint16_t* __restrict__ src, 
     }
   }
   if (P_s && !butterfly) {  // group sizes the butterfly does not cover: plain loop
-    const int L = cols / g;
-    for (int l = lane; l < L; l += 64) {
-      float sum = 0.0f;
-      for (int q = 0; q < g; ++q) sum += bf16_bits_to_f32(src[l * g + q]);
-      P_s[l] = sum * inv_g;
-    }
+    for (int l = lane; l < cols / g; l += 64) P_s[l] = plain_group_sum(src, l, g) * inv_g;
   }
   return sc;
 }
@@ -496,8 +515,12 @@ __device__ __forceinline__ float2 process_row(const uint16_t* __restrict__ src, 
 // own needs, so long rows are read once at full occupancy.
 template <int RB>
 __device__ __forceinline__ float2 process_row_block(const uint16_t* __restrict__ src, int cols,
-                                                    uint16_t* __restrict__ dst16, uint32_t* wave_amax, int tid) {
+                                                    uint16_t* __restrict__ dst16, uint32_t* wave_amax, float* P_s,
+                                                    int g, int tid) {
   const int nch = cols / 8;
+  const int lpg = g / 8;
+  const bool butterfly = P_s && group_in_wave(lpg);
+  const float inv_g = 1.0f / (float)g;
   uint32_t amax = 0;
   uint4 v[RB];
   for (int base = 0; base < nch; base += 256 * RB) {
@@ -507,8 +530,17 @@ __device__ __forceinline__ float2 process_row_block(const uint16_t* __restrict__
       v[c] = ch < nch ? *reinterpret_cast<const uint4*>(src + 8 * ch) : uint4{0, 0, 0, 0};
     }
 #pragma unroll
-    for (int c = 0; c < RB; ++c) amax = max_abs_bits(v[c], amax);
+    for (int c = 0; c < RB; ++c) {
+      amax = max_abs_bits(v[c], amax);
+      if (butterfly) {
+        const int ch = base + c * 256 + tid;
+        const float sum = group_sum(v[c], lpg);
+        if (ch < nch && (tid & (lpg - 1)) == 0) P_s[ch / lpg] = sum * inv_g;
+      }
+    }
   }
+  if (P_s && !butterfly)
+    for (int l = tid; l < cols / g; l += 256) P_s[l] = plain_group_sum(src, l, g) * inv_g;
   amax = wave_max_u32(amax);
   if ((tid & 63) == 0) wave_amax[tid >> 6] = amax;
   __syncthreads();
@@ -570,23 +602,18 @@ __global__ __launch_bounds__(256) void front_kernel(const FrontArgs a) {
     const int Lp = pooled_ld(L);
     uint16_t* P = a.P_out + (size_t)t * 2 * Lp;
     asm volatile("" ::: "memory");  // the row's own wavefront wrote P_s: its LDS accesses complete in order
-    for (int l = lane; l < Lp; l += 64) {
-      uint16_t hi = 0, lo = 0;
-      if (l < L) {
-        split_bf16(P_s[l], hi, lo);
-        if ((hi & 0x7f80) == 0x7f80) lo = 0;  // infinite: no remainder
-      }
-      P[l] = hi;
-      P[Lp + l] = lo;
-    }
+    for (int l = lane; l < Lp; l += 64) store_pooled(P, l, L, Lp, P_s);
     return;
   }
   bid -= a.nb_rows1;
   // ---- rows job 2: dy -> scale + fp16 copy ------------------------------------------------
   if constexpr (Y_WIDE) {
+    const int L = a.y_pool ? a.d_y / a.g : 0, Lp = pooled_ld(L);
+    float* P_s = a.y_pool ? P_all + 4 : nullptr;
     const float2 sc = process_row_block<RB>(a.y + (size_t)bid * a.d_y, a.d_y, a.y16 + (size_t)bid * a.d_y,
-                                            reinterpret_cast<uint32_t*>(P_all), tid);
+                                            reinterpret_cast<uint32_t*>(P_all), P_s, a.g, tid);
     if (tid == 0) a.rs_y[bid] = sc;
+    for (int l = tid; l < Lp; l += 256) store_pooled(a.P_out + (size_t)bid * 2 * Lp, l, L, Lp, P_s);
     return;
   }
   const int t = bid * ROWS_PER_BLOCK + wave;
@@ -660,12 +687,21 @@ static hipError_t launch_front_as(const FrontArgs& a, int nblocks, size_t smem, 
 static hipError_t launch_front_wide(const FrontArgs& a, int rb, int nblocks, size_t smem, hipStream_t st);
 
 static hipError_t launch_front(FrontArgs a, hipStream_t st) {
-  if (a.x && !a.P_out && !a.y && a.T <= kWideRows && a.d_in % 8 == 0 &&
-      a.d_in <= 256 * 8 * WIDE_BATCH) {
-    // few rows: a block per row; the factor job (if any) follows as a launch of its own
-    front_wide_kernel<<<a.T, 256, 0, st>>>(a.x, a.d_in, a.rs_x, a.x16);
-    if (hipError_t e = hipGetLastError(); e != hipSuccess || !a.f_alpha) return e;
+  bool y_wide = false;
+  const bool pooled_short = a.P_out && a.T > 128 && a.d_in <= 512 * ROW_BATCH;
+  if (a.x && !a.y && a.T <= kWideRows && a.d_in % 8 == 0 && a.d_in <= 256 * 8 * WIDE_BATCH && !pooled_short) {
+    if (!a.f_alpha && !a.P_out) {  // few rows and nothing else
+      front_wide_kernel<<<a.T, 256, 0, st>>>(a.x, a.d_in, a.rs_x, a.x16);
+      return hipGetLastError();
+    }
+    // few rows beside the factor job: a block each, in one launch with it (dense forward of 300 tokens, 4096 x 4096:
+    // 38.4 us with a launch of their own, 35.5 so; 128 of 1024 x 22016 27.0 / 24.1).  With pooling where a wavefront
+    // would take two sweeps or is nearly alone (forward and backward of 100 tokens, 13824 x 5120: 152 us by
+    // wavefronts, 145 so; 20 of 4096 x 11008 82 / 80; 1000 of 1024 x 8192 100 / 102).
+    a.y = a.x; a.Ty = a.T; a.d_y = a.d_in; a.rs_y = a.rs_x; a.y16 = a.x16;
+    a.y_pool = a.P_out != nullptr;
     a.x = nullptr;
+    y_wide = true;
   }
   int max_rank = 0;
   for (int p = 0; p < a.n_parts; ++p) max_rank = a.part[p].rank > max_rank ? a.part[p].rank : max_rank;
@@ -675,10 +711,10 @@ static hipError_t launch_front(FrontArgs a, hipStream_t st) {
   // per lane, before).  Rows beyond 32768 elements take two sweeps either way, and many of them are better
   // off by wavefronts (forward and backward, 512 x 33000: 1531 tokens 360 us against 373, 512 tokens 188
   // against 180).
-  const bool y_wide = a.y && a.d_y > 512 * ROW_BATCH && (a.d_y <= 2048 * 16 || a.Ty <= 512);
+  y_wide = y_wide || (a.y && a.d_y > 512 * ROW_BATCH && (a.d_y <= 2048 * 16 || a.Ty <= 512));
   a.nb_rows2 = a.y ? (y_wide ? a.Ty : ceil_div(a.Ty, ROWS_PER_BLOCK)) : 0;
   size_t smem = a.x && a.P_out ? (size_t)ROWS_PER_BLOCK * (a.d_in / a.g) * sizeof(float) : 0;
-  if (y_wide && smem < 4 * sizeof(uint32_t)) smem = 4 * sizeof(uint32_t);
+  if (y_wide) smem = std::max(smem, (4 + (a.y_pool ? (size_t)a.d_y / a.g : 0)) * sizeof(float));
   a.nb_fac = 0;
   if (a.f_alpha) {
     a.f_cols = factor_cols(a.f_L);

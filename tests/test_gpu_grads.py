@@ -27,6 +27,8 @@ TOL_GRAD = 1.2e-4
     (1000, 96, 8200, 3, 32, 64),    # three groups; more tiles than a run's
     (130, 1024, 8256, 4, 8, 8),     # 258 blocks: two launches at few tokens
     (4096, 256, 136, 4, 128, 64),   # two groups, two tiles of columns, 64 steps
+    (5, 4800, 64, 4, 40, 8),        # rows pooled by a block each in the forward, groups beside powers of two
+    (200, 4128, 64, 4, 32, 8),      # ... and beyond a wavefront's registers; 129 groups
 ])
 def test_gradients(gpu_api, tokens, d_in, d_out, bits, group, rank):
     cfg = synth.LayerConfig("grads", tokens, d_in, d_out, bits, group, rank, 0.5, seed=91)
