@@ -7,7 +7,7 @@
 
 namespace qalora {
 
-// v[q] = src[q][0] + src[q][stride] + ... over n copies; the loads of up to B copies are in flight together
+// v[q] = src[q][0] + src[q][stride] + ... over n copies; the loads of up to B (4 to 8) copies are in flight together
 template <int B, int Q>
 __device__ __forceinline__ void sum_slices(const f32x4* const (&src)[Q], size_t stride, int n, f32x4 (&v)[Q]) {
 #pragma unroll
@@ -25,13 +25,19 @@ __device__ __forceinline__ void sum_slices(const f32x4* const (&src)[Q], size_t 
       for (int q = 0; q < Q; ++q) v[q] += ld[z][q];
   };
   int z = 1;
-  if constexpr (B >= 8)
-    for (; z + 8 <= n; z += 8) add(std::integral_constant<int, 8>{}, z);
-  for (; z + 4 <= n; z += 4) add(std::integral_constant<int, 4>{}, z);
-  if (z + 2 <= n) add(std::integral_constant<int, 2>{}, z), z += 2;
-  if (z < n) add(std::integral_constant<int, 1>{}, z);
+  for (; z + B <= n; z += B) add(std::integral_constant<int, B>{}, z);
+  switch (n - z) {  // fewer than B: in flight together as well
+    case 7: if constexpr (B > 7) add(std::integral_constant<int, 7>{}, z); break;
+    case 6: if constexpr (B > 6) add(std::integral_constant<int, 6>{}, z); break;
+    case 5: if constexpr (B > 5) add(std::integral_constant<int, 5>{}, z); break;
+    case 4: if constexpr (B > 4) add(std::integral_constant<int, 4>{}, z); break;
+    case 3: add(std::integral_constant<int, 3>{}, z); break;
+    case 2: add(std::integral_constant<int, 2>{}, z); break;
+    case 1: add(std::integral_constant<int, 1>{}, z); break;
+    default: break;
+  }
 }
-template <int B = 4>
+template <int B = 8>
 __device__ __forceinline__ f32x4 sum_slices(const f32x4* src, size_t stride, int n) {
   const f32x4* s[1] = {src};
   f32x4 v[1];
