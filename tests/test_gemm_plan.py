@@ -18,7 +18,7 @@ SHAPES = [
     (4, 64, 256, 512, 264, (64, 1), (64, 1)),
     (3, 32, 300, 768, 520, (64, 4), (64, 3)),        # slices of three steps
     (2, 32, 130, 320, 2048, (64, 1), (64, 8)),
-    (4, 32, 520, 2048, 2048, (64, 3), (64, 3)),      # two blocks per unit, eight rows in the last tile; uneven slices
+    (4, 32, 520, 2048, 2048, (64, 3), (64, 3)),      # two blocks per unit, eight rows in the last tile; uneven slices, added one by one
     (2, 64, 129, 4096, 1024, (64, 8), (64, 4)),      # one token in the last of three tiles
     (4, 32, 24, 1024, 64, (64, 4), (64, 1)),         # one K step
     (4, 40, 200, 640, 768, (64, 1), (64, 4)),        # group that no step is made of: general addressing
