@@ -456,7 +456,7 @@ def probe_report(torch, api):
 def two_stream_backward(torch, api, synth):
     """Can the adapter-gradient kernels hide under the dx contraction?  The backward of the c2
     layer as two calls -- dx only (adapter-free: front pass and contraction) and gradients only
-    (front pass, dU product, gradient kernels, reduction) -- one after the other on one stream,
+    (front pass, gradient kernels) -- one after the other on one stream,
     and at the same time on two streams of equal priority."""
     cfg = synth.CONFIGS["c2"]
     L = Layer(api, torch, cfg, torch.bfloat16)
