@@ -143,12 +143,13 @@ struct Call {
 
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
-// Runs the C call without the interpreter lock; false: a Python exception is set.
-template <typename F>
-bool run(const char* name, F&& f) {
+// Runs the C call without the interpreter lock; false: a Python exception is set.  Its arguments are evaluated by
+// the caller, under the lock: reading a tensor's address can allocate (a lazily cloned one is copied then) and throw.
+template <typename... P, typename... A>
+bool run(const char* name, int (*f)(P...), A... args) {
   int rc;
   Py_BEGIN_ALLOW_THREADS
-  rc = f();
+  rc = f(args...);
   Py_END_ALLOW_THREADS
   if (rc == QALORA_OK) return true;
   PyObject* r = PyObject_CallFunction(raise_status, "is", rc, name);
@@ -208,10 +209,8 @@ FASTCALL(quantize, 2)
   const at::Tensor packed = at::empty({(int64_t)lib.qalora_packed_bytes(&c.desc)}, opts.dtype(at::kByte));
   const at::Tensor alpha = at::empty({c.L, c.desc.d_out}, opts.dtype(at::kFloat)), beta = at::empty_like(alpha);
   void* st = stream();
-  if (!run("qalora_quantize", [&] {
-        return lib.qalora_quantize(&c.desc, f32(W->data_ptr()), packed.data_ptr(), f32(alpha.data_ptr()), f32(beta.data_ptr()),
-                                   nullptr, 0, st);
-      }))
+  if (!run("qalora_quantize", lib.qalora_quantize, &c.desc, f32(W->data_ptr()), packed.data_ptr(), f32(alpha.data_ptr()),
+           f32(beta.data_ptr()), nullptr, 0, st))
     return nullptr;
   return tuple({wrap(packed), wrap(alpha), wrap(beta)});
 FASTCALL_END
@@ -229,10 +228,8 @@ FASTCALL(forward, 10)
   const at::Tensor ws = c.scratch(a[8], a[8] == Py_None ? lib.qalora_workspace_bytes(&c.desc, (int)c.T, QALORA_OP_FORWARD) : 0);
   PLAIN(c);
   void* st = stream();
-  if (!run("qalora_forward", [&] {
-        return lib.qalora_forward(&c.desc, (int)c.T, x, w.packed, f32(w.alpha), f32(w.beta), f32(w.A), f32(w.B), y.data_ptr(),
-                                  code, ws.data_ptr(), ws.nbytes(), st);
-      }))
+  if (!run("qalora_forward", lib.qalora_forward, &c.desc, (int)c.T, x, w.packed, f32(w.alpha), f32(w.beta), f32(w.A),
+           f32(w.B), y.data_ptr(), code, ws.data_ptr(), ws.nbytes(), st))
     return nullptr;
   return given_or(a[9], y);
 FASTCALL_END
@@ -254,10 +251,8 @@ FASTCALL(forward_keep, 11)
   c.need(c.ok && (size_t)kept.nbytes() >= keep);
   PLAIN(c);
   void* st = stream();
-  if (!run("qalora_forward_keep", [&] {
-        return lib.qalora_forward_keep(&c.desc, (int)c.T, x, w.packed, f32(w.alpha), f32(w.beta), f32(w.A), f32(w.B),
-                                       y.data_ptr(), code, kept.data_ptr(), ws.data_ptr(), ws.nbytes(), st);
-      }))
+  if (!run("qalora_forward_keep", lib.qalora_forward_keep, &c.desc, (int)c.T, x, w.packed, f32(w.alpha), f32(w.beta),
+           f32(w.A), f32(w.B), y.data_ptr(), code, kept.data_ptr(), ws.data_ptr(), ws.nbytes(), st))
     return nullptr;
   return tuple({given_or(a[9], y), given_or(a[10], kept)});
 FASTCALL_END
@@ -286,14 +281,10 @@ PyObject* backward_of(Call& c, void* dy, void* x, void* kept, const Weights& w, 
   float* gB = dB.defined() ? f32(dB.data_ptr()) : nullptr;
   void* st = stream();
   const bool done =
-      kept ? run("qalora_backward_kept", [&] {
-        return lib.qalora_backward_kept(&c.desc, (int)c.T, dy, kept, w.packed, f32(w.alpha), f32(w.beta), f32(w.A), f32(w.B),
-                                        pdx_data, code, gA, gB, acc, ws.data_ptr(), ws.nbytes(), st);
-      })
-           : run("qalora_backward", [&] {
-        return lib.qalora_backward(&c.desc, (int)c.T, dy, x, w.packed, f32(w.alpha), f32(w.beta), f32(w.A), f32(w.B), pdx_data,
-                                   code, gA, gB, acc, ws.data_ptr(), ws.nbytes(), st);
-      });
+      kept ? run("qalora_backward_kept", lib.qalora_backward_kept, &c.desc, (int)c.T, dy, kept, w.packed, f32(w.alpha),
+                 f32(w.beta), f32(w.A), f32(w.B), pdx_data, code, gA, gB, acc, ws.data_ptr(), ws.nbytes(), st)
+           : run("qalora_backward", lib.qalora_backward, &c.desc, (int)c.T, dy, x, w.packed, f32(w.alpha), f32(w.beta),
+                 f32(w.A), f32(w.B), pdx_data, code, gA, gB, acc, ws.data_ptr(), ws.nbytes(), st);
   if (!done) return nullptr;
   return tuple({dx.defined() ? given_or(pdx, dx) : Py_NewRef(Py_None), dA.defined() ? given_or(pdA, dA) : Py_NewRef(Py_None),
                 dB.defined() ? given_or(pdB, dB) : Py_NewRef(Py_None)});
@@ -342,10 +333,8 @@ FASTCALL(forward_deployed, 7)
   const at::Tensor ws = c.scratch(a[5], a[5] == Py_None ? lib.qalora_workspace_bytes(&c.desc, (int)c.T, QALORA_OP_FORWARD) : 0);
   PLAIN(c);
   void* st = stream();
-  if (!run("qalora_forward_deployed", [&] {
-        return lib.qalora_forward_deployed(&c.desc, (int)c.T, x, packed, deployed, y.data_ptr(), code, ws.data_ptr(), ws.nbytes(),
-                                           st);
-      }))
+  if (!run("qalora_forward_deployed", lib.qalora_forward_deployed, &c.desc, (int)c.T, x, packed, deployed, y.data_ptr(),
+           code, ws.data_ptr(), ws.nbytes(), st))
     return nullptr;
   return given_or(a[6], y);
 FASTCALL_END
@@ -365,9 +354,8 @@ FASTCALL(forward_factors16, 7)
       c.scratch(a[5], a[5] == Py_None ? lib.qalora_workspace_bytes(&c.desc, (int)c.T, QALORA_OP_FORWARD_FACTORS16) : 0);
   PLAIN(c);
   void* st = stream();
-  if (!run("qalora_forward_factors16", [&] {
-        return lib.qalora_forward_factors16(&c.desc, (int)c.T, x, packed, fac, y.data_ptr(), code, ws.data_ptr(), ws.nbytes(), st);
-      }))
+  if (!run("qalora_forward_factors16", lib.qalora_forward_factors16, &c.desc, (int)c.T, x, packed, fac, y.data_ptr(), code,
+           ws.data_ptr(), ws.nbytes(), st))
     return nullptr;
   return given_or(a[6], y);
 FASTCALL_END
@@ -451,10 +439,8 @@ FASTCALL(forward_shared, 11)
       a[8], a[8] == Py_None ? lib.qalora_shared_workspace_bytes(&c.desc, (int)c.T, QALORA_OP_FORWARD, p.n, p.p) : 0);
   PLAIN(c);
   void* st = stream();
-  if (!run("qalora_forward_shared", [&] {
-        return lib.qalora_forward_shared(&c.desc, (int)c.T, x, w.packed, f32(w.alpha), f32(w.beta), p.n, p.p, y.data_ptr(), code,
-                                         keep ? kept.data_ptr() : nullptr, ws.data_ptr(), ws.nbytes(), st);
-      }))
+  if (!run("qalora_forward_shared", lib.qalora_forward_shared, &c.desc, (int)c.T, x, w.packed, f32(w.alpha), f32(w.beta),
+           p.n, p.p, y.data_ptr(), code, keep ? kept.data_ptr() : nullptr, ws.data_ptr(), ws.nbytes(), st))
     return nullptr;
   if (!keep) return given_or(a[9], y);
   return tuple({given_or(a[9], y), given_or(a[10], kept)});
@@ -482,10 +468,8 @@ FASTCALL(backward_shared, 14)
   PLAIN(c);
   void* pdx = dx.defined() ? dx.data_ptr() : nullptr;
   void* st = stream();
-  if (!run("qalora_backward_shared", [&] {
-        return lib.qalora_backward_shared(&c.desc, (int)c.T, dy, x, kept, w.packed, f32(w.alpha), f32(w.beta), p.n, p.p, pdx, code,
-                                          acc, ws.data_ptr(), ws.nbytes(), st);
-      }))
+  if (!run("qalora_backward_shared", lib.qalora_backward_shared, &c.desc, (int)c.T, dy, x, kept, w.packed, f32(w.alpha),
+           f32(w.beta), p.n, p.p, pdx, code, acc, ws.data_ptr(), ws.nbytes(), st))
     return nullptr;
   return tuple({dx.defined() ? given_or(a[13], dx) : Py_NewRef(Py_None), Py_NewRef(a[10])});
 FASTCALL_END
@@ -513,9 +497,8 @@ FASTCALL(swiglu_forward_wide, 3)
     out = THPVariable_Unpack(a[2]);
   }
   void* st = stream();
-  if (!run("qalora_swiglu_forward_wide", [&] {
-        return lib.qalora_swiglu_forward_wide(gu->data_ptr(), out.data_ptr(), (size_t)rows, (size_t)cols, st);
-      }))
+  if (!run("qalora_swiglu_forward_wide", lib.qalora_swiglu_forward_wide, gu->data_ptr(), out.data_ptr(), (size_t)rows,
+           (size_t)cols, st))
     return nullptr;
   return given_or(a[2], out);
 FASTCALL_END
@@ -545,9 +528,8 @@ FASTCALL(swiglu_backward_wide, 4)
     out = THPVariable_Unpack(a[3]);
   }
   void* st = stream();
-  if (!run("qalora_swiglu_backward_wide", [&] {
-        return lib.qalora_swiglu_backward_wide(dh, gu->data_ptr(), out.data_ptr(), (size_t)rows, (size_t)cols, st);
-      }))
+  if (!run("qalora_swiglu_backward_wide", lib.qalora_swiglu_backward_wide, dh, gu->data_ptr(), out.data_ptr(), (size_t)rows,
+           (size_t)cols, st))
     return nullptr;
   return given_or(a[3], out);
 FASTCALL_END
@@ -592,10 +574,8 @@ FASTCALL(adamw_step, 9)
   // (api.py passes the number of elements of ws for its size in bytes)
   PLAIN(c);
   void* st = stream();
-  if (!run("qalora_adamw_step", [&] {
-        return lib.qalora_adamw_step(&hp, (int)step, (int)count, ptr[0], ptr[1], ptr[2], ptr[3], numel, zero, norm, ws->data_ptr(),
-                                     (size_t)ws->numel(), st);
-      }))
+  if (!run("qalora_adamw_step", lib.qalora_adamw_step, &hp, (int)step, (int)count, ptr[0], ptr[1], ptr[2], ptr[3], numel,
+           zero, norm, ws->data_ptr(), (size_t)ws->numel(), st))
     return nullptr;
   Py_RETURN_TRUE;
 FASTCALL_END

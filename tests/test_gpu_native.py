@@ -121,3 +121,20 @@ def test_adamw(gpu_api, monkeypatch):
     norm_b = torch.zeros(1, device="cuda")
     gpu_api.adamw_step(hp, 3, *b, zero_grads=True, grad_norm=norm_b, ws=ws)
     assert torch.equal(norm, norm_b) and all(torch.equal(s, t) for p, q in zip(a, b) for s, t in zip(p, q))
+
+
+def test_an_operand_that_cannot_be_read_raises(gpu_api):
+    # a lazily cloned tensor is copied when its address is taken: where there is no memory for the copy the call
+    # raises, and the interpreter goes on
+    W = torch.randn(4096, 8192, device="cuda")
+    d = gpu_api.make_desc(4096, 8192, 4, 32)
+    lazy = torch._lazy_clone(W)
+    torch.cuda.empty_cache()
+    room = torch.cuda.memory_reserved() + W.nbytes * 3 // 4   # the outputs take three eighths of W
+    torch.cuda.set_per_process_memory_fraction(room / torch.cuda.get_device_properties(0).total_memory)
+    try:
+        with pytest.raises(torch.OutOfMemoryError):
+            gpu_api._native.quantize(d, lazy)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert all(torch.equal(a, b) for a, b in zip(gpu_api.quantize(d, lazy), gpu_api.quantize(d, W)))
