@@ -39,9 +39,11 @@ struct Library {
 PyObject* raise_status = nullptr;  // api.py: (status, entry point) -> raises
 bool bound = false;
 
-// The operands of one call.  `ok` falls once anything is not plainly right.
+// The operands of one call, held until it returns (a list they came in can change while the interpreter lock is
+// released).  `ok` falls once anything is not plainly right.
 struct Call {
   bool ok = true;
+  std::vector<at::Tensor> held;
   qalora_desc desc{};
   c10::Device dev{c10::DeviceType::CPU};
   int64_t T = 0, L = 0;
@@ -64,6 +66,7 @@ struct Call {
     }
     if (first) dev = t.device();
     need(t.device() == dev);
+    if (ok) held.push_back(t);
     return ok ? &t : nullptr;
   }
   void* matrix(PyObject* o, at::ScalarType dtype, int64_t rows, int64_t cols) {

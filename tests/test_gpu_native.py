@@ -138,3 +138,21 @@ def test_an_operand_that_cannot_be_read_raises(gpu_api):
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert all(torch.equal(a, b) for a, b in zip(gpu_api.quantize(d, lazy), gpu_api.quantize(d, W)))
+
+
+def test_operands_live_through_the_call(gpu_api):
+    # a list changed while the call is under way: its tensors' memory is not another's before the launch
+    make = lambda v: [torch.full((4096,), v, device="cuda")]  # noqa: E731
+    p, g, m, v = make(1.0), make(1.0), make(0.0), make(0.0)
+    hp = gpu_api.AdamW(lr=1e-2, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.0, max_grad_norm=0.0)
+    ws, later = torch.empty(4096, dtype=torch.uint8, device="cuda"), []
+
+    class Flag:
+        def __bool__(self):
+            for ts in (p, g, m, v):
+                ts.clear()
+            later.extend(torch.zeros(4096, device="cuda") for _ in range(4))
+            return True
+
+    assert gpu_api._native.adamw_step(hp, 1, p, g, m, v, Flag(), None, ws) is True
+    assert len(later) == 4 and all(t.count_nonzero() == 0 for t in later)
