@@ -141,7 +141,8 @@ def _bind_native(lib):
     if not os.path.exists(path):
         raise RuntimeError(f"{path} not found: build it first (python -m paper_2309_14717_amd.build)")
     from . import _native as native
-    native.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_ENTRIES}, _check)
+    native.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_ENTRIES}, _check,
+                Desc, AdamW)
     _native = native
 
 

@@ -19,6 +19,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "../../include/qalora.h"
@@ -37,6 +38,7 @@ struct Library {
   QALORA_ENTRIES(QALORA_MEMBER)
 } lib;
 PyObject* raise_status = nullptr;  // api.py: (status, entry point) -> raises
+PyObject *desc_type = nullptr, *adamw_type = nullptr;  // api.py's mirrors of qalora_desc and qalora_adamw
 bool bound = false;
 
 // The operands of one call, held until it returns (a list they came in can change while the interpreter lock is
@@ -89,9 +91,9 @@ struct Call {
     return t->data_ptr();
   }
   template <typename S>
-  void read_struct(PyObject* o, S& out) {  // a ctypes mirror
+  void read_struct(PyObject* o, PyObject* type, S& out) {  // a ctypes mirror
     Py_buffer b;
-    if (!ok || PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) {
+    if (!ok || !PyObject_TypeCheck(o, reinterpret_cast<PyTypeObject*>(type)) || PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) {
       PyErr_Clear();
       ok = false;
       return;
@@ -101,7 +103,7 @@ struct Call {
     PyBuffer_Release(&b);
   }
   void layer(PyObject* d) {
-    read_struct(d, desc);
+    read_struct(d, desc_type, desc);
     need(ok && lib.qalora_check_desc(&desc) == QALORA_OK);
     if (ok) L = desc.d_in / desc.group;
   }
@@ -542,7 +544,7 @@ FASTCALL(adamw_step, 9)
   constexpr Py_ssize_t kMost = 32;
   Call c;
   qalora_adamw hp{};
-  c.read_struct(a[0], hp);
+  c.read_struct(a[0], adamw_type, hp);
   c.need(PyLong_CheckExact(a[1]) && (PyList_CheckExact(a[2]) || PyTuple_CheckExact(a[2])));
   PLAIN(c);
   const long step = PyLong_AsLong(a[1]);
@@ -583,10 +585,11 @@ FASTCALL(adamw_step, 9)
   Py_RETURN_TRUE;
 FASTCALL_END
 
-// bind({entry point: address}, raise_status)
+// bind({entry point: address}, raise_status, Desc, AdamW)
 PyObject* bind(PyObject*, PyObject* args) {
-  PyObject *table, *raiser;
-  if (!PyArg_ParseTuple(args, "O!O", &PyDict_Type, &table, &raiser)) return nullptr;
+  PyObject *table, *raiser, *desc, *adamw;
+  if (!PyArg_ParseTuple(args, "O!OO!O!", &PyDict_Type, &table, &raiser, &PyType_Type, &desc, &PyType_Type, &adamw))
+    return nullptr;
   Library next;
 #define QALORA_BIND(name)                                                    \
   {                                                                          \
@@ -600,8 +603,10 @@ PyObject* bind(PyObject*, PyObject* args) {
   }
   QALORA_ENTRIES(QALORA_BIND)
   lib = next;
-  Py_INCREF(raiser);
-  Py_XSETREF(raise_status, raiser);
+  for (auto [to, from] : {std::pair{&raise_status, raiser}, {&desc_type, desc}, {&adamw_type, adamw}}) {
+    Py_INCREF(from);
+    Py_XSETREF(*to, from);
+  }
   bound = true;
   Py_RETURN_NONE;
 }

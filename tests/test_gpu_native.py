@@ -95,7 +95,7 @@ def test_other_forms_are_left_to_python(gpu_api, layer):
     assert fwd() is not None
     bad = gpu_api.make_desc(512, 256, 5, 32)
     for kw in (dict(x=x.cpu()), dict(x=x.float()), dict(x=x[:, :256]), dict(x=x[0]), dict(x=x[:0]), dict(x=x.as_subclass(Sub)),
-               dict(x=None), dict(p=p[:-8]), dict(al=al.half()), dict(be=be.t()), dict(be=be[:, :-8]), dict(d=bad), dict(d=3),
+               dict(x=None), dict(p=p[:-8]), dict(al=al.half()), dict(be=be.t()), dict(be=be[:, :-8]), dict(d=bad), dict(d=3), dict(d=bytes(d)),
                dict(A=L["A"]), dict(A=L["A"], B=L["B"][:, :-8].contiguous()), dict(dt=torch.float16), dict(dt="float32"),
                dict(y=torch.empty(24, 255, device="cuda")), dict(y=torch.empty(24, 256, device="cuda", dtype=torch.half)),
                dict(ws=torch.empty(16)), dict(ws=7)):
@@ -116,6 +116,7 @@ def test_adamw(gpu_api, monkeypatch):
     assert gpu_api._native.adamw_step(hp, 3, *a, True, norm, ws) is True
     for wrong in ([a[0][:2], *a[1:]], [[a[0][0], a[0][2], a[0][1]], *a[1:]], [[t.double() for t in a[0]], *a[1:]],
                   [iter(a[0]), *a[1:]], [[], [], [], []]):
+        assert gpu_api._native.adamw_step(bytes(hp), 3, *a, False, None, ws) is None
         assert gpu_api._native.adamw_step(hp, 3, *wrong, False, None, ws) is None
     monkeypatch.setattr(gpu_api, "_native", PythonOnly())
     norm_b = torch.zeros(1, device="cuda")
@@ -151,8 +152,8 @@ def test_operands_live_through_the_call(gpu_api):
         def __bool__(self):
             for ts in (p, g, m, v):
                 ts.clear()
-            later.extend(torch.zeros(4096, device="cuda") for _ in range(4))
+            later.extend(torch.ones(4096, device="cuda") for _ in range(4))
             return True
 
     assert gpu_api._native.adamw_step(hp, 1, p, g, m, v, Flag(), None, ws) is True
-    assert len(later) == 4 and all(t.count_nonzero() == 0 for t in later)
+    assert len(later) == 4 and all(bool((t == 1).all()) for t in later)
