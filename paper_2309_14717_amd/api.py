@@ -118,7 +118,6 @@ def load() -> ctypes.CDLL:
     lib.qalora_adamw_step.argtypes = [vp, i, i, vp, vp, vp, vp, vp, i, vp, vp, sz, vp]
     lib.qalora_beta_from_zero_point.argtypes = [cp, vp, vp, vp, vp]
     lib.qalora_zero_point_from_beta.argtypes = [cp, vp, vp, vp, vp]
-    _bind_native(lib)
     _lib = lib
     return lib
 
@@ -132,11 +131,12 @@ _NATIVE_ENTRIES = (
     "qalora_swiglu_backward_wide")
 
 
-def _bind_native(lib):
+def _bind_native():
     """Hand the library's entry points to the native form of the calls below (csrc/binding.cpp).  Each function
     asks it first: it takes the calls whose arguments are plainly valid and returns None for all others, which
-    the checks here then look at one by one."""
+    the checks here then look at one by one.  (Host-side queries need the library alone.)"""
     global _native
+    lib = load()
     path = os.path.join(_HERE, "_native.so")
     if not os.path.exists(path):
         raise RuntimeError(f"{path} not found: build it first (python -m paper_2309_14717_amd.build)")
@@ -147,8 +147,8 @@ def _bind_native(lib):
 
 
 def _fast():
-    if _lib is None:
-        load()
+    if _native is None:
+        _bind_native()
     return _native
 
 

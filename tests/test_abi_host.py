@@ -32,6 +32,15 @@ def test_exports_every_declared_symbol(lib):
         assert getattr(lib, n) is not None
 
 
+def test_host_queries_need_the_library_alone(lib, monkeypatch, tmp_path):
+    d = api.make_desc(4096, 4096, 4, 32, 64, 0.25)
+    for name, value in (("_lib", None), ("_native", None), ("_HERE", str(tmp_path))):   # (no native form beside it)
+        monkeypatch.setattr(api, name, value)
+    assert api.packed_bytes(d) == 4096 * 4096 // 2 and api.workspace_bytes(d, 8, api.OP_FORWARD) > 0
+    with pytest.raises(RuntimeError, match="_native.so"):
+        api.forward(d, None, None, None, None)
+
+
 def test_status_strings(lib):
     for st in (0, -1, -2, -3, -4, -5):
         assert api.status_string(st).startswith("QALORA_")

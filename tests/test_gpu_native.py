@@ -9,6 +9,11 @@ from paper_2309_14717_amd import synth
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(autouse=True)
+def bound(gpu_api):
+    gpu_api._fast()
+
+
 class PythonOnly:
     """Stands for the native module: takes no call."""
     def __getattr__(self, name):
