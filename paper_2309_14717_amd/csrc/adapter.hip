@@ -50,7 +50,7 @@ __device__ __forceinline__ uint4 bf16x8_to_f16x8_scaled(uint4 v, float sc) {
 // ---------------------------------------------------------------------------------------
 // The "front" launch: every row-wise and elementwise preparation step of a forward or a
 // backward call, as independent jobs of ONE kernel (the steps are tiny; launches are not).
-//   rows job 1 : x -> row scale, fp16 scaled copy (forward), P = pool_g(x) as bf16 hi + lo (for the
+//   rows job 1 : x -> row scale, fp16 scaled copy (forward), P = pool_g(x) as bf16 pieces (for the
 //                gradients).  One wavefront per token, the row held in registers: a single
 //                sweep of 128-bit loads gives the maximum (scale), the group sums (wavefront
 //                butterfly over the g/8 lanes of a group) and the converted copy.
@@ -80,7 +80,7 @@ struct FrontArgs {
   float2* rs_x;         // optional
   uint16_t* x16;        // optional, [T, d_in]
   int g;
-  uint16_t* P_out;      // optional, bf16 [T][2 Lp] (pooled_ld): rows job 1 also pools x
+  uint16_t* P_out;      // optional, bf16 [T][kPieces Lp] (pooled_ld): rows job 1 also pools x
   FrontPart part[MAX_PARTS];
   int n_parts;
   // rows job 2 (dy; or x, where a block takes a row): scale and convert
@@ -448,15 +448,12 @@ __device__ __forceinline__ float plain_group_sum(const uint16_t* __restrict__ sr
   for (int q = 0; q < g; ++q) sum += bf16_bits_to_f32(src[l * g + q]);
   return sum;
 }
-// Pooled activation l of a token's row of Lp, as bf16 hi and lo.
+// Pooled activation l of a token's row of Lp, as its bf16 pieces.
 __device__ __forceinline__ void store_pooled(uint16_t* P, int l, int L, int Lp, const float* P_s) {
-  uint16_t hi = 0, lo = 0;
-  if (l < L) {
-    split_bf16(P_s[l], hi, lo);
-    if ((hi & 0x7f80) == 0x7f80) lo = 0;  // infinite: no remainder
-  }
-  P[l] = hi;
-  P[Lp + l] = lo;
+  uint16_t piece[kPieces] = {};
+  if (l < L) split_bf16(P_s[l], piece);
+#pragma unroll
+  for (int q = 0; q < kPieces; ++q) P[q * Lp + l] = piece[q];
 }
 
 // One wavefront processes one bf16 row: returns the row scale; optionally writes the fp16
@@ -600,7 +597,7 @@ __global__ __launch_bounds__(256) void front_kernel(const FrontArgs a) {
     if (lane == 0 && a.rs_x) a.rs_x[t] = sc;
     if (!a.P_out) return;
     const int Lp = pooled_ld(L);
-    uint16_t* P = a.P_out + (size_t)t * 2 * Lp;
+    uint16_t* P = a.P_out + (size_t)t * kPieces * Lp;
     asm volatile("" ::: "memory");  // the row's own wavefront wrote P_s: its LDS accesses complete in order
     for (int l = lane; l < Lp; l += 64) store_pooled(P, l, L, Lp, P_s);
     return;
@@ -613,7 +610,7 @@ __global__ __launch_bounds__(256) void front_kernel(const FrontArgs a) {
     const float2 sc = process_row_block<RB>(a.y + (size_t)bid * a.d_y, a.d_y, a.y16 + (size_t)bid * a.d_y,
                                             reinterpret_cast<uint32_t*>(P_all), P_s, a.g, tid);
     if (tid == 0) a.rs_y[bid] = sc;
-    for (int l = tid; l < Lp; l += 256) store_pooled(a.P_out + (size_t)bid * 2 * Lp, l, L, Lp, P_s);
+    for (int l = tid; l < Lp; l += 256) store_pooled(a.P_out + (size_t)bid * kPieces * Lp, l, L, Lp, P_s);
     return;
   }
   const int t = bid * ROWS_PER_BLOCK + wave;

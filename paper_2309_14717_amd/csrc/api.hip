@@ -86,7 +86,7 @@ BwdPlan plan_backward(const qalora_desc& d, int T, int n_parts, const int* part_
     p.total = off;
     return p;
   }
-  p.P = take((size_t)T * pooled_ld(L) * 4);
+  p.P = take((size_t)T * kPieces * pooled_ld(L) * 2);
   p.grads = grads_plan(T, L, d.d_out);
   if (!p.grads.fused) p.Z = take((size_t)p.grads.slots * L * d.d_out * 4);
   for (int q = 0; q < n_parts; ++q) {
@@ -288,19 +288,16 @@ int qalora_pack(const qalora_desc* d, const uint8_t* codes, void* packed, void* 
   return hipGetLastError() == hipSuccess ? QALORA_OK : QALORA_EHIP;
 }
 
-// What the forward leaves for the backward when asked to: P = pool_g(x) as bf16 hi and lo [T][2 Lp], and the
-// factor job's bounds.
+// What the forward leaves for the backward when asked to: the pieces of P = pool_g(x), bf16 [T][kPieces Lp], and
+// the factor job's bounds.
 struct KeptLayout {
   size_t P, bmax, total;
 };
-// (The size also counts s U [T, rank] in fp32 of every part, which buffers have room for since the gradients were
-// made from it; nothing is stored there.)
-static KeptLayout kept_layout(const qalora_desc& d, int T, int n_parts, const int* part_rank) {
+static KeptLayout kept_layout(const qalora_desc& d, int T) {
   KeptLayout k{};
   k.P = 0;
-  k.bmax = align_up((size_t)T * pooled_ld(d.d_in / d.group) * 4);
+  k.bmax = align_up((size_t)T * kPieces * pooled_ld(d.d_in / d.group) * 2);
   k.total = k.bmax + align_up((size_t)factor_job_blocks(d.d_in / d.group, d.d_out) * 4);
-  for (int q = 0; q < n_parts; ++q) k.total += align_up((size_t)T * part_rank[q] * 4);
   return k;
 }
 
@@ -349,7 +346,7 @@ int qalora_forward(const qalora_desc* d, int tokens, const void* x, const void* 
 
 size_t qalora_kept_bytes(const qalora_desc* d, int tokens) {
   if (qalora_check_desc(d) != QALORA_OK || tokens <= 0 || d->rank <= 0) return 0;
-  return kept_layout(*d, tokens, 1, &d->rank).total;
+  return kept_layout(*d, tokens).total;
 }
 
 int qalora_forward_keep(const qalora_desc* d, int tokens, const void* x, const void* packed,
@@ -411,7 +408,7 @@ static int shared_parts(const qalora_desc* d, int n_parts, const qalora_part* pa
 size_t qalora_shared_kept_bytes(const qalora_desc* d, int tokens, int n_parts, const qalora_part* parts) {
   PartSpec ps;
   if (tokens <= 0 || shared_parts(d, n_parts, parts, false, ps) != QALORA_OK) return 0;
-  return kept_layout(*d, tokens, ps.n, ps.ap.rank).total;
+  return kept_layout(*d, tokens).total;
 }
 
 size_t qalora_shared_workspace_bytes(const qalora_desc* d, int tokens, int op, int n_parts,
@@ -567,7 +564,7 @@ static int forward_impl(const qalora_desc* d, int tokens, const void* x, const v
   if (pre) fj.alpha = nullptr;  // the words exist already: no factor job
   uint16_t* P_keep = nullptr;
   if (keep) {
-    const KeptLayout k = kept_layout(*d, tokens, ps.n, ps.ap.rank);
+    const KeptLayout k = kept_layout(*d, tokens);
     P_keep = reinterpret_cast<uint16_t*>(static_cast<char*>(kept) + k.P);
     // the bounds on |W~'| the factor job finds anyway: with them the backward knows its scale
     fj.block_max = reinterpret_cast<float*>(static_cast<char*>(kept) + k.bmax);
@@ -640,7 +637,7 @@ static int backward_impl(const qalora_desc* d, int tokens, const void* dy, const
   uint32_t* words = reinterpret_cast<uint32_t*>(w + plan.fac);
   float* inv_scale = reinterpret_cast<float*>(w + plan.inv);
   KeptLayout kl{};
-  if (use_kept) kl = kept_layout(*d, tokens, ps.n, ps.ap.rank);
+  if (use_kept) kl = kept_layout(*d, tokens);
   if (dx) {
     fj.alpha = alpha;
     fj.beta = beta;

@@ -46,10 +46,17 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
   return (uint16_t)(pack_bf16x2(f, 0.0f) & 0xffffu);
 }
-// hi + lo split of an fp32 value into two bf16 (v ~= hi + lo to about 2^-17 relative).
-__device__ __forceinline__ void split_bf16(float v, uint16_t& hi, uint16_t& lo) {
-  hi = f32_to_bf16_bits(v);
-  lo = f32_to_bf16_bits(v - bf16_bits_to_f32(hi));
+// An fp32 value for the bf16 matrix cores: three pieces of eight significant bits each, cut off one after the other.
+// Their sum is the value (an infinity or NaN is the first piece alone).
+constexpr int kPieces = 3;
+__device__ __forceinline__ void split_bf16(float v, uint16_t (&piece)[kPieces]) {
+  const uint32_t w = __float_as_uint(v);
+  const bool finite = (w & 0x7f800000u) != 0x7f800000u;
+  const float r1 = finite ? v - __uint_as_float(w & 0xffff0000u) : 0.0f;
+  const float r2 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
+  piece[0] = (uint16_t)(w >> 16);
+  piece[1] = (uint16_t)(__float_as_uint(r1) >> 16);
+  piece[2] = (uint16_t)(__float_as_uint(r2) >> 16);
 }
 
 // A block's partial sums on their way to another block: 16-byte stores with the cache policy of a

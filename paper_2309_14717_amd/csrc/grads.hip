@@ -3,8 +3,8 @@
 //   dB = s U^T dy = s A^T Z,     dA = s P^T (dy B^T) = s Z B^T,     Z = P^T dy  [L x d_out],
 //
 // so dy meets only one large product, whatever the rank and however many adapters share x, and neither
-// U nor dU = s dy B^T is formed.  Z costs 2 T L d_out multiply-adds (P goes through the bf16 matrix cores as
-// hi + lo, accurate to about 2^-17), 2 / g of the dense backward's; what follows is L r d_out, in fp32 on
+// U nor dU = s dy B^T is formed.  Z costs 3 T L d_out multiply-adds (P goes through the bf16 matrix cores as
+// three pieces, which hold all its bits), 3 / g of the dense backward's; what follows is L r d_out, in fp32 on
 // v_mfma_f32_16x16x4_f32.
 //
 //   z_kernel       Z, in tiles of 128 groups x 128 columns and runs of tokens                     [slots][L][d_out]
@@ -32,7 +32,7 @@ constexpr int GZ_L = 128;  // groups per tile
 constexpr int GZ_C = 128;  // columns per tile of z_kernel
 constexpr int GF_C = 32;   // columns per block of finish_kernel and fused_kernel
 constexpr int GF_LD = 36;  // floats per LDS row of 32 columns
-constexpr int P_LD = 2 * GZ_L + 16;  // 16-bit elements per LDS row of P: four rows of a transposed read in distinct banks
+constexpr int P_LD = kPieces * GZ_L + 16;  // 16-bit elements per LDS row of P: four rows of a transposed read in distinct banks
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
@@ -73,7 +73,7 @@ template <int NC>
 __device__ __forceinline__ void z_tile(const ZArgs& a, int l0, int j0, int t0, int t1, uint16_t* lds,
                                        f32x16 (&acc)[ZTile<NC>::TL][ZTile<NC>::TC]) {
   using G = ZTile<NC>;
-  constexpr int P_LOADS = GZ_T * 2 * GZ_L / 8 / 256, Y_CH = NC / 8, Y_LOADS = GZ_T * Y_CH / 256;
+  constexpr int P_CH = GZ_L / 8, P_LOADS = GZ_T * P_CH / 256, Y_CH = NC / 8, Y_LOADS = GZ_T * Y_CH / 256;
   uint16_t* ps = lds;
   uint16_t* ys = lds + GZ_T * P_LD;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -81,50 +81,50 @@ __device__ __forceinline__ void z_tile(const ZArgs& a, int l0, int j0, int t0, i
   const int wl = (wave % G::kWavesL) * G::TL * 32, wc = (wave / G::kWavesL) * G::TC * 32;
   // A lane's offsets inside a step are constants (groups and columns outside the matrix point past the buffer);
   // the buffers start at the step's first token and end with the last one's row, so later tokens read zero.
-  uint32_t p_off[P_LOADS], y_off[Y_LOADS];
-#pragma unroll
-  for (int q = 0; q < P_LOADS; ++q) {  // 16 pieces of hi(P), 16 of lo(P) per token
-    const int idx = tid + 256 * q, c = idx & 31, l = l0 + 8 * (c & 15);
-    p_off[q] = l < a.Lp ? ((uint32_t)(idx >> 5) * (uint32_t)(2 * a.Lp) + (uint32_t)((c >> 4) * a.Lp + l)) * 2u : kOob;
-  }
-#pragma unroll
-  for (int q = 0; q < Y_LOADS; ++q) {
-    const int idx = tid + 256 * q, j = j0 + 8 * (idx % Y_CH);
-    y_off[q] = j < a.d_out ? ((uint32_t)(idx / Y_CH) * (uint32_t)a.d_out + (uint32_t)j) * 2u : kOob;
-  }
-  u32x4 pr[P_LOADS], yr[Y_LOADS];  // the next step's, while this one is worked on
+  const uint32_t p_row = (uint32_t)(kPieces * a.Lp) * 2u, y_row = (uint32_t)a.d_out * 2u;
+  const int pr0 = tid / P_CH, pl = l0 + 8 * (tid % P_CH), yr0 = tid / Y_CH, yj = j0 + 8 * (tid % Y_CH);
+  const bool p_ok = pl < a.Lp, y_ok = yj < a.d_out;
+  uint32_t p_off = (uint32_t)pr0 * p_row + 2u * (uint32_t)pl, y_off = (uint32_t)yr0 * y_row + 2u * (uint32_t)yj;
+  u32x4 pr[kPieces][P_LOADS], yr[Y_LOADS];  // the next step's, while this one is worked on
   auto fetch = [&](int t) {
     const size_t from = (size_t)min(t, t1), rows = (size_t)(t1 - (int)from);
-    const __amdgpu_buffer_rsrc_t rs_p = rsrc(a.P + from * 2 * a.Lp, rows * a.Lp * 4);
-    const __amdgpu_buffer_rsrc_t rs_y = rsrc(a.dy + from * a.d_out, rows * a.d_out * 2);
+    const __amdgpu_buffer_rsrc_t rs_p = rsrc(a.P + from * kPieces * a.Lp, rows * p_row);
+    const __amdgpu_buffer_rsrc_t rs_y = rsrc(a.dy + from * a.d_out, rows * y_row);
+    asm volatile("" : "+v"(p_off), "+v"(y_off));  // (a register for each load's offset, kept over the loop, is too many)
 #pragma unroll
-    for (int q = 0; q < P_LOADS; ++q) pr[q] = __builtin_amdgcn_raw_buffer_load_b128(rs_p, (int)p_off[q], 0, 0);
+    for (int q = 0; q < P_LOADS; ++q)
 #pragma unroll
-    for (int q = 0; q < Y_LOADS; ++q) yr[q] = __builtin_amdgcn_raw_buffer_load_b128(rs_y, (int)y_off[q], 0, 0);
+      for (int h = 0; h < kPieces; ++h) {
+        const uint32_t o = p_off + (uint32_t)(256 / P_CH * q) * p_row + 2u * (uint32_t)(h * a.Lp);
+        pr[h][q] = __builtin_amdgcn_raw_buffer_load_b128(rs_p, (int)(p_ok ? o : kOob), 0, 0);
+      }
+#pragma unroll
+    for (int q = 0; q < Y_LOADS; ++q) {
+      const uint32_t o = y_off + (uint32_t)(256 / Y_CH * q) * y_row;
+      yr[q] = __builtin_amdgcn_raw_buffer_load_b128(rs_y, (int)(y_ok ? o : kOob), 0, 0);
+    }
   };
   const bool busy = l0 + wl < a.L;
   fetch(t0);
   for (int t = t0; t < t1; t += GZ_T) {
 #pragma unroll
-    for (int q = 0; q < P_LOADS; ++q) {
-      const int idx = tid + 256 * q;
-      *reinterpret_cast<u32x4*>(ps + (idx >> 5) * P_LD + 8 * (idx & 31)) = pr[q];
-    }
+    for (int q = 0; q < P_LOADS; ++q)
 #pragma unroll
-    for (int q = 0; q < Y_LOADS; ++q) {
-      const int idx = tid + 256 * q;
-      *reinterpret_cast<u32x4*>(ys + idx / Y_CH * G::Y_LD + 8 * (idx % Y_CH)) = yr[q];
-    }
+      for (int h = 0; h < kPieces; ++h)
+        *reinterpret_cast<u32x4*>(ps + (pr0 + 256 / P_CH * q) * P_LD + h * GZ_L + pl - l0) = pr[h][q];
+#pragma unroll
+    for (int q = 0; q < Y_LOADS; ++q)
+      *reinterpret_cast<u32x4*>(ys + (yr0 + 256 / Y_CH * q) * G::Y_LD + yj - j0) = yr[q];
     lds_barrier();
     fetch(t + GZ_T);  // (past the end: reads zero)
     if (busy) {
       // the operands of the next sixteen tokens are read while the matrix cores work on these
-      bf16x8 y[2][G::TC], p[2][2][G::TL];
+      bf16x8 y[2][G::TC], p[2][kPieces][G::TL];
       auto read = [&](int kk) {
 #pragma unroll
         for (int c = 0; c < G::TC; ++c) y[kk & 1][c] = read_columns(ys + 16 * kk * G::Y_LD + wc + 32 * c, G::Y_LD, lane);
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < kPieces; ++h)
 #pragma unroll
           for (int l = 0; l < G::TL; ++l) p[kk & 1][h][l] = read_columns(ps + 16 * kk * P_LD + h * GZ_L + wl + 32 * l, P_LD, lane);
       };
@@ -134,7 +134,7 @@ __device__ __forceinline__ void z_tile(const ZArgs& a, int l0, int j0, int t0, i
         if (kk + 1 < GZ_T / 16) read(kk + 1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < kPieces; ++h)
 #pragma unroll
           for (int l = 0; l < G::TL; ++l)
 #pragma unroll

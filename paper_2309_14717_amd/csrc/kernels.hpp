@@ -136,7 +136,8 @@ struct MidTArgs {
 hipError_t launch_midt(int bits, const MidTArgs& a, int blocks, hipStream_t st);  // nonce set here
 
 // --- adapter.hip --------------------------------------------------------------------
-// Elements of a token's row of hi(P), and of lo(P) behind it, in the pooled activations' storage bf16 [T][2 Lp].
+// The pooled activations' storage is bf16 [T][kPieces Lp]: of a token's row the first pieces, then the second ones,
+// then the third (split_bf16).  Lp:
 __host__ __device__ inline int pooled_ld(int L) { return (L + 7) / 8 * 8; }
 
 // The adapters of up to MAX_PARTS linears that share their input x and are evaluated as one
@@ -178,10 +179,10 @@ hipError_t launch_factor_scale(const float* alpha, const float* cst, const float
                                size_t n, uint32_t* words, float* inv_scale, hipStream_t st);
 
 // Forward front launch: x -> rs (row scales), x16 = fp16(x * scale), the factor job, and, when
-// given, P_keep bf16 [T][2 Lp]: hi and lo of pool_g(x), for the gradients.
+// given, P_keep bf16 [T][kPieces Lp]: the pieces of pool_g(x), for the gradients.
 hipError_t launch_front_forward(const uint16_t* x, int T, int d_in, float2* rs, uint16_t* x16, int g,
                                 uint16_t* P_keep, const FactorJob& fac, hipStream_t st);
-// Backward front launch: dy -> rs_dy, dy16; the factor job; and, given x, P bf16 [T][2 Lp] as above.
+// Backward front launch: dy -> rs_dy, dy16; the factor job; and, given x, P bf16 [T][kPieces Lp] as above.
 hipError_t launch_front_backward(const uint16_t* dy, int T, int d_out, float2* rs_dy, uint16_t* dy16,
                                  const uint16_t* x, int d_in, int g, uint16_t* P, const FactorJob& fac,
                                  hipStream_t st);
@@ -206,7 +207,7 @@ GradsPlan grads_plan(int T, int L, int d_out);
 int grads_da_shares(int d_out);  // shares of dA that a part of so many columns leaves
 int grads_db_shares(int L);      // shares of dB that so many groups leave; 0: dB comes out whole
 struct ZArgs {
-  const uint16_t* P;   // bf16 [T][2 Lp]: hi and lo of the pooled activations
+  const uint16_t* P;   // bf16 [T][kPieces Lp]: the pooled activations' pieces
   const uint16_t* dy;  // bf16 [T, d_out], all parts
   int T, L, Lp, d_out;
   ZRuns runs;
