@@ -36,7 +36,7 @@ FLAGS = [
 # unnoticed (a local array the compiler does not promote to registers costs a round trip to
 # memory per element).
 NO_SCRATCH = {"gemm_dq.hip": "gemm_dq_kernel", "gemm_dq_192.hip": "gemm_dq_kernel", "midt.hip": "midt_kernel", "smallt.hip": "smallt_kernel", "smallt4.hip": "smallt4_kernel", "smallt4_f16.hip": "smallt4_kernel",
-              "adapter.hip": ("front_kernel", "front_wide_kernel"), "grads.hip": ("z_kernel", "finish_kernel", "fused_kernel", "tail_kernel")}
+              "adapter.hip": ("front_kernel", "front_wide_kernel"), "grads.hip": ("z_kernel", "finish_kernel", "fused_kernel", "du_kernel", "db_kernel", "tail_kernel")}
 
 
 def _as_tuple(v):

@@ -7,6 +7,7 @@
 #include "kernels.hpp"
 #include "midt_plan.hpp"
 
+#include <algorithm>
 #include <cmath>
 
 using namespace qalora;
@@ -37,7 +38,7 @@ struct BwdPlan {
   GemmPlan gemm;
   GradsPlan grads;
   size_t rs, a16, fac, cst, bmax, inv, P, Z, gpart, total;
-  size_t da_part[MAX_PARTS], db_part[MAX_PARTS];
+  size_t U[MAX_PARTS], du[MAX_PARTS], da_part[MAX_PARTS], db_part[MAX_PARTS];
 };
 
 // forward workspace: row scales, the fp16 copy of x, the factor words and their column scales,
@@ -87,13 +88,32 @@ BwdPlan plan_backward(const qalora_desc& d, int T, int n_parts, const int* part_
     return p;
   }
   p.P = take((size_t)T * kPieces * pooled_ld(L) * 2);
-  p.grads = grads_plan(T, L, d.d_out);
-  if (!p.grads.fused) p.Z = take((size_t)p.grads.slots * L * d.d_out * 4);
-  for (int q = 0; q < n_parts; ++q) {
-    p.da_part[q] = take((size_t)grads_da_shares(part_dout[q]) * L * part_rank[q] * 4);
-    p.db_part[q] = take((size_t)grads_db_shares(L) * part_rank[q] * part_dout[q] * 4);
+  p.grads = grads_plan(T, L, d.d_out, n_parts, part_rank, part_dout);
+  // What is behind P depends on the gradients' form, and the form on the tokens: the room is that of the largest form
+  // that up to T tokens take, each for T, so that a workspace serves every shorter batch too.  (The choice between the
+  // forms that are not fused is linear in the tokens on either side of kGradsShort: the ends show all.)
+  const size_t from = off;
+  auto carve = [&](const GradsPlan& g) {
+    const bool by_u = g.form == GRADS_BY_U;
+    off = from;
+    if (g.form == GRADS_BY_Z) p.Z = take((size_t)g.slots * L * d.d_out * 4);
+    for (int q = 0; q < n_parts; ++q) {
+      const size_t ld = round_up(part_rank[q], 8);
+      const int da = by_u ? grads_most_da_shares(T, L, n_parts) : grads_da_shares(part_dout[q]);
+      if (by_u) p.U[q] = take((size_t)T * kPieces * ld * 2);
+      if (by_u) p.du[q] = take(grads_most_du_rows(T) * ld * 4);
+      p.da_part[q] = take((size_t)da * L * part_rank[q] * 4);
+      p.db_part[q] = take((size_t)(by_u ? g.slots : grads_db_shares(L)) * part_rank[q] * part_dout[q] * 4);
+    }
+    p.total = std::max(p.total, off);
+  };
+  const bool fusable = grads_fusable(L, d.d_out);
+  if (fusable) carve(grads_plan(1, L, d.d_out, n_parts, part_rank, part_dout));
+  for (const int t : {fusable ? kGradsFusedTokens + 1 : 1, kGradsShort, kGradsShort + 1, T}) {
+    const GradsForm other = grads_plan(std::min(t, T), L, d.d_out, n_parts, part_rank, part_dout).form;
+    if (other != GRADS_FUSED && other != p.grads.form) carve(grads_plan(T, L, d.d_out, n_parts, part_rank, part_dout, &other));
   }
-  p.total = off;
+  carve(p.grads);
   return p;
 }
 BwdPlan plan_backward(const qalora_desc& d, int T) {
@@ -709,20 +729,38 @@ static int backward_impl(const qalora_desc* d, int tokens, const void* dy, const
   f.L = L;
   f.d_out = d->d_out;
   f.runs = z.runs;
+  UArgs u{};
+  u.P = P;
+  u.dy = dy16;
+  u.T = tokens;
+  u.L = L;
+  u.Lp = z.Lp;
+  u.d_out = d->d_out;
+  u.runs = z.runs;
+  u.da_tokens = plan.grads.da_tokens;
+  u.da_shares = plan.grads.da_shares;
+  const bool by_u = plan.grads.form == GRADS_BY_U;
   f.accumulate = tail.accumulate = accumulate;
-  f.n_parts = tail.n_parts = ps.n;
+  f.n_parts = tail.n_parts = u.n_parts = ps.n;
   for (int q = 0; q < ps.n; ++q) {
     float* da_part = reinterpret_cast<float*>(w + plan.da_part[q]);
     float* db_part = reinterpret_cast<float*>(w + plan.db_part[q]);
     const int rank = ps.ap.rank[q], dout = ps.ap.d_out[q];
     const float s = ps.ap.s[q];
     f.part[q] = FinishPart{ps.ap.A[q], ps.ap.B[q], s, rank, ps.ap.col0[q], dout, ps.dB[q], da_part, db_part};
-    tail.part[q] = TailPart{da_part, grads_da_shares(dout), (size_t)L * rank, s, ps.dA[q], 0};
-    if (const int n = grads_db_shares(L))  // (d_out is a multiple of 8)
-      tail.sum[tail.n_sums++] = TailSum{SplitSum{db_part, n, (size_t)rank * dout / 4, ps.dB[q], 0}, true, s, 0};
+    u.part[q] = UPart{ps.ap.A[q], ps.ap.B[q], rank, round_up(rank, 8), ps.ap.col0[q], dout,
+                      reinterpret_cast<uint16_t*>(w + plan.U[q]), reinterpret_cast<float*>(w + plan.du[q]),
+                      plan.grads.du_steps, plan.grads.du_slices[q], plan.grads.tile0[q], db_part, da_part};
+    const int da = by_u ? u.da_shares : grads_da_shares(dout);
+    tail.part[q] = TailPart{da_part, da, (size_t)L * rank, s, ps.dA[q], 0};
+    const SplitSum db{db_part, grads_db_shares(L), (size_t)rank * dout / 4, ps.dB[q], 0};  // (d_out is a multiple of 8)
+    if (by_u)
+      tail.sum[tail.n_sums++] = TailSum{db, true, s, 0, u.runs, plan.grads.tile0[q], dout};
+    else if (db.slices > 0)
+      tail.sum[tail.n_sums++] = TailSum{db, true, s, 0, ZRuns{}, 0, 0};
   }
-  if (dx_sum.n4 > 0) tail.sum[tail.n_sums++] = TailSum{dx_sum, false, 1.0f, 0};
-  if (launch_grads(plan.grads, z, f, st) != hipSuccess) return QALORA_EHIP;
+  if (dx_sum.n4 > 0) tail.sum[tail.n_sums++] = TailSum{dx_sum, false, 1.0f, 0, ZRuns{}, 0, 0};
+  if ((by_u ? launch_grads_by_u(plan.grads, u, st) : launch_grads(plan.grads, z, f, st)) != hipSuccess) return QALORA_EHIP;
   return launch_tail(tail, st) == hipSuccess ? QALORA_OK : QALORA_EHIP;
 }
 

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "grads_plan.hpp"
+
 namespace qalora {
 
 // --- quantize.hip -------------------------------------------------------------------
@@ -143,7 +145,6 @@ __host__ __device__ inline int pooled_ld(int L) { return (L + 7) / 8 * 8; }
 // The adapters of up to MAX_PARTS linears that share their input x and are evaluated as one
 // wide layer (q/k/v; gate/up): part p owns columns [col0, col0 + d_out) of it.  A single layer
 // is one part covering all columns; n = 0 means no adapter.
-constexpr int MAX_PARTS = 4;
 struct AdapterParts {
   int n;
   const float* A[MAX_PARTS];  // [L, rank]
@@ -191,21 +192,6 @@ hipError_t launch_merge(const float* beta, const float* A, const float* B, int L
                         int rank, int g, float s, float* beta_out, hipStream_t st);
 
 // --- grads.hip: the adapters' gradients --------------------------------------------------
-// How Z = pool_g(x)^T dy is computed: in equal runs of units (a tile's step of tokens), or for few tokens inside
-// the launch that uses it.
-struct ZRuns {
-  int steps, units, blocks;  // of a tile; in all; one run each
-  __host__ __device__ int first(int b) const { return (int)((long)b * units / blocks); }            // unit of block b
-  __host__ __device__ int owner(int u) const { return (int)(((long)(u + 1) * blocks - 1) / units); }  // block of unit u
-};
-struct GradsPlan {
-  bool fused;
-  ZRuns runs;  // else
-  int slots;   // partial sums of a tile, at most
-};
-GradsPlan grads_plan(int T, int L, int d_out);
-int grads_da_shares(int d_out);  // shares of dA that a part of so many columns leaves
-int grads_db_shares(int L);      // shares of dB that so many groups leave; 0: dB comes out whole
 struct ZArgs {
   const uint16_t* P;   // bf16 [T][kPieces Lp]: the pooled activations' pieces
   const uint16_t* dy;  // bf16 [T, d_out], all parts
@@ -230,6 +216,25 @@ struct FinishArgs {
   int n_parts;
 };
 hipError_t launch_grads(const GradsPlan& plan, const ZArgs& z, const FinishArgs& f, hipStream_t st);
+struct UPart {
+  const float *A, *B;
+  int rank, ld;        // ld: the rank as a multiple of 8
+  int col0, d_out;
+  uint16_t* U;         // bf16 [T][kPieces ld]
+  float* du;           // [du_slices][T, ld]
+  int du_steps, du_slices, tile0;
+  float* db_part;      // [slots][rank, d_out]
+  float* da_part;      // [da_shares][L, rank]
+};
+struct UArgs {
+  const uint16_t *P, *dy;  // as in ZArgs
+  int T, L, Lp, d_out;
+  ZRuns runs;
+  int da_tokens, da_shares;
+  UPart part[MAX_PARTS];
+  int n_parts;
+};
+hipError_t launch_grads_by_u(const GradsPlan& plan, const UArgs& a, hipStream_t st);
 struct SplitSum {  // out = sum over the slices of a split product's partial results
   const float* partial;  // [slices][4 n4]
   int slices;
@@ -250,6 +255,8 @@ struct TailSum {
   bool gradient;   // out = (accumulate ? out : 0) + s sum, fp32
   float s;
   int block0;      // filled in by the launcher
+  ZRuns runs;      // of a gradient: where given, the slices of a tile of its columns are its runs' (tiles from tile0)
+  int tile0, d_out;
 };
 struct TailArgs {
   TailPart part[MAX_PARTS];
