@@ -4,6 +4,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "front_plan.hpp"
 #include "kernels.hpp"
 
 namespace qalora {
@@ -660,14 +661,6 @@ __global__ __launch_bounds__(256) void front_wide_kernel(const uint16_t* __restr
   }
 }
 
-// Columns per block of the factor job: as many (up to 16) as keep its LDS tile of L x columns
-// fp32 values within 32 KB, so that the row jobs of the same launch keep their occupancy.
-static int factor_cols(int L) {
-  int fc = 16;
-  while (fc > 1 && (size_t)L * fc * 4 > 32 * 1024) fc >>= 1;
-  return fc;
-}
-
 constexpr size_t kFrontLdsMax = 160 * 1024;  // a compute unit's LDS
 template <int RB, bool Y_WIDE>
 static hipError_t launch_front_as(const FrontArgs& a, int nblocks, size_t smem, hipStream_t st) {
@@ -691,14 +684,12 @@ static hipError_t launch_front(FrontArgs a, hipStream_t st) {
       front_wide_kernel<<<a.T, 256, 0, st>>>(a.x, a.d_in, a.rs_x, a.x16);
       return hipGetLastError();
     }
-    // few rows beside the factor job: a block each, in one launch with it (dense forward of 300 tokens, 4096 x 4096:
-    // 38.4 us with a launch of their own, 35.5 so; 128 of 1024 x 22016 27.0 / 24.1).  With pooling where a wavefront
-    // would take two sweeps or is nearly alone (forward and backward of 100 tokens, 13824 x 5120: 152 us by
-    // wavefronts, 145 so; 20 of 4096 x 11008 82 / 80; 1000 of 1024 x 8192 100 / 102).
-    a.y = a.x; a.Ty = a.T; a.d_y = a.d_in; a.rs_y = a.rs_x; a.y16 = a.x16;
-    a.y_pool = a.P_out != nullptr;
-    a.x = nullptr;
-    y_wide = true;
+    if (front_rows_by_block(a.T, a.f_fold, a.P_out != nullptr, a.f_L, a.f_dout)) {
+      a.y = a.x; a.Ty = a.T; a.d_y = a.d_in; a.rs_y = a.rs_x; a.y16 = a.x16;
+      a.y_pool = a.P_out != nullptr;
+      a.x = nullptr;
+      y_wide = true;
+    }
   }
   int max_rank = 0;
   for (int p = 0; p < a.n_parts; ++p) max_rank = a.part[p].rank > max_rank ? a.part[p].rank : max_rank;
