@@ -41,8 +41,15 @@ struct BwdPlan {
   size_t U[MAX_PARTS], du[MAX_PARTS], da_part[MAX_PARTS], db_part[MAX_PARTS];
 };
 
-// forward workspace: row scales, the fp16 copy of x, the factor words and their column scales,
-// then the split-K partials if any.  Independent of the adapter: the factor job folds it in.
+// Shapes of the mid-token kernel, but for the operands' size.
+inline bool midt_group(const qalora_desc& d) {
+  return (d.group == 32 || d.group == 64 || d.group == 128) && d.d_in % 128 == 0;
+}
+
+// forward workspace: row scales, the fp16 copy of x, the factor words and their column scales, then room for
+// the split-K partials of any batch of up to so many tokens, and no less than the mid-token kernel's (a part that fits in
+// the dense kernel's room for five tokens left it half its blocks, or none).  Independent of the adapter: the
+// factor job folds it in.
 FwdPlan plan_forward(const qalora_desc& d, int T) {
   FwdPlan p{};
   const size_t L = (size_t)(d.d_in / d.group);
@@ -57,7 +64,7 @@ FwdPlan plan_forward(const qalora_desc& d, int T) {
   p.fac = take(L * d.d_out * 4);
   p.inv = take((size_t)d.d_out * 4);
   p.gemm = gemm_dq_plan(d.bits, T, d.d_out, d.d_in, d.group);
-  p.gpart = take(gemm_dq_partial_room(T, d.d_out));
+  p.gpart = take(std::max(gemm_dq_partial_room(T, d.d_out), midt_group(d) ? midt_room(d.d_in, d.d_out, T) : 0));
   p.total = off;
   return p;
 }
@@ -146,9 +153,7 @@ inline bool use_smallt(const qalora_desc& d, int tokens) {
 
 // The mid-token kernel: the same shapes at every code width, beyond the few-token kernels' range.
 inline bool midt_shape(const qalora_desc& d, int tokens) {
-  if (tokens > MT_MAX_TOKENS) return false;
-  if (d.group != 32 && d.group != 64 && d.group != 128) return false;
-  if (d.d_in % 128 != 0) return false;
+  if (tokens > MT_MAX_TOKENS || !midt_group(d)) return false;
   // (the deployment stream of 4-bit codes is half as large again; triple and stream take the same path)
   return addressable(d, tokens) && plane0_words(4, d.d_in, d.d_out) * 6 < kAddressable;
 }

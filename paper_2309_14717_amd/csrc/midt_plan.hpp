@@ -41,7 +41,7 @@ inline double midt_cost(int units, int CU, int S, double unit, int tt, int nb, i
 
 // Blocks of the launch, at most one per compute unit, given the room for flags (ST_HEAD_BYTES) and partials
 // behind them (runs of whole slabs need none).  0 where the room leaves too few: the dense kernel is for
-// these (layers of up to about 2048 x 2048, and large groups, whose factors leave little room).
+// these (none where the room is midt_room).
 // Runs on every call, so it ends early: it goes from the most blocks down, and once the units alone cost more
 // than the best so far (or than is allowed above the cheapest) fewer blocks only do more each.
 inline int midt_blocks(int bits, int d_in, int d_out, int tokens, size_t scratch) {
@@ -73,6 +73,13 @@ inline int midt_blocks(int bits, int d_in, int d_out, int tokens, size_t scratch
     }
   }
   return best > 0 && best_cost <= midt_short_of(bits) * free_cost ? best : 0;
+}
+
+// Room that holds the partials of any count for up to so many tokens; 8.4 MB at most.
+inline size_t midt_room(int d_in, int d_out, int tokens) {
+  const long units = (long)ceil_div(d_in / 128, MT_DEEP) * ceil_div(d_out, MT_SLAB);
+  const size_t blocks = units < ST_MAX_BLOCKS ? (size_t)units : (size_t)ST_MAX_BLOCKS;
+  return ST_HEAD_BYTES + blocks * midt_tiles(tokens < MT_MAX_TOKENS ? tokens : MT_MAX_TOKENS) * 4 * 128 * 16;
 }
 
 }  // namespace qalora

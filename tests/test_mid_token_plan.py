@@ -6,6 +6,7 @@ import random
 import pytest
 
 from host_code import host_library
+from paper_2309_14717_amd import api
 
 HEAD, PARTIAL = 2304, 4 * 8192   # flags and status word; the partial of a block at 64 tokens
 
@@ -78,3 +79,16 @@ def test_search_is_shorter(plan, d_in, d_out):
     full, early = (min(plan.us_per_call(f, d_in, d_out) for _ in range(7)) for f in (1, 0))
     print(f"plan {d_in}x{d_out}: {early:.2f} us, all counts {full:.2f}")
     assert early < 0.75 * full
+
+
+@pytest.mark.parametrize("group", [32, 64, 128])
+def test_the_workspace_leaves_room_for_any_count(plan, group):
+    """The dense kernel's room for slices alone, in proportion to the tokens, was too little for few of them: 4096 x 4096
+    deployed at 5 tokens ran on 128 blocks where 224 are the cheapest, and with groups of 128 on the dense kernel."""
+    for bits in (4, 3, 2):
+        for d_in in range(1024, 8193, 512):
+            for d_out in (8, 512, 1032, 2048, 2720, 4096, 8192):
+                desc = api.make_desc(d_in, d_out, bits, group)
+                for tokens in (5, 6, 8, 11, 16, 17, 32, 33, 48, 49, 64):
+                    free = plan.blocks(bits, d_in, d_out, tokens, ctypes.c_size_t(1 << 30))
+                    assert api.mid_blocks(desc, tokens) == free > 0
