@@ -130,20 +130,14 @@ def test_adamw(gpu_api, monkeypatch):
 
 
 def test_an_operand_that_cannot_be_read_raises(gpu_api):
-    # a lazily cloned tensor is copied when its address is taken: where there is no memory for the copy the call
-    # raises, and the interpreter goes on
-    W = torch.randn(4096, 8192, device="cuda")
-    d = gpu_api.make_desc(4096, 8192, 4, 32)
-    lazy = torch._lazy_clone(W)
-    torch.cuda.empty_cache()
-    room = torch.cuda.memory_reserved() + W.nbytes * 3 // 4   # the outputs take three eighths of W
-    torch.cuda.set_per_process_memory_fraction(room / torch.cuda.get_device_properties(0).total_memory)
-    try:
-        with pytest.raises(torch.OutOfMemoryError):
-            gpu_api._native.quantize(d, lazy)
-    finally:
-        torch.cuda.set_per_process_memory_fraction(1.0)
-    assert all(torch.equal(a, b) for a, b in zip(gpu_api.quantize(d, lazy), gpu_api.quantize(d, W)))
+    # taking a tensor's address can throw (a lazily cloned one is copied then, and there may be no memory): the call
+    # raises, and the interpreter goes on.  (Not tested with such a clone: PyTorch has already counted it as copied.)
+    d, W = gpu_api.make_desc(512, 256, 4, 32), torch.randn(512, 256, device="cuda")
+    shut = W.clone()
+    torch._C._set_throw_on_mutable_data_ptr(shut)
+    with pytest.raises(RuntimeError, match="Cannot access data pointer"):
+        gpu_api._native.quantize(d, shut)
+    assert gpu_api._native.quantize(d, W) is not None
 
 
 def test_operands_live_through_the_call(gpu_api):
