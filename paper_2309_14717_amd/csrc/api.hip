@@ -166,6 +166,25 @@ inline size_t smallt_workspace(const qalora_desc& d, int tokens) {
   return ST_HEAD_BYTES + align_up((size_t)blocks * per_block * 4);
 }
 
+// What a forward call needs (adapter-free for the few-token kernels); the same on 16-bit factors, for which the matrix path
+// expands alpha and beta behind the adapter-free forward's workspace.
+inline size_t forward_need(const qalora_desc& d, int tokens) {
+  const size_t dense = plan_forward(d, tokens).total;
+  return use_smallt(d, tokens) ? std::max(dense, smallt_workspace(d, tokens)) : dense;
+}
+inline size_t factors16_need(const qalora_desc& d, int tokens) {
+  if (use_smallt(d, tokens)) return smallt_workspace(d, tokens);
+  return align_up(plan_forward(d, tokens).total) + 2 * align_up((size_t)(d.d_in / d.group) * d.d_out * 4);
+}
+// What the few-token kernels need for any batch of up to so many tokens (launch shapes change behind these counts): the
+// sizes that callers ask for include it, so that a workspace serves every shorter batch.
+inline size_t smallt_most(const qalora_desc& d, int tokens) {
+  size_t most = 0;
+  for (const int t : {4, 8, 16, 32})
+    if (use_smallt(d, std::min(t, tokens))) most = std::max(most, smallt_workspace(d, std::min(t, tokens)));
+  return most;
+}
+
 static_assert(MAX_PARTS == QALORA_MAX_PARTS, "the header documents this limit");
 static_assert(ST_STATUS_OFFSET == QALORA_WS_STATUS_OFFSET, "the header documents this offset");
 
@@ -243,24 +262,9 @@ size_t qalora_workspace_bytes(const qalora_desc* d, int tokens, int op) {
     case QALORA_OP_QUANTIZE:
     case QALORA_OP_MERGE: return 0;
     case QALORA_OP_QUANTIZE_COMPENSATED: return align_up((size_t)d->d_in * d->d_out * 4);
-    case QALORA_OP_FORWARD: {
-      if (tokens <= 0) return 0;
-      size_t need = plan_forward(*d, tokens).total;
-      if (use_smallt(*d, tokens)) {
-        const size_t st = smallt_workspace(*d, tokens);
-        if (st > need) need = st;
-      }
-      return need;
-    }
-    case QALORA_OP_FORWARD_FACTORS16: {
-      if (tokens <= 0) return 0;
-      if (use_smallt(*d, tokens)) return smallt_workspace(*d, tokens);
-      // matrix path: the adapter-free forward's workspace, then alpha and beta expanded to fp32
-      qalora_desc plain = *d;
-      plain.rank = 0;
-      return align_up(qalora_workspace_bytes(&plain, tokens, QALORA_OP_FORWARD)) +
-             2 * align_up((size_t)(d->d_in / d->group) * d->d_out * 4);
-    }
+    case QALORA_OP_FORWARD: return tokens > 0 ? std::max(forward_need(*d, tokens), smallt_most(*d, tokens)) : 0;
+    case QALORA_OP_FORWARD_FACTORS16:
+      return tokens > 0 ? std::max(factors16_need(*d, tokens), smallt_most(*d, tokens)) : 0;
     case QALORA_OP_BACKWARD: return tokens > 0 ? plan_backward(*d, tokens).total : 0;
     default: return 0;
   }
@@ -920,7 +924,7 @@ int qalora_forward_factors16(const qalora_desc* d, int tokens, const void* x, co
   if (misaligned(x) || misaligned(packed) || misaligned(factors16) || misaligned(y) || misaligned(ws))
     return QALORA_EALIGN;
   if (!addressable(*d, tokens)) return QALORA_EUNSUPPORTED;
-  const size_t need = qalora_workspace_bytes(d, tokens, QALORA_OP_FORWARD_FACTORS16);
+  const size_t need = factors16_need(*d, tokens);
   if (!ws || ws_bytes < need) return QALORA_EWORKSPACE;
   if (use_smallt(*d, tokens)) {
     SmallTArgs a{};
@@ -942,7 +946,7 @@ int qalora_forward_factors16(const qalora_desc* d, int tokens, const void* x, co
   }
   qalora_desc plain = *d;
   plain.rank = 0;
-  const size_t fwd_ws = align_up(qalora_workspace_bytes(&plain, tokens, QALORA_OP_FORWARD));
+  const size_t fwd_ws = align_up(plan_forward(plain, tokens).total);
   if (const int mrc = forward_mid(*d, tokens, x, packed, nullptr, nullptr, factors16, nullptr, y, y_dtype, ws, fwd_ws,
                                   as_stream(stream));
       mrc >= 0)

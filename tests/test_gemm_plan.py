@@ -62,11 +62,12 @@ def test_plan_of(plan, bits, group, tokens, d_in, d_out, fwd, bwd):
     assert (plan.rows(bits, tokens, d_in, d_out, group), plan.slices(bits, tokens, d_in, d_out, group)) == bwd
 
 
-@pytest.mark.parametrize("d_in,d_out", [(512, 512), (1024, 1024), (4096, 11008), (13824, 520), (22016, 8192)])
-def test_a_longer_batch_needs_no_less_workspace(d_in, d_out):
-    """One workspace sized for the longest batch serves the shorter ones (beyond the few-token kernels)."""
-    for op in (api.OP_FORWARD, api.OP_BACKWARD):
-        sizes = [api.workspace_bytes(api.make_desc(d_in, d_out, 4, 32), t, op) for t in range(33, 4200, 13)]
+@pytest.mark.parametrize("d_in,d_out", [(512, 512), (1024, 1024), (4096, 11008), (13824, 520), (22016, 8192), (1024, 8192)])
+@pytest.mark.parametrize("bits,group", [(4, 32), (3, 64), (2, 128), (4, 8)])
+def test_a_longer_batch_needs_no_less_workspace(d_in, d_out, bits, group):
+    """One workspace sized for the longest batch serves the shorter ones.  (The backward with an adapter: test_grads_plan.)"""
+    for op in (api.OP_FORWARD, api.OP_FORWARD_FACTORS16, api.OP_BACKWARD):
+        sizes = [api.workspace_bytes(api.make_desc(d_in, d_out, bits, group), t, op) for t in (*range(1, 70), *range(70, 4200, 13))]
         assert sizes == sorted(sizes)
 
 
