@@ -88,7 +88,7 @@ BwdPlan plan_backward(const qalora_desc& d, int T, int n_parts, const int* part_
   p.cst = take((size_t)L * d.d_out * 4);
   p.bmax = take((size_t)p.nmax * 4);
   p.inv = take(16);
-  p.gemm = gemm_dq_plan(d.bits, T, d.d_in, d.d_out, d.group);
+  p.gemm = gemm_dq_plan(d.bits, T, d.d_in, d.d_out, d.group, true);
   p.gpart = take(gemm_dq_partial_room(T, d.d_in));
   if (n_parts <= 0) {
     p.total = off;

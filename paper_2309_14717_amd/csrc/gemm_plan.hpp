@@ -35,7 +35,11 @@ inline size_t gemm_dq_partial_room(int M, int N) {
 // average; heights and splits planned one after the other, with at least eight steps per slice, were 13 %
 // from it (per call of 512 tokens: 1024 x 4096 38.6 -> 24.5 us, 2048 x 2048 36.9 -> 31.1, 4096 x 4096 48.9 -> 44.6;
 // 1024 tokens of 4096 x 4096 71.3 -> 62.2).
-inline GemmPlan gemm_dq_plan(int bits, int M, int N, int K_main, int group) {
+// The general form (offsets of every load worked out per step) goes by the same constants but for two (us before / with
+// these): its forward's 64-row step is longer (300 tokens of 4800 x 11008, g 96 88 / 70; 512 of 3072 x 4096 41 / 37), and
+// its 3-bit backward has one such block on a unit, not two (130 tokens, 13824 x 2720 58 / 52, 11008 x 4072 65 / 60; 107
+// sizes of it 0.6 % shorter on average, none longer).  The backward takes it where d_out is no multiple of 64.
+inline GemmPlan gemm_dq_plan(int bits, int M, int N, int K_main, int group, bool bwd = false) {
   struct Tile {
     int rows;
     double step, block;  // of a K step and of a block's prologue and epilogue
@@ -44,8 +48,9 @@ inline GemmPlan gemm_dq_plan(int bits, int M, int N, int K_main, int group) {
   constexpr double kPairStep = 0.98, kPairBlock = 2.0;  // two 64-row blocks on every unit
   constexpr double kClock = 0.1;       // of a round's time that its idle units give back (power)
   constexpr int kUnits = 256;
-  const double bits_step = bits == 3 ? 1.28 : 1.0;  // two planes to put together
   const bool fast = gemm_fast_shape(K_main, group);
+  const bool single = !fast && bits == 3 && bwd;  // one 64-row block per unit (gemm_min_waves)
+  const double bits_step = single ? 1.5 : (bits == 3 ? 1.28 : 1.0);  // two planes to put together
   const int nk = ceil_div(K_main, kGemmStep);
   const double out_us = (double)M * N * 1e-6;
   const size_t room = gemm_dq_partial_room(M, N);
@@ -60,9 +65,9 @@ inline GemmPlan gemm_dq_plan(int bits, int M, int N, int K_main, int group) {
       const int steps = ceil_div(nk, ks);
       if (ceil_div(nk, steps) != ks) continue;  // a slice would be empty
       const long blocks = tiles * ks;
-      const double one = steps * t.step * bits_step + t.block;
+      const double one = steps * (t.rows == 64 && !fast && !bwd ? 0.665 : t.step) * bits_step + t.block;
       double cost;
-      if (t.rows == 64) {
+      if (t.rows == 64 && !single) {
         const double pair = steps * kPairStep * bits_step + kPairBlock;
         const long rounds = blocks / (2 * kUnits), rest = blocks - rounds * 2 * kUnits;
         cost = rounds * pair + (rest > kUnits ? pair : (rest > 0 ? one : 0.0));

@@ -34,6 +34,10 @@ def plan(tmp_path_factory):
 #include "gemm_plan.hpp"
 extern "C" int rows(int bits, int M, int N, int K, int g) { return qalora::gemm_dq_plan(bits, M, N, K, g).tile_rows; }
 extern "C" int slices(int bits, int M, int N, int K, int g) { return qalora::gemm_dq_plan(bits, M, N, K, g).ksplit; }
+extern "C" int general(int bits, int M, int N, int K, int g, int bwd) {
+  const qalora::GemmPlan p = qalora::gemm_dq_plan(bits, M, N, K, g, bwd);
+  return 100 * p.tile_rows + p.ksplit;
+}
 extern "C" size_t room(int M, int N) { return qalora::gemm_dq_partial_room(M, N); }
 extern "C" int fast(int K, int g) { return qalora::gemm_fast_shape(K, g); }
 """)
@@ -60,6 +64,18 @@ def test_plans_are_launchable(plan):
 def test_plan_of(plan, bits, group, tokens, d_in, d_out, fwd, bwd):
     assert (plan.rows(bits, tokens, d_out, d_in, group), plan.slices(bits, tokens, d_out, d_in, group)) == fwd
     assert (plan.rows(bits, tokens, d_in, d_out, group), plan.slices(bits, tokens, d_in, d_out, group)) == bwd
+
+
+@pytest.mark.parametrize("bits,tokens,d_in,d_out,group,bwd,best", [
+    (4, 300, 4800, 11008, 96, 0, (64, 2)),      # us: 70, in (64, 1) 88
+    (2, 512, 3072, 4096, 96, 0, (128, 4)),      # 37, in (64, 2) 41
+    (3, 130, 13824, 2720, 32, 1, (128, 2)),     # 52, in (64, 3) 58
+    (3, 100, 4096, 11000, 32, 1, (128, 16)),    # 43, in (64, 8) 45
+])
+def test_general_form_has_its_own_costs(plan, bits, tokens, d_in, d_out, group, bwd, best):
+    N, K = (d_in, d_out) if bwd else (d_out, d_in)
+    assert not plan.fast(K, group)
+    assert divmod(plan.general(bits, tokens, N, K, group, bwd), 100) == best
 
 
 @pytest.mark.parametrize("d_in,d_out", [(512, 512), (1024, 1024), (4096, 11008), (13824, 520), (22016, 8192), (1024, 8192)])
