@@ -1,5 +1,7 @@
 """The native form of the binding's calls (csrc/binding.cpp): it takes plainly valid calls and gives what the Python
 form gives, bit for bit; everything else it leaves alone (None), so the Python form's checks and messages stand."""
+import ctypes
+
 import pytest
 import torch
 
@@ -28,14 +30,19 @@ def layer(gpu_api):
     L["deployed"] = gpu_api.deploy(L["desc"], *L["w"])
     L["f16"] = gpu_api.pack_factors16(L["desc"], *L["w"][1:])
     L["kept"] = gpu_api.forward_keep(L["desc"], L["x"], *L["w"], *L["ad"])[1]
+    gen = torch.Generator("cuda").manual_seed(3)
+    rand = lambda *n: torch.randn(n, device="cuda", generator=gen) * 0.02  # noqa: E731
+    L["parts"] = [(rand(16, 8), rand(8, 96), 0.5), (rand(16, 24), rand(24, 160), 2)]
+    L["kept2"] = gpu_api.forward_shared(L["desc"], L["x"], *L["w"], L["parts"], keep=True)[1]
     return L
 
 
 def calls(api, L):
-    """name -> (function, positional arguments as a user gives them, as the native form gets them)"""
+    """name of the native form, and what else tells it apart -> (function, positional arguments as a user gives them, as
+    the native form gets them)"""
     d, x, dy, w, ad, bf, f = L["desc"], L["x"], L["dy"], L["w"], L["ad"], torch.bfloat16, torch.float32
-    parts = [(L["A"], L["B"], 0.5)]
-    grads = [(torch.ones_like(L["A"]), torch.ones_like(L["B"]))]
+    parts = L["parts"]
+    grads = [(torch.ones_like(A), torch.ones_like(B)) for A, B, _ in parts]
     gu, dh = dy.repeat(1, 2), dy
     N = None
     return {
@@ -48,6 +55,8 @@ def calls(api, L):
         "forward_factors16": (api.forward_factors16, (d, x, L["packed"], L["f16"], f, N, N)),
         "forward_shared": (api.forward_shared, (d, x, *w, parts, False, bf, N, N, N)),
         "backward_shared": (api.backward_shared, (d, dy, x, N, *w, parts, True, bf, grads, True, N, N)),
+        "forward_shared keep": (api.forward_shared, (d, x, *w, parts, True, f, N, N, N)),
+        "backward_shared kept": (api.backward_shared, (d, dy, N, L["kept2"], *w, parts, True, f, grads, False, N, N)),
         "swiglu_forward_wide": (api.swiglu_forward_strided, (gu, 256, N)),
         "swiglu_backward_wide": (api.swiglu_backward_strided, (dh, gu, 256, N)),
     }
@@ -59,20 +68,77 @@ def flat(out):
     return [t for o in out if o is not None for t in flat(o)]
 
 
-@pytest.mark.parametrize("name", ["quantize", "forward", "forward_keep", "backward", "backward_kept", "forward_deployed",
-                                  "forward_factors16", "forward_shared", "backward_shared", "swiglu_forward_wide",
-                                  "swiglu_backward_wide"])
-def test_same_results(gpu_api, layer, monkeypatch, name):
-    fn, args = calls(gpu_api, layer)[name]
-    native = flat(getattr(gpu_api._native, name)(*args))
-    _, args = calls(gpu_api, layer)[name]
-    monkeypatch.setattr(gpu_api, "_native", PythonOnly())
-    python = flat(fn(*args))
+CALLS = ["quantize", "forward", "forward_keep", "backward", "backward_kept", "forward_deployed", "forward_factors16",
+         "forward_shared", "backward_shared", "swiglu_forward_wide", "swiglu_backward_wide", "forward_shared keep",
+         "backward_shared kept"]
+
+
+def same(name, native, python):
+    native, python = flat(native), flat(python)
     assert len(native) == len(python) > 0
     for i, (a, b) in enumerate(zip(native, python)):
         assert a.dtype == b.dtype and a.shape == b.shape
-        if not (name == "forward_keep" and i == 1):   # (the kept bytes are the library's own, and not all written)
+        if not (name in ("forward_keep", "forward_shared keep") and i == 1):   # (the kept bytes are the library's own, and not all written)
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("name", CALLS)
+def test_same_results(gpu_api, layer, monkeypatch, name):
+    fn, args = calls(gpu_api, layer)[name]
+    native = getattr(gpu_api._native, name.split()[0])(*args)
+    _, args = calls(gpu_api, layer)[name]
+    monkeypatch.setattr(gpu_api, "_native", PythonOnly())
+    same(name, native, fn(*args))
+
+
+def others(v):
+    """In place of an argument: what another caller might pass."""
+    if isinstance(v, torch.Tensor):
+        yield from (None, v.cpu(), v[:-1], v[:0], v[0], v.repeat_interleave(2, -1)[..., ::2])
+        if v.is_floating_point():
+            yield v.double()
+        if v.dim() == 2:
+            yield from (v[:, :-8].contiguous(), v.t())
+    elif isinstance(v, torch.dtype):
+        yield from (torch.float16, "float32", None)
+    elif isinstance(v, int) and not isinstance(v, bool):
+        yield from (v - 8, 0, -v, 1 << 62, None)
+    elif isinstance(v, list):   # of tuples
+        yield from (None, [], v[:1], v * 3, tuple(v), iter(v), v + [()], [t[:1] for t in v])
+        for i in range(len(v[0])):
+            for o in others(v[0][i]):
+                yield [(*v[0][:i], o, *v[0][i + 1:]), *v[1:]]
+
+
+@pytest.mark.parametrize("name", CALLS)
+def test_the_same_calls_are_refused(gpu_api, layer, monkeypatch, name):
+    """One argument at a time is another: where the native form takes the call the Python form gives the same, where it
+    fails the Python form fails alike, and what the Python form refuses the native form leaves alone."""
+    def outcome(python, i, k):
+        fn, args = calls(gpu_api, layer)[name]
+        args = (*args[:i], list(others(args[i]))[k], *args[i + 1:])
+        with monkeypatch.context() as m:
+            if python:
+                m.setattr(gpu_api, "_native", PythonOnly())
+            try:
+                return (fn if python else getattr(gpu_api._native, name.split()[0]))(*args)
+            except gpu_api.QaloraError as e:
+                return str(e)
+            except (ValueError, TypeError, AttributeError, RuntimeError, IndexError, OverflowError, ctypes.ArgumentError) as e:
+                return e
+    _, args = calls(gpu_api, layer)[name]
+    left = 0
+    for i in range(len(args)):
+        for k in range(len(list(others(args[i])))):
+            native, python = outcome(False, i, k), outcome(True, i, k)
+            if native is None:
+                left += 1
+            elif isinstance(native, str):
+                assert native == python, (i, k)
+            else:
+                assert not isinstance(native, Exception) and not isinstance(python, (str, Exception)), (i, k, native, python)
+                same(name, native, python)
+    assert left > 0
 
 
 def test_given_outputs_are_used_and_returned(gpu_api, layer):
