@@ -37,7 +37,7 @@ struct BwdPlan {
   int nmax;
   GemmPlan gemm;
   GradsPlan grads;
-  size_t rs, a16, fac, cst, bmax, inv, P, Z, gpart, total;
+  size_t rs, a16, fac, cst, bmax, inv, P, grad_parts, Z, gpart, total;
   size_t U[MAX_PARTS], du[MAX_PARTS], da_part[MAX_PARTS], db_part[MAX_PARTS];
 };
 
@@ -46,85 +46,99 @@ inline bool midt_group(const qalora_desc& d) {
   return (d.group == 32 || d.group == 64 || d.group == 128) && d.d_in % 128 == 0;
 }
 
-// forward workspace: row scales, the fp16 copy of x, the factor words and their column scales, then room for
-// the split-K partials of any batch of up to so many tokens, and no less than the mid-token kernel's (a part that fits in
-// the dense kernel's room for five tokens left it half its blocks, or none).  Independent of the adapter: the
-// factor job folds it in.
-FwdPlan plan_forward(const qalora_desc& d, int T) {
-  FwdPlan p{};
-  const size_t L = (size_t)(d.d_in / d.group);
+// A plan holds where things lie in a call's workspace and what the call needs of it.  The sizes that callers ask for
+// (..._bytes) are no less than what any shorter batch needs: one workspace serves them all.
+struct Carver {
   size_t off = 0;
-  auto take = [&](size_t bytes) {
+  size_t take(size_t bytes) {
     const size_t o = off;
     off += align_up(bytes);
     return o;
-  };
-  p.rs = take((size_t)T * sizeof(float2));
-  p.a16 = take((size_t)round_up(T, 256) * d.d_in * 2);
-  p.fac = take(L * d.d_out * 4);
-  p.inv = take((size_t)d.d_out * 4);
+  }
+};
+
+// forward workspace: row scales, the fp16 copy of x, the factor words and their column scales, then the split-K
+// partials if any, and up to 64 tokens no less than the mid-token kernel's (a part that fits in the dense kernel's
+// for five tokens left it half its blocks, or none).  Independent of the adapter: the factor job folds it in.
+FwdPlan plan_forward(const qalora_desc& d, int T) {
+  FwdPlan p{};
+  Carver c;
+  const size_t L = (size_t)(d.d_in / d.group);
+  p.rs = c.take((size_t)T * sizeof(float2));
+  p.a16 = c.take((size_t)round_up(T, 256) * d.d_in * 2);
+  p.fac = c.take(L * d.d_out * 4);
+  p.inv = c.take((size_t)d.d_out * 4);
   p.gemm = gemm_dq_plan(d.bits, T, d.d_out, d.d_in, d.group);
-  p.gpart = take(std::max(gemm_dq_partial_room(T, d.d_out), midt_group(d) ? midt_room(d.d_in, d.d_out, T) : 0));
-  p.total = off;
+  p.gpart = c.off;
+  p.total = c.off + align_up(std::max(gemm_dq_partials(p.gemm, T, d.d_out),
+                                      T <= MT_MAX_TOKENS && midt_group(d) ? midt_room(d.d_in, d.d_out, T) : 0));
   return p;
+}
+size_t forward_bytes(const qalora_desc& d, int T) {
+  return plan_forward(d, T).gpart + align_up(std::max(gemm_dq_most_partials(d.bits, T, d.d_out, d.d_in, d.group, false),
+                                                      midt_group(d) ? midt_room(d.d_in, d.d_out, T) : 0));
 }
 
 // backward workspace: what the dx contraction needs (row scales, fp16 copy of dy, factor words
-// and their first stage), then P = pool(x), the partial sums of Z and per adapter part the shares of dA and dB.
-// n_parts = 0: adapter-free, only dx.
+// and their first stage), then P = pool(x), the partial sums of the gradients' products and per adapter part the shares of
+// dA and dB, and the split-K partials of dx if any.  n_parts = 0: adapter-free, only dx.
+size_t carve_gradients(BwdPlan& p, Carver& c, const GradsPlan& g, const qalora_desc& d, int T, int n_parts,
+                       const int* part_rank, const int* part_dout) {
+  const int L = d.d_in / d.group;
+  const bool by_u = g.form == GRADS_BY_U;
+  if (g.form == GRADS_BY_Z) p.Z = c.take((size_t)g.slots * L * d.d_out * 4);
+  for (int q = 0; q < n_parts; ++q) {
+    const size_t ld = round_up(part_rank[q], 8);
+    const int da = by_u ? grads_most_da_shares(T, L, n_parts) : grads_da_shares(part_dout[q]);
+    if (by_u) p.U[q] = c.take((size_t)T * kPieces * ld * 2);
+    if (by_u) p.du[q] = c.take(grads_most_du_rows(T) * ld * 4);
+    p.da_part[q] = c.take((size_t)da * L * part_rank[q] * 4);
+    p.db_part[q] = c.take((size_t)(by_u ? g.slots : grads_db_shares(L)) * part_rank[q] * part_dout[q] * 4);
+  }
+  return c.off;
+}
 BwdPlan plan_backward(const qalora_desc& d, int T, int n_parts, const int* part_rank, const int* part_dout) {
   BwdPlan p{};
+  Carver c;
   const int L = d.d_in / d.group;
   p.nmax = factor_job_blocks(L, d.d_out);
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    const size_t o = off;
-    off += align_up(bytes);
-    return o;
-  };
-  p.rs = take((size_t)T * sizeof(float2));
-  p.a16 = take((size_t)round_up(T, 256) * d.d_out * 2);
-  p.fac = take((size_t)L * d.d_out * 4);
-  p.cst = take((size_t)L * d.d_out * 4);
-  p.bmax = take((size_t)p.nmax * 4);
-  p.inv = take(16);
+  p.rs = c.take((size_t)T * sizeof(float2));
+  p.a16 = c.take((size_t)round_up(T, 256) * d.d_out * 2);
+  p.fac = c.take((size_t)L * d.d_out * 4);
+  p.cst = c.take((size_t)L * d.d_out * 4);
+  p.bmax = c.take((size_t)p.nmax * 4);
+  p.inv = c.take(16);
   p.gemm = gemm_dq_plan(d.bits, T, d.d_in, d.d_out, d.group, true);
-  p.gpart = take(gemm_dq_partial_room(T, d.d_in));
-  if (n_parts <= 0) {
-    p.total = off;
-    return p;
+  if (n_parts > 0) {
+    p.P = c.take((size_t)T * kPieces * pooled_ld(L) * 2);
+    p.grad_parts = c.off;
+    p.grads = grads_plan(T, L, d.d_out, n_parts, part_rank, part_dout);
+    carve_gradients(p, c, p.grads, d, T, n_parts, part_rank, part_dout);
   }
-  p.P = take((size_t)T * kPieces * pooled_ld(L) * 2);
-  p.grads = grads_plan(T, L, d.d_out, n_parts, part_rank, part_dout);
-  // What is behind P depends on the gradients' form, and the form on the tokens: the room is that of the largest form
-  // that up to T tokens take, each for T, so that a workspace serves every shorter batch too.  (The choice between the
-  // forms that are not fused is linear in the tokens on either side of kGradsShort: the ends show all.)
-  const size_t from = off;
-  auto carve = [&](const GradsPlan& g) {
-    const bool by_u = g.form == GRADS_BY_U;
-    off = from;
-    if (g.form == GRADS_BY_Z) p.Z = take((size_t)g.slots * L * d.d_out * 4);
-    for (int q = 0; q < n_parts; ++q) {
-      const size_t ld = round_up(part_rank[q], 8);
-      const int da = by_u ? grads_most_da_shares(T, L, n_parts) : grads_da_shares(part_dout[q]);
-      if (by_u) p.U[q] = take((size_t)T * kPieces * ld * 2);
-      if (by_u) p.du[q] = take(grads_most_du_rows(T) * ld * 4);
-      p.da_part[q] = take((size_t)da * L * part_rank[q] * 4);
-      p.db_part[q] = take((size_t)(by_u ? g.slots : grads_db_shares(L)) * part_rank[q] * part_dout[q] * 4);
-    }
-    p.total = std::max(p.total, off);
-  };
-  const bool fusable = grads_fusable(L, d.d_out);
-  if (fusable) carve(grads_plan(1, L, d.d_out, n_parts, part_rank, part_dout));
-  for (const int t : {fusable ? kGradsFusedTokens + 1 : 1, kGradsShort, kGradsShort + 1, T}) {
-    const GradsForm other = grads_plan(std::min(t, T), L, d.d_out, n_parts, part_rank, part_dout).form;
-    if (other != GRADS_FUSED && other != p.grads.form) carve(grads_plan(T, L, d.d_out, n_parts, part_rank, part_dout, &other));
-  }
-  carve(p.grads);
+  p.gpart = c.off;
+  p.total = c.off + align_up(gemm_dq_partials(p.gemm, T, d.d_in));
   return p;
 }
-BwdPlan plan_backward(const qalora_desc& d, int T) {
-  return plan_backward(d, T, d.rank > 0 ? 1 : 0, &d.rank, &d.d_out);
+size_t backward_bytes(const qalora_desc& d, int T, int n_parts, const int* part_rank, const int* part_dout) {
+  BwdPlan p = plan_backward(d, T, n_parts, part_rank, part_dout);
+  size_t most = p.gpart;
+  // The gradients' form depends on the tokens: the room is that of the largest form that up to T tokens take, each for T.
+  // (The choice between the forms that are not fused is linear in the tokens on either side of kGradsShort: the ends show
+  // all.)
+  if (n_parts > 0) {
+    const int L = d.d_in / d.group;
+    auto carve = [&](const GradsPlan& g) {
+      Carver c{p.grad_parts};
+      most = std::max(most, carve_gradients(p, c, g, d, T, n_parts, part_rank, part_dout));
+    };
+    const bool fusable = grads_fusable(L, d.d_out);
+    if (fusable) carve(grads_plan(1, L, d.d_out, n_parts, part_rank, part_dout));
+    for (const int t : {fusable ? kGradsFusedTokens + 1 : 1, kGradsShort, kGradsShort + 1, T}) {
+      const GradsForm form = grads_plan(std::min(t, T), L, d.d_out, n_parts, part_rank, part_dout).form;
+      if (form != GRADS_FUSED) carve(grads_plan(T, L, d.d_out, n_parts, part_rank, part_dout, &form));
+    }
+  }
+  return most + align_up(gemm_dq_most_partials(d.bits, T, d.d_in, d.d_out, d.group, true));
 }
 
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
@@ -166,15 +180,11 @@ inline size_t smallt_workspace(const qalora_desc& d, int tokens) {
   return ST_HEAD_BYTES + align_up((size_t)blocks * per_block * 4);
 }
 
-// What a forward call needs (adapter-free for the few-token kernels); the same on 16-bit factors, for which the matrix path
-// expands alpha and beta behind the adapter-free forward's workspace.
-inline size_t forward_need(const qalora_desc& d, int tokens) {
-  const size_t dense = plan_forward(d, tokens).total;
-  return use_smallt(d, tokens) ? std::max(dense, smallt_workspace(d, tokens)) : dense;
-}
+// What a forward on 16-bit factors needs: for the matrix path alpha and beta are expanded behind the adapter-free forward's
+// workspace.
+inline size_t expanded_factors(const qalora_desc& d) { return 2 * align_up((size_t)(d.d_in / d.group) * d.d_out * 4); }
 inline size_t factors16_need(const qalora_desc& d, int tokens) {
-  if (use_smallt(d, tokens)) return smallt_workspace(d, tokens);
-  return align_up(plan_forward(d, tokens).total) + 2 * align_up((size_t)(d.d_in / d.group) * d.d_out * 4);
+  return use_smallt(d, tokens) ? smallt_workspace(d, tokens) : plan_forward(d, tokens).total + expanded_factors(d);
 }
 // What the few-token kernels need for any batch of up to so many tokens (launch shapes change behind these counts): the
 // sizes that callers ask for include it, so that a workspace serves every shorter batch.
@@ -262,10 +272,12 @@ size_t qalora_workspace_bytes(const qalora_desc* d, int tokens, int op) {
     case QALORA_OP_QUANTIZE:
     case QALORA_OP_MERGE: return 0;
     case QALORA_OP_QUANTIZE_COMPENSATED: return align_up((size_t)d->d_in * d->d_out * 4);
-    case QALORA_OP_FORWARD: return tokens > 0 ? std::max(forward_need(*d, tokens), smallt_most(*d, tokens)) : 0;
+    case QALORA_OP_FORWARD: return tokens > 0 ? std::max(forward_bytes(*d, tokens), smallt_most(*d, tokens)) : 0;
     case QALORA_OP_FORWARD_FACTORS16:
-      return tokens > 0 ? std::max(factors16_need(*d, tokens), smallt_most(*d, tokens)) : 0;
-    case QALORA_OP_BACKWARD: return tokens > 0 ? plan_backward(*d, tokens).total : 0;
+      if (tokens <= 0) return 0;
+      return std::max(use_smallt(*d, tokens) ? 0 : forward_bytes(*d, tokens) + expanded_factors(*d), smallt_most(*d, tokens));
+    case QALORA_OP_BACKWARD:
+      return tokens > 0 ? backward_bytes(*d, tokens, d->rank > 0 ? 1 : 0, &d->rank, &d->d_out) : 0;
     default: return 0;
   }
 }
@@ -444,8 +456,8 @@ size_t qalora_shared_workspace_bytes(const qalora_desc* d, int tokens, int op, i
                                      const qalora_part* parts) {
   PartSpec ps;
   if (tokens <= 0 || shared_parts(d, n_parts, parts, false, ps) != QALORA_OK) return 0;
-  if (op == QALORA_OP_FORWARD) return plan_forward(*d, tokens).total;
-  if (op == QALORA_OP_BACKWARD) return plan_backward(*d, tokens, ps.n, ps.ap.rank, ps.ap.d_out).total;
+  if (op == QALORA_OP_FORWARD) return forward_bytes(*d, tokens);
+  if (op == QALORA_OP_BACKWARD) return backward_bytes(*d, tokens, ps.n, ps.ap.rank, ps.ap.d_out);
   return 0;
 }
 
@@ -946,7 +958,7 @@ int qalora_forward_factors16(const qalora_desc* d, int tokens, const void* x, co
   }
   qalora_desc plain = *d;
   plain.rank = 0;
-  const size_t fwd_ws = align_up(plan_forward(plain, tokens).total);
+  const size_t fwd_ws = plan_forward(plain, tokens).total;
   if (const int mrc = forward_mid(*d, tokens, x, packed, nullptr, nullptr, factors16, nullptr, y, y_dtype, ws, fwd_ws,
                                   as_stream(stream));
       mrc >= 0)

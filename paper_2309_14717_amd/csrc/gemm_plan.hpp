@@ -1,12 +1,15 @@
 // Launch shape of the dequantising product (gemm_dq.hip).
 #pragma once
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace qalora {
 
 constexpr int kGemmStep = 64;  // K values per step
 constexpr int kGemmMaxSplits = 16;
-constexpr size_t kGemmPartialRoom = 64ull << 20;  // a 256 x 256 fp32 tile per compute unit
+constexpr size_t kGemmPartialRoom = 256ull << 20;
+constexpr size_t kGemmFastPartialRoom = 64ull << 20;  // a 256 x 256 fp32 tile per compute unit
 
 // What the fast addressing path of gemm_dq_kernel needs besides padded activation copies.
 inline bool gemm_fast_shape(int K_main, int group) {
@@ -18,11 +21,9 @@ struct GemmPlan {
   int ksplit;     // slices of K
 };
 
-// The slices' copies of the output stay within gemm_dq_partial_room, which grows with the tokens: so does the
-// workspace, and one sized for a longer batch serves every shorter one.
-inline size_t gemm_dq_partial_room(int M, int N) {
-  const size_t most = (size_t)kGemmMaxSplits * M * N * 4;
-  return most < kGemmPartialRoom ? most : kGemmPartialRoom;
+// What the slices' copies of the output may take (the fast form's; or either's).
+inline size_t gemm_dq_partial_room(int M, int N, bool fast = false) {
+  return std::min((size_t)kGemmMaxSplits * M * N * 4, fast ? kGemmFastPartialRoom : kGemmPartialRoom);
 }
 
 // Tile rows and K splits of the dequantising product, searched together: a launch takes
@@ -39,6 +40,11 @@ inline size_t gemm_dq_partial_room(int M, int N) {
 // these): its forward's 64-row step is longer (300 tokens of 4800 x 11008, g 96 88 / 70; 512 of 3072 x 4096 41 / 37), and
 // its 3-bit backward has one such block on a unit, not two (130 tokens, 13824 x 2720 58 / 52, 11008 x 4072 65 / 60; 107
 // sizes of it 0.6 % shorter on average, none longer).  The backward takes it where d_out is no multiple of 64.
+// The fast form's slices may take 64 MB: units without a tile give their power to the others, so larger outputs lose by
+// slices (90 sweeps of 350 .. 914 tokens: 10 % slower in slices that take more; 914 tokens of 22016 -> 8192 backward 355 us
+// whole, 405 in two).  The general form, further from the power limit, gains by them up to 256 MB (147 sweeps of 350 .. 2700
+// tokens: 0.4 % from the best on average, 10 % at most; within 64 MB 2.6 and 30; 3-bit backward of 1056 tokens, 9088 x 13480
+// 524 / 412).
 inline GemmPlan gemm_dq_plan(int bits, int M, int N, int K_main, int group, bool bwd = false) {
   struct Tile {
     int rows;
@@ -53,7 +59,7 @@ inline GemmPlan gemm_dq_plan(int bits, int M, int N, int K_main, int group, bool
   const double bits_step = single ? 1.5 : (bits == 3 ? 1.28 : 1.0);  // two planes to put together
   const int nk = ceil_div(K_main, kGemmStep);
   const double out_us = (double)M * N * 1e-6;
-  const size_t room = gemm_dq_partial_room(M, N);
+  const size_t room = gemm_dq_partial_room(M, N, fast);
   GemmPlan best{};
   double best_cost = 0;
   for (const Tile& t : kTiles) {
@@ -75,7 +81,11 @@ inline GemmPlan gemm_dq_plan(int bits, int M, int N, int K_main, int group, bool
         const long rounds = blocks / kUnits, rest = blocks - rounds * kUnits;
         cost = rounds * one + (rest > 0 ? one * (1.0 - kClock * (1.0 - (double)rest / kUnits)) : 0.0);
       }
-      if (ks > 1) cost += 3.0 + 0.34 * ks + out_us * (0.73 * ks + 0.6);
+      if (ks > 1) {
+        cost += 3.0 + 0.34 * ks + out_us * (0.73 * ks + 0.6);
+        const double bytes = 4.0 * ks * M * N;  // (beyond some 64 MB not all of them stay in the last-level cache)
+        if (bytes > kGemmFastPartialRoom) cost += 0.9 / 4e6 * (bytes - kGemmFastPartialRoom);
+      }
       if (best.tile_rows == 0 || cost < best_cost) {
         best = GemmPlan{t.rows, ks};
         best_cost = cost;
@@ -83,6 +93,32 @@ inline GemmPlan gemm_dq_plan(int bits, int M, int N, int K_main, int group, bool
     }
   }
   return best;
+}
+
+inline size_t gemm_dq_partials(const GemmPlan& p, int M, int N) { return p.ksplit > 1 ? (size_t)p.ksplit * M * N * 4 : 0; }
+
+// ... for any batch of up to M tokens, which is what a workspace has room for.  Batches that have the same tiles get the
+// fewer slices the longer they are (a slice's cost grows with the tokens, a step's does not), so the slices at either end
+// of a range of them bound what is between.
+inline size_t gemm_dq_most_partials(int bits, int M, int N, int K_main, int group, bool bwd) {
+  size_t most = 0;
+  auto slices = [&](int m) { return gemm_dq_plan(bits, m, N, K_main, group, bwd).ksplit; };
+  auto room = [&](int m) { return gemm_dq_partial_room(m, N, gemm_fast_shape(K_main, group)); };
+  auto bytes = [&](int ks, int m) { return ks > 1 ? std::min((size_t)ks * m * N * 4, room(m)) : 0; };
+  for (int last = M; last > 0 && room(last) > most; last = (last - 1) / 64 * 64) {
+    int lo = (last - 1) / 64 * 64 + 1, ks = slices(lo);  // every tile is whole 64-row ones
+    while (lo <= last && bytes(ks, last) > most) {  // runs of batches with as many slices
+      int same = lo, more = last + 1;
+      for (int step = more - same; step > 1; step = more - same) {
+        const int mid = same + step / 2;
+        (slices(mid) == ks ? same : more) = mid;
+      }
+      most = std::max(most, bytes(ks, same));
+      lo = more;
+      if (lo <= last) ks = slices(lo);
+    }
+  }
+  return most;
 }
 
 }  // namespace qalora

@@ -31,6 +31,7 @@ SHAPES = [
 @pytest.fixture(scope="module")
 def plan(tmp_path_factory):
     lib = host_library(tmp_path_factory.mktemp("gemm_plan"), "gemm_plan", """
+#include <algorithm>
 #include "gemm_plan.hpp"
 extern "C" int rows(int bits, int M, int N, int K, int g) { return qalora::gemm_dq_plan(bits, M, N, K, g).tile_rows; }
 extern "C" int slices(int bits, int M, int N, int K, int g) { return qalora::gemm_dq_plan(bits, M, N, K, g).ksplit; }
@@ -38,10 +39,17 @@ extern "C" int general(int bits, int M, int N, int K, int g, int bwd) {
   const qalora::GemmPlan p = qalora::gemm_dq_plan(bits, M, N, K, g, bwd);
   return 100 * p.tile_rows + p.ksplit;
 }
+extern "C" size_t most(int bits, int M, int N, int K, int g, int bwd) { return qalora::gemm_dq_most_partials(bits, M, N, K, g, bwd); }
+// of every batch of up to M tokens, one after the other
+extern "C" size_t needed(int bits, int M, int N, int K, int g, int bwd) {
+  size_t v = 0;
+  for (int m = 1; m <= M; ++m) v = std::max(v, qalora::gemm_dq_partials(qalora::gemm_dq_plan(bits, m, N, K, g, bwd), m, N));
+  return v;
+}
 extern "C" size_t room(int M, int N) { return qalora::gemm_dq_partial_room(M, N); }
 extern "C" int fast(int K, int g) { return qalora::gemm_fast_shape(K, g); }
 """)
-    lib.room.restype = ctypes.c_size_t
+    lib.room.restype = lib.most.restype = lib.needed.restype = ctypes.c_size_t
     return lib
 
 
@@ -76,6 +84,20 @@ def test_general_form_has_its_own_costs(plan, bits, tokens, d_in, d_out, group, 
     N, K = (d_in, d_out) if bwd else (d_out, d_in)
     assert not plan.fast(K, group)
     assert divmod(plan.general(bits, tokens, N, K, group, bwd), 100) == best
+
+
+def test_large_outputs_are_split(plan):
+    # us: 421 in slices, 522 whole
+    assert divmod(plan.general(3, 2048, 5120, 13800, 128, 1), 100)[1] > 1
+
+
+def test_partials_of_shorter_batches(plan):
+    """The room that a workspace has for partial sums is what some batch of up to its tokens needs."""
+    rng = random.Random(9)
+    for _ in range(150):
+        M, N, K = rng.choice([1, 64, 65, 256, 300, 1000, rng.randint(1, 3000)]), 8 * rng.randint(1, 2800), 8 * rng.randint(1, 2800)
+        args = (rng.choice([2, 3, 4]), M, N, K, rng.choice([32, 64, 96]), rng.randint(0, 1))
+        assert plan.most(*args) == plan.needed(*args), args
 
 
 @pytest.mark.parametrize("d_in,d_out", [(512, 512), (1024, 1024), (4096, 11008), (13824, 520), (22016, 8192), (1024, 8192)])
