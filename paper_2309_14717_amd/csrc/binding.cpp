@@ -20,7 +20,6 @@
 #include <algorithm>
 #include <cstring>
 #include <utility>
-#include <vector>
 
 #include "../../include/qalora.h"
 
@@ -42,16 +41,23 @@ PyObject *desc_type = nullptr, *adamw_type = nullptr;  // api.py's mirrors of qa
 bool bound = false;
 
 // The operands of one call, held until it returns (a list they came in can change while the interpreter lock is
-// released).  `ok` falls once anything is not plainly right.
+// released).  Held by their Python objects: a tensor's own count is atomic (AdamW over 14 adapter tensors, host time a
+// call: 7.7 us by tensors in a vector, 6.6 so).  `ok` falls once anything is not plainly right.
 struct Call {
+  static constexpr int kMostHeld = 4 * 32 + 16;  // an optimiser step's
   bool ok = true;
-  std::vector<at::Tensor> held;
+  int n_held = 0;
+  PyObject* held[kMostHeld];
   qalora_desc desc{};
   c10::Device dev{c10::DeviceType::CPU};
   int64_t T = 0, L = 0;
 
   // (under a mode the allocations below would have to go through Python)
   Call() { ok = bound && !at::impl::torch_function_mode_enabled() && !c10::impl::dispatch_mode_enabled(); }
+  ~Call() {
+    while (n_held > 0) Py_DECREF(held[--n_held]);
+  }
+  Call(const Call&) = delete;
   void need(bool v) { ok = ok && v; }
 
   // an ordinary, contiguous tensor on a GPU, the call's from the first one on
@@ -68,8 +74,11 @@ struct Call {
     }
     if (first) dev = t.device();
     need(t.device() == dev);
-    if (ok) held.push_back(t);
-    return ok ? &t : nullptr;
+    need(n_held < kMostHeld);
+    if (!ok) return nullptr;
+    Py_INCREF(o);
+    held[n_held++] = o;
+    return &t;
   }
   void* matrix(PyObject* o, at::ScalarType dtype, int64_t rows, int64_t cols) {
     const at::Tensor* t = tensor(o);
