@@ -678,21 +678,21 @@ static hipError_t launch_front_wide(const FrontArgs& a, int rb, int nblocks, siz
 
 static hipError_t launch_front(FrontArgs a, hipStream_t st) {
   bool y_wide = false;
+  int max_rank = 0;
+  for (int p = 0; p < a.n_parts; ++p) max_rank = a.part[p].rank > max_rank ? a.part[p].rank : max_rank;
   const bool pooled_short = a.P_out && a.T > 128 && a.d_in <= 512 * ROW_BATCH;
   if (a.x && !a.y && a.T <= kWideRows && a.d_in % 8 == 0 && a.d_in <= 256 * 8 * WIDE_BATCH && !pooled_short) {
     if (!a.f_alpha && !a.P_out) {  // few rows and nothing else
       front_wide_kernel<<<a.T, 256, 0, st>>>(a.x, a.d_in, a.rs_x, a.x16);
       return hipGetLastError();
     }
-    if (front_rows_by_block(a.T, a.f_fold, a.P_out != nullptr, a.f_L, a.f_dout)) {
+    if (front_rows_by_block(a.T, a.d_in, a.g, a.f_dout, a.f_fold, max_rank, a.P_out != nullptr)) {
       a.y = a.x; a.Ty = a.T; a.d_y = a.d_in; a.rs_y = a.rs_x; a.y16 = a.x16;
       a.y_pool = a.P_out != nullptr;
       a.x = nullptr;
       y_wide = true;
     }
   }
-  int max_rank = 0;
-  for (int p = 0; p < a.n_parts; ++p) max_rank = a.part[p].rank > max_rank ? a.part[p].rank : max_rank;
   a.nb_rows1 = a.x ? ceil_div(a.T, ROWS_PER_BLOCK) : 0;
   // dy rows that do not fit the smallest register batch of one wavefront: a block each (backward front
   // launch, 4096 rows of 22016: 123 -> 87 us, 1531 rows of 13824: 44 -> 34; two sweeps, or one at 28 pieces

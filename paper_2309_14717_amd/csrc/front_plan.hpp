@@ -14,19 +14,24 @@ inline int factor_cols(int L) {
   return fc;
 }
 
-// Few rows of a forward beside its factor job, in one launch with it (a launch of their own before it: 2 to 4 us more
-// almost everywhere): a block each, or a wavefront?  Blocks of rows alternate with the job's, and those that fold an
-// adapter are long: where more than the 1024 that run at once (37 KB of LDS and the registers leave four a unit) come
-// before the job's last one, a second round of it follows the rows.  Forward and backward, us by wavefronts / by blocks,
-// rank 64 to 128: 13824 x 13824, 128 tokens 373 / 367, 200 451 / 461, 640 838 / 869; 5120 x 13824, 200 186 / 185, 640
-// 293 / 298; 11008 x 4096, 300 164 / 160, 640 212 / 206; 13824 x 5120 (rank 16), 512 252 / 245.  Without pooling a
-// wavefront does less: 4096 x 4096, 200 tokens 75 / 75, 512 113 / 115.  Adapter-free the job is short, and a wavefront a
-// row does as well from about a hundred on: 22016 x 8192, 65 tokens 92 / 91, 400 207 / 208, 800 350 / 358;
-// 8192 x 22016, 640 281 / 290; 13824 x 5120, 100 50 / 52.
-inline bool front_rows_by_block(int T, bool fold, bool pooled, int L, int d_out) {
-  if (!fold) return T <= 96;
-  const int job = ceil_div(d_out, factor_cols(L));
-  return job + std::min(job, T) <= 1024 && (pooled || T <= 256);
+// Up to 1024 rows of a forward beside its factor job, in one launch with it (a launch of their own before it: 2 to 4 us more
+// almost everywhere): a block each, or a wavefront?  A wavefront takes a row of up to 4096 elements in one sweep and is
+// hidden under the job; longer rows are read twice and end the launch where the job's blocks are short, which is where
+// groups are few (L, that is long rows of large groups) and the rank is low.  Blocks of rows in turn delay a long job, more
+// so where more than the 1024 blocks that run at once (37 KB of LDS and the registers leave four a unit) come before
+// the job's last one.  Fitted to 630 pairs with an adapter (rank 16 to 128, with pooling and without) and 184 without,
+// 40 to 1000 tokens of 1024 x 1024 to 13824 x 13824 and 22016 x 8192: 0.2 % from the better one on average, 3.5 % at most (always
+// blocks: 0.8 and 12; with an adapter by their number alone, and without one up to 96 rows: 0.8 and 15, 2.2 and 17).  us by
+// wavefronts / by blocks: adapter-free, 300 tokens of 13824 x 5120, g 128 83 / 74, g 32 87 / 88; 700 of 8192 x 22016, g 32 339 / 348;
+// with pooling, 200 of 13824 x 13824, rank 16 g 128 128 / 112, rank 128 g 32 166 / 181.
+inline bool front_rows_by_block(int T, int d_in, int g, int d_out, bool fold, int rank, bool pooled) {
+  if (T <= 64) return true;
+  const bool one_sweep = d_in <= 4096;
+  if (!fold) return one_sweep ? T <= 256 : g >= 64;
+  const int job = ceil_div(d_out, factor_cols(d_in / g)), longer = rank + 24;
+  const bool at_once = job + std::min(job, T) <= 1024;
+  if (one_sweep) return at_once && (pooled || T <= 256) && longer < 4 * g;
+  return (pooled ? 3 : 2) * g > (at_once ? longer : 2 * longer);
 }
 
 }  // namespace qalora
