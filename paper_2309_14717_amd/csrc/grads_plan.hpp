@@ -42,20 +42,20 @@ inline int grads_db_shares(int L) { return L <= GZ_L ? 0 : ceil_div(L, GZ_L); }
 // Fused: few tokens and no more blocks than compute units (forward and backward of 64 tokens, 1024 x 1024 rank
 // 16: 37.7 us against 42.1 with two; 512 of 4096 x 4096 rank 64: 107 / 112; 1024 of 2048 x 2048: 86.9 / 85.1; 128 of
 // 4096 x 11008, 344 blocks: 108.6 / 106.5).
-// Else by Z or by U, whichever a linear model says is shorter: Z makes T d_out L products (L in whole tiles) and
-// L r d_out fp32 ones, with shares of dA to every 32 columns; U two times T d_out r (tiles of 32, 64, 128), and reads
-// dy twice.  Coefficients (us) fitted to 364 pairs of steps (32 to 3000 tokens, 32 to 344 groups, ranks 8 to 128, 1024
-// to 11008 columns): the choice is 0.07 % of the step from the better one on average, 4.5 % at most (up to 128 tokens
-// the launches by U are chains of waits: 64 tokens of 13824 x 2720 rank 64 91 / 99).  Forward and
-// backward, Z / U in us: 3000 tokens of 4096 x 4096 rank 64 250 / 253, with g 128 and rank 128 237 / 271; of 5120 x 4096
-// rank 64 314 / 309; 1500 of 11008 x 4096 399 / 387; 800 of 11008 x 11008 rank 128 698 / 646, 32 of them 251 / 199.
+// Else by Z or by U, whichever a linear model says is shorter: Z makes T d_out L products and L r d_out fp32 ones, with
+// shares of dA to every 32 columns; U two times T d_out r (tiles of 32, 64, 128), and reads dy twice.  Coefficients (us) fitted
+// to 490 pairs (40 to 4096 tokens, 32 to 432 groups, ranks 16 to 128, 2048 to 22016 columns): the choice costs 0.3 % of the
+// gradients' launches on average and 0.1 % of the step, 9 % of one at most (short batches, where launches by U are chains of
+// waits).  The gradients and the conversion of dy, Z / U in us: 4096 tokens of 4096 x 4096 rank 64 48 / 51, of 11008 x 4096 79 / 59;
+// 1531 of 5120 x 13824 g 64 rank 64 60.7 / 65.8; 700 of 4096 x 4096 rank 16 29.6 / 24.8; 4096 of 4096 x 22016 rank 64
+// 168 / 178, rank 16 160 / 143.
 inline int grads_group_tile(int L) { return L <= 32 ? 32 : (L <= 64 ? 64 : GZ_L); }  // rows of a tile of Z
 inline bool grads_fusable(int L, int d_out) { return ceil_div(d_out, GF_C) * ceil_div(L, GZ_L) <= 256; }
 inline GradsForm grads_form(int T, int L, int d_out, int max_rank, int rank_tile) {
   if (T <= kGradsFusedTokens && grads_fusable(L, d_out)) return GRADS_FUSED;
   const double l_tiles = grads_group_tile(L) * ceil_div(L, GZ_L), tokens = round_up(T, GZ_T), n = d_out;
-  const double z_less_u = -9.8 + 1e-9 * tokens * n * (5.1 * l_tiles - 22.0 * rank_tile + 650.0) + 53e-9 * n * L * max_rank +
-                          5.2e-6 * n * l_tiles - (T <= kGradsShort ? 6.0 : 0.0);
+  const double z_less_u = -3.26 + 1e-9 * tokens * n * (4.2 * L - 16.9 * rank_tile + 378.0) + 46.5e-9 * n * L * max_rank +
+                          n * (5.11e-6 * l_tiles - 6.15e-6 * rank_tile) - (T <= kGradsShort ? 2.17 : 0.0);
   return z_less_u > 0 ? GRADS_BY_U : GRADS_BY_Z;
 }
 
@@ -66,9 +66,10 @@ inline int grads_most_da_shares(int T, int L, int n_parts) {
   return std::min(ceil_div(T, GA_T), std::min(128, std::max(16, 256 / (ceil_div(L, GZ_L) * n_parts))));
 }
 
-// Runs of z_kernel and db_kernel: a block per compute unit, two where the runs are long -- a unit with two blocks takes
-// 1.2 us per step instead of 1.4, but twice as many partial sums are written and read again (4096 tokens: 4096 x 22016
-// 66 us against 98, 4096 x 4096 20.3 + 13.2 with their sums against 18.8 + 10.6).
+// Runs of z_kernel and db_kernel: a block per compute unit, two where the runs are long: two cover each other's waits, but
+// leave twice as many partial sums.  For Z from 3000 units on (two against one, 216 calls: 4 % longer below 3000, 2 to 3 %
+// shorter to 6000, 8 above; 4096 tokens of 5120 x 13824 g 64 116 us against 122), for dB from 8192 (with dA's blocks beside them:
+// 2 to 6 % longer below).
 // dU: blocks of 64 tokens up to 1024, else of 256 (4096 tokens of 4096 x 22016 rank 64: 72 us in blocks of 64, 63 in
 // those; 1024 of 4096 x 4096 9.7 / 10.3), and as many partial sums as fill the chip, up to 24 or 16: dA's blocks add
 // them (20 tokens of 13824 x 13824 rank 128: 29 us with 16, 20 with 24).
@@ -77,11 +78,11 @@ inline GradsPlan grads_plan(int T, int L, int d_out, int n_parts, const int* ran
                             const GradsForm* form = nullptr) {
   GradsPlan p{};
   const int steps = ceil_div(T, GZ_T);
-  auto in_runs = [&](int tiles) {
+  auto in_runs = [&](int tiles, long most_for_one) {
     const long units = (long)steps * tiles;
     p.runs.steps = steps;
     p.runs.units = (int)units;
-    p.runs.blocks = (int)std::min(units, units > 8192 ? 512L : 256L);
+    p.runs.blocks = (int)std::min(units, units > most_for_one ? 512L : 256L);
     p.slots = std::min(steps, ceil_div(p.runs.blocks, tiles) + 1);
   };
   int max_rank = 0, tiles = 0, all = 0;
@@ -93,9 +94,9 @@ inline GradsPlan grads_plan(int T, int L, int d_out, int n_parts, const int* ran
   }
   p.rank_tile = max_rank <= 32 ? 32 : (max_rank <= 64 ? 64 : 128);
   p.form = form ? *form : grads_form(T, L, d_out, max_rank, p.rank_tile);
-  if (p.form == GRADS_BY_Z) in_runs(ceil_div(d_out, GZ_C) * ceil_div(L, GZ_L));
+  if (p.form == GRADS_BY_Z) in_runs(ceil_div(d_out, GZ_C) * ceil_div(L, GZ_L), 3000);
   if (p.form != GRADS_BY_U) return p;
-  in_runs(tiles);
+  in_runs(tiles, 8192);
   p.du_long = T > 1024;
   const int most = p.du_long ? 16 : kGradsDuSlices;
   const int slices = std::max(1, std::min(most, p.du_long ? 256 / ceil_div(T, 256) : 512 / ceil_div(T, 64)));

@@ -26,7 +26,8 @@ SHAPES = [
     (641, 416, 520, 4, 32, 16),     # the first in two; 13 groups
     (700, 2080, 1032, 4, 8, 33),    # 260 groups: three tiles of them, runs that cross tiles
     (1000, 96, 8200, 3, 32, 64),    # three groups; more tiles than a run's
-    (130, 1024, 8256, 4, 8, 8),     # 258 blocks: two launches at few tokens
+    (130, 1024, 8256, 4, 8, 8),     # 258 blocks: two launches at few tokens (by U: the rank is low)
+    (130, 1024, 8256, 4, 8, 100),   # ... by Z
     (4096, 256, 136, 4, 128, 64),   # two groups, two tiles of columns, 64 steps
     (65, 1920, 264, 4, 32, 24),     # 60 groups: tiles of 64
     (700, 1920, 520, 4, 32, 24),    # ... in two launches
@@ -40,7 +41,7 @@ BY_U = [
     (65, 3080, 6152, 8, ((6152, 100),)),                   # a token in the second block; columns beside a step
     (1025, 3080, 2056, 8, ((2056, 8),)),                   # blocks of 256 tokens, one of one; rank of one chunk
     (1300, 13824, 4096, 32, ((4096, 128),)),               # ... with the largest rank; several steps a share of dA
-    (700, 4128, 6176, 32, ((2080, 40), (32, 128), (4064, 8))),   # parts: widths beside steps and tiles, three ranks
+    (700, 4128, 6176, 16, ((2080, 40), (32, 128), (4064, 8))),   # parts: widths beside steps and tiles, three ranks
 ]
 
 

@@ -18,6 +18,7 @@ def plan(tmp_path_factory):
 #include "grads_plan.hpp"
 using namespace qalora;
 extern "C" int form(int T, int L, int d_out, int rank) { return grads_plan(T, L, d_out, 1, &rank, &d_out).form; }
+extern "C" int blocks(int T, int L, int d_out, int rank) { return grads_plan(T, L, d_out, 1, &rank, &d_out).runs.blocks; }
 // 0, or what is wrong
 extern "C" int check(int T, int L, int n, const int* rank, const int* part) {
   int d_out = 0;
@@ -50,12 +51,16 @@ extern "C" int check(int T, int L, int n, const int* rank, const int* part) {
 
 def test_forms(plan):
     for tokens, d_in, d_out, bits, group, rank in SHAPES:
-        assert plan.form(tokens, d_in // group, d_out, rank) != U
+        assert (plan.form(tokens, d_in // group, d_out, rank) == U) == ((tokens, rank) == (130, 8))
     for tokens, d_in, d_out, group, parts in BY_U:
         assert plan.form(tokens, d_in // group, d_out, max(r for _, r in parts)) == U
     # the benchmark's layers
     assert plan.form(64, 32, 1024, 16) == FUSED and plan.form(4096, 128, 4096, 64) == BY_Z
     assert plan.form(4096, 344, 4096, 64) == U and plan.form(4096, 8, 8192, 128) == BY_Z
+    # measured: 7 to 20 % of the gradients' launches longer the other way
+    assert plan.form(1531, 80, 13824, 64) == BY_Z and plan.form(700, 128, 4096, 16) == U
+    assert plan.form(4096, 128, 22016, 64) == BY_Z and plan.form(4096, 128, 22016, 16) == U
+    assert [plan.blocks(t, 128, 4096, 64) for t in (4096, 5952, 6016)] == [256, 256, 512]   # 2976 and 3008 units
 
 
 def test_plans_are_launchable(plan):
