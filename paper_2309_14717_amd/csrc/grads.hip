@@ -36,10 +36,10 @@ constexpr int GF_LD = 36;  // floats per LDS row of 32 columns
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-template <int NL, int NC>
-struct ZTile {  // how four wavefronts share a tile of NL rows (groups, or ranks) x NC columns
-  static constexpr int kWavesL = NC < 128 ? NL / 32 : (NL >= 64 ? 2 : 1);  // (32 columns and fewer than 128 rows: the rest idle)
-  static constexpr int kWavesC = NC < 128 ? 1 : 4 / kWavesL;
+template <int NL, int NC, int NT = 256>
+struct ZTile {  // how NT threads' wavefronts share a tile of NL rows (groups, or ranks) x NC columns
+  static constexpr int kWavesL = NC < 128 ? NL / 32 : (NL >= 64 ? NT / 128 : 1);  // (32 columns and fewer than 128 rows: the rest idle)
+  static constexpr int kWavesC = NC < 128 ? 1 : NT / 64 / kWavesL;
   static constexpr int TL = NL / kWavesL / 32, TC = NC / kWavesC / 32;
   // 16-bit elements per LDS row (a token): four rows of a transposed read in distinct banks
   static constexpr int P_LD = kPieces * NL + 16, Y_LD = NC + 16;
@@ -78,14 +78,14 @@ __device__ __forceinline__ bf16x8 read_columns(const uint16_t* tile, int ld, int
 }
 
 // acc += P[t0 .. t1)^T dy[t0 .. t1) of the NL rows from l0 (of L, P's pieces being Lp apart) and the NC columns from j0,
-// by 256 threads.  Rows and columns outside the matrix hold anything (the callers drop them).
-template <int NL, int NC>
+// by NT threads.  Rows and columns outside the matrix hold anything (the callers drop them).
+template <int NL, int NC, int NT = 256>
 __device__ __forceinline__ void z_tile(const uint16_t* P, int L, int Lp, const uint16_t* dy, int d_out, int l0, int j0,
                                        int t0, int t1, uint16_t* lds,
-                                       f32x16 (&acc)[ZTile<NL, NC>::TL][ZTile<NL, NC>::TC]) {
-  using G = ZTile<NL, NC>;
+                                       f32x16 (&acc)[ZTile<NL, NC, NT>::TL][ZTile<NL, NC, NT>::TC]) {
+  using G = ZTile<NL, NC, NT>;
   constexpr int P_LD = G::P_LD;
-  constexpr int P_CH = NL / 8, P_LOADS = GZ_T * P_CH / 256, Y_CH = NC / 8, Y_LOADS = GZ_T * Y_CH / 256;
+  constexpr int P_CH = NL / 8, P_LOADS = GZ_T * P_CH / NT, Y_CH = NC / 8, Y_LOADS = GZ_T * Y_CH / NT;
   uint16_t* ps = lds;
   uint16_t* ys = lds + GZ_T * P_LD;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -107,12 +107,12 @@ __device__ __forceinline__ void z_tile(const uint16_t* P, int L, int Lp, const u
     for (int q = 0; q < P_LOADS; ++q)
 #pragma unroll
       for (int h = 0; h < kPieces; ++h) {
-        const uint32_t o = p_off + (uint32_t)(256 / P_CH * q) * p_row + 2u * (uint32_t)(h * Lp);
+        const uint32_t o = p_off + (uint32_t)(NT / P_CH * q) * p_row + 2u * (uint32_t)(h * Lp);
         pr[h][q] = __builtin_amdgcn_raw_buffer_load_b128(rs_p, (int)(p_ok ? o : kOob), 0, 0);
       }
 #pragma unroll
     for (int q = 0; q < Y_LOADS; ++q) {
-      const uint32_t o = y_off + (uint32_t)(256 / Y_CH * q) * y_row;
+      const uint32_t o = y_off + (uint32_t)(NT / Y_CH * q) * y_row;
       yr[q] = __builtin_amdgcn_raw_buffer_load_b128(rs_y, (int)(y_ok ? o : kOob), 0, 0);
     }
   };
@@ -123,35 +123,37 @@ __device__ __forceinline__ void z_tile(const uint16_t* P, int L, int Lp, const u
     for (int q = 0; q < P_LOADS; ++q)
 #pragma unroll
       for (int h = 0; h < kPieces; ++h)
-        *reinterpret_cast<u32x4*>(ps + (pr0 + 256 / P_CH * q) * P_LD + h * NL + pl - l0) = pr[h][q];
+        *reinterpret_cast<u32x4*>(ps + (pr0 + NT / P_CH * q) * P_LD + h * NL + pl - l0) = pr[h][q];
 #pragma unroll
     for (int q = 0; q < Y_LOADS; ++q)
-      *reinterpret_cast<u32x4*>(ys + (yr0 + 256 / Y_CH * q) * G::Y_LD + yj - j0) = yr[q];
+      *reinterpret_cast<u32x4*>(ys + (yr0 + NT / Y_CH * q) * G::Y_LD + yj - j0) = yr[q];
     lds_barrier();
     fetch(t + GZ_T);  // (past the end: reads zero)
     if (busy) {
-      // the operands of the next sixteen tokens are read while the matrix cores work on these
-      bf16x8 y[2][G::TC], p[2][kPieces][G::TL];
+      // the operands of the next sixteen tokens are read while the matrix cores work on these (with 512 threads
+      // there are no registers for both, and other wavefronts on the SIMD to work on)
+      constexpr int D = NT > 256 ? 1 : 2;
+      bf16x8 y[D][G::TC], p[D][kPieces][G::TL];
       auto read = [&](int kk) {
 #pragma unroll
-        for (int c = 0; c < G::TC; ++c) y[kk & 1][c] = read_columns(ys + 16 * kk * G::Y_LD + wc + 32 * c, G::Y_LD, lane);
+        for (int c = 0; c < G::TC; ++c) y[kk % D][c] = read_columns(ys + 16 * kk * G::Y_LD + wc + 32 * c, G::Y_LD, lane);
 #pragma unroll
         for (int h = 0; h < kPieces; ++h)
 #pragma unroll
-          for (int l = 0; l < G::TL; ++l) p[kk & 1][h][l] = read_columns(ps + 16 * kk * P_LD + h * NL + wl + 32 * l, P_LD, lane);
+          for (int l = 0; l < G::TL; ++l) p[kk % D][h][l] = read_columns(ps + 16 * kk * P_LD + h * NL + wl + 32 * l, P_LD, lane);
       };
       read(0);
 #pragma unroll
       for (int kk = 0; kk < GZ_T / 16; ++kk) {
-        if (kk + 1 < GZ_T / 16) read(kk + 1);
-        __builtin_amdgcn_sched_barrier(0);
+        if (kk + D - 1 < GZ_T / 16 && (D > 1 || kk > 0)) read(kk + D - 1);
+        if constexpr (D > 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int h = 0; h < kPieces; ++h)
 #pragma unroll
           for (int l = 0; l < G::TL; ++l)
 #pragma unroll
             for (int c = 0; c < G::TC; ++c)
-              acc[l][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[kk & 1][h][l], y[kk & 1][c], acc[l][c], 0, 0, 0);
+              acc[l][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[kk % D][h][l], y[kk % D][c], acc[l][c], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -266,10 +268,16 @@ __device__ __forceinline__ const FinishPart& part_of(const FinishArgs& a, int j0
 // Equal runs of (tile, step) units, tile by tile: a tile that several blocks work on has a partial sum from each,
 // in the slots 0, 1, ... in order.
 // (NL: grads_group_tile)
+// Tiles of 128 groups by eight wavefronts: a block per unit is two on a SIMD, of which one works while the other waits for
+// loads, LDS or a barrier (by four: one; forward and backward of 4096 tokens, 4096 x 4096 308.9 us by four and 306.8 by
+// eight, 1531 of 5120 x 13824 g 64 520.2 / 515.6; the same where two blocks share a unit, 2298 for the MLP block).
+// (P as fp32 in memory, cut into pieces on the way to LDS, is a third fewer bytes but longer: the cutting is on every
+// step's chain, 316.6 / 320.0 and 528.2 / 532.5 by four.)
+constexpr int z_threads(int NL) { return NL < GZ_L ? 256 : 512; }
 template <int NL>
-__global__ __launch_bounds__(256, 2) void z_kernel(const ZArgs a) {
+__global__ __launch_bounds__(z_threads(NL), z_threads(NL) / 128) void z_kernel(const ZArgs a) {
   extern __shared__ __align__(16) uint16_t zlds[];
-  using G = ZTile<NL, GZ_C>;
+  using G = ZTile<NL, GZ_C, z_threads(NL)>;
   const int cols = ceil_div(a.d_out, GZ_C), lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wl = (wave % G::kWavesL) * G::TL * 32, wc = (wave / G::kWavesL) * G::TC * 32;
   const int b = (int)blockIdx.x, u1 = a.runs.first(b + 1);
@@ -283,7 +291,7 @@ __global__ __launch_bounds__(256, 2) void z_kernel(const ZArgs a) {
       for (int c = 0; c < G::TC; ++c)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[l][c][r] = 0.0f;
-    z_tile<NL, GZ_C>(a.P, a.L, a.Lp, a.dy, a.d_out, l0, j0, k0 * GZ_T, min(a.T, k1 * GZ_T), zlds, acc);
+    z_tile<NL, GZ_C, z_threads(NL)>(a.P, a.L, a.Lp, a.dy, a.d_out, l0, j0, k0 * GZ_T, min(a.T, k1 * GZ_T), zlds, acc);
     float* Z = a.Z + (size_t)(b - a.runs.owner(tile * a.runs.steps)) * a.L * a.d_out;
 #pragma unroll
     for (int l = 0; l < G::TL; ++l)
@@ -747,7 +755,7 @@ static hipError_t launch_z(const GradsPlan& plan, const ZArgs& z, const FinishAr
   static std::atomic<uint64_t> granted_z{0}, granted_f{0};
   if (hipError_t e = grant(z_kernel<NL>, lds, granted_z); e != hipSuccess) return e;
   if (hipError_t e = grant(finish_kernel, most, granted_f); e != hipSuccess) return e;
-  z_kernel<NL><<<plan.runs.blocks, 256, lds, st>>>(z);
+  z_kernel<NL><<<plan.runs.blocks, z_threads(NL), lds, st>>>(z);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   finish_kernel<<<blocks, 64 * FINISH_WAVES, finish, st>>>(f);
   return hipGetLastError();
