@@ -31,6 +31,8 @@ SHAPES = [
     (4096, 256, 136, 4, 128, 64),   # two groups, two tiles of columns, 64 steps
     (65, 1920, 264, 4, 32, 24),     # 60 groups: tiles of 64
     (700, 1920, 520, 4, 32, 24),    # ... in two launches
+    (650, 2208, 200, 4, 32, 100),   # 69 groups: the tile's third quarter begins; columns end inside the second tile
+    (705, 3104, 136, 2, 32, 40),    # 97 groups: its last quarter begins
     (5, 4800, 64, 4, 40, 8),        # rows pooled by a block each in the forward, groups beside powers of two
     (200, 4128, 64, 4, 32, 8),      # ... and beyond a wavefront's registers; 129 groups
 ]
