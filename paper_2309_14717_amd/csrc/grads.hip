@@ -15,10 +15,11 @@
 //
 // By U: where the rank is well below the groups (further below, with its kernels).
 //
-// 4096 tokens, rank 64: 4096 x 4096 by Z 24 + 11 + 5 us (with two pieces of P 19 + 11 + 5, but gradients ten times as far
+// 4096 tokens, rank 64: 4096 x 4096 by Z 23 + 12 + 5 us (with two pieces of P 19 + 11 + 5, but gradients ten times as far
 // from the exact ones; each gradient from its own pass over dy, with B, U and P rounded to two pieces: 44).
-// What bounds it: bytes of dy once (33.6 MB for 4096 x 4096) and Z's partial sums written and read (2 MB a slot there);
-// the matrix work is a third of that.  Both of Z's operands have the contraction index (tokens) as their slow one: they
+// What bounds it: the chain of a step (loads, LDS, matrix work) on a unit that holds little else, then bytes: dy once (33.6
+// MB for 4096 x 4096), P for every tile and Z's partial sums written and read (2 MB a slot there).  Counters of 4096 tokens of
+// 4096 x 22016: 337 MB fetched (dy 180, P 3), matrix cores busy for 35 % of the launch.  Both of Z's operands have the contraction index (tokens) as their slow one: they
 // are staged as they lie in memory and read transposed (ds_read_b64_tr_b16: a group of 16 lanes turns four rows
 // of sixteen columns), so that no 16-bit gather or packing is left.
 #include <algorithm>
@@ -365,7 +366,7 @@ __global__ __launch_bounds__(256) void fused_kernel(const ZArgs z, const FinishA
 //   tail_kernel
 // 1000 tokens of 13824 x 13824, rank 128 (432 groups): 32 + 29 + 10 us, by Z 69 + 71 + 20; 20 of them 20 + 14 + 8 and
 // 14 + 64 + 26; 4096 of 11008 x 4096 rank 64 25 + 20 + 6 and 61 + 14 + 6; 4096 of 4096 x 4096 19 + 18 + 5 and
-// 24 + 11 + 5.  Bound by dy's bytes, twice, and by B's, read from L2 by every block of tokens (22016 columns, rank 64,
+// 23 + 12 + 5.  Bound by dy's bytes, twice, and by B's, read from L2 by every block of tokens (22016 columns, rank 64,
 // 4096 tokens: 361 MB of B in blocks of 64 tokens, 102 us; in blocks of 256 90 MB, 64 us).
 constexpr int GU_LD = 72;    // 16-bit elements per LDS row of 64 columns
 constexpr int GA_LD = 144;   // floats per LDS row of 128 groups or ranks: four rows in distinct banks

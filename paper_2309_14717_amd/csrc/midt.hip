@@ -17,7 +17,9 @@
 //     exact).  No column's scale has to be known before, and none ends below the factor job's.
 // What bounds it: the weight's bytes (135 MB of 8192 x 22016 at g = 32 are 25 us) and the issue time
 // of the SIMDs, on which matrix and vector instructions take turns: per 16 columns x 32 rows 60
-// cycles of rebuilding whatever the token count and 16 per sixteen tokens.  (A form with exact
+// cycles of rebuilding whatever the token count and 16 per sixteen tokens (20 us at 64 tokens).  The two add up: a
+// wavefront has one unit of weights in flight, and x is staged again for every slab (180 MB beside the 135).  Counters
+// at that size: 160 MB fetched, matrix cores busy for 19 % and vector instructions issued for 32 % of 47 us.  (A form with exact
 // integer codes and alpha applied to the sums spends 24 more cycles per sixteen tokens and took
 // 4.4 us instead of 2.8 per 256 x 256 weights at 64 tokens; beyond 64 tokens the dense kernel, which
 // rebuilds a weight once for 256 rows, is the better one.)
