@@ -86,7 +86,7 @@ __device__ __forceinline__ void z_tile(const uint16_t* P, int L, int Lp, const u
                                        f32x16 (&acc)[ZTile<NL, NC, NT>::TL][ZTile<NL, NC, NT>::TC]) {
   using G = ZTile<NL, NC, NT>;
   constexpr int P_LD = G::P_LD;
-  constexpr int P_CH = NL / 8, P_LOADS = GZ_T * P_CH / NT, Y_CH = NC / 8, Y_LOADS = GZ_T * Y_CH / NT;
+  constexpr int P_CH = NL / 8, P_LOADS = GZ_T * P_CH / NT, Y_CH = NC / 8, Y_LOADS = ceil_div(GZ_T * Y_CH, NT);
   uint16_t* ps = lds;
   uint16_t* ys = lds + GZ_T * P_LD;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -96,7 +96,8 @@ __device__ __forceinline__ void z_tile(const uint16_t* P, int L, int Lp, const u
   // the buffers start at the step's first token and end with the last one's row, so later tokens read zero.
   const uint32_t p_row = (uint32_t)(kPieces * Lp) * 2u, y_row = (uint32_t)d_out * 2u;
   const int pr0 = tid / P_CH, pl = l0 + 8 * (tid % P_CH), yr0 = tid / Y_CH, yj = j0 + 8 * (tid % Y_CH);
-  const bool p_ok = pl < Lp, y_ok = yj < d_out;
+  const bool y_mine = GZ_T * Y_CH >= NT || yr0 < GZ_T;  // (more threads than pieces of dy)
+  const bool p_ok = pl < Lp, y_ok = yj < d_out && y_mine;
   uint32_t p_off = (uint32_t)pr0 * p_row + 2u * (uint32_t)pl, y_off = (uint32_t)yr0 * y_row + 2u * (uint32_t)yj;
   u32x4 pr[kPieces][P_LOADS], yr[Y_LOADS];  // the next step's, while this one is worked on
   auto fetch = [&](int t) {
@@ -127,13 +128,13 @@ __device__ __forceinline__ void z_tile(const uint16_t* P, int L, int Lp, const u
         *reinterpret_cast<u32x4*>(ps + (pr0 + NT / P_CH * q) * P_LD + h * NL + pl - l0) = pr[h][q];
 #pragma unroll
     for (int q = 0; q < Y_LOADS; ++q)
-      *reinterpret_cast<u32x4*>(ys + (yr0 + NT / Y_CH * q) * G::Y_LD + yj - j0) = yr[q];
+      if (y_mine) *reinterpret_cast<u32x4*>(ys + (yr0 + NT / Y_CH * q) * G::Y_LD + yj - j0) = yr[q];
     lds_barrier();
     fetch(t + GZ_T);  // (past the end: reads zero)
     if (busy) {
       // the operands of the next sixteen tokens are read while the matrix cores work on these (with 512 threads
       // there are no registers for both, and other wavefronts on the SIMD to work on)
-      constexpr int D = NT > 256 ? 1 : 2;
+      constexpr int D = NT > 256 && NC >= 128 ? 1 : 2;
       bf16x8 y[D][G::TC], p[D][kPieces][G::TL];
       auto read = [&](int kk) {
 #pragma unroll
@@ -337,21 +338,26 @@ __global__ __launch_bounds__(64 * FINISH_WAVES) void finish_kernel(const FinishA
   finish.run();
 }
 
+// (128 groups: eight wavefronts here too, of which four hold Z; all stage its operands and share what follows.  Forward and
+// backward by four / by eight, us: 115 tokens of 3968 x 1504, rank 128 85.6 / 79.2; 248 of 6912 x 1912, rank 128 111.2 / 106.7;
+// 311 of 9728 x 1408, g 128 rank 64 97.8 / 94.2; 25 of 13568 x 896, rank 16 71.0 / 70.1.)
 template <int NL>
-__global__ __launch_bounds__(256) void fused_kernel(const ZArgs z, const FinishArgs a) {
+__global__ __launch_bounds__(z_threads(NL)) void fused_kernel(const ZArgs z, const FinishArgs a) {
   extern __shared__ __align__(16) uint16_t zlds[];
-  using G = ZTile<NL, GF_C>;
+  using G = ZTile<NL, GF_C, z_threads(NL)>;
   const int j0 = (int)blockIdx.x * GF_C, l0 = (int)blockIdx.y * GZ_L, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  Finish<4> finish(a, part_of(a, j0), j0, l0, reinterpret_cast<float*>(zlds + G::kLds / 2));
+  Finish<z_threads(NL) / 64> finish(a, part_of(a, j0), j0, l0, reinterpret_cast<float*>(zlds + G::kLds / 2));
   f32x16 acc[1][1];
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[0][0][r] = 0.0f;
-  z_tile<NL, GF_C>(z.P, z.L, z.Lp, z.dy, z.d_out, l0, j0, 0, z.T, zlds, acc);
+  z_tile<NL, GF_C, z_threads(NL)>(z.P, z.L, z.Lp, z.dy, z.d_out, l0, j0, 0, z.T, zlds, acc);
   const int c = lane & 31;
+  if (wave < GZ_L / 32) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int row = 32 * wave + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    finish.zs[row * GF_LD + c] = (l0 + row < a.L && j0 + c < a.d_out) ? acc[0][0][r] : 0.0f;
+    for (int r = 0; r < 16; ++r) {
+      const int row = 32 * wave + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+      finish.zs[row * GF_LD + c] = (l0 + row < a.L && j0 + c < a.d_out) ? acc[0][0][r] : 0.0f;
+    }
   }
   finish.run();
 }
@@ -749,7 +755,7 @@ static hipError_t launch_z(const GradsPlan& plan, const ZArgs& z, const FinishAr
     constexpr size_t lds = ZTile<NL, GF_C>::kLds;
     static std::atomic<uint64_t> granted{0};
     if (hipError_t e = grant(fused_kernel<NL>, lds + most, granted); e != hipSuccess) return e;
-    fused_kernel<NL><<<blocks, 256, lds + finish, st>>>(z, f);
+    fused_kernel<NL><<<blocks, z_threads(NL), lds + finish, st>>>(z, f);
     return hipGetLastError();
   }
   constexpr size_t lds = ZTile<NL, GZ_C>::kLds;

@@ -41,7 +41,7 @@ inline int grads_db_shares(int L) { return L <= GZ_L ? 0 : ceil_div(L, GZ_L); }
 // Which form.
 // Fused: few tokens and no more blocks than compute units (forward and backward of 64 tokens, 1024 x 1024 rank
 // 16: 37.7 us against 42.1 with two; 512 of 4096 x 4096 rank 64: 107 / 112; 1024 of 2048 x 2048: 86.9 / 85.1; 128 of
-// 4096 x 11008, 344 blocks: 108.6 / 106.5).
+// 4096 x 11008, 344 blocks: 108.6 / 106.5; 128 groups by four wavefronts, eight are 1 to 8 % of the step faster).
 // Else by Z or by U, whichever a linear model says is shorter: Z makes T d_out L products and L r d_out fp32 ones, with
 // shares of dA to every 32 columns; U two times T d_out r (tiles of 32, 64, 128), and reads dy twice.  Coefficients (us) fitted
 // to 490 pairs (40 to 4096 tokens, 32 to 432 groups, ranks 16 to 128, 2048 to 22016 columns): the choice costs 0.3 % of the
